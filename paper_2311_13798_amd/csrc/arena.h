@@ -89,12 +89,15 @@ __host__ __device__ inline int task_x1(int64_t t) { return (int)(t & 1023); }
 // bound reaches that of x = 0, so no task is heavier than the heaviest single
 // vertex and light vertices do not each reload the slot.  Calls emit(x0, x1)
 // for every task and returns their number.
-__device__ inline double log_binom(int n, int r) {
+__host__ __device__ inline double log_binom(int n, int r) {
     return lgamma((double)n + 1) - lgamma((double)r + 1) - lgamma((double)(n - r) + 1);
 }
+__host__ __device__ inline bool root_split(int c, int l0, double log_threshold) {
+    return l0 >= 4 && c >= l0 + 8 && log_binom(c, l0) > log_threshold;
+}
 template <class F>
-__device__ inline int root_tasks(int c, int l0, double log_threshold, F&& emit) {
-    if (l0 < 4 || c < l0 + 8 || log_binom(c, l0) <= log_threshold) {
+__host__ __device__ inline int root_tasks(int c, int l0, double log_threshold, F&& emit) {
+    if (!root_split(c, l0, log_threshold)) {
         emit(0, c);
         return 1;
     }
@@ -149,7 +152,11 @@ struct BuildGraph {
 };
 struct SearchArgs {
     ArenaView A;
+    // task it: tasks[it] for it < nexplicit, then the whole root of
+    // slots[it - nexplicit]
     const int64_t* tasks;
+    int64_t nexplicit;
+    const int32_t* slots;
     int64_t ntasks;
     int32_t k;
     int32_t opts;

@@ -325,6 +325,7 @@ ebbkc_status enqueue(ebbkc_batch* b, hipStream_t s) {
         SearchArgs a{};
         a.tasks = b->tasks + off;
         a.task_graph = b->tgraph + off;
+        a.nexplicit = nt;
         a.ntasks = nt;
         a.views = b->build ? nullptr : b->views;
         a.bviews = b->build ? b->bviews : nullptr;

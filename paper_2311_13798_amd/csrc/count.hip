@@ -68,28 +68,138 @@ inline unsigned grid_for(int64_t n, int per = 256) {
 
 // ---------------------------------------------------------------- kernels
 
-__global__ void k_seed_flags(const int32_t* __restrict__ byrank, const int32_t* __restrict__ subsize, int64_t m,
-                             int32_t* __restrict__ flag) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < m; r += (int64_t)gridDim.x * blockDim.x)
-        flag[r] = subsize[byrank[r]] >= 1;
+// Slots: the items (ranks, or positions of the vertex order) with a non-empty
+// sub-branch, in order.  One tile of items per workgroup: k_seed_sums adds up
+// its slots, vertices and row words (and the slots of every size), k_seed_parts
+// turns the tile sums into offsets, k_seed_fill reads the tile again and writes
+// its slots.  Inside a tile the three sums travel as one 64-bit word (at most
+// 2^11 slots, 2^19 vertices, 2^21 row words), so one scan serves all three.
+constexpr int SEED_BLOCK = 256, SEED_ITEMS = 8, SEED_TILE = SEED_BLOCK * SEED_ITEMS;
+constexpr int SIZE_BINS = 64 * MAX_W + 1;
+
+struct SeedSums {
+    int64_t slots, vtx, words;
+};
+
+__device__ __forceinline__ int seed_size(const int32_t* __restrict__ id, const int32_t* __restrict__ size,
+                                         bool by_id, int64_t r) {
+    return by_id ? size[id[r]] : size[r];
+}
+__device__ __forceinline__ uint64_t seed_pack(int c) {
+    return c > 0 ? (1ull << 48) | ((uint64_t)c << 24) | (uint64_t)(c * width_of(c)) : 0ull;
 }
 
-__global__ void k_seed_fill(const int32_t* __restrict__ byrank, const int32_t* __restrict__ subsize,
-                            const int32_t* __restrict__ flag, const int64_t* __restrict__ pos, int64_t m,
-                            int32_t* __restrict__ seed_eid, int32_t* __restrict__ seed_c,
-                            int32_t* __restrict__ seed_rank, int64_t* __restrict__ rwords,
-                            int64_t* __restrict__ vcount, int* __restrict__ err) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < m; r += (int64_t)gridDim.x * blockDim.x) {
-        if (!flag[r]) continue;
-        const int64_t s = pos[r];
-        const int32_t e = byrank[r], c = subsize[e];
-        if (c > 64 * MAX_W) atomicOr(err, ERR_WIDTH);
-        seed_eid[s] = e;
-        seed_c[s] = c;
-        seed_rank[s] = (int32_t)r;
-        rwords[s] = (int64_t)c * width_of(c);
-        vcount[s] = c;
+__global__ __launch_bounds__(SEED_BLOCK) void k_seed_sums(const int32_t* __restrict__ id,
+                                                          const int32_t* __restrict__ size, bool by_id, int64_t n,
+                                                          SeedSums* __restrict__ part,
+                                                          unsigned long long* __restrict__ bins, int* __restrict__ err) {
+    __shared__ uint32_t h[SIZE_BINS];
+    __shared__ uint64_t ws[SEED_BLOCK / EBB_WAVE];
+    for (int i = threadIdx.x; i < SIZE_BINS; i += SEED_BLOCK) h[i] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * SEED_TILE;
+    uint64_t acc = 0;
+#pragma unroll
+    for (int j = 0; j < SEED_ITEMS; ++j) {
+        const int64_t r = base + j * SEED_BLOCK + threadIdx.x;
+        if (r >= n) continue;
+        int c = seed_size(id, size, by_id, r);
+        if (c <= 0) continue;
+        if (c > 64 * MAX_W) {
+            atomicOr(err, ERR_WIDTH);
+            c = 64 * MAX_W;
+        }
+        atomicAdd(&h[c], 1u);
+        acc += seed_pack(c);
     }
+    acc = wave_sum(acc);
+    if (lane_id() == 0) ws[threadIdx.x / EBB_WAVE] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < SEED_BLOCK / EBB_WAVE; ++i) acc += ws[i];
+        part[blockIdx.x] = SeedSums{(int64_t)(acc >> 48), (int64_t)((acc >> 24) & 0xFFFFFF), (int64_t)(acc & 0xFFFFFF)};
+    }
+    for (int i = threadIdx.x; i < SIZE_BINS; i += SEED_BLOCK)
+        if (h[i]) atomicAdd(&bins[i], (unsigned long long)h[i]);
+}
+
+// one workgroup: exclusive scan of the tile sums in place, the totals in *tot
+__global__ __launch_bounds__(SEED_BLOCK) void k_seed_parts(SeedSums* __restrict__ part, int64_t np,
+                                                           SeedSums* __restrict__ tot) {
+    __shared__ SeedSums wt[SEED_BLOCK / EBB_WAVE];
+    const int lane = lane_id(), w = threadIdx.x / EBB_WAVE;
+    SeedSums carry{0, 0, 0};
+    for (int64_t base = 0; base < np; base += SEED_BLOCK) {
+        const int64_t i = base + threadIdx.x;
+        const SeedSums v = i < np ? part[i] : SeedSums{0, 0, 0};
+        const SeedSums inc{wave_incl_scan(v.slots), wave_incl_scan(v.vtx), wave_incl_scan(v.words)};
+        if (lane == EBB_WAVE - 1) wt[w] = inc;
+        __syncthreads();
+        SeedSums b = carry;
+        for (int q = 0; q < SEED_BLOCK / EBB_WAVE; ++q) {
+            const SeedSums t = wt[q];
+            if (q < w) {
+                b.slots += t.slots;
+                b.vtx += t.vtx;
+                b.words += t.words;
+            }
+            carry.slots += t.slots;
+            carry.vtx += t.vtx;
+            carry.words += t.words;
+        }
+        if (i < np) part[i] = SeedSums{b.slots + inc.slots - v.slots, b.vtx + inc.vtx - v.vtx, b.words + inc.words - v.words};
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *tot = carry;
+}
+
+// The slots of each tile: id, size, offsets, and the sort key of the slot
+// order (class ascending, sizes descending: size 64 W - i of class W is bin
+// 64 (W - 1) + i).  rthr (vertex slots): an item's out-edges start at the rank
+// equal to the vertices of the slots before it; the threshold is one below.
+__global__ __launch_bounds__(SEED_BLOCK) void k_seed_fill(const int32_t* __restrict__ id,
+                                                          const int32_t* __restrict__ size, bool by_id, int64_t n,
+                                                          const SeedSums* __restrict__ part,
+                                                          int32_t* __restrict__ seed_id, int32_t* __restrict__ seed_c,
+                                                          int32_t* __restrict__ rthr, int64_t* __restrict__ row_off,
+                                                          int64_t* __restrict__ vtx_off, uint8_t* __restrict__ key) {
+    __shared__ uint64_t ws[SEED_BLOCK / EBB_WAVE];
+    const int lane = lane_id(), w = threadIdx.x / EBB_WAVE;
+    SeedSums b = part[blockIdx.x];
+    const int64_t base = (int64_t)blockIdx.x * SEED_TILE;
+    for (int j = 0; j < SEED_ITEMS; ++j) {
+        const int64_t r = base + j * SEED_BLOCK + threadIdx.x;
+        const int c = r < n ? seed_size(id, size, by_id, r) : 0;
+        const uint64_t v = seed_pack(c), inc = wave_incl_scan(v);
+        if (lane == EBB_WAVE - 1) ws[w] = inc;
+        __syncthreads();
+        uint64_t before = inc - v, all = 0;
+#pragma unroll
+        for (int q = 0; q < SEED_BLOCK / EBB_WAVE; ++q) {
+            if (q < w) before += ws[q];
+            all += ws[q];
+        }
+        if (c > 0) {
+            const int64_t s = b.slots + (int64_t)(before >> 48), vo = b.vtx + (int64_t)((before >> 24) & 0xFFFFFF);
+            seed_id[s] = id[r];
+            seed_c[s] = c;
+            row_off[s] = b.words + (int64_t)(before & 0xFFFFFF);
+            vtx_off[s] = vo;
+            if (rthr) rthr[s] = (int32_t)(vo - 1);
+            const int W = width_of(c);
+            key[s] = (uint8_t)(64 * (W - 1) + 64 * W - c);
+        }
+        b.slots += (int64_t)(all >> 48);
+        b.vtx += (int64_t)((all >> 24) & 0xFFFFFF);
+        b.words += (int64_t)(all & 0xFFFFFF);
+        __syncthreads();
+    }
+}
+
+__global__ void k_seed_ranks(const int32_t* __restrict__ seed_eid, const int32_t* __restrict__ rank, int64_t n,
+                             int32_t* __restrict__ out) {
+    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n; s += (int64_t)gridDim.x * blockDim.x)
+        out[s] = rank[seed_eid[s]];
 }
 
 // node-parallel roots: |N+(v)| (neighbours later in the vertex order) per vertex
@@ -105,44 +215,25 @@ __global__ void k_vertex_out(const int32_t* __restrict__ rp, const int32_t* __re
     }
 }
 
-__global__ void k_vertex_flags(const int32_t* __restrict__ cout, int32_t n, int32_t* __restrict__ flag) {
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x)
-        flag[p] = cout[p] >= 1;
-}
+// root ranges of the slots of one size: segment j is the range [x0, x1) of
+// every one of the slots order[first ..]; its tasks start at pref[j]
+struct TaskSeg {
+    int64_t pref;
+    int32_t first;
+    int16_t x0, x1;
+};
 
-// slot of the vertex at position p: its out-edges are the ranks [R, R + c) (edges are ranked
-// lexicographically by their endpoints' positions), so its sub-branch is the neighbourhood through
-// edges ranked after R - 1
-__global__ void k_vertex_fill(const int32_t* __restrict__ cout, const int32_t* __restrict__ byvpos,
-                              const int64_t* __restrict__ rstart, const int32_t* __restrict__ flag,
-                              const int64_t* __restrict__ pos, int32_t n, int32_t* __restrict__ seed_v,
-                              int32_t* __restrict__ seed_c, int32_t* __restrict__ seed_rthr,
-                              int32_t* __restrict__ seed_rank, int64_t* __restrict__ rwords,
-                              int64_t* __restrict__ vcount, int* __restrict__ err) {
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
-        if (!flag[p]) continue;
-        const int64_t s = pos[p];
-        const int32_t c = cout[p];
-        if (c > 64 * MAX_W) atomicOr(err, ERR_WIDTH);
-        seed_v[s] = byvpos[p];
-        seed_c[s] = c;
-        seed_rthr[s] = (int32_t)(rstart[p] - 1);
-        seed_rank[s] = (int32_t)rstart[p];
-        rwords[s] = (int64_t)c * width_of(c);
-        vcount[s] = c;
+__global__ void k_task_expand(const TaskSeg* __restrict__ seg, int nseg, int64_t n, const int32_t* __restrict__ order,
+                              int64_t* __restrict__ tasks) {
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
+        int lo = 0, hi = nseg;  // the last segment starting at or before t
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (seg[mid].pref <= t) lo = mid; else hi = mid;
+        }
+        const TaskSeg g = seg[lo];
+        tasks[t] = task_pack(order[g.first + (t - g.pref)], g.x0, g.x1);
     }
-}
-
-// slots of one width class, in slot order
-__global__ void k_class_flags(const int32_t* __restrict__ seed_c, int64_t n, int W, int32_t* __restrict__ flag) {
-    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n; s += (int64_t)gridDim.x * blockDim.x)
-        flag[s] = width_of(seed_c[s]) == W;
-}
-
-__global__ void k_class_fill(const int32_t* __restrict__ flag, const int64_t* __restrict__ pos, int64_t n,
-                             int32_t* __restrict__ list) {
-    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n; s += (int64_t)gridDim.x * blockDim.x)
-        if (flag[s]) list[pos[s]] = (int32_t)s;
 }
 
 __global__ void k_task_counts(const int32_t* __restrict__ seed_c, int64_t i0, int64_t n, int l0, double log_thr,
@@ -221,13 +312,6 @@ struct DBuf {
     T* release() { T* q = p; p = nullptr; return q; }
 };
 
-struct SlotArrays {
-    uint64_t* rows = nullptr;
-    int32_t* gid = nullptr;
-    int16_t* col = nullptr;
-    uint64_t* ned = nullptr;
-};
-
 }  // namespace
 
 hipError_t ensure_tables(int dev, hipStream_t s) { return ensure_binom(dev, s); }
@@ -270,207 +354,169 @@ ebbkc_status subsize_impl(ebbkc_graph* g, hipStream_t s) {
     return EBBKC_OK;
 }
 
-static ebbkc_status build_slots(ebbkc_graph* g, int64_t ns, const int32_t* seid, const int32_t* sc,
-                                const int32_t* srthr, const int64_t* roff, const int64_t* voff, const int64_t tot[2],
-                                int64_t* tmp, SlotArrays& out, hipStream_t s);
+// Host copy of the rank of every slot of the edge arena (rank-range counts,
+// per-seed counts), made on first use.
+static ebbkc_status seed_ranks(ebbkc_graph* g, hipStream_t s) {
+    if ((int64_t)g->seed_rank_host.size() == g->nseeds) return EBBKC_OK;
+    DBuf<int32_t> r;
+    CHKH(r.alloc(g->nseeds));
+    hipLaunchKernelGGL(k_seed_ranks, dim3(grid_for(g->nseeds)), dim3(256), 0, s, g->seed_eid, g->rank, g->nseeds, r.p);
+    CHKH(hipGetLastError());
+    std::vector<int32_t> h((size_t)g->nseeds);
+    CHKH(hipMemcpyAsync(h.data(), r.p, sizeof(int32_t) * g->nseeds, hipMemcpyDeviceToHost, s));
+    CHKH(hipStreamSynchronize(s));
+    g->seed_rank_host.swap(h);
+    return EBBKC_OK;
+}
+
+// A set of slots and their sub-branches, built from n items: ids (edges by
+// rank, or vertices by position) and sizes (by id, or by item).
+struct SlotSet {
+    DBuf<int32_t> seed, c, rthr, order;
+    DBuf<int64_t> roff, voff;
+    DBuf<uint64_t> rows, ned;
+    DBuf<int32_t> gid;
+    DBuf<int16_t> col;
+    SizeCounts count;
+    SeedSums tot{0, 0, 0};
+};
+
+static ebbkc_status build_slots(ebbkc_graph* g, const int32_t* id, const int32_t* size, bool by_id, int64_t n,
+                                bool vertex, SlotSet& S, hipStream_t s) {
+    int* err = (int*)(g->d_counters + 6);
+    const int64_t nt = (n + SEED_TILE - 1) / SEED_TILE;
+    // tile sums, then the totals and the sizes' counts (read back together)
+    struct Head {
+        SeedSums tot;
+        unsigned long long bins[SIZE_BINS];
+    } h{};
+    DBuf<SeedSums> part;
+    DBuf<Head> head;
+    CHKH(part.alloc(nt));
+    CHKH(head.alloc(1));
+    CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
+    CHKH(hipMemsetAsync(head.p, 0, sizeof(Head), s));
+    if (n > 0) {
+        hipLaunchKernelGGL(k_seed_sums, dim3((unsigned)nt), dim3(SEED_BLOCK), 0, s, id, size, by_id, n, part.p,
+                           head.p->bins, err);
+        hipLaunchKernelGGL(k_seed_parts, dim3(1), dim3(SEED_BLOCK), 0, s, part.p, nt, &head.p->tot);
+    }
+    int herr = 0;
+    CHKH(hipMemcpyAsync(&h, head.p, sizeof(Head), hipMemcpyDeviceToHost, s));
+    CHKH(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
+    CHKH(hipStreamSynchronize(s));
+    if (herr & ERR_WIDTH) return EBBKC_E_WIDTH;
+    S.tot = h.tot;
+    for (int c = 0; c < SIZE_BINS; ++c) S.count.n[c] = (int64_t)h.bins[c];
+    const int64_t ns = S.tot.slots;
+    CHKH(S.seed.alloc(ns));
+    CHKH(S.c.alloc(ns));
+    if (vertex) CHKH(S.rthr.alloc(ns));
+    CHKH(S.order.alloc(ns));
+    CHKH(S.roff.alloc(ns));
+    CHKH(S.voff.alloc(ns));
+    CHKH(S.rows.alloc(S.tot.words));
+    CHKH(S.gid.alloc(S.tot.vtx));
+    CHKH(S.col.alloc(S.tot.vtx));
+    CHKH(S.ned.alloc(ns));
+    if (ns == 0) return EBBKC_OK;
+    DBuf<uint8_t> key;
+    DBuf<int64_t> hist, htmp;
+    CHKH(key.alloc(ns));
+    CHKH(hist.alloc(radix_hist_elems(ns)));
+    CHKH(htmp.alloc(scan_tmp_elems(radix_hist_elems(ns)) + 64));
+    hipLaunchKernelGGL(k_seed_fill, dim3((unsigned)nt), dim3(SEED_BLOCK), 0, s, id, size, by_id, n, part.p, S.seed.p,
+                       S.c.p, S.rthr.p, S.roff.p, S.voff.p, key.p);
+    CHKH(hipGetLastError());
+    // the slot order: by width class, largest sub-branches first
+    CHKH(bin_sort_u8(key.p, ns, (uint32_t*)S.order.p, hist.p, htmp.p, s));
+    for (int W = MAX_W; W >= 1; --W) {
+        const int64_t nw = S.count.of_class(W);
+        if (!nw) continue;
+        BuildArgs b{};
+        b.G = graph_view(g);
+        b.list = S.order.p + S.count.class_start(W);
+        b.n = nw;
+        b.seed_eid = S.seed.p;
+        b.seed_c = S.c.p;
+        b.seed_rthr = S.rthr.p;
+        b.row_off = S.roff.p;
+        b.vtx_off = S.voff.p;
+        b.rows = S.rows.p;
+        b.gid = S.gid.p;
+        b.col = S.col.p;
+        b.nedges = S.ned.p;
+        b.vcol = g->opt.ordering == EBBKC_ORDER_COLOR ? g->vcol : nullptr;
+        b.next = (unsigned long long*)(g->d_counters + W - 1);
+        b.err = err;
+        CHKH(launch_build(W, b, g->cu_count, s));
+    }
+    CHKH(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
+    CHKH(hipStreamSynchronize(s));
+    if (herr & ERR_WIDTH) return EBBKC_E_WIDTH;
+    return EBBKC_OK;
+}
 
 ebbkc_status arena_impl(ebbkc_graph* g, hipStream_t s) {
     if (g->arena_built) return EBBKC_OK;
     ebbkc_status st = ensure_counters(g);
     if (st) return st;
-    hipEvent_t e0, e1;
-    CHKH(hipEventCreate(&e0));
-    CHKH(hipEventCreate(&e1));
-    CHKH(hipEventRecord(e0, s));
     st = subsize_impl(g, s);
     if (st) return st;
-    const int64_t m = g->m;
-    DBuf<int32_t> flag, srank;
-    DBuf<int64_t> pos, tmp, rwords, vcount;
-    CHKH(flag.alloc(m));
-    CHKH(pos.alloc(m + 1));
-    CHKH(tmp.alloc(scan_tmp_elems(m + 1) + 64));
-    CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
-    int* err = (int*)(g->d_counters + 6);
-    if (m) hipLaunchKernelGGL(k_seed_flags, dim3(grid_for(m)), dim3(256), 0, s, g->byrank, g->subsize, m, flag.p);
-    CHKH(exclusive_scan_i32(flag.p, pos.p, m, pos.p + m, tmp.p, s));
-    int64_t ns = 0;
-    CHKH(hipMemcpyAsync(&ns, pos.p + m, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    CHKH(hipStreamSynchronize(s));
-    DBuf<int32_t> seid, sc;
-    DBuf<int64_t> roff, voff;
-    CHKH(seid.alloc(ns));
-    CHKH(sc.alloc(ns));
-    CHKH(srank.alloc(ns));
-    CHKH(rwords.alloc(ns + 1));
-    CHKH(vcount.alloc(ns + 1));
-    CHKH(roff.alloc(ns + 1));
-    CHKH(voff.alloc(ns + 1));
-    if (m)
-        hipLaunchKernelGGL(k_seed_fill, dim3(grid_for(m)), dim3(256), 0, s, g->byrank, g->subsize, flag.p, pos.p, m,
-                           seid.p, sc.p, srank.p, rwords.p, vcount.p, err);
-    CHKH(exclusive_scan_i64(rwords.p, roff.p, ns, roff.p + ns, tmp.p, s));
-    CHKH(exclusive_scan_i64(vcount.p, voff.p, ns, voff.p + ns, tmp.p, s));
-    int64_t tot[2] = {0, 0};
-    int herr = 0;
-    CHKH(hipMemcpyAsync(&tot[0], roff.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    CHKH(hipMemcpyAsync(&tot[1], voff.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    CHKH(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
-    g->seed_rank_host.resize((size_t)ns);
-    if (ns) CHKH(hipMemcpyAsync(g->seed_rank_host.data(), srank.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost, s));
-    CHKH(hipStreamSynchronize(s));
-    if (herr & ERR_WIDTH) return EBBKC_E_WIDTH;
-    SlotArrays out;
-    st = build_slots(g, ns, seid.p, sc.p, nullptr, roff.p, voff.p, tot, tmp.p, out, s);
+    SlotSet S;
+    st = build_slots(g, g->byrank, g->subsize, true, g->m, false, S, s);
     if (st) return st;
-    CHKH(hipEventRecord(e1, s));
-    CHKH(hipStreamSynchronize(s));
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    g->arena_ms = ms;
-    g->nseeds = ns;
-    g->seed_eid = seid.release();
-    g->seed_c = sc.release();
-    g->row_off = roff.release();
-    g->vtx_off = voff.release();
-    g->arows = out.rows;
-    g->agid = out.gid;
-    g->acol = out.col;
-    g->nedges = out.ned;
-    g->arena_bytes = (int64_t)(tot[0] * 8 + tot[1] * 6 + ns * 32);
+    g->nseeds = S.tot.slots;
+    g->seed_eid = S.seed.release();
+    g->seed_c = S.c.release();
+    g->seed_order = S.order.release();
+    g->seed_sizes = S.count;
+    g->row_off = S.roff.release();
+    g->vtx_off = S.voff.release();
+    g->arows = S.rows.release();
+    g->agid = S.gid.release();
+    g->acol = S.col.release();
+    g->nedges = S.ned.release();
+    g->arena_bytes = (int64_t)(S.tot.words * 8 + S.tot.vtx * 6 + S.tot.slots * 32);
     g->device_bytes += g->arena_bytes;
     g->arena_built = true;
-    return EBBKC_OK;
-}
-
-// The sub-branches of ns slots -- seed edges (srthr null) or vertices with
-// the rank threshold of their out-edges -- built per width class into newly
-// allocated rows / gid / col / nedges (owned by the caller on success).
-static ebbkc_status build_slots(ebbkc_graph* g, int64_t ns, const int32_t* seid, const int32_t* sc,
-                                const int32_t* srthr, const int64_t* roff, const int64_t* voff, const int64_t tot[2],
-                                int64_t* tmp, SlotArrays& out, hipStream_t s) {
-    int* err = (int*)(g->d_counters + 6);
-    int herr = 0;
-    DBuf<uint64_t> rows, ned;
-    DBuf<int32_t> gid;
-    DBuf<int16_t> col;
-    CHKH(rows.alloc(tot[0]));
-    CHKH(gid.alloc(tot[1]));
-    CHKH(col.alloc(tot[1]));
-    CHKH(ned.alloc(ns));
-    // per width class: the slot list, then the build kernel
-    DBuf<int32_t> cflag, clist;
-    DBuf<int64_t> cpos;
-    CHKH(cflag.alloc(ns));
-    CHKH(clist.alloc(ns));
-    CHKH(cpos.alloc(ns + 1));
-    for (int W = MAX_W; W >= 1 && ns > 0; --W) {
-        hipLaunchKernelGGL(k_class_flags, dim3(grid_for(ns)), dim3(256), 0, s, sc, ns, W, cflag.p);
-        CHKH(exclusive_scan_i32(cflag.p, cpos.p, ns, cpos.p + ns, tmp, s));
-        hipLaunchKernelGGL(k_class_fill, dim3(grid_for(ns)), dim3(256), 0, s, cflag.p, cpos.p, ns, clist.p);
-        int64_t nw = 0;
-        CHKH(hipMemcpyAsync(&nw, cpos.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        CHKH(hipStreamSynchronize(s));
-        if (!nw) continue;
-        CHKH(hipMemsetAsync(g->d_counters + W - 1, 0, sizeof(uint64_t), s));
-        BuildArgs b{};
-        b.G = graph_view(g);
-        b.list = clist.p;
-        b.n = nw;
-        b.seed_eid = seid;
-        b.seed_c = sc;
-        b.seed_rthr = srthr;
-        b.row_off = roff;
-        b.vtx_off = voff;
-        b.rows = rows.p;
-        b.gid = gid.p;
-        b.col = col.p;
-        b.nedges = ned.p;
-        b.vcol = g->opt.ordering == EBBKC_ORDER_COLOR ? g->vcol : nullptr;
-        b.next = (unsigned long long*)(g->d_counters + W - 1);
-        b.err = err;
-        CHKH(launch_build(W, b, g->cu_count, s));
-        CHKH(hipStreamSynchronize(s));  // clist is reused by the next class
-    }
-    CHKH(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
-    CHKH(hipStreamSynchronize(s));
-    if (herr & ERR_WIDTH) return EBBKC_E_WIDTH;
-    out.rows = rows.release();
-    out.gid = gid.release();
-    out.col = col.release();
-    out.ned = ned.release();
     return EBBKC_OK;
 }
 
 // Node-parallel VBBkC (ordering DEGEN_VERTEX_NP): one slot per vertex v with a
 // non-empty N+(v) (neighbours later in the degeneracy order), its sub-branch
 // G[N+(v)] built by the same kernel (the neighbourhood through edges ranked
-// after v's first out-edge, all edges among it), in position order.
+// after v's first out-edge, all edges among it), in position order.  Edges are
+// ranked lexicographically by their endpoints' positions, so the vertex whose
+// slot follows R out-edges has the out-edges ranked [R, R + |N+(v)|).
 static ebbkc_status vertex_arena_impl(ebbkc_graph* g, hipStream_t s) {
     VertexArena& A = g->varena;
     if (A.built) return EBBKC_OK;
     ebbkc_status st = ensure_counters(g);
     if (st) return st;
     const int32_t n = g->n;
-    DBuf<int32_t> cout, byvpos, flag, seid, sc, srthr, srank;
-    DBuf<int64_t> rstart, pos, tmp, rwords, vcount, roff, voff;
+    DBuf<int32_t> cout, byvpos;
     CHKH(cout.alloc(n));
     CHKH(byvpos.alloc(n));
-    CHKH(flag.alloc(n));
-    CHKH(rstart.alloc(n + 1));
-    CHKH(pos.alloc(n + 1));
-    CHKH(tmp.alloc(scan_tmp_elems(n + 1) + 64));
-    CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
-    int* err = (int*)(g->d_counters + 6);
-    if (n) {
+    if (n)
         hipLaunchKernelGGL(k_vertex_out, dim3(grid_for(n)), dim3(256), 0, s, g->rp, g->ci, g->vpos, n, cout.p,
                            byvpos.p);
-        hipLaunchKernelGGL(k_vertex_flags, dim3(grid_for(n)), dim3(256), 0, s, cout.p, n, flag.p);
-    }
-    CHKH(exclusive_scan_i32(cout.p, rstart.p, n, rstart.p + n, tmp.p, s));
-    CHKH(exclusive_scan_i32(flag.p, pos.p, n, pos.p + n, tmp.p, s));
-    int64_t ns = 0;
-    CHKH(hipMemcpyAsync(&ns, pos.p + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    CHKH(hipStreamSynchronize(s));
-    CHKH(seid.alloc(ns));
-    CHKH(sc.alloc(ns));
-    CHKH(srthr.alloc(ns));
-    CHKH(srank.alloc(ns));
-    CHKH(rwords.alloc(ns + 1));
-    CHKH(vcount.alloc(ns + 1));
-    CHKH(roff.alloc(ns + 1));
-    CHKH(voff.alloc(ns + 1));
-    if (n)
-        hipLaunchKernelGGL(k_vertex_fill, dim3(grid_for(n)), dim3(256), 0, s, cout.p, byvpos.p, rstart.p, flag.p,
-                           pos.p, n, seid.p, sc.p, srthr.p, srank.p, rwords.p, vcount.p, err);
-    CHKH(exclusive_scan_i64(rwords.p, roff.p, ns, roff.p + ns, tmp.p, s));
-    CHKH(exclusive_scan_i64(vcount.p, voff.p, ns, voff.p + ns, tmp.p, s));
-    int64_t tot[2] = {0, 0};
-    int herr = 0;
-    CHKH(hipMemcpyAsync(&tot[0], roff.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    CHKH(hipMemcpyAsync(&tot[1], voff.p + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    CHKH(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s));
-    std::vector<int32_t> rank_host((size_t)ns);
-    if (ns) CHKH(hipMemcpyAsync(rank_host.data(), srank.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost, s));
-    CHKH(hipStreamSynchronize(s));
-    if (herr & ERR_WIDTH) return EBBKC_E_WIDTH;
-    SlotArrays out;
-    st = build_slots(g, ns, seid.p, sc.p, srthr.p, roff.p, voff.p, tot, tmp.p, out, s);
+    SlotSet S;
+    st = build_slots(g, byvpos.p, cout.p, false, n, true, S, s);
     if (st) return st;
-    A.nseeds = ns;
-    A.seed_v = seid.release();
-    A.seed_c = sc.release();
-    A.seed_rthr = srthr.release();
-    A.row_off = roff.release();
-    A.vtx_off = voff.release();
-    A.rows = out.rows;
-    A.gid = out.gid;
-    A.col = out.col;
-    A.nedges = out.ned;
-    A.rank_host.swap(rank_host);
-    A.bytes = (int64_t)(tot[0] * 8 + tot[1] * 6 + ns * 36);
+    A.nseeds = S.tot.slots;
+    A.seed_v = S.seed.release();
+    A.seed_c = S.c.release();
+    A.seed_rthr = S.rthr.release();
+    A.seed_order = S.order.release();
+    A.seed_sizes = S.count;
+    A.row_off = S.roff.release();
+    A.vtx_off = S.voff.release();
+    A.rows = S.rows.release();
+    A.gid = S.gid.release();
+    A.col = S.col.release();
+    A.nedges = S.ned.release();
+    A.bytes = (int64_t)(S.tot.words * 8 + S.tot.vtx * 6 + S.tot.slots * 36);
     g->device_bytes += A.bytes;
     A.built = true;
     return EBBKC_OK;
@@ -482,13 +528,14 @@ static void swap_arenas(ebbkc_graph* g) {
     std::swap(g->nseeds, A.nseeds);
     std::swap(g->seed_eid, A.seed_v);
     std::swap(g->seed_c, A.seed_c);
+    std::swap(g->seed_order, A.seed_order);
+    std::swap(g->seed_sizes, A.seed_sizes);
     std::swap(g->row_off, A.row_off);
     std::swap(g->vtx_off, A.vtx_off);
     std::swap(g->arows, A.rows);
     std::swap(g->agid, A.gid);
     std::swap(g->acol, A.col);
     std::swap(g->nedges, A.nedges);
-    std::swap(g->seed_rank_host, A.rank_host);
     std::swap(g->arena_built, A.built);
     g->np_active = !g->np_active;
 }
@@ -496,6 +543,11 @@ static void swap_arenas(ebbkc_graph* g) {
 static ebbkc_status read_total(ebbkc_graph* g, uint64_t* out, hipStream_t s) {
     CHKH(hipMemcpyAsync(g->h_counters, g->d_counters, CNT_WORDS * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     CHKH(hipStreamSynchronize(s));
+    for (int w = 0; w < MAX_W; ++w) {
+        float ms = 0.f;
+        if (g->tev_set[w] && hipEventElapsedTime(&ms, g->tev[w][0], g->tev[w][1]) == hipSuccess) g->last_ms[w] = ms;
+        g->tev_set[w] = false;
+    }
     const int err = (int)g->h_counters[6];
     if (err & ERR_WIDTH) return EBBKC_E_WIDTH;
     if (err & ERR_DEPTH) return EBBKC_E_K_RANGE;
@@ -567,9 +619,49 @@ static size_t task_bytes(int64_t n, int64_t T) {
            rnd256((size_t)(scan_tmp_elems(hn) + 64) * 8) + 4096;
 }
 
-// One search launch per width class over a sorted task list (classes are
-// contiguous).  list = false: counts (per_task optional); list = true: tuples.
-static ebbkc_status run_tasks(ebbkc_graph* g, int32_t k, const int64_t* tsorted, const uint64_t ccount[4],
+// The tasks of one width class: explicit words, then whole roots of slots.
+struct ClassTasks {
+    const int64_t* tasks = nullptr;
+    int64_t ntasks = 0;
+    const int32_t* slots = nullptr;
+    int64_t nslots = 0;
+    int cmax = 64 * MAX_W;  // no sub-branch of the class's tasks is larger
+};
+struct TaskPlan {
+    ClassTasks cls[MAX_W];
+    // classes contiguous in one sorted list of explicit tasks
+    static TaskPlan of_list(const int64_t* tsorted, const uint64_t ccount[4]) {
+        TaskPlan p;
+        for (int w = 0; w < MAX_W; ++w) {
+            p.cls[w].tasks = tsorted;
+            p.cls[w].ntasks = (int64_t)ccount[w];
+            p.cls[w].cmax = 64 * (w + 1);
+            tsorted += ccount[w];
+        }
+        return p;
+    }
+};
+
+// Whether a search below roots of at most cmax vertices can hand a node over:
+// a pushed node has l in 4 .. l0 - 2 (it is a child) and at most cmax - 2
+// candidates, with at least `bound` l-subsets.  Otherwise the launch goes
+// without the queue: its counters cost every wave several atomics on the same
+// words, and clearing its items a launch.
+static bool can_split(int l0, int cmax, uint64_t bound) {
+    for (int l = 4; l <= l0 - 2; ++l) {
+        if (cmax - 2 < l) break;
+        double b = 1.0;
+        for (int j = 1; j <= l; ++j) b = b * (cmax - 2 - l + j) / j;
+        if (b * 1.0001 >= (double)bound) return true;
+    }
+    return false;
+}
+
+// One search launch per width class.  list = false: counts (per_task
+// optional); list = true: tuples.  per_task and task_off run over the classes
+// in order.  Their times are read once the stream has been waited for
+// (read_total).
+static ebbkc_status run_tasks(ebbkc_graph* g, int32_t k, const TaskPlan& plan,
                               uint64_t* per_task, const uint64_t* task_off, int32_t* out, void* gframes, bool list,
                               hipStream_t s, bool noalloc = false, SplitItem* squeue = nullptr,
                               unsigned long long* sq = nullptr) {
@@ -590,18 +682,21 @@ static ebbkc_status run_tasks(ebbkc_graph* g, int32_t k, const int64_t* tsorted,
     // listings up to k = 8 sort and hash each tuple as it is written
     unsigned long long* fused = list && k <= LIST_FUSED_K ? (unsigned long long*)(g->d_counters + 8) : nullptr;
     if (fused) CHKH(hipMemsetAsync(fused, 0, 2 * sizeof(uint64_t), s));
-    hipEvent_t ev[MAX_W + 1][2] = {};
     int64_t off = 0;
     for (int W = 1; W <= MAX_W; ++W) {
-        const int64_t nt = (int64_t)ccount[W - 1];
+        const ClassTasks& ct = plan.cls[W - 1];
+        const int64_t nt = ct.ntasks + ct.nslots;
+        g->tev_set[W - 1] = false;
         if (!nt) continue;
-        if (!noalloc) {
-            CHKH(hipEventCreate(&ev[W][0]));
-            CHKH(hipEventCreate(&ev[W][1]));
-        }
+        const bool timed = !noalloc && !list;
+        if (timed)
+            for (hipEvent_t& e : g->tev[W - 1])
+                if (!e) CHKH(hipEventCreate(&e));
         SearchArgs a{};
         a.A = ArenaView{g->seed_eid, g->seed_c, g->row_off, g->vtx_off, g->arows, g->agid, g->acol};
-        a.tasks = tsorted + off;
+        a.tasks = ct.tasks;
+        a.nexplicit = ct.ntasks;
+        a.slots = ct.slots;
         a.ntasks = nt;
         a.k = k;
         a.opts = opts_of(g->opt);
@@ -621,23 +716,24 @@ static ebbkc_status run_tasks(ebbkc_graph* g, int32_t k, const int64_t* tsorted,
         a.list_checksums = fused;
         a.gframes = gframes;
         // runtime splitting: counts only (a queued node's count is not a task's own)
-        if (squeue && !list && !truss && !per_task && g->opt.node_split != -1 && g->opt.blocks_per_cu != -1) {
+        const uint64_t bound = g->opt.node_split == 1 ? 0 : (g->opt.node_split >= 2 ? (uint64_t)g->opt.node_split : NODE_SPLIT_DEFAULT);
+        if (squeue && !list && !truss && !per_task && g->opt.node_split != -1 && g->opt.blocks_per_cu != -1 &&
+            can_split(k - 2, ct.cmax, bound)) {
             a.squeue = squeue;
             a.sq = sq;
             a.split_mode = g->opt.node_split == 1 ? SPLIT_FORCED : SPLIT_ON_DEMAND;
-            a.split_bound = g->opt.node_split == 1 ? 0 : (g->opt.node_split >= 2 ? (uint64_t)g->opt.node_split : NODE_SPLIT_DEFAULT);
+            a.split_bound = bound;
             CHKH(launch_sq_reset(sq, squeue, s));
         }
         if (g->opt.count_work && !list && !truss) a.wave_time = (unsigned long long*)(g->d_counters + 32 + 4 * (W - 1));
-        CHKH(hipMemsetAsync(a.next, 0, sizeof(uint64_t), s));
-        if (ev[W][0]) CHKH(hipEventRecord(ev[W][0], s));
+        if (timed) CHKH(hipEventRecord(g->tev[W - 1][0], s));
         if (list) {
             CHKH(launch_list(W, a, g->cu_count, s));
         } else if (truss) {
             TrussArgs t{};
             t.A = a.A;
-            t.tasks = a.tasks;
-            t.ntasks = a.ntasks;
+            t.tasks = a.tasks;  // explicit tasks only
+            t.ntasks = a.nexplicit;
             t.k = k;
             t.opts = a.opts;
             t.tplex = g->opt.t_plex;
@@ -657,16 +753,11 @@ static ebbkc_status run_tasks(ebbkc_graph* g, int32_t k, const int64_t* tsorted,
                 CHKH(hipMemcpyAsync(g->d_counters + 48 + W - 1, sq + SQ_PUSHED, sizeof(uint64_t),
                                     hipMemcpyDeviceToDevice, s));
         }
-        if (ev[W][1]) CHKH(hipEventRecord(ev[W][1], s));
+        if (timed) {
+            CHKH(hipEventRecord(g->tev[W - 1][1], s));
+            g->tev_set[W - 1] = true;
+        }
         off += nt;
-    }
-    CHKH(hipStreamSynchronize(s));
-    for (int W = 1; W <= MAX_W; ++W) {
-        if (!ev[W][0]) continue;
-        float ms = 0.f;
-        if (hipEventElapsedTime(&ms, ev[W][0], ev[W][1]) == hipSuccess && !list) g->last_ms[W - 1] = ms;
-        (void)hipEventDestroy(ev[W][0]);
-        (void)hipEventDestroy(ev[W][1]);
     }
     return EBBKC_OK;
 }
@@ -687,6 +778,59 @@ static Carve carve_for(ebbkc_graph* g, const ScratchSrc& src, size_t bytes) {
 
 static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end, uint64_t* out,
                                hipStream_t s, const ScratchSrc& src);
+
+// slots [*i0, *i1) of the seeds ranked in [r_begin, r_end)
+static ebbkc_status slots_of_ranks(ebbkc_graph* g, int64_t r_begin, int64_t r_end, int64_t* i0, int64_t* i1,
+                                   hipStream_t s) {
+    ebbkc_status st = seed_ranks(g, s);
+    if (st) return st;
+    const auto& SR = g->seed_rank_host;
+    *i0 = std::lower_bound(SR.begin(), SR.end(), (int32_t)std::min<int64_t>(r_begin, INT32_MAX)) - SR.begin();
+    *i1 = std::lower_bound(SR.begin(), SR.end(), (int32_t)std::min<int64_t>(r_end, INT32_MAX)) - SR.begin();
+    return EBBKC_OK;
+}
+
+// The tasks of every slot at l0: the root ranges of the sizes whose roots are
+// split, heaviest first, as segments over the slot order (their number is
+// returned, -1 past 2^32), and the sizes below them as whole roots, taken
+// straight from the slot order.
+static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan& plan, std::vector<TaskSeg>& segs) {
+    const SizeCounts& N = g->seed_sizes;
+    int64_t T = 0, pos = 0;  // pos: first slot of the size in the slot order
+    for (int W = 1; W <= MAX_W; ++W) {
+        ClassTasks& ct = plan.cls[W - 1];
+        struct Range {
+            int usable, first, x0, x1;
+            int64_t slots;
+        };
+        std::vector<Range> rs;
+        ct.slots = nullptr;
+        ct.cmax = 0;
+        for (int c = 64 * W; c > 64 * (W - 1); --c) {
+            const int64_t nc = N.n[c];
+            if (nc == 0) continue;
+            if (c >= l0) {
+                if (!ct.cmax) ct.cmax = c;
+                if (root_split(c, l0, log_thr)) {
+                    root_tasks(c, l0, log_thr, [&](int x0, int x1) {
+                        rs.push_back({x0 == 0 && x1 >= c ? c : c - 1 - x0, (int)pos, x0, x1, nc});
+                    });
+                } else {
+                    if (!ct.slots) ct.slots = g->seed_order + pos;
+                    ct.nslots += nc;
+                }
+            }
+            pos += nc;
+        }
+        std::stable_sort(rs.begin(), rs.end(), [](const Range& a, const Range& b) { return a.usable > b.usable; });
+        for (const Range& r : rs) {
+            segs.push_back(TaskSeg{T, r.first, (int16_t)r.x0, (int16_t)r.x1});
+            T += r.slots;
+            ct.ntasks += r.slots;
+        }
+    }
+    return T < ((int64_t)1 << 32) ? T : -1;
+}
 
 ebbkc_status count_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end, const int64_t* d_eids, int64_t ne,
                         uint64_t* d_per_seed, uint64_t* out, hipStream_t s) {
@@ -720,14 +864,15 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     if (r_end < 0 || r_end > g->m) r_end = g->m;
     if (r_begin < 0) r_begin = 0;
     for (int i = 0; i < 4; ++i) g->last_ms[i] = 0.0;
+    for (bool& b : g->tev_set) b = false;
     for (int i = 0; i < 4; ++i) g->last_work[i] = 0;
     for (int W = 0; W < 4; ++W)
         for (int i = 0; i < 4; ++i) g->last_work_class[W][i] = 0;
-    CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
     unsigned long long* total = (unsigned long long*)(g->d_counters + 4);
     if (k == 3) {  // sum of |V(g_i)| over the seeds
         st = subsize_impl(g, s);
         if (st) return st;
+        CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
         if (r_end > r_begin)
             hipLaunchKernelGGL(k_sum_range, dim3(grid_for(r_end - r_begin)), dim3(256), 0, s, g->byrank, g->subsize,
                                (const uint64_t*)nullptr, r_begin, r_end, total);
@@ -737,11 +882,12 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     st = arena_impl(g, s);
     if (st) return st;
     CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
-    const auto& SR = g->seed_rank_host;
-    const int64_t i0 =
-        std::lower_bound(SR.begin(), SR.end(), (int32_t)std::min<int64_t>(r_begin, INT32_MAX)) - SR.begin();
-    const int64_t i1 =
-        std::lower_bound(SR.begin(), SR.end(), (int32_t)std::min<int64_t>(r_end, INT32_MAX)) - SR.begin();
+    int64_t i0 = 0, i1 = g->nseeds;
+    const bool whole = r_begin == 0 && r_end == g->m;
+    if (!whole) {
+        st = slots_of_ranks(g, r_begin, r_end, &i0, &i1, s);
+        if (st) return st;
+    }
     const int64_t n = i1 - i0;
     if (k == 4) {  // sum of |E(g_i)| over the seeds
         if (n > 0)
@@ -759,9 +905,40 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     const int64_t Tmax = n * (int64_t)(64 * MAX_W);
     const bool deep = k > SEARCH_DEEP_K;
     int64_t waves_max = 0;
-    for (int W = 1; W <= MAX_W; ++W)
+    for (int W = 1; W <= MAX_W && deep; ++W)
         waves_max = std::max(waves_max, search_grid_waves(W, false, Tmax, g->cu_count, g->opt.blocks_per_cu));
     const size_t fbytes = deep ? (size_t)waves_max * GLOBAL_FRAMES * search_frame_bytes(MAX_W) : 0;
+    const size_t qbytes = rnd256((size_t)SQ_CAP * sizeof(SplitItem)) + rnd256(SQ_WORDS * sizeof(uint64_t));
+    if (whole && !noalloc && g->opt.ordering != EBBKC_ORDER_TRUSS) {
+        // every slot: the tasks follow from the slot order, so none is
+        // counted, sorted or stored but the ranges of split roots
+        TaskPlan plan;
+        std::vector<TaskSeg> segs;
+        const int64_t T = plan_whole(g, l0, log_thr, plan, segs);
+        if (T < 0) return EBBKC_E_OOM;
+        const size_t sbytes = rnd256(segs.size() * sizeof(TaskSeg));
+        Carve cv = carve_for(g, src, rnd256((size_t)T * 8) + sbytes + rnd256(fbytes) + qbytes + 4096);
+        if (!cv.base) return e_space;
+        int64_t* tasks = cv.take<int64_t>(T);
+        TaskSeg* dseg = cv.take<TaskSeg>((int64_t)segs.size());
+        void* gframes = deep ? (void*)cv.take<char>((int64_t)fbytes) : nullptr;
+        SplitItem* squeue = cv.take<SplitItem>(SQ_CAP);
+        unsigned long long* sq = cv.take<unsigned long long>(SQ_WORDS);
+        if (!tasks || !dseg || (deep && !gframes) || !squeue || !sq) return e_space;
+        if (T > 0) {
+            CHKH(hipMemcpyAsync(dseg, segs.data(), segs.size() * sizeof(TaskSeg), hipMemcpyHostToDevice, s));
+            hipLaunchKernelGGL(k_task_expand, dim3(grid_for(T)), dim3(256), 0, s, dseg, (int)segs.size(), T,
+                               g->seed_order, tasks);
+            CHKH(hipGetLastError());
+            for (int w = 0, o = 0; w < MAX_W; ++w) {
+                plan.cls[w].tasks = tasks + o;
+                o += plan.cls[w].ntasks;
+            }
+        }
+        st = run_tasks(g, k, plan, nullptr, nullptr, nullptr, gframes, false, s, noalloc, squeue, sq);
+        if (st) return st;
+        return read_total(g, out, s);
+    }
     // count the real number of tasks first with a small scratch, then size
     Carve cv0 = carve_for(g, src, task_bytes(n, 1));
     int32_t* tcount = cv0.take<int32_t>(n);
@@ -774,7 +951,6 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     CHKH(hipMemcpyAsync(&T, toff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     CHKH(hipStreamSynchronize(s));
     if (T == 0) return read_total(g, out, s);
-    const size_t qbytes = rnd256((size_t)SQ_CAP * sizeof(SplitItem)) + rnd256(SQ_WORDS * sizeof(uint64_t));
     Carve cv = carve_for(g, src, task_bytes(n, T) + rnd256(fbytes) + qbytes);
     if (!cv.base) return e_space;
     int64_t* tsorted = nullptr;
@@ -789,9 +965,24 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     if (!squeue || !sq) return e_space;
 
     // ---- search, one launch per width class
-    st = run_tasks(g, k, tsorted, ccount, nullptr, nullptr, nullptr, gframes, false, s, noalloc, squeue, sq);
+    st = run_tasks(g, k, TaskPlan::of_list(tsorted, ccount), nullptr, nullptr, nullptr, gframes, false, s, noalloc,
+                   squeue, sq);
     if (st) return st;
     return read_total(g, out, s);
+}
+
+// The tasks of every slot at l0 when they are the slot order itself: no root
+// split, no sub-branch of 256 vertices.
+static bool plan_unsplit(const ebbkc_graph* g, int l0, double log_thr, TaskPlan& plan, int64_t* T) {
+    const SizeCounts& N = g->seed_sizes;
+    if (N.n[64 * MAX_W]) return false;
+    for (int c = l0; c < 64 * MAX_W; ++c)
+        if (N.n[c] && root_split(c, l0, log_thr)) return false;
+    std::vector<TaskSeg> none;
+    (void)plan_whole(g, l0, log_thr, plan, none);
+    *T = 0;
+    for (const ClassTasks& ct : plan.cls) *T += ct.nslots;
+    return true;
 }
 
 static int bits_for(uint64_t x) {
@@ -821,28 +1012,36 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
         st = arena_impl(g, s);
         if (st) return st;
         CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
-        const auto& SR = g->seed_rank_host;
-        const int64_t i0 =
-            std::lower_bound(SR.begin(), SR.end(), (int32_t)std::min<int64_t>(r_begin, INT32_MAX)) - SR.begin();
-        const int64_t i1 =
-            std::lower_bound(SR.begin(), SR.end(), (int32_t)std::min<int64_t>(r_end, INT32_MAX)) - SR.begin();
+        int64_t i0 = 0, i1 = g->nseeds;
+        const bool whole = r_begin == 0 && r_end == g->m;
+        if (!whole) {
+            st = slots_of_ranks(g, r_begin, r_end, &i0, &i1, s);
+            if (st) return st;
+        }
         const int64_t n = i1 - i0;
         if (n > 0) {
             const int l0 = k - 2;
             const double thr = g->opt.split_threshold > 0 ? (double)g->opt.split_threshold : (double)(1 << 22);
             const double log_thr = g->opt.split_threshold < 0 ? 1e300 : std::log(thr);
-            Carve cv0{(char*)scratch_get(g, task_bytes(n, 1)), 0, 0};
-            cv0.cap = g->scratch_bytes;
-            int32_t* tcount = cv0.take<int32_t>(n);
-            int64_t* toff = cv0.take<int64_t>(n + 1);
-            int64_t* tmp = cv0.take<int64_t>(scan_tmp_elems(n + 1) + 64);
-            if (!tcount || !toff || !tmp) return EBBKC_E_OOM;
-            hipLaunchKernelGGL(k_task_counts, dim3(grid_for(n)), dim3(256), 0, s, g->seed_c, i0, n, l0, log_thr,
-                               tcount);
-            CHKH(exclusive_scan_i32(tcount, toff, n, toff + n, tmp, s));
+            // every slot and none split (nor of size 256, whose place among
+            // the tasks of size 255 the order does not keep): the slot order
+            // is the task order
+            TaskPlan plan;
             int64_t T = 0;
-            CHKH(hipMemcpyAsync(&T, toff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            CHKH(hipStreamSynchronize(s));
+            const bool by_order = whole && g->opt.ordering != EBBKC_ORDER_TRUSS && plan_unsplit(g, l0, log_thr, plan, &T);
+            if (!by_order) {
+                Carve cv0{(char*)scratch_get(g, task_bytes(n, 1)), 0, 0};
+                cv0.cap = g->scratch_bytes;
+                int32_t* tcount = cv0.take<int32_t>(n);
+                int64_t* toff = cv0.take<int64_t>(n + 1);
+                int64_t* tmp = cv0.take<int64_t>(scan_tmp_elems(n + 1) + 64);
+                if (!tcount || !toff || !tmp) return EBBKC_E_OOM;
+                hipLaunchKernelGGL(k_task_counts, dim3(grid_for(n)), dim3(256), 0, s, g->seed_c, i0, n, l0, log_thr,
+                                   tcount);
+                CHKH(exclusive_scan_i32(tcount, toff, n, toff + n, tmp, s));
+                CHKH(hipMemcpyAsync(&T, toff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+                CHKH(hipStreamSynchronize(s));
+            }
             if (T > 0) {
                 // pass 1 runs the count kernel, pass 2 the listing kernel: frames
                 // in device memory when either needs them
@@ -852,23 +1051,26 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
                 const size_t fbytes = deep ? (size_t)std::max(waves, wsearch) * GLOBAL_FRAMES *
                                                  std::max(list_frame_bytes(MAX_W), search_frame_bytes(MAX_W))
                                            : 0;
-                const size_t need = task_bytes(n, T) + rnd256(fbytes) + 2 * rnd256((size_t)(T + 1) * 8) +
+                const size_t need = (by_order ? 4096 : task_bytes(n, T)) + rnd256(fbytes) + 2 * rnd256((size_t)(T + 1) * 8) +
                                     rnd256((size_t)(scan_tmp_elems(T + 1) + 64) * 8);
                 if (!scratch_get(g, need)) return EBBKC_E_OOM;
                 Carve cv{(char*)g->scratch, 0, g->scratch_bytes};
-                int64_t* tsorted = nullptr;
-                uint64_t ccount[4] = {0, 0, 0, 0};
-                int64_t T2 = 0;
-                st = make_tasks(g, i0, n, l0, log_thr, s, cv, &tsorted, &T2, ccount);
-                if (st) return st;
+                if (!by_order) {
+                    int64_t* tsorted = nullptr;
+                    uint64_t ccount[4] = {0, 0, 0, 0};
+                    int64_t T2 = 0;
+                    st = make_tasks(g, i0, n, l0, log_thr, s, cv, &tsorted, &T2, ccount);
+                    if (st) return st;
+                    plan = TaskPlan::of_list(tsorted, ccount);
+                }
                 void* gframes = deep ? (void*)cv.take<char>((int64_t)fbytes) : nullptr;
                 uint64_t* per_task = cv.take<uint64_t>(T + 1);
                 uint64_t* task_off = cv.take<uint64_t>(T + 1);
                 int64_t* stmp = cv.take<int64_t>(scan_tmp_elems(T + 1) + 64);
                 if ((deep && !gframes) || !per_task || !task_off || !stmp) return EBBKC_E_OOM;
                 // pass 1: per-task counts
-                CHKH(hipMemsetAsync(g->d_counters + 4, 0, 4 * sizeof(uint64_t), s));
-                st = run_tasks(g, k, tsorted, ccount, per_task, nullptr, nullptr, gframes, false, s);
+                CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
+                st = run_tasks(g, k, plan, per_task, nullptr, nullptr, gframes, false, s);
                 if (st) return st;
                 st = read_total(g, &N, s);
                 if (st) return st;
@@ -876,7 +1078,8 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
                 if (N > cap) return EBBKC_E_BUFFER_TOO_SMALL;
                 CHKH(exclusive_scan_i64((const int64_t*)per_task, (int64_t*)task_off, T, nullptr, stmp, s));
                 // pass 2: tuples
-                st = run_tasks(g, k, tsorted, ccount, per_task, task_off, d_buf, gframes, true, s);
+                CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
+                st = run_tasks(g, k, plan, per_task, task_off, d_buf, gframes, true, s);
                 if (st) return st;
                 uint64_t herr = 0;
                 CHKH(hipMemcpyAsync(&herr, g->d_counters + 6, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
@@ -989,6 +1192,8 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
     std::vector<int64_t> tasks[MAX_W];
     std::vector<int64_t> where[MAX_W];
     std::vector<uint64_t> res((size_t)ne, 0);
+    st = seed_ranks(g, s);
+    if (st) return st;
     const auto& SR = g->seed_rank_host;
     for (int64_t i = 0; i < ne; ++i) {
         const int64_t e = he[(size_t)i];
@@ -1020,7 +1225,7 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
         for (int W = 0; W < MAX_W; ++W) flat.insert(flat.end(), tasks[W].begin(), tasks[W].end());
         CHKH(hipMemcpyAsync(dt, flat.data(), sizeof(int64_t) * T, hipMemcpyHostToDevice, s));
         CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
-        st = run_tasks(g, k, dt, ccount, pt, nullptr, nullptr, gframes, false, s);
+        st = run_tasks(g, k, TaskPlan::of_list(dt, ccount), pt, nullptr, nullptr, gframes, false, s);
         if (st) return st;
         uint64_t tot = 0;
         st = read_total(g, &tot, s);

@@ -8,6 +8,22 @@
 
 #include "../../include/ebbkc.h"
 
+// Slots by sub-branch size; the slot order holds the classes W = 1..4 one after
+// the other, each with its largest sub-branches first.
+struct SizeCounts {
+    int64_t n[257] = {};
+    int64_t of_class(int W) const {
+        int64_t t = 0;
+        for (int c = 64 * (W - 1) + 1; c <= 64 * W; ++c) t += n[c];
+        return t;
+    }
+    int64_t class_start(int W) const {
+        int64_t t = 0;
+        for (int c = 1; c <= 64 * (W - 1); ++c) t += n[c];
+        return t;
+    }
+};
+
 // Sub-branches of the node-parallel VBBkC roots (one slot per vertex with a
 // non-empty N+(v), in position order); swapped with the edge arena while a
 // count runs on them.
@@ -17,13 +33,14 @@ struct VertexArena {
     int32_t* seed_v = nullptr;     // vertex of each slot
     int32_t* seed_c = nullptr;     // |N+(v)|
     int32_t* seed_rthr = nullptr;  // rank of v's first out-edge minus one
+    int32_t* seed_order = nullptr;
+    SizeCounts seed_sizes;
     int64_t* row_off = nullptr;
     int64_t* vtx_off = nullptr;
     uint64_t* rows = nullptr;
     int32_t* gid = nullptr;
     int16_t* col = nullptr;
     uint64_t* nedges = nullptr;
-    std::vector<int32_t> rank_host;  // rank of each slot's first out-edge (ascending)
     int64_t bytes = 0;
 };
 
@@ -64,9 +81,11 @@ struct ebbkc_graph {
 
     // sub-branch arena (built on the first count with k >= 4)
     bool arena_built = false;
-    int64_t nseeds = 0;          // edges with |V(g_i)| >= 2, in rank order
+    int64_t nseeds = 0;          // edges with |V(g_i)| >= 1, in rank order
     int32_t* seed_eid = nullptr;
     int32_t* seed_c = nullptr;
+    int32_t* seed_order = nullptr; // slots by width class, largest sub-branches first
+    SizeCounts seed_sizes;         // slots per |V(g_i)|
     int64_t* row_off = nullptr;
     int64_t* vtx_off = nullptr;
     uint64_t* arows = nullptr;
@@ -74,10 +93,9 @@ struct ebbkc_graph {
     int16_t* acol = nullptr;
     uint64_t* nedges = nullptr;
     int64_t arena_bytes = 0;
-    std::vector<int32_t> seed_rank_host; // rank of each slot (ascending)
+    std::vector<int32_t> seed_rank_host; // rank of each slot (ascending; filled on demand)
     std::vector<int32_t> seed_c_host;    // |V(g_i)| of each slot (filled on demand)
     std::vector<int32_t> rank_host;      // rank of each edge (filled on demand)
-    double arena_ms = 0.0;
 
     // per-call scratch (grown on demand, freed by destroy)
     void* scratch = nullptr;
@@ -87,6 +105,8 @@ struct ebbkc_graph {
     size_t scratch_bytes = 0;
     uint64_t* d_counters = nullptr;   // small device counters
     uint64_t* h_counters = nullptr;   // pinned mirror
+    hipEvent_t tev[4][2] = {};        // around each class's launch (created on first use)
+    bool tev_set[4] = {};             // recorded by the call in progress
     double last_ms[4] = {0, 0, 0, 0};
     uint64_t last_work[4] = {0, 0, 0, 0};
     uint64_t last_work_class[4][4] = {};

@@ -124,9 +124,10 @@ __global__ __launch_bounds__(256) void k_list(SearchArgs a) {
         if (lane == 0) it = atomicAdd(a.next, 1ull);
         it = uni64(__shfl(it, 0, 64));
         if ((int64_t)it >= a.ntasks) break;
-        const int64_t task = a.tasks[it];
-        const int64_t slot = task_slot(task);
-        const int x0 = task_x0(task), x1 = task_x1(task);
+        const bool listed = (int64_t)it < a.nexplicit;
+        const int64_t task = listed ? a.tasks[it] : 0;
+        const int64_t slot = listed ? task_slot(task) : (int64_t)a.slots[(int64_t)it - a.nexplicit];
+        const int x0 = listed ? task_x0(task) : 0, x1 = listed ? task_x1(task) : 64 * W;
         const int c = uniform_i32(a.A.seed_c[slot]);
         const int64_t ro = a.A.row_off[slot], vo = a.A.vtx_off[slot];
         const int32_t e = a.A.seed_eid[slot];

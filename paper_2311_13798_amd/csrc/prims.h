@@ -23,4 +23,8 @@ int64_t radix_hist_elems(int64_t n);
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
                           int bits, int64_t* hist, int64_t* tmp, hipStream_t s);
 
+// Stable counting sort of n byte keys: out[i] = index of the i-th item in key
+// order.  hist and tmp as for radix_sort_u64.
+hipError_t bin_sort_u8(const uint8_t* keys, int64_t n, uint32_t* out, int64_t* hist, int64_t* tmp, hipStream_t s);
+
 }  // namespace ebb

@@ -108,7 +108,8 @@ constexpr int RS_ITEMS = 16;
 constexpr int RS_TILE = RS_BLOCK * RS_ITEMS;
 constexpr int RS_WAVES = RS_BLOCK / EBB_WAVE;
 
-__global__ void k_rs_hist(const uint64_t* __restrict__ keys, int64_t n, int shift, int64_t nb,
+template <typename K>
+__global__ void k_rs_hist(const K* __restrict__ keys, int64_t n, int shift, int64_t nb,
                           int64_t* __restrict__ hist) {
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0;
@@ -122,8 +123,10 @@ __global__ void k_rs_hist(const uint64_t* __restrict__ keys, int64_t n, int shif
     hist[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
 
-__global__ void k_rs_scatter(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                             uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, int64_t n, int shift,
+// vin null: an item's value is its index; kout / vout null: not written
+template <typename K>
+__global__ void k_rs_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
+                             K* __restrict__ kout, uint32_t* __restrict__ vout, int64_t n, int shift,
                              int64_t nb, const int64_t* __restrict__ off) {
     __shared__ uint32_t run[256];
     __shared__ uint32_t wcnt[RS_WAVES][256];
@@ -133,8 +136,8 @@ __global__ void k_rs_scatter(const uint64_t* __restrict__ kin, const uint32_t* _
     for (int j = 0; j < RS_ITEMS; ++j) {
         int64_t i = base + j * RS_BLOCK + tid;
         bool valid = i < n;
-        uint64_t key = valid ? kin[i] : 0;
-        uint32_t val = (valid && vin) ? vin[i] : 0;
+        K key = valid ? kin[i] : 0;
+        uint32_t val = !valid ? 0 : (vin ? vin[i] : (uint32_t)i);
         int d = (int)((key >> shift) & 0xFF);
         uint64_t peers = ballot(valid);
 #pragma unroll
@@ -152,7 +155,7 @@ __global__ void k_rs_scatter(const uint64_t* __restrict__ kin, const uint32_t* _
             uint32_t before = 0;
             for (int q = 0; q < w; ++q) before += wcnt[q][d];
             int64_t pos = off[(int64_t)d * nb + blockIdx.x] + run[d] + before + lrank;
-            kout[pos] = key;
+            if (kout) kout[pos] = key;
             if (vout) vout[pos] = val;
         }
         __syncthreads();
@@ -179,6 +182,17 @@ hipError_t exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_
 
 int64_t radix_hist_elems(int64_t n) { return 256 * ((n + RS_TILE - 1) / RS_TILE) + 1; }
 
+hipError_t bin_sort_u8(const uint8_t* keys, int64_t n, uint32_t* out, int64_t* hist, int64_t* tmp, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    const int64_t nb = (n + RS_TILE - 1) / RS_TILE;
+    hipLaunchKernelGGL(k_rs_hist<uint8_t>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, keys, n, 0, nb, hist);
+    hipError_t e = exclusive_scan_i64(hist, hist, 256 * nb, nullptr, tmp, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_rs_scatter<uint8_t>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, keys, (const uint32_t*)nullptr,
+                       (uint8_t*)nullptr, out, n, 0, nb, hist);
+    return hipGetLastError();
+}
+
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
                           int bits, int64_t* hist, int64_t* tmp, hipStream_t s) {
     if (n <= 1 || bits <= 0) return hipSuccess;
@@ -188,10 +202,10 @@ hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, ui
     int passes = (bits + 7) / 8;
     for (int p = 0; p < passes; ++p) {
         int shift = p * 8;
-        hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, n, shift, nb, hist);
+        hipLaunchKernelGGL(k_rs_hist<uint64_t>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, n, shift, nb, hist);
         hipError_t e = exclusive_scan_i64(hist, hist, 256 * nb, nullptr, tmp, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, va, kb, vb, n, shift, nb,
+        hipLaunchKernelGGL(k_rs_scatter<uint64_t>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, va, kb, vb, n, shift, nb,
                            hist);
         uint64_t* kt = ka; ka = kb; kb = kt;
         uint32_t* vt = va; va = vb; vb = vt;

@@ -794,11 +794,12 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             took_item = true;
             it = uni64((uint64_t)a.squeue[qitem].it);
         }
-        const int64_t task = a.tasks[it];
-        const int64_t slot = task_slot(task);
+        const bool listed = (int64_t)it < a.nexplicit;
+        const int64_t task = listed ? a.tasks[it] : 0;
+        const int64_t slot = listed ? task_slot(task) : (int64_t)a.slots[(int64_t)it - a.nexplicit];
         // a queued node is a whole node below the root: every first vertex
-        const int x0 = qitem >= 0 ? 0 : task_x0(task);
-        const int x1 = qitem >= 0 ? 64 * W : task_x1(task);
+        const int x0 = !listed || qitem >= 0 ? 0 : task_x0(task);
+        const int x1 = !listed || qitem >= 0 ? 64 * W : task_x1(task);
         const int gi = a.task_graph ? uniform_i32(a.task_graph[it]) : 0;
         const int k = a.graph_k ? uniform_i32(a.graph_k[gi]) : a.k;
         int c = 0;
