@@ -23,6 +23,23 @@ constexpr int SEARCH_DEEP_K = 2 + 2 * LDS_FRAMES + 4;
 constexpr int LIST_DEEP_K = 2 + 2 * LIST_LDS_FRAMES + 2;
 constexpr int MAX_K = 2 + 2 * (LDS_FRAMES + GLOBAL_FRAMES) + 4;
 
+// How the waves of a persistent launch draw its n items.  The first `heavy`
+// items are one ticket each; the others are dealt into nchunks tickets, chunk
+// j holding heavy + j, heavy + j + nchunks, ... (items are sorted by weight, so
+// strided chunks weigh the same), or, when chunk_len > 0, chunk_len
+// consecutive items each.  A wave's first ticket is its own number, later ones
+// come from the counter.  One counter for all waves serves about 140 M tickets
+// a second (7 ns each, whatever the number of waves), which bounded every
+// launch of light items when each was a ticket of its own: k_search<1> at
+// k = 5 took 7.3 ns per task on R-MAT s18 and on ER(2000, 0.05) alike.
+struct Tickets {
+    unsigned long long* next;
+    int64_t n, heavy, nchunks;
+    int32_t chunk_len;
+    int32_t dealt;  // 1: first tickets by wave number; 0: every ticket from the counter (launches that
+                    // share the device with others, whose workgroups may start late)
+};
+
 // Graph arrays the build kernel reads.
 struct GraphView {
     const int32_t* rp;
@@ -69,7 +86,9 @@ struct BuildArgs {
     const int32_t* vcol;  // colours of G kept in every g_i, or null: each g_i coloured on its own
     const int32_t* seed_rthr;  // vertex slots: seed_eid holds the vertex, its sub-branch is its
                                // neighbourhood through edges ranked after seed_rthr; null: edge slots
+    int64_t heavy;             // list entries drawn one at a time (Tickets)
     unsigned long long* next;
+    Tickets tickets;           // filled by launch_build
     int* err;
 };
 
@@ -158,6 +177,9 @@ struct SearchArgs {
     int64_t nexplicit;
     const int32_t* slots;
     int64_t ntasks;
+    int64_t heavy;              // tasks drawn one at a time, the first ones (Tickets)
+    int32_t shared;             // 1: other launches run beside this one (Tickets.dealt = 0)
+    Tickets tickets;            // filled by launch_search / launch_list
     int32_t k;
     int32_t opts;
     float k4_weight;            // dense 4-clique evaluation cost weight (<= 0: never)

@@ -59,6 +59,7 @@ struct ebbkc_batch {
     void* gframes = nullptr;
     int64_t ntasks = 0;
     uint64_t ccount[4] = {0, 0, 0, 0};
+    int64_t heavy[4] = {0, 0, 0, 0};  // tasks of each class drawn one at a time (Tickets)
     int32_t kmax = 0;
     // host results
     unsigned long long* h_tot = nullptr;
@@ -136,22 +137,35 @@ __global__ void k_bgather(const int64_t* __restrict__ tasks, const int32_t* __re
     }
 }
 
-// tasks per width class: counted per lane, summed per wave, one atomic per
-// wave and class (one atomic per task on four counters took 17 s for the
-// 1.46e9 tasks of the 4,096-graph batch)
-__global__ void k_bclass_hist(const uint64_t* __restrict__ keys, int64_t n, int gbits,
-                              unsigned long long* __restrict__ cls) {
-    uint64_t per_class[4] = {0, 0, 0, 0};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int w = (int)((keys[i] >> (8 + gbits)) & 3);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) per_class[q] += q == w ? 1 : 0;
+// Bounds in the sorted keys by binary search, one lane each: lane w < 4 the
+// end of width class w, lane 4 + w (lists sorted by size inside a class) the
+// first task of class w with at most c_light usable vertices.  (A pass over
+// all keys that counts the classes took 0.7 ms for 4 M tasks.)
+__global__ void k_bclass_bounds(const uint64_t* __restrict__ keys, int64_t n, int gbits, int c_light,
+                                unsigned long long* __restrict__ out) {
+    const int t = threadIdx.x;
+    if (t >= 8) return;
+    const uint64_t key = t < 4 ? (uint64_t)(t + 1) << (8 + gbits) : ((uint64_t)(t - 4) << 8) | (uint64_t)(255 - c_light);
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (keys[mid] < key) lo = mid + 1; else hi = mid;
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint64_t t = wave_sum(per_class[q]);
-        if (lane_id() == 0 && t) atomicAdd(&cls[q], (unsigned long long)t);
+    out[t] = (unsigned long long)lo;
+}
+
+// The largest c with at most 2^18 l-subsets for every l <= l0: tasks with that
+// many usable vertices are drawn in chunks.
+int light_size(int l0) {
+    for (int c = 64; c > 8; --c) {
+        double b = 1.0, most = 0.0;
+        for (int j = 1; j <= l0 && j <= c; ++j) {
+            b = b * (c - j + 1) / j;
+            most = std::max(most, b);
+        }
+        if (most <= (double)(1 << 18)) return c;
     }
+    return 8;
 }
 
 // zero the counters and per-graph totals (a kernel, so the captured graph
@@ -291,12 +305,20 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
     CHKB(dev_alloc(b, (void**)&b->tasks, sizeof(int64_t) * total, s));
     CHKB(dev_alloc(b, (void**)&b->tgraph, sizeof(int32_t) * total, s));
     hipLaunchKernelGGL(k_bgather, dim3(gridn(total)), dim3(256), 0, s, tasks, tg, vals, total, b->tasks, b->tgraph);
-    CHKB(hipMemsetAsync(b->ctr, 0, 16 * sizeof(unsigned long long), s));
-    hipLaunchKernelGGL(k_bclass_hist, dim3(gridn(total)), dim3(256), 0, s, keys, total, gbits, b->ctr);
-    unsigned long long cc[4];
+    hipLaunchKernelGGL(k_bclass_bounds, dim3(1), dim3(64), 0, s, keys, total, gbits,
+                       light_size(std::max(1, b->kmax - 2)), b->ctr);
+    uint64_t cc[8];
     CHKB(hipMemcpyAsync(cc, b->ctr, sizeof(cc), hipMemcpyDeviceToHost, s));
     CHKB(hipStreamSynchronize(s));
-    for (int w = 0; w < 4; ++w) b->ccount[w] = cc[w];
+    for (int w = 0; w < 4; ++w) {
+        const uint64_t begin = w ? cc[w - 1] : 0;
+        b->ccount[w] = cc[w] - begin;
+        const uint64_t light = std::min(std::max(cc[4 + w], begin), cc[w]);
+        // at most sixteen single tasks per wave: past them a chunk is a small
+        // part of a wave's share whatever its tasks weigh
+        b->heavy[w] = b->build ? 0
+                               : std::min<int64_t>((int64_t)(light - begin), (int64_t)64 * 16 * b->cu_count);
+    }
     for (auto p : toffs) dev_free(b, p, s);
     void* ptrs[] = {tasks, tg, keys, keys2, vals, vals2, hist, htmp};
     for (void* p : ptrs) dev_free(b, p, s);
@@ -327,6 +349,8 @@ ebbkc_status enqueue(ebbkc_batch* b, hipStream_t s) {
         a.task_graph = b->tgraph + off;
         a.nexplicit = nt;
         a.ntasks = nt;
+        a.heavy = b->heavy[W - 1];
+        a.shared = b->async_mem;
         a.views = b->build ? nullptr : b->views;
         a.bviews = b->build ? b->bviews : nullptr;
         a.graph_k = b->gk;

@@ -369,6 +369,10 @@ static ebbkc_status seed_ranks(ebbkc_graph* g, hipStream_t s) {
     return EBBKC_OK;
 }
 
+// sub-branches up to this size are drawn in chunks when they are built (each
+// takes a wave a few microseconds)
+constexpr int BUILD_LIGHT_C = 40;
+
 // A set of slots and their sub-branches, built from n items: ids (edges by
 // rank, or vertices by position) and sizes (by id, or by item).
 struct SlotSet {
@@ -437,6 +441,7 @@ static ebbkc_status build_slots(ebbkc_graph* g, const int32_t* id, const int32_t
         b.G = graph_view(g);
         b.list = S.order.p + S.count.class_start(W);
         b.n = nw;
+        b.heavy = S.count.larger(BUILD_LIGHT_C, W);
         b.seed_eid = S.seed.p;
         b.seed_c = S.c.p;
         b.seed_rthr = S.rthr.p;
@@ -625,6 +630,7 @@ struct ClassTasks {
     int64_t ntasks = 0;
     const int32_t* slots = nullptr;
     int64_t nslots = 0;
+    int64_t heavy = INT64_MAX;  // tasks drawn one at a time, the first ones
     int cmax = 64 * MAX_W;  // no sub-branch of the class's tasks is larger
 };
 struct TaskPlan {
@@ -698,6 +704,7 @@ static ebbkc_status run_tasks(ebbkc_graph* g, int32_t k, const TaskPlan& plan,
         a.nexplicit = ct.ntasks;
         a.slots = ct.slots;
         a.ntasks = nt;
+        a.heavy = ct.heavy;
         a.k = k;
         a.opts = opts_of(g->opt);
         a.k4_weight = k4_weight_of(g->opt.dense_k4);
@@ -790,6 +797,16 @@ static ebbkc_status slots_of_ranks(ebbkc_graph* g, int64_t r_begin, int64_t r_en
     return EBBKC_OK;
 }
 
+// Whole roots with more than 2^18 l0-subsets are drawn one at a time: a wave
+// tests about one subset per lane and instruction at worst, so a smaller root
+// takes it some tens of microseconds at most, less than its share of the
+// ticket counter (4,096 waves at 7 ns a ticket).
+static bool heavy_root(int c, int l0) {
+    double b = 1.0;
+    for (int j = 1; j <= l0; ++j) b = b * (c - l0 + j) / j;
+    return b > (double)(1 << 18);
+}
+
 // The tasks of every slot at l0: the root ranges of the sizes whose roots are
 // split, heaviest first, as segments over the slot order (their number is
 // returned, -1 past 2^32), and the sizes below them as whole roots, taken
@@ -806,6 +823,7 @@ static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan
         std::vector<Range> rs;
         ct.slots = nullptr;
         ct.cmax = 0;
+        ct.heavy = 0;
         for (int c = 64 * W; c > 64 * (W - 1); --c) {
             const int64_t nc = N.n[c];
             if (nc == 0) continue;
@@ -818,6 +836,7 @@ static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan
                 } else {
                     if (!ct.slots) ct.slots = g->seed_order + pos;
                     ct.nslots += nc;
+                    if (heavy_root(c, l0)) ct.heavy += nc;
                 }
             }
             pos += nc;
@@ -827,6 +846,7 @@ static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan
             segs.push_back(TaskSeg{T, r.first, (int16_t)r.x0, (int16_t)r.x1});
             T += r.slots;
             ct.ntasks += r.slots;
+            ct.heavy += r.slots;
         }
     }
     return T < ((int64_t)1 << 32) ? T : -1;

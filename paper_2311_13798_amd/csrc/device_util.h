@@ -1,5 +1,6 @@
 // device_util.h -- wave-level helpers for the bitmap kernels (wave64).
 #pragma once
+#include "arena.h"
 #include "common.h"
 
 namespace ebb {
@@ -92,6 +93,69 @@ __device__ __forceinline__ void prefix_mask(int c, uint64_t (&p)[W]) {
         int lo = 64 * w;
         p[w] = c >= lo + 64 ? ~0ull : (c > lo ? ((1ull << (c - lo)) - 1) : 0ull);
     }
+}
+
+// The items a wave draws from a launch's Tickets (arena.h); every value is
+// wave-uniform.
+struct Drawn {
+    int64_t cur = 0, left = 0, step = 0;
+    bool started = false;
+    // the next item, or -1 when none is left
+    __device__ __forceinline__ int64_t next(const Tickets& T) {
+        if (left == 0) {
+            const int64_t waves = T.dealt ? (int64_t)gridDim.x * (blockDim.x / EBB_WAVE) : 0;
+            const int64_t total = T.heavy + T.nchunks;
+            uint64_t t;
+            if (!started && T.dealt) {  // consecutive tickets on different compute units
+                t = (uint64_t)(threadIdx.x / EBB_WAVE) * gridDim.x + blockIdx.x;
+                started = true;
+            } else {
+                if (total <= waves) return -1;
+                t = 0;
+                if (lane_id() == 0) t = waves + atomicAdd(T.next, 1ull);
+            }
+            t = uni64(t);
+            if ((int64_t)t >= total) return -1;
+            if ((int64_t)t < T.heavy) {
+                cur = t;
+                left = 1;
+                step = 0;
+            } else if (T.chunk_len > 0) {
+                cur = T.heavy + ((int64_t)t - T.heavy) * T.chunk_len;
+                left = T.n - cur < T.chunk_len ? T.n - cur : T.chunk_len;
+                step = 1;
+            } else {
+                const int64_t j = (int64_t)t - T.heavy;
+                cur = T.heavy + j;
+                left = (T.n - T.heavy - j + T.nchunks - 1) / T.nchunks;
+                step = T.nchunks;
+            }
+        }
+        const int64_t it = cur;
+        cur += step;
+        --left;
+        return it;
+    }
+};
+
+// Tickets of n items for a launch of `waves` waves: every light item dealt to
+// one chunk per wave when nothing heavy comes first (then no wave touches the
+// counter), else two per wave, since the waves come to them at different times.
+// consecutive > 0: chunks of up to that many neighbours, sixteen or more per wave.
+inline Tickets make_tickets(unsigned long long* next, int64_t n, int64_t heavy, int64_t waves, int consecutive,
+                            bool shared) {
+    Tickets T{next, n, heavy < n ? heavy : n, 0, 0, shared ? 0 : 1};
+    const int64_t light = T.n - T.heavy;
+    if (consecutive > 0) {
+        int64_t len = light / (16 * waves);
+        len = len < 1 ? 1 : (len > consecutive ? consecutive : len);
+        T.chunk_len = (int32_t)len;
+        T.nchunks = (light + len - 1) / len;
+    } else {
+        const int64_t most = T.heavy ? 2 * waves : waves;
+        T.nchunks = light < most ? light : most;
+    }
+    return T;
 }
 
 }  // namespace ebb

@@ -17,6 +17,12 @@ struct SizeCounts {
         for (int c = 64 * (W - 1) + 1; c <= 64 * W; ++c) t += n[c];
         return t;
     }
+    // slots of class W with more than c0 vertices
+    int64_t larger(int c0, int W) const {
+        int64_t t = 0;
+        for (int c = 64 * (W - 1) + 1; c <= 64 * W; ++c) t += c > c0 ? n[c] : 0;
+        return t;
+    }
     int64_t class_start(int W) const {
         int64_t t = 0;
         for (int c = 1; c <= 64 * (W - 1); ++c) t += n[c];

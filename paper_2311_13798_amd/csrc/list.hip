@@ -119,14 +119,13 @@ __global__ __launch_bounds__(256) void k_list(SearchArgs a) {
     constexpr bool fused = FUSED;  // k <= 8
     uint64_t ho = 0, hu = 0;
 
+    Drawn drawn;
     for (;;) {
-        unsigned long long it = 0;
-        if (lane == 0) it = atomicAdd(a.next, 1ull);
-        it = uni64(__shfl(it, 0, 64));
-        if ((int64_t)it >= a.ntasks) break;
-        const bool listed = (int64_t)it < a.nexplicit;
+        const int64_t it = drawn.next(a.tickets);
+        if (it < 0) break;
+        const bool listed = it < a.nexplicit;
         const int64_t task = listed ? a.tasks[it] : 0;
-        const int64_t slot = listed ? task_slot(task) : (int64_t)a.slots[(int64_t)it - a.nexplicit];
+        const int64_t slot = listed ? task_slot(task) : (int64_t)a.slots[it - a.nexplicit];
         const int x0 = listed ? task_x0(task) : 0, x1 = listed ? task_x1(task) : 64 * W;
         const int c = uniform_i32(a.A.seed_c[slot]);
         const int64_t ro = a.A.row_off[slot], vo = a.A.vtx_off[slot];
@@ -507,7 +506,7 @@ inline unsigned gridn(int64_t n) {
 }
 
 template <int W, bool FUSED>
-hipError_t launch_list_w(const SearchArgs& a, int cus, hipStream_t s) {
+hipError_t launch_list_w(SearchArgs a, int cus, hipStream_t s) {
     auto kern = k_list<W, FUSED>;
     const size_t smem = 4 * sizeof(ListMem<W>);
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -519,6 +518,7 @@ hipError_t launch_list_w(const SearchArgs& a, int cus, hipStream_t s) {
     int64_t grid = (int64_t)occ * cus, need = (a.ntasks + 3) / 4;
     if (grid > need) grid = need;
     if (grid < 1) grid = 1;
+    a.tickets = make_tickets(a.next, a.ntasks, a.heavy, 4 * grid, 0, false);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), smem, s, a);
     return hipGetLastError();
 }

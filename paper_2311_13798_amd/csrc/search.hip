@@ -20,6 +20,7 @@
 // Nodes with l = 4 or 5 hand their children (l = 2 or 3) to lanes, one child
 // per lane, after renumbering onto one word fewer when the node's candidate
 // set fits; everything above is wave-uniform with the lanes owning rows.
+#include <atomic>
 #include <type_traits>
 
 #include "arena.h"
@@ -769,13 +770,13 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         }
     }
 
+    Drawn drawn;
     for (;;) {
-        unsigned long long it = 0;
+        int64_t it = 0;
         int64_t qitem = -1;
         if (!on_queue) {
-            if (lane == 0) it = atomicAdd(a.next, 1ull);
-            it = uni64(__shfl(it, 0, 64));
-            if ((int64_t)it >= a.ntasks) {
+            it = drawn.next(a.tickets);
+            if (it < 0) {
                 if (!splitting) break;
                 on_queue = true;
                 if (lane == 0) {
@@ -792,11 +793,11 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             qitem = queue_take(a);
             if (qitem < 0) break;
             took_item = true;
-            it = uni64((uint64_t)a.squeue[qitem].it);
+            it = (int64_t)uni64((uint64_t)a.squeue[qitem].it);
         }
-        const bool listed = (int64_t)it < a.nexplicit;
+        const bool listed = it < a.nexplicit;
         const int64_t task = listed ? a.tasks[it] : 0;
-        const int64_t slot = listed ? task_slot(task) : (int64_t)a.slots[(int64_t)it - a.nexplicit];
+        const int64_t slot = listed ? task_slot(task) : (int64_t)a.slots[it - a.nexplicit];
         // a queued node is a whole node below the root: every first vertex
         const int x0 = !listed || qitem >= 0 ? 0 : task_x0(task);
         const int x1 = !listed || qitem >= 0 ? 64 * W : task_x1(task);
@@ -1352,7 +1353,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                 if (r + SQ_SLACK < (unsigned long long)SQ_CAP) {
                     const unsigned long long si = sq_add(&sq[SQ_RESERVE], 1);
                     SplitItem& I = a.squeue[si];
-                    I.it = (int64_t)it;
+                    I.it = it;
 #pragma unroll
                     for (int w = 0; w < MAX_W; ++w) I.P[w] = w < W ? Pn[w] : 0;
                     I.l = ln;
@@ -1734,8 +1735,15 @@ __global__ __launch_bounds__(256, 2) void k_search_truss(TrussArgs a) {
 
 namespace {
 
+// Workgroups per compute unit of the kernel, asked for once per device: the
+// two calls took about 10 us of every launch.
 template <int W, bool BUILD>
-int64_t grid_blocks(int64_t ntasks, int cus, int blocks_per_cu) {
+int search_occupancy() {
+    static std::atomic<int> known[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return -1;
+    const bool slot = dev >= 0 && dev < 64;
+    if (slot && known[dev].load(std::memory_order_acquire) > 0) return known[dev].load(std::memory_order_acquire);
     auto kern = k_search<W, BUILD>;
     const size_t smem = 4 * sizeof(SearchMem<W>);
     if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
@@ -1743,6 +1751,14 @@ int64_t grid_blocks(int64_t ntasks, int cus, int blocks_per_cu) {
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 256, smem) != hipSuccess) return -1;
     if (occ < 1) occ = 1;
+    if (slot) known[dev].store(occ, std::memory_order_release);
+    return occ;
+}
+
+template <int W, bool BUILD>
+int64_t grid_blocks(int64_t ntasks, int cus, int blocks_per_cu) {
+    int occ = search_occupancy<W, BUILD>();
+    if (occ < 0) return -1;
     if (blocks_per_cu > 0 && blocks_per_cu < occ) occ = blocks_per_cu;
     // blocks_per_cu = -2: one persistent workgroup per CU fewer than fit, so a
     // launch on another stream always finds room
@@ -1758,9 +1774,12 @@ int64_t grid_blocks(int64_t ntasks, int cus, int blocks_per_cu) {
 }
 
 template <int W, bool BUILD>
-hipError_t launch_w(const SearchArgs& a, int cus, int bpc, hipStream_t s) {
+hipError_t launch_w(SearchArgs a, int cus, int bpc, hipStream_t s) {
     const int64_t grid = grid_blocks<W, BUILD>(a.ntasks, cus, bpc);
     if (grid < 0) return hipErrorInvalidValue;
+    // tasks that build their sub-branch are sorted by graph, not by weight:
+    // neighbours share the graph's arrays in cache
+    a.tickets = make_tickets(a.next, a.ntasks, a.heavy, 4 * grid, BUILD ? 8 : 0, a.shared);
     hipLaunchKernelGGL((k_search<W, BUILD>), dim3((unsigned)grid), dim3(256), 4 * sizeof(SearchMem<W>), s, a);
     return hipGetLastError();
 }

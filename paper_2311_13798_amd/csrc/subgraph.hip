@@ -50,11 +50,10 @@ __global__ __launch_bounds__(256) void k_build(BuildArgs a) {
     const int lane = lane_id();
     const GraphView& G = a.G;
 
+    Drawn drawn;
     for (;;) {
-        unsigned long long it = 0;
-        if (lane == 0) it = atomicAdd(a.next, 1ull);
-        it = uni64(__shfl(it, 0, 64));
-        if ((int64_t)it >= a.n) break;
+        const int64_t it = drawn.next(a.tickets);
+        if (it < 0) break;
         const int32_t s = a.list[it];
         const int32_t e = a.seed_eid[s];
         // a vertex slot is the edge slot with both ends at the vertex: its
@@ -91,7 +90,7 @@ __global__ __launch_bounds__(256) void k_build(BuildArgs a) {
 
 namespace {
 template <int W>
-hipError_t launch_build_w(const BuildArgs& a, int cus, hipStream_t s) {
+hipError_t launch_build_w(BuildArgs a, int cus, hipStream_t s) {
     auto kern = k_build<W>;
     const size_t smem = 4 * sizeof(BuildMem<W>);
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -103,6 +102,7 @@ hipError_t launch_build_w(const BuildArgs& a, int cus, hipStream_t s) {
     int64_t grid = (int64_t)occ * cus, need = (a.n + 3) / 4;
     if (grid > need) grid = need;
     if (grid < 1) grid = 1;
+    a.tickets = make_tickets(a.next, a.n, a.heavy, 4 * grid, 0, false);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), smem, s, a);
     return hipGetLastError();
 }
