@@ -336,7 +336,7 @@ void* scratch_get(ebbkc_graph* g, size_t bytes) {
     return g->scratch;
 }
 
-static ebbkc_status ensure_counters(ebbkc_graph* g) {
+ebbkc_status ensure_counters(ebbkc_graph* g) {
     if (!g->d_counters) {
         if (hipMalloc((void**)&g->d_counters, CNT_WORDS * sizeof(uint64_t)) != hipSuccess) return EBBKC_E_OOM;
         if (hipHostMalloc((void**)&g->h_counters, CNT_WORDS * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess)

@@ -128,6 +128,7 @@ ebbkc_status count_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_en
                         int64_t ne, uint64_t* d_per_seed, uint64_t* out, hipStream_t s);
 ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end, int32_t* d_buf, uint64_t cap,
                        uint32_t flags, uint64_t* out_written, uint64_t* out_checksums, hipStream_t s);
+ebbkc_status ensure_counters(ebbkc_graph* g);  // d_counters and their pinned mirror
 ebbkc_status subsize_impl(ebbkc_graph* g, hipStream_t s);
 ebbkc_status arena_impl(ebbkc_graph* g, hipStream_t s);
 hipError_t ensure_tables(int dev, hipStream_t s);

@@ -16,8 +16,7 @@
 //              qualifies s jumps to the smallest remaining support
 //   adjacency  erank (rank of each CSR entry), rows re-sorted by rank
 //              descending, and degree-oriented rows in the same order
-#include <chrono>
-#include <vector>
+#include <algorithm>
 
 #include "arena.h"
 #include "common.h"
@@ -55,8 +54,11 @@ __global__ void k_validate_rows(const int32_t* __restrict__ rp, int32_t n, int64
     if (u < n && rp[u + 1] < rp[u]) atomicOr(err, 4);
 }
 
+// Runs after k_validate_rows on the same stream and reads nothing through row
+// offsets found bad there.
 __global__ void k_validate_entries(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci, int32_t n,
                                    int64_t nnz, int* __restrict__ err) {
+    if (*(volatile int*)err & 7) return;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x) {
         int32_t u = row_of(rp, n, p);
         int32_t v = ci[p];
@@ -103,86 +105,247 @@ __device__ __forceinline__ bool oriented_before(int32_t a, int32_t da, int32_t b
     return da < db || (da == db && a < b);
 }
 
-// out-degree of every vertex under the degree orientation
-__global__ void k_out_count(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci, int32_t n,
-                            int32_t* __restrict__ ocnt) {
-    int wid = (blockIdx.x * blockDim.x + threadIdx.x) / EBB_WAVE;
-    int nw = gridDim.x * blockDim.x / EBB_WAVE;
-    for (int32_t a = wid; a < n; a += nw) {
-        int32_t da = rp[a + 1] - rp[a], c = 0;
-        for (int32_t p = rp[a] + lane_id(); p < rp[a + 1]; p += EBB_WAVE) {
-            int32_t b = ci[p];
-            c += oriented_before(a, da, b, rp[b + 1] - rp[b]);
-        }
-        c = wave_sum(c);
-        if (lane_id() == 0) ocnt[a] = c;
+// which CSR entries are out-entries under the degree orientation; nbr: the
+// entry's neighbour (id-sorted rows) or rrow (rank-sorted rows)
+__global__ void k_out_flags(const int32_t* __restrict__ rp, const int32_t* __restrict__ src,
+                            const int32_t* __restrict__ ci, const int2* __restrict__ rrow, int64_t nnz,
+                            int32_t* __restrict__ flag) {
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t a = src[p], b = rrow ? rrow[p].x : ci[p];
+        flag[p] = oriented_before(a, rp[a + 1] - rp[a], b, rp[b + 1] - rp[b]);
     }
 }
 
-// Ordered compaction of each row's out-entries.  mode 0: id-sorted rows
-// (col, eid); mode 1: rank-sorted rows (col, rank) taken from rrow.
+// The out-entries in row order at their scanned positions: (neighbour, edge
+// id), or the rank-sorted entry itself; and the out-rows' offsets.  (One wave
+// walking each row instead took 2.4 ms on R-MAT s18, whose longest row has
+// 25,000 entries.)
 __global__ void k_out_fill(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                           const int32_t* __restrict__ eid, const int2* __restrict__ rrow, int32_t n,
-                           const int64_t* __restrict__ ooff, int2* __restrict__ out, int32_t* __restrict__ osrc,
-                           int mode) {
-    int wid = (blockIdx.x * blockDim.x + threadIdx.x) / EBB_WAVE;
-    int nw = gridDim.x * blockDim.x / EBB_WAVE;
-    for (int32_t a = wid; a < n; a += nw) {
-        int32_t da = rp[a + 1] - rp[a];
-        int64_t w = ooff[a];
-        for (int32_t base = rp[a]; base < rp[a + 1]; base += EBB_WAVE) {
-            int32_t p = base + lane_id();
-            bool in = p < rp[a + 1];
-            int2 val = make_int2(0, 0);
-            bool keep = false;
-            if (in) {
-                int32_t b = mode == 0 ? ci[p] : rrow[p].x;
-                keep = oriented_before(a, da, b, rp[b + 1] - rp[b]);
-                val = mode == 0 ? make_int2(b, eid[p]) : rrow[p];
+                           const int32_t* __restrict__ eid, const int2* __restrict__ rrow, int32_t n, int64_t nnz,
+                           const int32_t* __restrict__ flag, const int64_t* __restrict__ pos, int2* __restrict__ out,
+                           int32_t* __restrict__ orp) {
+    const int64_t step = (int64_t)gridDim.x * blockDim.x, t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t p = t0; p < nnz; p += step)
+        if (flag[p]) out[pos[p]] = rrow ? rrow[p] : make_int2(ci[p], eid[p]);
+    if (orp)
+        for (int64_t a = t0; a <= n; a += step) orp[a] = rp[a] < nnz ? (int32_t)pos[rp[a]] : (int32_t)(nnz / 2);
+}
+
+// ---- triangles
+// Triangle a->b, a->w, b->w (degree orientation) is found once, at a: out(a)
+// is put into an LDS hash, and groups of 16 lanes stream out(b) of each b in
+// out(a) through it.  Rows of up to TRI_WAVE_D entries take one wave, longer
+// ones a workgroup (with a hash for TRI_BLOCK_D or TRI_HASH_D entries); rows
+// past TRI_HASH_D (none below 4 M edges: an out-degree is at most sqrt(2 m))
+// are searched in place.  On R-MAT s18 (82.8 M triangles) the passes take 5.3
+// and 12.8 ms; a thread per edge with a binary search per entry and three
+// atomics per triangle took 17.9 ms each.
+//
+// Of a triangle's three incidences the one of (a,b) is counted in a register
+// and the one of (a,w) in LDS, so only the one of (b,w) needs a device
+// atomic.  Pass 0 counts: sup[e] = all of them, nab / naw (by out-row position)
+// those e has as (a,b) and as (a,w).  Pass 1 writes the incidence pairs: an
+// edge's list holds its (a,b) pairs, then its (a,w) pairs, then its (b,w)
+// pairs, whose next place is cursor[e].
+constexpr int TRI_WAVE_D = 32, TRI_BLOCK_D = 512, TRI_HASH_D = 2816, TRI_GROUP = 16;
+
+// open addressing over SLOTS slots, at most D of them taken (D < SLOTS)
+template <int SLOTS, int D>
+struct TriHash {
+    int32_t key[SLOTS];
+    int32_t cnt[D];  // (a,w) incidences by position in out(a)
+    int16_t val[SLOTS];
+};
+
+__device__ __forceinline__ uint32_t tri_hash(int32_t w) { return ((uint32_t)w * 2654435761u) >> 12; }
+
+template <int SLOTS, int D>
+__device__ __forceinline__ void tri_insert(TriHash<SLOTS, D>& H, int32_t w, int i) {
+    uint32_t h = tri_hash(w);
+    for (;; ++h) {
+        h &= SLOTS - 1;
+        if (atomicCAS(&H.key[h], -1, w) == -1) break;
+    }
+    H.val[h] = (int16_t)i;
+}
+
+template <int SLOTS, int D>
+__device__ __forceinline__ int tri_find(const TriHash<SLOTS, D>& H, int32_t w) {
+    uint32_t h = tri_hash(w);
+    for (;;) {
+        h &= SLOTS - 1;
+        const int32_t k = H.key[h];
+        if (k == w) return H.val[h];
+        if (k < 0) return -1;
+        ++h;
+    }
+}
+
+struct TriArgs {
+    const int32_t* orp;
+    const int2* orow;
+    int32_t n;
+    int32_t* sup;
+    int32_t* nab;
+    int32_t* naw;
+    const int64_t* inc_off;
+    unsigned long long* cursor;
+    int2* inc;
+};
+
+// The b of out(a) numbered first, first + stride, ... by a group of lanes
+template <int PASS, class Find, class Count>
+__device__ __forceinline__ void tri_stream(const TriArgs& T, int a0, int d, int first, int stride, Find&& find,
+                                           Count&& count_aw) {
+    const int gl = lane_id() & (TRI_GROUP - 1), gbase = lane_id() & ~(TRI_GROUP - 1);
+    for (int i = first; i < d; i += stride) {
+        const int2 ab = T.orow[a0 + i];
+        const int b0 = T.orp[ab.x], b1 = T.orp[ab.x + 1];
+        int c = 0;
+        int64_t at = 0;
+        if (PASS == 1) at = T.inc_off[ab.y];
+        int t = b0 + gl;
+        int2 nxt = t < b1 ? T.orow[t] : make_int2(-1, 0);
+        for (int base = b0; base < b1; base += TRI_GROUP) {
+            const int2 bw = nxt;
+            t += TRI_GROUP;
+            nxt = t < b1 ? T.orow[t] : make_int2(-1, 0);
+            const int j = bw.x >= 0 ? find(bw.x) : -1;
+            if (PASS == 0) {
+                if (j >= 0) {
+                    ++c;
+                    count_aw(j);
+                    atomicAdd(&T.sup[bw.y], 1);
+                }
+            } else {
+                const uint32_t hits = (uint32_t)(ballot(j >= 0) >> gbase) & ((1u << TRI_GROUP) - 1);
+                if (j >= 0) {
+                    const int32_t eaw = T.orow[a0 + j].y;
+                    T.inc[at + __popc(hits & ((1u << gl) - 1))] = make_int2(eaw, bw.y);
+                    T.inc[T.inc_off[eaw] + T.nab[a0 + j] + count_aw(j)] = make_int2(ab.y, bw.y);
+                    T.inc[atomicAdd(&T.cursor[bw.y], 1ull)] = make_int2(ab.y, eaw);
+                }
+                at += __popc(hits);
             }
-            uint64_t mask = ballot(keep);
-            if (keep) {
-                int64_t q = w + popc64(mask & lanemask_lt());
-                out[q] = val;
-                if (osrc) osrc[q] = a;
-            }
-            w += popc64(mask);
+        }
+        if (PASS == 0) {
+#pragma unroll
+            for (int o = TRI_GROUP / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, TRI_GROUP);
+            if (gl == 0) T.nab[a0 + i] = c;
         }
     }
 }
 
-// Triangles a->b, a->w, b->w found from oriented entry (a->b) by looking up
-// each w of out(b) in out(a).  pass 0: count into sup; pass 1: write the
-// incidence pairs.
-__global__ void k_triangles(const int64_t* __restrict__ ooff, const int2* __restrict__ orow_id,
-                            const int32_t* __restrict__ osrc, int64_t mo, int32_t* __restrict__ sup,
-                            int64_t* __restrict__ cursor, int2* __restrict__ inc, int pass) {
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < mo; q += (int64_t)gridDim.x * blockDim.x) {
-        int32_t a = osrc[q];
-        int2 ab = orow_id[q];
-        int32_t b = ab.x, e_ab = ab.y;
-        int64_t a0 = ooff[a], a1 = ooff[a + 1];
-        for (int64_t t = ooff[b]; t < ooff[b + 1]; ++t) {
-            int2 bw = orow_id[t];
-            // binary search bw.x in out(a) (id-sorted)
-            int64_t lo = a0, hi = a1;
-            while (lo < hi) {
-                int64_t mid = (lo + hi) >> 1;
-                if (orow_id[mid].x < bw.x) lo = mid + 1; else hi = mid;
-            }
-            if (lo < a1 && orow_id[lo].x == bw.x) {
-                int32_t e_aw = orow_id[lo].y, e_bw = bw.y;
-                if (pass == 0) {
-                    atomicAdd(&sup[e_ab], 1);
-                    atomicAdd(&sup[e_aw], 1);
-                    atomicAdd(&sup[e_bw], 1);
-                } else {
-                    inc[atomicAdd((unsigned long long*)&cursor[e_ab], 1ull)] = make_int2(e_aw, e_bw);
-                    inc[atomicAdd((unsigned long long*)&cursor[e_aw], 1ull)] = make_int2(e_ab, e_bw);
-                    inc[atomicAdd((unsigned long long*)&cursor[e_bw], 1ull)] = make_int2(e_ab, e_aw);
-                }
-            }
+// The rows with more than TRI_WAVE_D entries, listed in two sizes; list[0 / 1]
+// hold the listed rows' numbers, then list + 2 the short ones and list + 2 + n
+// the long ones.
+__global__ void k_tri_rows(const int32_t* __restrict__ orp, int32_t n, int32_t* __restrict__ list) {
+    for (int32_t base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
+        const int32_t a = base + threadIdx.x;
+        const int d = a < n ? orp[a + 1] - orp[a] : 0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bool mine = q == 0 ? d > TRI_WAVE_D && d <= TRI_BLOCK_D : d > TRI_BLOCK_D;
+            const uint64_t mk = ballot(mine);
+            if (!mk) continue;
+            int at = 0;
+            if (lane_id() == 0) at = atomicAdd(&list[q], popc64(mk));
+            at = uniform_i32(at);
+            if (mine) list[2 + (int64_t)q * n + at + popc64(mk & lanemask_lt())] = a;
         }
+    }
+}
+
+// rows of up to TRI_WAVE_D entries: a wave each
+template <int PASS>
+__global__ __launch_bounds__(TB) void k_tri_wave(TriArgs T) {
+    using Hash = TriHash<2 * TRI_WAVE_D, TRI_WAVE_D>;
+    static_assert(2 * TRI_WAVE_D == EBB_WAVE, "a lane clears a slot");
+    __shared__ Hash mem[TB / EBB_WAVE];
+    Hash& H = mem[threadIdx.x / EBB_WAVE];
+    const int lane = lane_id();
+    const int wid = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / EBB_WAVE);
+    const int nw = (int)(gridDim.x * (int64_t)blockDim.x / EBB_WAVE);
+    for (int a = wid; a < T.n; a += nw) {
+        const int a0 = uniform_i32(T.orp[a]), d = uniform_i32(T.orp[a + 1]) - a0;
+        if (d > TRI_WAVE_D) continue;
+        if (d < 2) {
+            if (PASS == 0 && d == 1 && lane == 0) T.nab[a0] = T.naw[a0] = 0;
+            continue;
+        }
+        H.key[lane] = -1;
+        if (lane < TRI_WAVE_D) H.cnt[lane] = 0;
+        wave_sync();
+        int2 own = make_int2(0, 0);
+        if (lane < d) {
+            own = T.orow[a0 + lane];
+            tri_insert(H, own.x, lane);
+        }
+        wave_sync();
+        tri_stream<PASS>(T, a0, d, lane / TRI_GROUP, EBB_WAVE / TRI_GROUP,
+                         [&](int32_t w) { return tri_find(H, w); }, [&](int j) { return atomicAdd(&H.cnt[j], 1); });
+        wave_sync();
+        if (PASS == 0 && lane < d) {
+            T.naw[a0 + lane] = H.cnt[lane];
+            const int add = H.cnt[lane] + T.nab[a0 + lane];
+            if (add) atomicAdd(&T.sup[own.y], add);
+        }
+        wave_sync();
+    }
+}
+
+// longer rows (list of *count): a workgroup each
+template <int PASS, int SLOTS, int D>
+__global__ __launch_bounds__(TB) void k_tri_block(TriArgs T, const int32_t* __restrict__ list,
+                                                  const int32_t* __restrict__ count) {
+    __shared__ TriHash<SLOTS, D> H;
+    static_assert(D < SLOTS, "a free slot ends every search");
+    const int rows = *count, first = threadIdx.x / TRI_GROUP, stride = TB / TRI_GROUP;
+    for (int r = blockIdx.x; r < rows; r += gridDim.x) {
+        const int a = list[r], a0 = T.orp[a], d = T.orp[a + 1] - a0;
+        if (d <= D) {
+            for (int i = threadIdx.x; i < SLOTS; i += TB) H.key[i] = -1;
+            for (int i = threadIdx.x; i < d; i += TB) H.cnt[i] = 0;
+            __syncthreads();
+            for (int i = threadIdx.x; i < d; i += TB) tri_insert(H, T.orow[a0 + i].x, i);
+            __syncthreads();
+            tri_stream<PASS>(T, a0, d, first, stride, [&](int32_t w) { return tri_find(H, w); },
+                             [&](int j) { return atomicAdd(&H.cnt[j], 1); });
+            __syncthreads();
+            if (PASS == 0)
+                for (int i = threadIdx.x; i < d; i += TB) T.naw[a0 + i] = H.cnt[i];
+        } else {  // out(a) searched in device memory; (a,w) counted there too
+            for (int i = threadIdx.x; i < d; i += TB) atomicExch(&T.naw[a0 + i], 0);
+            __syncthreads();
+            tri_stream<PASS>(
+                T, a0, d, first, stride,
+                [&](int32_t w) {
+                    int lo = a0, hi = a0 + d;
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (T.orow[mid].x < w) lo = mid + 1; else hi = mid;
+                    }
+                    return lo < a0 + d && T.orow[lo].x == w ? lo - a0 : -1;
+                },
+                [&](int j) { return atomicAdd(&T.naw[a0 + j], 1); });
+            __syncthreads();
+        }
+        if (PASS == 0)
+            for (int i = threadIdx.x; i < d; i += TB) {
+                const int add = (d <= D ? H.cnt[i] : atomicAdd(&T.naw[a0 + i], 0)) + T.nab[a0 + i];
+                if (add) atomicAdd(&T.sup[T.orow[a0 + i].y], add);
+            }
+        __syncthreads();
+    }
+}
+
+// where the (b,w) incidences of every edge go
+__global__ void k_tri_cursor(const int2* __restrict__ orow, const int32_t* __restrict__ nab,
+                             const int32_t* __restrict__ naw, const int64_t* __restrict__ inc_off, int64_t m,
+                             unsigned long long* __restrict__ cursor) {
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < m; q += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t e = orow[q].y;
+        cursor[e] = (unsigned long long)(inc_off[e] + nab[q] + naw[q]);
     }
 }
 
@@ -247,45 +410,355 @@ __global__ void k_peel_assign(const int32_t* __restrict__ front, int64_t nf, int
     }
 }
 
-// one wave per frontier edge, lanes over its incident triangles
-__global__ void k_peel_triangles(const int32_t* __restrict__ front, int64_t nf, const int64_t* __restrict__ inc_off,
-                                 const int2* __restrict__ inc, const int32_t* __restrict__ rnd, int32_t r,
-                                 int32_t* __restrict__ sup) {
-    int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / EBB_WAVE;
-    int64_t nw = (int64_t)gridDim.x * blockDim.x / EBB_WAVE;
-    for (int64_t i = wid; i < nf; i += nw) {
-        int32_t e = front[i];
-        for (int64_t t = inc_off[e] + lane_id(); t < inc_off[e + 1]; t += EBB_WAVE) {
-            int2 fg = inc[t];
-            int32_t rf = rnd[fg.x], rg = rnd[fg.y];
-            bool pf = rf < 0 || rf == r, pg = rg < 0 || rg == r;
-            if (!(pf && pg)) continue;  // destroyed in an earlier round
-            int32_t mine = e;
-            if (rf == r && fg.x < mine) mine = fg.x;
-            if (rg == r && fg.y < mine) mine = fg.y;
-            if (mine != e) continue;
-            if (rf < 0) atomicSub(&sup[fg.x], 1);
-            if (rg < 0) atomicSub(&sup[fg.y], 1);
+// ---------------------------------------------------------------- truss peel
+// The whole level-synchronous peel in one cooperative launch.  A round's
+// frontier is the edges whose support reached the level in the round before:
+// the decrement that takes an edge from level + 1 to level appends it to the
+// next frontier, so a round costs its own triangles and one grid barrier, and
+// the live edges are only scanned when the level changes.  An edge's round is
+// stored when it is appended; positions in pi_tau follow afterwards by a
+// stable sort of the rounds over the edge ids.  While a round runs, an edge
+// already appended to the next one (round r + 1) still counts as present.
+//
+// The rounds are bound by latency: a chain of about seven dependent accesses
+// and the barrier each, 1,278 of them on R-MAT s18 (26 ms, 20 us a round) and
+// 796 on R-MAT of 50,000 vertices (9 ms).  The host loop this replaces (six
+// launches, a copy and a wait per round, every live edge read three times)
+// took 90 and 51 ms.
+//
+// Words that several workgroups touch are read and written with relaxed
+// device-scope atomics, which go past the compute units' vector caches and
+// the L2s of the eight dies; a workgroup waits for its stores before it
+// arrives at the barrier.  (Release / acquire fences there instead write back
+// and drop whole caches: 14 us a barrier of 256 workgroups against 4.3 us,
+// 1.7 us with 64.)  Every wait is bounded: past PEEL_WAIT_TICKS a workgroup
+// sets the error word and returns, and so do the others.
+constexpr int PEEL_TB = 1024, PEEL_GROUP = 16;
+// 64 workgroups, 128 from 2 M edges on: more of them share a round's triangles,
+// fewer make the barrier cheaper (prepare of R-MAT s18, m = 3.8 M: 55.3 ms with
+// 64, 50.0 with 128, 52.1 with 256; R-MAT of 50,000 vertices, m = 0.65 M: 14.8,
+// 15.2, 17.3 ms).
+constexpr int64_t PEEL_GRID = 64, PEEL_GRID_WIDE = 128, PEEL_WIDE_M = 2 << 20;
+constexpr int PEEL_Q = 4096;      // appended edges collected per workgroup before they are written
+// Edges with more than PEEL_SHORT triangles are listed and taken by a wave
+// each, those with more than PEEL_LONG by the whole workgroup: a step of four
+// triangles a lane costs about 3 us of dependent accesses, so a group takes a
+// short edge in one step and a wave a long one in sixteen.
+constexpr int PEEL_STEP = 4, PEEL_SHORT = PEEL_GROUP * PEEL_STEP, PEEL_LONG = 16 * 64 * PEEL_STEP;
+constexpr int PEEL_LONGQ = 2048;
+constexpr uint64_t PEEL_WAIT_TICKS = 2000000000ull;  // 20 s of the 100 MHz clock
+constexpr uint32_t PEEL_WAIT_SPINS = 1u << 28;
+
+struct PeelCtl {
+    uint32_t arrived;   // barrier arrivals
+    int32_t err;
+    int32_t nf[3];      // frontier sizes: this round's, the next one's, and the one cleared meanwhile
+    int32_t minsup[3];  // least support of the live edges, by scan; likewise
+    int32_t tau, rounds;
+};
+
+template <typename T>
+__device__ __forceinline__ T dev_load(const T* p) {
+    return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void dev_store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+struct PeelArgs {
+    int32_t m;
+    const int64_t* inc_off;
+    const int2* inc;
+    int32_t* sup;
+    int32_t* rnd;      // -1 at the start
+    int32_t* level;
+    int32_t* subsize;  // triangles an edge is the first edge of in pi_tau
+    int32_t* front[2];
+    int32_t* live;     // per workgroup: its live edges (PEEL_TB * live_chunks entries each)
+    int32_t live_chunks;
+    PeelCtl* ctl;
+};
+
+struct PeelMem {
+    int32_t q[PEEL_Q];
+    int32_t lq[PEEL_LONGQ];
+    int32_t qn, ln, lnext, base, mn, sum;
+    int32_t ok;
+    int32_t wcnt[PEEL_TB / EBB_WAVE];
+};
+
+// Every workgroup has arrived (generation gen, counted from 1) and its stores
+// are done; false after PEEL_WAIT_TICKS or when another one gave up.
+__device__ bool peel_barrier(PeelMem& M, PeelCtl* ctl, uint32_t gen) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t target = gen * gridDim.x;
+        const uint64_t t0 = wall_clock64();
+        int ok = 1;
+        __hip_atomic_fetch_add(&ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (uint32_t spin = 0; (int32_t)(dev_load(&ctl->arrived) - target) < 0; ++spin) {
+            if (dev_load(&ctl->err) || wall_clock64() - t0 > PEEL_WAIT_TICKS || spin > PEEL_WAIT_SPINS) {
+                dev_store(&ctl->err, 1);
+                ok = 0;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
         }
+        M.ok = ok;
+    }
+    __syncthreads();
+    asm volatile("" ::: "memory");
+    return M.ok != 0;
+}
+
+// add edge e to the next frontier
+__device__ __forceinline__ void peel_append(PeelMem& M, const PeelArgs& A, int32_t* next, int32_t* nf_next, int32_t e,
+                                            int32_t round) {
+    dev_store(&A.rnd[e], round);
+    const int i = atomicAdd(&M.qn, 1);
+    if (i < PEEL_Q) M.q[i] = e;
+    else dev_store(&next[atomicAdd(nf_next, 1)], e);  // the queue is full: straight to the frontier
+}
+
+// write the collected edges to the next frontier
+__device__ __forceinline__ void peel_flush(PeelMem& M, int32_t* next, int32_t* nf_next) {
+    __syncthreads();
+    const int n = M.qn < PEEL_Q ? M.qn : PEEL_Q;
+    if (threadIdx.x == 0 && n) M.base = atomicAdd(nf_next, n);
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += PEEL_TB) dev_store(&next[M.base + i], M.q[i]);
+    __syncthreads();
+    if (threadIdx.x == 0) M.qn = 0;
+}
+
+// One triangle of frontier edge e (round r, level s): 1 when e is its first
+// edge in pi_tau among the edges still present; then the edges that stay lose
+// one support.
+__device__ __forceinline__ int peel_triangle(PeelMem& M, const PeelArgs& A, int32_t* next, int32_t* nf_next, int32_t e,
+                                             int2 fg, int32_t rf, int32_t rg, int32_t r, int32_t s) {
+    if ((rf >= 0 && rf < r) || (rg >= 0 && rg < r)) return 0;  // destroyed in an earlier round
+    if ((rf == r && fg.x < e) || (rg == r && fg.y < e)) return 0;
+    if (rf != r && atomicSub(&A.sup[fg.x], 1) == s + 1) peel_append(M, A, next, nf_next, fg.x, r + 1);
+    if (rg != r && atomicSub(&A.sup[fg.y], 1) == s + 1) peel_append(M, A, next, nf_next, fg.y, r + 1);
+    return 1;
+}
+
+// triangles [t, t1) of edge e, every stride-th, PEEL_STEP at a time
+__device__ __forceinline__ int peel_edge(PeelMem& M, const PeelArgs& A, int32_t* next, int32_t* nf_next, int32_t e,
+                                         int64_t t, int64_t t1, int stride, int32_t r, int32_t s) {
+    int c = 0;
+    for (; t < t1; t += PEEL_STEP * stride) {
+        int2 fg[PEEL_STEP];
+        int32_t rf[PEEL_STEP], rg[PEEL_STEP];
+#pragma unroll
+        for (int j = 0; j < PEEL_STEP; ++j) fg[j] = t + j * stride < t1 ? A.inc[t + j * stride] : make_int2(-1, -1);
+#pragma unroll
+        for (int j = 0; j < PEEL_STEP; ++j) {
+            rf[j] = fg[j].x >= 0 ? dev_load(&A.rnd[fg[j].x]) : 0;
+            rg[j] = fg[j].x >= 0 ? dev_load(&A.rnd[fg[j].y]) : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < PEEL_STEP; ++j)
+            if (fg[j].x >= 0) c += peel_triangle(M, A, next, nf_next, e, fg[j], rf[j], rg[j], r, s);
+    }
+    return c;
+}
+
+__global__ __launch_bounds__(PEEL_TB) void k_peel(PeelArgs A) {
+    __shared__ PeelMem M;
+    PeelCtl* ctl = A.ctl;
+    const int lane = lane_id(), wave = threadIdx.x / EBB_WAVE;
+    int32_t* live = A.live + (int64_t)blockIdx.x * A.live_chunks * PEEL_TB;
+    if (threadIdx.x == 0) M.qn = 0;
+    __syncthreads();
+    uint32_t gen = 0;
+    int cur = 0;      // ctl->nf slot of the frontier in work
+    int scan = 0;     // ctl->minsup slot of the next scan
+    int nlive = -1;   // -1: every edge of this workgroup's chunks (chunk i of PEEL_TB edges goes to
+                      // workgroup i mod grid)
+    int32_t r = 0, s = 0, tau = 0;
+    for (;;) {
+        // ---- the live edges: those at or below s form round r's frontier,
+        // the others stay listed and give the least support left
+        {
+            const int nxt = (cur + 1) % 3;
+            int32_t* next = A.front[r & 1];
+            int32_t* nf_next = &ctl->nf[nxt];
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                dev_store(&ctl->nf[(cur + 2) % 3], 0);
+                dev_store(&ctl->minsup[(scan + 1) % 3], 0x7fffffff);
+            }
+            if (threadIdx.x == 0) M.mn = 0x7fffffff;
+            __syncthreads();
+            const bool all = nlive < 0;
+            const int total = all ? A.live_chunks * PEEL_TB : nlive;
+            int kept = 0, mn = 0x7fffffff;
+            for (int i0 = 0; i0 < total; i0 += PEEL_TB) {
+                const int i = i0 + threadIdx.x;
+                int64_t e = -1;
+                if (i < total) {
+                    e = all ? ((int64_t)(i0 / PEEL_TB) * gridDim.x + blockIdx.x) * PEEL_TB + threadIdx.x : live[i];
+                    if (e >= A.m) e = -1;
+                }
+                bool keep = false;
+                if (e >= 0 && dev_load(&A.rnd[e]) < 0) {
+                    const int32_t x = dev_load(&A.sup[e]);
+                    keep = x > s;
+                    if (keep) mn = x < mn ? x : mn;
+                    else peel_append(M, A, next, nf_next, (int32_t)e, r);
+                }
+                const uint64_t mk = ballot(keep);
+                if (lane == 0) M.wcnt[wave] = popc64(mk);
+                __syncthreads();  // also: every entry of the chunk is read before its place is written
+                int before = 0, chunk = 0;
+                for (int w = 0; w < PEEL_TB / EBB_WAVE; ++w) {
+                    const int c = M.wcnt[w];
+                    before += w < wave ? c : 0;
+                    chunk += c;
+                }
+                if (keep) live[kept + before + popc64(mk & lanemask_lt())] = (int32_t)e;
+                kept += chunk;
+                __syncthreads();
+            }
+            nlive = kept;
+            mn = wave_min(mn);
+            if (lane == 0 && mn < 0x7fffffff) atomicMin(&M.mn, mn);
+            peel_flush(M, next, nf_next);
+            if (threadIdx.x == 0 && M.mn < 0x7fffffff) atomicMin(&ctl->minsup[scan], M.mn);
+            if (!peel_barrier(M, ctl, ++gen)) return;
+            cur = nxt;
+            const int32_t least = dev_load(&ctl->minsup[scan]);
+            scan = (scan + 1) % 3;
+            if (dev_load(&ctl->nf[cur]) == 0) {
+                if (least == 0x7fffffff) break;  // no edge is left
+                s = least;
+                continue;
+            }
+        }
+        // ---- rounds at level s until no edge qualifies
+        for (int nf = dev_load(&ctl->nf[cur]); nf > 0; ++r) {
+            tau = s;
+            const int nxt = (cur + 1) % 3;
+            const int32_t* front = A.front[r & 1];
+            int32_t* next = A.front[(r + 1) & 1];
+            int32_t* nf_next = &ctl->nf[nxt];
+            if (blockIdx.x == 0 && threadIdx.x == 0) dev_store(&ctl->nf[(cur + 2) % 3], 0);
+            if (threadIdx.x == 0) M.ln = M.lnext = 0;
+            __syncthreads();
+            const int gl = threadIdx.x % PEEL_GROUP, g = threadIdx.x / PEEL_GROUP;
+            constexpr int GROUPS = PEEL_TB / PEEL_GROUP;
+            // groups of 16 lanes take an edge each, consecutive ones on different workgroups
+            for (int i = g * gridDim.x + blockIdx.x; i < nf; i += GROUPS * gridDim.x) {
+                const int32_t e = dev_load(&front[i]);
+                const int64_t t0 = A.inc_off[e], t1 = A.inc_off[e + 1];
+                if (gl == 0) A.level[e] = s;
+                if (t1 - t0 > PEEL_SHORT) {
+                    int at = PEEL_LONGQ;
+                    if (gl == 0) at = atomicAdd(&M.ln, 1);
+                    at = __shfl(at, 0, PEEL_GROUP);
+                    if (at < PEEL_LONGQ) {
+                        if (gl == 0) M.lq[at] = e;
+                        continue;
+                    }
+                }
+                int c = peel_edge(M, A, next, nf_next, e, t0 + gl, t1, PEEL_GROUP, r, s);
+#pragma unroll
+                for (int o = PEEL_GROUP / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, PEEL_GROUP);
+                if (gl == 0) A.subsize[e] = c;
+            }
+            __syncthreads();
+            // the listed edges: each wave takes the next one
+            const int nl = M.ln < PEEL_LONGQ ? M.ln : PEEL_LONGQ;
+            bool longer = false;
+            for (;;) {
+                int i = 0;
+                if (lane == 0) i = atomicAdd(&M.lnext, 1);
+                i = uniform_i32(i);
+                if (i >= nl) break;
+                const int32_t e = M.lq[i];
+                const int64_t t0 = A.inc_off[e], t1 = A.inc_off[e + 1];
+                if (t1 - t0 > PEEL_LONG) {
+                    longer = true;
+                    continue;
+                }
+                const int c = wave_sum(peel_edge(M, A, next, nf_next, e, t0 + lane, t1, EBB_WAVE, r, s));
+                if (lane == 0) A.subsize[e] = c;
+            }
+            // the longest ones: the whole workgroup, one after the other
+            if (__syncthreads_or(longer)) {
+                for (int i = 0; i < nl; ++i) {
+                    const int32_t e = M.lq[i];
+                    const int64_t t0 = A.inc_off[e], t1 = A.inc_off[e + 1];
+                    if (t1 - t0 <= PEEL_LONG) continue;
+                    if (threadIdx.x == 0) M.sum = 0;
+                    __syncthreads();
+                    const int c = wave_sum(peel_edge(M, A, next, nf_next, e, t0 + threadIdx.x, t1, PEEL_TB, r, s));
+                    if (lane == 0 && c) atomicAdd(&M.sum, c);
+                    __syncthreads();
+                    if (threadIdx.x == 0) A.subsize[e] = M.sum;
+                }
+            }
+            peel_flush(M, next, nf_next);
+            if (!peel_barrier(M, ctl, ++gen)) return;
+            cur = nxt;
+            nf = dev_load(&ctl->nf[cur]);
+        }
+        s = tau + 1;  // the next level that may hold an edge
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl->tau = tau;
+        ctl->rounds = r;
     }
 }
 
-__global__ void k_erank_keys(const int32_t* __restrict__ src, const int32_t* __restrict__ eid,
-                             const int32_t* __restrict__ rank, int64_t nnz, int64_t m, int32_t* __restrict__ erank,
-                             uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x) {
-        int32_t r = rank[eid[p]];
-        erank[p] = r;
-        keys[p] = (uint64_t)src[p] * (uint64_t)m + (uint64_t)(m - 1 - r);
-        vals[p] = (uint32_t)p;
+// frontier sizes and minima before the launch
+__global__ void k_peel_begin(PeelCtl* ctl, int32_t* __restrict__ rnd, int32_t m) {
+    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) {
+        *ctl = PeelCtl{};
+        for (int32_t& x : ctl->minsup) x = 0x7fffffff;
+    }
+    for (int32_t j = i; j < m; j += gridDim.x * blockDim.x) rnd[j] = -1;
+}
+
+__global__ void k_erank(const int32_t* __restrict__ eid, const int32_t* __restrict__ rank, int64_t nnz,
+                        int32_t* __restrict__ erank) {
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += (int64_t)gridDim.x * blockDim.x)
+        erank[p] = rank[eid[p]];
+}
+
+// The 2 m (vertex, neighbour) entries by descending rank of their edge: entry
+// 2 i + h is the h-th direction of the edge of rank m - 1 - i.  A stable sort
+// by vertex then gives every row its entries by descending rank.
+__global__ void k_rrow_keys(const int32_t* __restrict__ byrank, const int32_t* __restrict__ eu,
+                            const int32_t* __restrict__ ev, int64_t m, uint32_t* __restrict__ keys,
+                            uint32_t* __restrict__ vals) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t e = byrank[m - 1 - i];
+        keys[2 * i] = (uint32_t)eu[e];
+        keys[2 * i + 1] = (uint32_t)ev[e];
+        vals[2 * i] = (uint32_t)(2 * i);
+        vals[2 * i + 1] = (uint32_t)(2 * i + 1);
     }
 }
 
-__global__ void k_gather_rrow(const uint32_t* __restrict__ perm, const int32_t* __restrict__ ci,
-                              const int32_t* __restrict__ erank, int64_t nnz, int2* __restrict__ rrow) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * blockDim.x) {
-        uint32_t p = perm[i];
-        rrow[i] = make_int2(ci[p], erank[p]);
+__global__ void k_gather_rrow(const uint32_t* __restrict__ perm, const int32_t* __restrict__ byrank,
+                              const int32_t* __restrict__ eu, const int32_t* __restrict__ ev, int64_t m,
+                              int2* __restrict__ rrow) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 2 * m; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t v = perm[i];
+        const int32_t r = (int32_t)(m - 1 - (v >> 1)), e = byrank[r];
+        rrow[i] = make_int2((v & 1) ? eu[e] : ev[e], r);
+    }
+}
+
+__global__ void k_round_keys(const int32_t* __restrict__ rnd, int64_t m, uint32_t* __restrict__ keys,
+                             uint32_t* __restrict__ vals) {
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
+        keys[e] = (uint32_t)rnd[e];
+        vals[e] = (uint32_t)e;
     }
 }
 
@@ -430,11 +903,6 @@ __global__ void k_lex_edge_keys(const int32_t* __restrict__ eu, const int32_t* _
     }
 }
 
-__global__ void k_copy_i64_to_i32(const int64_t* __restrict__ a, int32_t* __restrict__ b, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        b[i] = (int32_t)a[i];
-}
-
 template <typename T>
 struct DBuf {
     T* p = nullptr;
@@ -476,21 +944,13 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     CHK(hipMemcpyAsync(rp.p, row_ptr, sizeof(int32_t) * (size_t)(n + 1), kind, s));
     if (nnz) CHK(hipMemcpyAsync(ci.p, col_idx, sizeof(int32_t) * (size_t)nnz, kind, s));
 
-    // small host-visible status block: [0] err, [1] dmax
-    int* hstat = nullptr;
-    int* dstat = nullptr;
-    CHK(hipHostMalloc((void**)&hstat, 4 * sizeof(int), hipHostMallocDefault));
-    struct HostFree { int* p; ~HostFree() { if (p) (void)hipHostFree(p); } } hf{hstat};
-    DBuf<int> stat;
-    CHK(stat.alloc(4));
-    dstat = stat.p;
+    // status words: [0] err, [1] dmax, [2] vertices still uncoloured; read back
+    // through the handle's pinned mirror
+    if (ebbkc_status st = ensure_counters(g)) return st;
+    int* dstat = (int*)g->d_counters;
+    int* hstat = (int*)g->h_counters;
     CHK(hipMemsetAsync(dstat, 0, 4 * sizeof(int), s));
-    // row offsets first: the entry checks index rows through them
     hipLaunchKernelGGL(k_validate_rows, dim3(grid_for(n + 1)), dim3(TB), 0, s, rp.p, n, nnz, dstat);
-    CHK(hipGetLastError());
-    CHK(hipMemcpyAsync(hstat, dstat, sizeof(int), hipMemcpyDeviceToHost, s));
-    CHK(hipStreamSynchronize(s));
-    if (hstat[0] != 0) return EBBKC_E_BAD_CSR;
     if (nnz) hipLaunchKernelGGL(k_validate_entries, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, ci.p, n, nnz, dstat);
     CHK(hipGetLastError());
     CHK(hipMemcpyAsync(hstat, dstat, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -520,101 +980,124 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     CHK(hipGetLastError());
 
     // ---- degree orientation (id-sorted out rows with edge ids)
-    DBuf<int32_t> ocnt, osrc;
-    DBuf<int64_t> ooff;
+    DBuf<int32_t> oflag, orp;
+    DBuf<int64_t> opos;
     DBuf<int2> orow_id;
-    CHK(ocnt.alloc(n));
-    CHK(ooff.alloc(n + 1));
+    CHK(oflag.alloc(nnz));
+    CHK(opos.alloc(nnz));
+    CHK(orp.alloc(n + 1));
     CHK(orow_id.alloc(m));
-    CHK(osrc.alloc(m));
-    const unsigned wgrid = 4096;  // wave-per-row kernels, grid-stride
-    if (n) hipLaunchKernelGGL(k_out_count, dim3(wgrid), dim3(TB), 0, s, rp.p, ci.p, n, ocnt.p);
-    CHK(exclusive_scan_i32(ocnt.p, ooff.p, n, ooff.p + n, scan_tmp.p, s));
-    if (n)
-        hipLaunchKernelGGL(k_out_fill, dim3(wgrid), dim3(TB), 0, s, rp.p, ci.p, eid.p, (const int2*)nullptr, n,
-                           ooff.p, orow_id.p, osrc.p, 0);
+    if (nnz)
+        hipLaunchKernelGGL(k_out_flags, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, src.p, ci.p, (const int2*)nullptr,
+                           nnz, oflag.p);
+    CHK(exclusive_scan_i32(oflag.p, opos.p, nnz, nullptr, scan_tmp.p, s));
+    hipLaunchKernelGGL(k_out_fill, dim3(grid_for(nnz > n ? nnz : n + 1)), dim3(TB), 0, s, rp.p, ci.p, eid.p,
+                       (const int2*)nullptr, n, nnz, oflag.p, opos.p, orow_id.p, orp.p);
     CHK(hipGetLastError());
 
     // ---- supports and triangle incidence
-    DBuf<int32_t> sup;
+    DBuf<int32_t> sup, nab, naw, trows;
     DBuf<int64_t> inc_off, cursor;
     CHK(sup.alloc(m));
+    CHK(nab.alloc(m));
+    CHK(naw.alloc(m));
+    CHK(trows.alloc(2 + 2 * (int64_t)n));
     CHK(inc_off.alloc(m + 1));
     CHK(hipMemsetAsync(sup.p, 0, sizeof(int32_t) * (size_t)(m > 0 ? m : 1), s));
-    if (m)
-        hipLaunchKernelGGL(k_triangles, dim3(grid_for(m)), dim3(TB), 0, s, ooff.p, orow_id.p, osrc.p, m, sup.p,
-                           (int64_t*)nullptr, (int2*)nullptr, 0);
+    CHK(hipMemsetAsync(trows.p, 0, 2 * sizeof(int32_t), s));
+    TriArgs tri{orp.p, orow_id.p, n, sup.p, nab.p, naw.p, nullptr, nullptr, nullptr};
+    const unsigned twave = (unsigned)std::min<int64_t>(2048, (n + 3) / 4);
+    const unsigned tblock = (unsigned)std::min<int64_t>(2048, n);
+    if (m) {
+        hipLaunchKernelGGL(k_tri_rows, dim3(grid_for(n)), dim3(TB), 0, s, orp.p, n, trows.p);
+        hipLaunchKernelGGL((k_tri_block<0, 4096, TRI_HASH_D>), dim3(tblock), dim3(TB), 0, s, tri, trows.p + 2 + n,
+                           trows.p + 1);
+        hipLaunchKernelGGL((k_tri_block<0, 1024, TRI_BLOCK_D>), dim3(tblock), dim3(TB), 0, s, tri, trows.p + 2, trows.p);
+        hipLaunchKernelGGL(k_tri_wave<0>, dim3(twave), dim3(TB), 0, s, tri);
+        CHK(hipGetLastError());
+    }
     CHK(exclusive_scan_i32(sup.p, inc_off.p, m, inc_off.p + m, scan_tmp.p, s));
     int64_t h_ninc = 0;
-    CHK(hipMemcpyAsync(&h_ninc, inc_off.p + m, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    CHK(hipMemcpyAsync(g->h_counters + 8, inc_off.p + m, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     CHK(hipMemcpyAsync(hstat + 1, dstat + 1, sizeof(int), hipMemcpyDeviceToHost, s));
     CHK(hipStreamSynchronize(s));
+    h_ninc = (int64_t)g->h_counters[8];
     g->max_degree = hstat[1];
     DBuf<int2> inc;
     CHK(inc.alloc(h_ninc));
     CHK(cursor.alloc(m + 1));
-    CHK(hipMemcpyAsync(cursor.p, inc_off.p, sizeof(int64_t) * (size_t)(m + 1), hipMemcpyDeviceToDevice, s));
-    if (m)
-        hipLaunchKernelGGL(k_triangles, dim3(grid_for(m)), dim3(TB), 0, s, ooff.p, orow_id.p, osrc.p, m, sup.p,
-                           cursor.p, inc.p, 1);
+    if (m) {
+        hipLaunchKernelGGL(k_tri_cursor, dim3(grid_for(m)), dim3(TB), 0, s, orow_id.p, nab.p, naw.p, inc_off.p, m,
+                           (unsigned long long*)cursor.p);
+        tri.inc_off = inc_off.p;
+        tri.cursor = (unsigned long long*)cursor.p;
+        tri.inc = inc.p;
+        if (h_ninc) {
+            hipLaunchKernelGGL((k_tri_block<1, 4096, TRI_HASH_D>), dim3(tblock), dim3(TB), 0, s, tri, trows.p + 2 + n,
+                               trows.p + 1);
+            hipLaunchKernelGGL((k_tri_block<1, 1024, TRI_BLOCK_D>), dim3(tblock), dim3(TB), 0, s, tri, trows.p + 2,
+                               trows.p);
+            hipLaunchKernelGGL(k_tri_wave<1>, dim3(twave), dim3(TB), 0, s, tri);
+        }
+    }
     CHK(hipGetLastError());
     DBuf<int32_t> sup0;
     CHK(sup0.alloc(m));
     CHK(hipMemcpyAsync(sup0.p, sup.p, sizeof(int32_t) * (size_t)(m > 0 ? m : 1), hipMemcpyDeviceToDevice, s));
 
-    // ---- level-synchronous peel
-    DBuf<int32_t> live, keep, front, flag, rnd, level, rank;
-    DBuf<int64_t> pos;
-    DBuf<PeelState> st;
-    CHK(live.alloc(m));
-    CHK(keep.alloc(m));
-    CHK(front.alloc(m));
-    CHK(flag.alloc(m));
-    CHK(rnd.alloc(m));
+    // ---- level-synchronous peel: rounds, levels and |V(g_i)|, then the ranks
+    // by a stable sort of the rounds over the edge ids
+    DBuf<int32_t> live, front0, front1, rnd, level, rank, subsize, byrank;
+    DBuf<PeelCtl> ctl;
+    DBuf<uint32_t> rk1, rk2, rv2;
+    DBuf<int64_t> rhist, rtmp;
+    const int64_t sorted = nnz;  // the larger of the two sorts that share the buffers
     CHK(level.alloc(m));
     CHK(rank.alloc(m));
-    CHK(pos.alloc(m + 1));
-    CHK(st.alloc(1));
-    PeelState* hst = nullptr;
-    CHK(hipHostMalloc((void**)&hst, sizeof(PeelState), hipHostMallocDefault));
-    struct HostFree2 { PeelState* p; ~HostFree2() { if (p) (void)hipHostFree(p); } } hf2{hst};
+    CHK(subsize.alloc(m));
+    CHK(byrank.alloc(m));
+    CHK(rk1.alloc(sorted));
+    CHK(rk2.alloc(sorted));
+    CHK(rv2.alloc(sorted));
+    CHK(rhist.alloc(radix_hist_elems(sorted)));
+    CHK(rtmp.alloc(scan_tmp_elems(radix_hist_elems(sorted)) + 64));
     if (m) {
-        hipLaunchKernelGGL(k_iota, dim3(grid_for(m)), dim3(TB), 0, s, live.p, m);
-        hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(m)), dim3(TB), 0, s, rnd.p, m, -1);
-    }
-    int64_t nlive = m, ranked = 0;
-    int32_t lev = 0, r = 0, maxlev = 0;
-    while (ranked < m) {
-        unsigned gl = grid_for(nlive, TB * 8);  // about eight entries per thread
-        if (gl > 2048) gl = 2048;
-        hipLaunchKernelGGL(k_peel_reset, dim3(1), dim3(1), 0, s, st.p);
-        hipLaunchKernelGGL(k_peel_flag, dim3(gl), dim3(TB), 0, s, live.p, nlive, sup.p, lev, flag.p, st.p);
-        CHK(exclusive_scan_i32(flag.p, pos.p, nlive, &st.p->nf, scan_tmp.p, s));
-        CHK(hipMemcpyAsync(hst, st.p, sizeof(PeelState), hipMemcpyDeviceToHost, s));
-        CHK(hipStreamSynchronize(s));
-        int64_t nf = hst->nf;
-        if (nf == 0) {
-            lev = hst->minsup;  // next level that has an edge
-            continue;
-        }
-        hipLaunchKernelGGL(k_peel_compact, dim3(gl), dim3(TB), 0, s, live.p, nlive, flag.p, pos.p, front.p, keep.p);
-        unsigned gf = grid_for(nf);
-        if (gf > 8192) gf = 8192;
-        hipLaunchKernelGGL(k_peel_assign, dim3(gf), dim3(TB), 0, s, front.p, nf, lev, ranked, r, level.p, rank.p,
-                           rnd.p);
-        unsigned gw = grid_for(nf * EBB_WAVE);
-        if (gw > 16384) gw = 16384;
-        hipLaunchKernelGGL(k_peel_triangles, dim3(gw), dim3(TB), 0, s, front.p, nf, inc_off.p, inc.p, rnd.p, r,
-                           sup.p);
+        CHK(rnd.alloc(m));
+        CHK(front0.alloc(m));
+        CHK(front1.alloc(m));
+        CHK(ctl.alloc(1));
+        const int64_t chunks = (m + PEEL_TB - 1) / PEEL_TB;
+        const int64_t grid = std::min<int64_t>(m >= PEEL_WIDE_M ? PEEL_GRID_WIDE : PEEL_GRID, (chunks + 1) / 2);
+        PeelArgs pa{};
+        pa.m = (int32_t)m;
+        pa.inc_off = inc_off.p;
+        pa.inc = inc.p;
+        pa.sup = sup.p;
+        pa.rnd = rnd.p;
+        pa.level = level.p;
+        pa.subsize = subsize.p;
+        pa.front[0] = front0.p;
+        pa.front[1] = front1.p;
+        pa.live_chunks = (int32_t)((chunks + grid - 1) / grid);
+        CHK(live.alloc(grid * pa.live_chunks * PEEL_TB));
+        pa.live = live.p;
+        pa.ctl = ctl.p;
+        hipLaunchKernelGGL(k_peel_begin, dim3(std::min(grid_for(m), 2048u)), dim3(TB), 0, s, ctl.p, rnd.p, (int32_t)m);
         CHK(hipGetLastError());
-        if (lev > maxlev) maxlev = lev;
-        ranked += nf;
-        nlive -= nf;
-        ++r;
-        int32_t* t = live.p; live.p = keep.p; keep.p = t;
+        void* args[] = {&pa};
+        CHK(hipLaunchCooperativeKernel((void*)k_peel, dim3((unsigned)grid), dim3(PEEL_TB), args, 0, s));
+        CHK(hipMemcpyAsync(g->h_counters, ctl.p, sizeof(PeelCtl), hipMemcpyDeviceToHost, s));
+        CHK(hipStreamSynchronize(s));
+        const PeelCtl* hc = (const PeelCtl*)g->h_counters;
+        if (hc->err) return EBBKC_E_HIP;
+        g->tau = hc->tau;
+        g->rounds = hc->rounds;
+        hipLaunchKernelGGL(k_round_keys, dim3(grid_for(m)), dim3(TB), 0, s, rnd.p, m, rk1.p, (uint32_t*)byrank.p);
+        CHK(radix_sort_u32(rk1.p, (uint32_t*)byrank.p, rk2.p, rv2.p, m, bits_for((uint64_t)(g->rounds - 1)), rhist.p,
+                           rtmp.p, s));
+        hipLaunchKernelGGL(k_scatter_pos, dim3(grid_for(m)), dim3(TB), 0, s, (const uint32_t*)byrank.p, m, rank.p);
+        CHK(hipGetLastError());
     }
-    g->tau = maxlev;
-    g->rounds = r;
 
     // ---- root edge order from a vertex order (ablation orderings): edges in the
     // lexicographic order of their endpoints' positions replace pi_tau; levels
@@ -657,6 +1140,9 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
             // vertex of degree <= s leaves in one round, placed by (round, id)
             DBuf<int32_t> deg, vlive, vkeep, vfront, vflag, vrnd;
             DBuf<int64_t> vps;
+            DBuf<PeelState> st;
+            PeelState* hst = (PeelState*)g->h_counters;
+            CHK(st.alloc(1));
             CHK(deg.alloc(n));
             CHK(vlive.alloc(n));
             CHK(vkeep.alloc(n));
@@ -702,6 +1188,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
                                v1.p);
             CHK(radix_sort_u64(k1.p, v1.p, k2.p, v2.p, m, bits_for((uint64_t)n * (uint64_t)n), rh.p, rht.p, s));
             hipLaunchKernelGGL(k_scatter_pos, dim3(grid_for(m)), dim3(TB), 0, s, v1.p, m, rank.p);
+            CHK(hipMemcpyAsync(byrank.p, v1.p, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToDevice, s));
             CHK(hipGetLastError());
         }
         g->vpos = vpos.release();
@@ -710,38 +1197,22 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
 
     // ---- rank-tagged adjacency
     DBuf<int32_t> erank;
-    DBuf<uint64_t> keys, keys2;
-    DBuf<uint32_t> vals, vals2;
-    DBuf<int64_t> hist;
+    DBuf<uint32_t> rv1;
     DBuf<int2> rrow, orow;
-    DBuf<int32_t> orp, byrank;
     CHK(erank.alloc(nnz));
-    CHK(keys.alloc(nnz));
-    CHK(keys2.alloc(nnz));
-    CHK(vals.alloc(nnz));
-    CHK(vals2.alloc(nnz));
-    int64_t hn = radix_hist_elems(nnz);
-    CHK(hist.alloc(hn));
-    DBuf<int64_t> hist_tmp;
-    CHK(hist_tmp.alloc(scan_tmp_elems(hn) + 16));
+    CHK(rv1.alloc(nnz));
     CHK(rrow.alloc(nnz));
-    if (nnz) {
-        hipLaunchKernelGGL(k_erank_keys, dim3(grid_for(nnz)), dim3(TB), 0, s, src.p, eid.p, rank.p, nnz, m, erank.p,
-                           keys.p, vals.p);
-        int bits = bits_for((uint64_t)n * (uint64_t)m);
-        CHK(radix_sort_u64(keys.p, vals.p, keys2.p, vals2.p, nnz, bits, hist.p, hist_tmp.p, s));
-        hipLaunchKernelGGL(k_gather_rrow, dim3(grid_for(nnz)), dim3(TB), 0, s, vals.p, ci.p, erank.p, nnz, rrow.p);
-    }
-    CHK(orp.alloc(n + 1));
     CHK(orow.alloc(m));
-    if (n) {
-        hipLaunchKernelGGL(k_copy_i64_to_i32, dim3(grid_for(n + 1)), dim3(TB), 0, s, ooff.p, orp.p, (int64_t)n + 1);
-        hipLaunchKernelGGL(k_out_fill, dim3(wgrid), dim3(TB), 0, s, rp.p, ci.p, eid.p, rrow.p, n, ooff.p, orow.p,
-                           (int32_t*)nullptr, 1);
-    }
-    CHK(byrank.alloc(m));
-    if (m) {
-        hipLaunchKernelGGL(k_byrank, dim3(grid_for(m)), dim3(TB), 0, s, rank.p, m, byrank.p);
+    if (nnz) {
+        hipLaunchKernelGGL(k_erank, dim3(grid_for(nnz)), dim3(TB), 0, s, eid.p, rank.p, nnz, erank.p);
+        hipLaunchKernelGGL(k_rrow_keys, dim3(grid_for(m)), dim3(TB), 0, s, byrank.p, eu.p, ev.p, m, rk1.p, rv1.p);
+        CHK(radix_sort_u32(rk1.p, rv1.p, rk2.p, rv2.p, nnz, bits_for((uint64_t)(n - 1)), rhist.p, rtmp.p, s));
+        hipLaunchKernelGGL(k_gather_rrow, dim3(grid_for(nnz)), dim3(TB), 0, s, rv1.p, byrank.p, eu.p, ev.p, m, rrow.p);
+        hipLaunchKernelGGL(k_out_flags, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, src.p, ci.p, rrow.p, nnz, oflag.p);
+        CHK(exclusive_scan_i32(oflag.p, opos.p, nnz, nullptr, scan_tmp.p, s));
+        hipLaunchKernelGGL(k_out_fill, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, ci.p, eid.p, rrow.p, n, nnz, oflag.p,
+                           opos.p, orow.p, (int32_t*)nullptr);
+        CHK(hipGetLastError());
     }
     // ---- adjacency bitmap for sub-branch builds by pair tests (small graphs)
     DBuf<uint64_t> adj;
@@ -777,6 +1248,10 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     g->orp = orp.release();
     g->orow = orow.release();
     g->byrank = byrank.release();
+    if (g->opt.ordering == EBBKC_ORDER_HYBRID || g->opt.ordering == EBBKC_ORDER_TRUSS) {
+        g->subsize = subsize.release();  // of pi_tau; another edge order has other sub-branches
+        g->subsize_ready = true;
+    }
     if (with_adj) {
         g->adj = adj.release();
         g->acum = acum.release();

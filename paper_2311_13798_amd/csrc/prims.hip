@@ -193,30 +193,40 @@ hipError_t bin_sort_u8(const uint8_t* keys, int64_t n, uint32_t* out, int64_t* h
     return hipGetLastError();
 }
 
-hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
+template <typename K>
+static hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, int64_t n,
                           int bits, int64_t* hist, int64_t* tmp, hipStream_t s) {
     if (n <= 1 || bits <= 0) return hipSuccess;
     int64_t nb = (n + RS_TILE - 1) / RS_TILE;
-    uint64_t *ka = keys, *kb = keys_alt;
+    K *ka = keys, *kb = keys_alt;
     uint32_t *va = vals, *vb = vals ? vals_alt : nullptr;
     int passes = (bits + 7) / 8;
     for (int p = 0; p < passes; ++p) {
         int shift = p * 8;
-        hipLaunchKernelGGL(k_rs_hist<uint64_t>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, n, shift, nb, hist);
+        hipLaunchKernelGGL(k_rs_hist<K>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, n, shift, nb, hist);
         hipError_t e = exclusive_scan_i64(hist, hist, 256 * nb, nullptr, tmp, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_rs_scatter<uint64_t>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, va, kb, vb, n, shift, nb,
+        hipLaunchKernelGGL(k_rs_scatter<K>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, va, kb, vb, n, shift, nb,
                            hist);
-        uint64_t* kt = ka; ka = kb; kb = kt;
+        K* kt = ka; ka = kb; kb = kt;
         uint32_t* vt = va; va = vb; vb = vt;
     }
     if (passes & 1) {
-        hipError_t e = hipMemcpyAsync(keys, ka, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s);
+        hipError_t e = hipMemcpyAsync(keys, ka, sizeof(K) * n, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return e;
         if (vals) e = hipMemcpyAsync(vals, va, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return e;
     }
     return hipGetLastError();
+}
+
+hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
+                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s) {
+    return radix_sort<uint64_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s);
+}
+hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, int64_t n,
+                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s) {
+    return radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s);
 }
 
 }  // namespace ebb
