@@ -247,6 +247,11 @@ struct TrussArgs {
     uint64_t* per_task;
 };
 
+// The members of every edge slot, in any order, at gid + next[rank of the
+// seed] (an entry per edge rank, advanced past them): the opposite vertex of
+// every triangle of which the seed is the first edge.
+hipError_t launch_candidates(const GraphView& G, int32_t n, unsigned long long* next, int32_t* gid, int32_t* rows_tmp,
+                             hipStream_t s);
 hipError_t launch_build(int W, const BuildArgs& a, int cus, hipStream_t s);
 hipError_t launch_search_truss(int W, const TrussArgs& a, int cus, hipStream_t s);
 size_t truss_slab_bytes(int cus);

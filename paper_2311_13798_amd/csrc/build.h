@@ -14,9 +14,10 @@
 //                  its rank found from the bitmap's cumulative counts): about
 //                  c^2 / 2 tests, against about c times the out-degree for a
 //                  scan.  Otherwise every member's degree-oriented row prefix
-//                  ranked after r is scanned (all members' prefixes flattened
-//                  over the wave's lanes) against an LDS hash of V(g_i); each
-//                  such edge is met exactly once.  Both give the same rows.
+//                  ranked after r is streamed, one member at a time over the
+//                  wave's lanes, against an LDS hash of V(g_i); each such edge
+//                  is met exactly once, and the rows are made symmetric by bit
+//                  transposes.  Both give the same rows.
 //   3. colouring   greedy colouring (colours 1, 2, ...) visiting vertices by
 //                  non-increasing degree in g_i, ties to the smaller vertex
 //                  id (Section 4.3; Algorithm EBBkC-H colours each g_i).
@@ -31,26 +32,31 @@
 
 namespace ebb {
 
+// hash slots: at most a quarter of them taken
 template <int W>
-constexpr int hash_size() { return W <= 1 ? 128 : (W <= 2 ? 256 : 512); }
+constexpr int hash_size() { return W <= 1 ? 256 : (W <= 2 ? 512 : 1024); }
+template <int W>
+constexpr int hash_bits() { return W <= 1 ? 8 : (W <= 2 ? 9 : 10); }
+constexpr uint16_t HASH_FREE = 0xFFFF;
 
 // LDS bytes of the build's work areas (BuildScratch) for width class W
 template <int W>
-constexpr int build_scratch_bytes() { return 4 * 64 * W + 4 * 64 * W + 4 * hash_size<W>() + 2 * hash_size<W>() + 2 * 64 * W; }
+constexpr int build_scratch_bytes() { return 4 * 64 * W + 4 * 64 * W + 2 * hash_size<W>() + 2 * 64 * W; }
 
-__device__ __forceinline__ uint32_t hslot(int32_t key, int hs) {
-    return ((uint32_t)key * 2654435761u) & (uint32_t)(hs - 1);
+template <int W>
+__device__ __forceinline__ uint32_t hslot(int32_t key) {
+    return ((uint32_t)key * 2654435761u) >> (32 - hash_bits<W>());
 }
 
 // The build's LDS work areas: candidate ids, a per-vertex key, the open
-// addressing hash (id -> local index) and a visiting sequence.
+// addressing hash (slot -> local index, whose id gid holds) and a visiting
+// sequence.
 template <int W>
 struct BuildScratch {
-    int32_t* gid;   // [64 W]
-    int32_t* key;   // [64 W]
-    int32_t* hkey;  // [hash_size]
-    int16_t* hval;  // [hash_size]
-    int16_t* seq;   // [64 W]
+    int32_t* gid;    // [64 W]
+    int32_t* key;    // [64 W]
+    uint16_t* hidx;  // [hash_size]
+    int16_t* seq;    // [64 W]
     // carve the areas out of `base` (4-byte aligned, build_scratch_bytes<W>() bytes)
     __device__ static BuildScratch carve(void* base) {
         char* p = reinterpret_cast<char*>(base);
@@ -59,26 +65,45 @@ struct BuildScratch {
         p += 4 * 64 * W;
         S.key = reinterpret_cast<int32_t*>(p);
         p += 4 * 64 * W;
-        S.hkey = reinterpret_cast<int32_t*>(p);
-        p += 4 * hash_size<W>();
-        S.hval = reinterpret_cast<int16_t*>(p);
+        S.hidx = reinterpret_cast<uint16_t*>(p);
         p += 2 * hash_size<W>();
         S.seq = reinterpret_cast<int16_t*>(p);
         return S;
     }
 };
 
+// local index of vertex id `key`, or -1
 template <int W>
 __device__ __forceinline__ int hash_find(const BuildScratch<W>& S, int32_t key) {
-    constexpr int HS = hash_size<W>();
-    uint32_t h = hslot(key, HS);
-    for (int t = 0; t < HS; ++t) {
-        int32_t kk = S.hkey[h];
-        if (kk == key) return S.hval[h];
-        if (kk < 0) return -1;
-        h = (h + 1) & (HS - 1);
+    uint32_t h = hslot<W>(key);
+    for (;;) {  // some slot is free
+        const uint16_t i = S.hidx[h];
+        if (i == HASH_FREE) return -1;
+        if (S.gid[i] == key) return i;
+        h = (h + 1) & (hash_size<W>() - 1);
     }
-    return -1;
+}
+
+// the c ids of S.gid into the hash: every id tries its slot, the ones that
+// find it taken (or lose it to another lane) move on
+template <int W>
+__device__ __forceinline__ void hash_build(const BuildScratch<W>& S, int c) {
+    const int lane = lane_id();
+    for (int j = lane; j < hash_size<W>() / 2; j += 64) reinterpret_cast<uint32_t*>(S.hidx)[j] = 0xFFFFFFFFu;
+    wave_sync();
+    for (int i0 = 0; i0 < c; i0 += 64) {
+        const int i = i0 + lane;
+        bool wait = i < c;
+        uint32_t h = wait ? hslot<W>(S.gid[i]) : 0;
+        while (ballot(wait)) {
+            const bool try_now = wait && S.hidx[h] == HASH_FREE;
+            if (try_now) S.hidx[h] = (uint16_t)i;
+            wave_sync();
+            if (try_now && S.hidx[h] == (uint16_t)i) wait = false;
+            else if (wait) h = (h + 1) & (hash_size<W>() - 1);
+            wave_sync();
+        }
+    }
 }
 
 // Whether (x, w) is an edge of G ranked after r: a bit of the adjacency
@@ -145,24 +170,121 @@ __device__ __forceinline__ int prefix_after(const int32_t* __restrict__ rp, cons
     return lo - base;
 }
 
+// Edges of g_i by streaming the members' degree-oriented rows: rows[j] |= bit
+// i for every edge met at member i, one direction only (the lanes of a step
+// hold different j, so their LDS updates do not collide), then made symmetric.
+// The members are taken one after the other by the whole wave: their offsets
+// and prefix lengths are lane values read into scalars, so a step of 64
+// entries is a load (issued a step ahead), a hash probe and the update, about
+// 30 instructions; VALU-bound.  R-MAT s18 streams 9.1e9 entries for its 3.3 M
+// sub-branches: the three classes' builds take 18.0, 11.2 and 6.5 ms (flattening
+// all prefixes over the lanes, with a binary search of the member per entry,
+// and finding the members again by row searches took 56.6, 57.9 and 33.3 ms).
+template <int W>
+__device__ __forceinline__ void scan_edges(const GraphView& G, int32_t r, int c, uint64_t (*rows)[W],
+                                           const BuildScratch<W>& S) {
+    const int lane = lane_id();
+    int off[W], len[W];
+    {
+        // prefixes ranked after r: binary searches of the W members of a lane side by side
+        int lo[W], hi[W];
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            const int i = lane + 64 * q;
+            const int32_t w = i < c ? S.gid[i] : -1;
+            off[q] = w >= 0 ? G.orp[w] : 0;
+            lo[q] = off[q];
+            hi[q] = w >= 0 ? G.orp[w + 1] : 0;
+        }
+        bool more = true;
+        while (more) {
+            int y[W];
+#pragma unroll
+            for (int q = 0; q < W; ++q) y[q] = lo[q] < hi[q] ? G.orow[(lo[q] + hi[q]) >> 1].y : 0;
+            more = false;
+#pragma unroll
+            for (int q = 0; q < W; ++q) {
+                if (lo[q] < hi[q]) {
+                    const int mid = (lo[q] + hi[q]) >> 1;
+                    if (y[q] > r) lo[q] = mid + 1; else hi[q] = mid;
+                }
+                more |= lo[q] < hi[q];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < W; ++q) len[q] = lo[q] - off[q];
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        // members with a non-empty prefix
+        uint64_t todo = uni64(ballot(len[q] > 0));
+        if (!todo) continue;
+        int i = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        int p = __builtin_amdgcn_readlane(off[q], i), e = p + __builtin_amdgcn_readlane(len[q], i);
+        int32_t nb = p + lane < e ? G.orow[p + lane].x : -1;
+        for (;;) {
+            // the step after this one: the member's next 64 entries, or the next member
+            const int ci_ = i;
+            const int32_t cur = nb;
+            bool last = false;
+            p += 64;
+            if (p >= e) {
+                last = todo == 0;
+                if (!last) {
+                    i = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    p = __builtin_amdgcn_readlane(off[q], i);
+                    e = p + __builtin_amdgcn_readlane(len[q], i);
+                }
+            }
+            nb = !last && p + lane < e ? G.orow[p + lane].x : -1;
+            if (cur >= 0) {
+                const int j = hash_find(S, cur);
+                if (j >= 0) atomicOr((unsigned long long*)&rows[j][q], 1ull << ci_);
+            }
+            if (last) break;
+        }
+    }
+    wave_sync();
+    uint64_t T[W][W];
+#pragma unroll
+    for (int q = 0; q < W; ++q)
+#pragma unroll
+        for (int w = 0; w < W; ++w) T[q][w] = lane + 64 * q < c ? rows[lane + 64 * q][w] : 0;
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < W; ++q)
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint64_t t = T[q][w] | transpose64(T[w][q]);
+            if (lane + 64 * q < c) rows[lane + 64 * q][w] = t;
+        }
+}
+
 // Steps 1-3 for the seed (u, v) of rank r (a vertex slot passes u = v and the
-// rank threshold of its out-edges): candidates into S.gid, their symmetric
-// adjacency bitmap into rows (candidate order), colours into col.  Returns
-// c = |V(g_i)| (uniform), or -1 when c exceeds 64 W or differs from expect
-// (expect < 0: not checked); *twoE = 2 |E(g_i)|.
+// rank threshold of its out-edges): candidates into S.gid -- those given (the
+// c = expect members in any order), else found --, their symmetric adjacency
+// bitmap into rows (candidate order), colours into col.  Returns c = |V(g_i)|
+// (uniform), or -1 when c exceeds 64 W or differs from expect (expect < 0: not
+// checked); *twoE = 2 |E(g_i)|.
 template <int W>
 __device__ int build_subbranch(const GraphView& G, int32_t u, int32_t v, int32_t r, int expect,
-                               const int32_t* __restrict__ vcol, uint64_t (*rows)[W], int16_t* col,
-                               const BuildScratch<W>& S, uint32_t* twoE) {
+                               const int32_t* __restrict__ given, const int32_t* __restrict__ vcol,
+                               uint64_t (*rows)[W], int16_t* col, const BuildScratch<W>& S, uint32_t* twoE) {
     const int lane = lane_id();
     constexpr int CAP = 64 * W;
-    constexpr int HS = hash_size<W>();
 
     // ---- 1. candidates
+    int c = 0;
+    if (given) {
+        c = expect;
+        if (c > CAP) return -1;
+        for (int i = lane; i < c; i += 64) S.gid[i] = given[i];
+    } else {
     const int lu = prefix_after(G.rp, G.rrow, u, r), lv = prefix_after(G.rp, G.rrow, v, r);
     const int32_t xs = lu <= lv ? u : v, ys = lu <= lv ? v : u;
     const int lx = lu <= lv ? lu : lv;
-    int c = 0;
     const int32_t xrow = G.rp[xs];
     for (int base = 0; base < lx; base += 64 * BUILD_PB) {
         int32_t wv[BUILD_PB], yv[BUILD_PB];
@@ -184,6 +306,7 @@ __device__ int build_subbranch(const GraphView& G, int32_t u, int32_t v, int32_t
             }
             c += popc64(mk);
         }
+    }
     }
     c = uniform_i32(c);
     if (c > CAP || (expect >= 0 && c != expect)) return -1;
@@ -219,62 +342,9 @@ __device__ int build_subbranch(const GraphView& G, int32_t u, int32_t v, int32_t
             }
         }
     } else {
-        for (int j = lane; j < HS; j += 64) S.hkey[j] = -1;
         wave_sync();
-        for (int i = lane; i < c; i += 64) {
-            const int32_t key = S.gid[i];
-            uint32_t h = hslot(key, HS);
-            while (true) {
-                const int32_t old = atomicCAS(&S.hkey[h], -1, key);
-                if (old == -1) { S.hval[h] = (int16_t)i; break; }
-                h = (h + 1) & (HS - 1);
-            }
-        }
-        wave_sync();
-        {
-            int plen[W];
-#pragma unroll
-            for (int q = 0; q < W; ++q) {
-                const int i = lane + 64 * q;
-                plen[q] = 0;
-                if (i < c) {
-                    const int32_t w = S.gid[i];
-                    int lo = G.orp[w], hi = G.orp[w + 1];
-                    const int base = lo;
-                    while (lo < hi) {
-                        int mid = (lo + hi) >> 1;
-                        if (G.orow[mid].y > r) lo = mid + 1; else hi = mid;
-                    }
-                    plen[q] = lo - base;
-                }
-            }
-            int total = 0;
-#pragma unroll
-            for (int q = 0; q < W; ++q) {
-                const int inc = wave_incl_scan(plen[q]);
-                const int i = lane + 64 * q;
-                if (i < c) S.key[i] = total + inc - plen[q];
-                total += __shfl(inc, 63, 64);
-            }
-            wave_sync();
-            for (int base = 0; base < total; base += 64) {
-                const int j = base + lane;
-                if (j < total) {
-                    int lo = 0, hi = c;  // last member whose offset is <= j
-                    while (hi - lo > 1) {
-                        int mid = (lo + hi) >> 1;
-                        if (S.key[mid] <= j) lo = mid; else hi = mid;
-                    }
-                    const int i = lo;
-                    const int2 yr = G.orow[G.orp[S.gid[i]] + (j - S.key[i])];
-                    const int jj = hash_find(S, yr.x);
-                    if (jj >= 0) {
-                        atomicOr((unsigned long long*)&rows[i][jj >> 6], 1ull << (jj & 63));
-                        atomicOr((unsigned long long*)&rows[jj][i >> 6], 1ull << (i & 63));
-                    }
-                }
-            }
-        }
+        hash_build(S, c);
+        scan_edges(G, r, c, rows, S);
     }
     wave_sync();
 

@@ -157,12 +157,14 @@ __global__ __launch_bounds__(SEED_BLOCK) void k_seed_parts(SeedSums* __restrict_
 // order (class ascending, sizes descending: size 64 W - i of class W is bin
 // 64 (W - 1) + i).  rthr (vertex slots): an item's out-edges start at the rank
 // equal to the vertices of the slots before it; the threshold is one below.
+// next (by rank): where launch_candidates writes a slot's members.
 __global__ __launch_bounds__(SEED_BLOCK) void k_seed_fill(const int32_t* __restrict__ id,
                                                           const int32_t* __restrict__ size, bool by_id, int64_t n,
                                                           const SeedSums* __restrict__ part,
                                                           int32_t* __restrict__ seed_id, int32_t* __restrict__ seed_c,
                                                           int32_t* __restrict__ rthr, int64_t* __restrict__ row_off,
-                                                          int64_t* __restrict__ vtx_off, uint8_t* __restrict__ key) {
+                                                          int64_t* __restrict__ vtx_off, uint8_t* __restrict__ key,
+                                                          unsigned long long* __restrict__ next) {
     __shared__ uint64_t ws[SEED_BLOCK / EBB_WAVE];
     const int lane = lane_id(), w = threadIdx.x / EBB_WAVE;
     SeedSums b = part[blockIdx.x];
@@ -186,6 +188,7 @@ __global__ __launch_bounds__(SEED_BLOCK) void k_seed_fill(const int32_t* __restr
             row_off[s] = b.words + (int64_t)(before & 0xFFFFFF);
             vtx_off[s] = vo;
             if (rthr) rthr[s] = (int32_t)(vo - 1);
+            if (next) next[r] = (unsigned long long)vo;
             const int W = width_of(c);
             key[s] = (uint8_t)(64 * (W - 1) + 64 * W - c);
         }
@@ -429,9 +432,16 @@ static ebbkc_status build_slots(ebbkc_graph* g, const int32_t* id, const int32_t
     CHKH(key.alloc(ns));
     CHKH(hist.alloc(radix_hist_elems(ns)));
     CHKH(htmp.alloc(scan_tmp_elems(radix_hist_elems(ns)) + 64));
+    DBuf<unsigned long long> next;
+    DBuf<int32_t> trows;
+    if (!vertex) {
+        CHKH(next.alloc(n));
+        CHKH(trows.alloc(2 + 2 * (int64_t)g->n));
+    }
     hipLaunchKernelGGL(k_seed_fill, dim3((unsigned)nt), dim3(SEED_BLOCK), 0, s, id, size, by_id, n, part.p, S.seed.p,
-                       S.c.p, S.rthr.p, S.roff.p, S.voff.p, key.p);
+                       S.c.p, S.rthr.p, S.roff.p, S.voff.p, key.p, next.p);
     CHKH(hipGetLastError());
+    if (!vertex) CHKH(launch_candidates(graph_view(g), g->n, next.p, S.gid.p, trows.p, s));
     // the slot order: by width class, largest sub-branches first
     CHKH(bin_sort_u8(key.p, ns, (uint32_t*)S.order.p, hist.p, htmp.p, s));
     for (int W = MAX_W; W >= 1; --W) {

@@ -56,6 +56,22 @@ __device__ __forceinline__ int wmin_i32(int x) {
                min(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
 }
 
+// Transpose of a 64 x 64 bit matrix held one row per lane: lane i gets the
+// bits i of all lanes, lane j's at position j (blocks swapped across lanes
+// lane ^ 32, ^ 16, .. ^ 1).  Every lane must be active.
+__device__ __forceinline__ uint64_t transpose64(uint64_t x) {
+    const int lane = lane_id();
+    constexpr uint64_t M[6] = {0x00000000FFFFFFFFull, 0x0000FFFF0000FFFFull, 0x00FF00FF00FF00FFull,
+                               0x0F0F0F0F0F0F0F0Full, 0x3333333333333333ull, 0x5555555555555555ull};
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        const int s = 32 >> b;
+        const uint64_t y = __shfl_xor(x, s, 64);
+        x = (lane & s) ? (x & ~M[b]) | ((y >> s) & M[b]) : (x & M[b]) | ((y << s) & ~M[b]);
+    }
+    return x;
+}
+
 // bits strictly above x within word w of a multi-word row
 __device__ __forceinline__ uint64_t upper_mask(int x, int w) {
     int xw = x >> 6, xb = x & 63;

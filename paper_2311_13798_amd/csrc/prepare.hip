@@ -181,6 +181,11 @@ __device__ __forceinline__ int tri_find(const TriHash<SLOTS, D>& H, int32_t w) {
     }
 }
 
+// Pass 2 runs over the rank-tagged rows (orow holds ranks instead of edge ids)
+// and gives each triangle's first edge its opposite vertex: cursor by rank,
+// gid the members (6.8 ms on R-MAT s18, where the search of every seed's
+// shorter row prefix in the other endpoint's row was most of a small
+// sub-branch's build).
 struct TriArgs {
     const int32_t* orp;
     const int2* orow;
@@ -191,12 +196,14 @@ struct TriArgs {
     const int64_t* inc_off;
     unsigned long long* cursor;
     int2* inc;
+    int32_t* gid;
+    const int32_t *rp, *ci, *erank;  // id-sorted rows (pass 2)
 };
 
 // The b of out(a) numbered first, first + stride, ... by a group of lanes
-template <int PASS, class Find, class Count>
-__device__ __forceinline__ void tri_stream(const TriArgs& T, int a0, int d, int first, int stride, Find&& find,
-                                           Count&& count_aw) {
+template <int PASS, class Find, class Count, class Rank>
+__device__ __forceinline__ void tri_stream(const TriArgs& T, int a, int a0, int d, int first, int stride, Find&& find,
+                                           Count&& count_aw, Rank&& rank_aw) {
     const int gl = lane_id() & (TRI_GROUP - 1), gbase = lane_id() & ~(TRI_GROUP - 1);
     for (int i = first; i < d; i += stride) {
         const int2 ab = T.orow[a0 + i];
@@ -211,7 +218,13 @@ __device__ __forceinline__ void tri_stream(const TriArgs& T, int a0, int d, int 
             t += TRI_GROUP;
             nxt = t < b1 ? T.orow[t] : make_int2(-1, 0);
             const int j = bw.x >= 0 ? find(bw.x) : -1;
-            if (PASS == 0) {
+            if (PASS == 2) {
+                if (j >= 0) {
+                    const int32_t raw = rank_aw(j);
+                    const int32_t r = ab.y < raw ? (ab.y < bw.y ? ab.y : bw.y) : (raw < bw.y ? raw : bw.y);
+                    T.gid[atomicAdd(&T.cursor[r], 1ull)] = r == ab.y ? bw.x : r == raw ? ab.x : a;
+                }
+            } else if (PASS == 0) {
                 if (j >= 0) {
                     ++c;
                     count_aw(j);
@@ -282,8 +295,9 @@ __global__ __launch_bounds__(TB) void k_tri_wave(TriArgs T) {
             tri_insert(H, own.x, lane);
         }
         wave_sync();
-        tri_stream<PASS>(T, a0, d, lane / TRI_GROUP, EBB_WAVE / TRI_GROUP,
-                         [&](int32_t w) { return tri_find(H, w); }, [&](int j) { return atomicAdd(&H.cnt[j], 1); });
+        tri_stream<PASS>(T, a, a0, d, lane / TRI_GROUP, EBB_WAVE / TRI_GROUP,
+                         [&](int32_t w) { return tri_find(H, w); }, [&](int j) { return atomicAdd(&H.cnt[j], 1); },
+                         [&](int j) { return T.orow[a0 + j].y; });
         wave_sync();
         if (PASS == 0 && lane < d) {
             T.naw[a0 + lane] = H.cnt[lane];
@@ -309,25 +323,32 @@ __global__ __launch_bounds__(TB) void k_tri_block(TriArgs T, const int32_t* __re
             __syncthreads();
             for (int i = threadIdx.x; i < d; i += TB) tri_insert(H, T.orow[a0 + i].x, i);
             __syncthreads();
-            tri_stream<PASS>(T, a0, d, first, stride, [&](int32_t w) { return tri_find(H, w); },
-                             [&](int j) { return atomicAdd(&H.cnt[j], 1); });
+            tri_stream<PASS>(T, a, a0, d, first, stride, [&](int32_t w) { return tri_find(H, w); },
+                             [&](int j) { return atomicAdd(&H.cnt[j], 1); }, [&](int j) { return T.orow[a0 + j].y; });
             __syncthreads();
             if (PASS == 0)
                 for (int i = threadIdx.x; i < d; i += TB) T.naw[a0 + i] = H.cnt[i];
         } else {  // out(a) searched in device memory; (a,w) counted there too
-            for (int i = threadIdx.x; i < d; i += TB) atomicExch(&T.naw[a0 + i], 0);
-            __syncthreads();
+            if (PASS != 2) {
+                for (int i = threadIdx.x; i < d; i += TB) atomicExch(&T.naw[a0 + i], 0);
+                __syncthreads();
+            }
+            // (the rank-tagged rows of pass 2 are not sorted by id: there the
+            // CSR row is searched, where an edge to w found from b is an
+            // out-edge of a too)
+            const int32_t* ids = PASS == 2 ? T.ci : nullptr;
+            const int s0 = PASS == 2 ? T.rp[a] : a0, s1 = PASS == 2 ? T.rp[a + 1] : a0 + d;
             tri_stream<PASS>(
-                T, a0, d, first, stride,
+                T, a, a0, d, first, stride,
                 [&](int32_t w) {
-                    int lo = a0, hi = a0 + d;
+                    int lo = s0, hi = s1;
                     while (lo < hi) {
                         const int mid = (lo + hi) >> 1;
-                        if (T.orow[mid].x < w) lo = mid + 1; else hi = mid;
+                        if ((ids ? ids[mid] : T.orow[mid].x) < w) lo = mid + 1; else hi = mid;
                     }
-                    return lo < a0 + d && T.orow[lo].x == w ? lo - a0 : -1;
+                    return lo < s1 && (ids ? ids[lo] : T.orow[lo].x) == w ? lo - s0 : -1;
                 },
-                [&](int j) { return atomicAdd(&T.naw[a0 + j], 1); });
+                [&](int j) { return atomicAdd(&T.naw[a0 + j], 1); }, [&](int j) { return T.erank[s0 + j]; });
             __syncthreads();
         }
         if (PASS == 0)
@@ -337,6 +358,16 @@ __global__ __launch_bounds__(TB) void k_tri_block(TriArgs T, const int32_t* __re
             }
         __syncthreads();
     }
+}
+
+// one pass over all rows (listed in rows by k_tri_rows)
+template <int PASS>
+hipError_t launch_tri(const TriArgs& T, const int32_t* rows, hipStream_t s) {
+    const unsigned gw = (unsigned)std::min<int64_t>(2048, (T.n + 3) / 4), gb = (unsigned)std::min<int64_t>(2048, T.n);
+    hipLaunchKernelGGL((k_tri_block<PASS, 4096, TRI_HASH_D>), dim3(gb), dim3(TB), 0, s, T, rows + 2 + T.n, rows + 1);
+    hipLaunchKernelGGL((k_tri_block<PASS, 1024, TRI_BLOCK_D>), dim3(gb), dim3(TB), 0, s, T, rows + 2, rows);
+    hipLaunchKernelGGL(k_tri_wave<PASS>, dim3(gw), dim3(TB), 0, s, T);
+    return hipGetLastError();
 }
 
 // where the (b,w) incidences of every edge go
@@ -919,6 +950,24 @@ int bits_for(uint64_t x) {
 
 }  // namespace
 
+hipError_t launch_candidates(const GraphView& G, int32_t n, unsigned long long* next, int32_t* gid, int32_t* rows_tmp,
+                             hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipError_t e = hipMemsetAsync(rows_tmp, 0, 2 * sizeof(int32_t), s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_tri_rows, dim3(grid_for(n)), dim3(TB), 0, s, G.orp, n, rows_tmp);
+    TriArgs T{};
+    T.orp = G.orp;
+    T.orow = G.orow;
+    T.n = n;
+    T.cursor = next;
+    T.gid = gid;
+    T.rp = G.rp;
+    T.ci = G.ci;
+    T.erank = G.erank;
+    return launch_tri<2>(T, rows_tmp, s);
+}
+
 #define CHK(expr)                                   \
     do {                                            \
         hipError_t e_ = (expr);                     \
@@ -1005,16 +1054,16 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     CHK(inc_off.alloc(m + 1));
     CHK(hipMemsetAsync(sup.p, 0, sizeof(int32_t) * (size_t)(m > 0 ? m : 1), s));
     CHK(hipMemsetAsync(trows.p, 0, 2 * sizeof(int32_t), s));
-    TriArgs tri{orp.p, orow_id.p, n, sup.p, nab.p, naw.p, nullptr, nullptr, nullptr};
-    const unsigned twave = (unsigned)std::min<int64_t>(2048, (n + 3) / 4);
-    const unsigned tblock = (unsigned)std::min<int64_t>(2048, n);
+    TriArgs tri{};
+    tri.orp = orp.p;
+    tri.orow = orow_id.p;
+    tri.n = n;
+    tri.sup = sup.p;
+    tri.nab = nab.p;
+    tri.naw = naw.p;
     if (m) {
         hipLaunchKernelGGL(k_tri_rows, dim3(grid_for(n)), dim3(TB), 0, s, orp.p, n, trows.p);
-        hipLaunchKernelGGL((k_tri_block<0, 4096, TRI_HASH_D>), dim3(tblock), dim3(TB), 0, s, tri, trows.p + 2 + n,
-                           trows.p + 1);
-        hipLaunchKernelGGL((k_tri_block<0, 1024, TRI_BLOCK_D>), dim3(tblock), dim3(TB), 0, s, tri, trows.p + 2, trows.p);
-        hipLaunchKernelGGL(k_tri_wave<0>, dim3(twave), dim3(TB), 0, s, tri);
-        CHK(hipGetLastError());
+        CHK(launch_tri<0>(tri, trows.p, s));
     }
     CHK(exclusive_scan_i32(sup.p, inc_off.p, m, inc_off.p + m, scan_tmp.p, s));
     int64_t h_ninc = 0;
@@ -1032,13 +1081,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
         tri.inc_off = inc_off.p;
         tri.cursor = (unsigned long long*)cursor.p;
         tri.inc = inc.p;
-        if (h_ninc) {
-            hipLaunchKernelGGL((k_tri_block<1, 4096, TRI_HASH_D>), dim3(tblock), dim3(TB), 0, s, tri, trows.p + 2 + n,
-                               trows.p + 1);
-            hipLaunchKernelGGL((k_tri_block<1, 1024, TRI_BLOCK_D>), dim3(tblock), dim3(TB), 0, s, tri, trows.p + 2,
-                               trows.p);
-            hipLaunchKernelGGL(k_tri_wave<1>, dim3(twave), dim3(TB), 0, s, tri);
-        }
+        if (h_ninc) CHK(launch_tri<1>(tri, trows.p, s));
     }
     CHK(hipGetLastError());
     DBuf<int32_t> sup0;

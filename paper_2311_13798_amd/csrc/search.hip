@@ -830,7 +830,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             const BuildScratch<W> S = BuildScratch<W>::carve(&M.md[0]);
             const int32_t e = (int32_t)slot;
             uint32_t twoE = 0;
-            if (build_subbranch<W>(B.G, B.G.eu[e], B.G.ev[e], B.G.rank[e], c, B.vcol, M.rows, M.col, S, &twoE) < 0) {
+            if (build_subbranch<W>(B.G, B.G.eu[e], B.G.ev[e], B.G.rank[e], c, nullptr, B.vcol, M.rows, M.col, S, &twoE) < 0) {
                 if (lane == 0) atomicOr(a.err, ERR_WIDTH);
                 goto task_done;
             }

@@ -61,7 +61,10 @@ __global__ __launch_bounds__(256) void k_build(BuildArgs a) {
         const int32_t u = a.seed_rthr ? e : G.eu[e], v = a.seed_rthr ? e : G.ev[e];
         const int32_t r = a.seed_rthr ? a.seed_rthr[s] : G.rank[e];
         uint32_t twoE = 0;
-        const int c = build_subbranch<W>(G, u, v, r, a.seed_c[s], a.vcol, M.rows, M.col, S, &twoE);
+        const int64_t ro = a.row_off[s], vo = a.vtx_off[s];
+        // edge slots hold their members already (launch_candidates)
+        const int c = build_subbranch<W>(G, u, v, r, a.seed_c[s], a.seed_rthr ? nullptr : a.gid + vo, a.vcol, M.rows,
+                                         M.col, S, &twoE);
         if (c < 0) {
             if (lane == 0) atomicOr(a.err, ERR_WIDTH);
             continue;
@@ -69,7 +72,6 @@ __global__ __launch_bounds__(256) void k_build(BuildArgs a) {
         // relabel by colour desc, id asc, and write the slot
         int npos[W];
         order_positions<W>(c, M.col, S, npos);
-        const int64_t ro = a.row_off[s], vo = a.vtx_off[s];
 #pragma unroll
         for (int q = 0; q < W; ++q) {
             const int i = lane + 64 * q;
