@@ -96,8 +96,8 @@ def source_sha256(read=None) -> str:
             with open(os.path.join(CSRC, name), encoding="utf-8") as fh:
                 return fh.read()
     h = hashlib.sha256()
-    for f in ("search.hip", "build.h", "arena.h", "device_util.h", "common.h"):
-        h.update(code_of(read(f)).encode())
+    for f in ("search.hip", "search_kernel.h", "binom.h", "build.h", "arena.h", "device_util.h", "common.h"):
+        h.update(code_of(read(f) or "").encode())
     return h.hexdigest()
 
 

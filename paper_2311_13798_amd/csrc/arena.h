@@ -5,6 +5,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
+
+#include "../../include/ebbkc.h"
+
 namespace ebb {
 
 enum : int { ERR_WIDTH = 1, ERR_OVERFLOW = 2, ERR_DEPTH = 4, ERR_CAP = 8, ERR_QUEUE = 16 };
@@ -113,6 +117,15 @@ __host__ __device__ inline double log_binom(int n, int r) {
 }
 __host__ __device__ inline bool root_split(int c, int l0, double log_threshold) {
     return l0 >= 4 && c >= l0 + 8 && log_binom(c, l0) > log_threshold;
+}
+// The split threshold as a logarithm.  count_l4: a count whose whole roots at
+// l0 = 4 may be counted from their missing pairs, which a range of root
+// vertices may not; a whole root costs at most a few milliseconds there
+// whichever way it is counted, so by default none is split (R-MAT s18, k = 6:
+// 99.5 ms with ranges, 15.9 ms without).
+inline double split_log(const ebbkc_options& o, int l0, bool count_l4) {
+    if (o.split_threshold < 0 || (count_l4 && l0 == 4 && o.split_threshold == 0 && o.dense_k4 >= 0)) return 1e300;
+    return std::log(o.split_threshold > 0 ? (double)o.split_threshold : (double)(1 << 22));
 }
 template <class F>
 __host__ __device__ inline int root_tasks(int c, int l0, double log_threshold, F&& emit) {
@@ -255,6 +268,13 @@ hipError_t launch_candidates(const GraphView& G, int32_t n, unsigned long long* 
 hipError_t launch_build(int W, const BuildArgs& a, int cus, hipStream_t s);
 hipError_t launch_search_truss(int W, const TrussArgs& a, int cus, hipStream_t s);
 size_t truss_slab_bytes(int cus);
+// per width class (search_w<W>.hip): launch, workgroups of a launch, tables
+template <int W>
+hipError_t search_launch(bool build, const SearchArgs& a, int cus, int bpc, hipStream_t s);
+template <int W>
+int64_t search_blocks(bool build, int64_t ntasks, int cus, int bpc);
+template <int W>
+hipError_t search_tables(hipStream_t s);
 hipError_t launch_search(int W, bool build, const SearchArgs& a, int cus, int blocks_per_cu, hipStream_t s);
 int64_t search_grid_waves(int W, bool build, int64_t ntasks, int cus, int blocks_per_cu);
 size_t search_frame_bytes(int W);

@@ -114,9 +114,9 @@ __global__ void k_btask_fill(const int32_t* __restrict__ seed_c, int64_t n, int 
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int c = seed_c[i];
         if (c < l0) continue;
-        const int W = width_of(c);
         int64_t o = base + toff[i];
         root_tasks(c, l0, log_thr, [&](int x0, int x1) {
+            const int W = width_of(c - x0);  // the search drops the vertices before x0
             tasks[o] = task_pack(i, x0, x1);
             tgraph[o] = graph;
             const int usable = x0 == 0 && x1 >= c ? c : c - 1 - x0;
@@ -233,10 +233,9 @@ void free_tasks(ebbkc_batch* b) {
 ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
     free_tasks(b);
     const int n = (int)b->graphs.size();
-    const double thr = b->opt.split_threshold > 0 ? (double)b->opt.split_threshold : (double)(1 << 22);
     // a task that builds its g_i would rebuild it for every root range: one
     // task per seed there (the runtime split queue balances heavy ones)
-    const double log_thr = b->opt.split_threshold < 0 || b->build ? 1e300 : std::log(thr);
+    auto log_thr_of = [&](int l0) { return b->build ? 1e300 : split_log(b->opt, l0, true); };
     // per graph: task counts and offsets (scratch sized for the largest graph)
     std::vector<int64_t> gbase((size_t)n + 1, 0);
     std::vector<int64_t*> toffs((size_t)n, nullptr);
@@ -257,7 +256,8 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
         const int64_t ns = seeds_of(g);
         int64_t* to = nullptr;
         CHKB(dev_alloc(b, (void**)&to, sizeof(int64_t) * (ns + 1), s));
-        hipLaunchKernelGGL(k_btask_counts, dim3(gridn(ns)), dim3(256), 0, s, sizes_of(g), ns, k - 2, log_thr, tc);
+        hipLaunchKernelGGL(k_btask_counts, dim3(gridn(ns)), dim3(256), 0, s, sizes_of(g), ns, k - 2, log_thr_of(k - 2),
+                           tc);
         CHKB(exclusive_scan_i32(tc, to, ns, to + ns, tmp, s));
         CHKB(hipMemcpyAsync(&tcount[(size_t)i], to + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         toffs[(size_t)i] = to;
@@ -298,7 +298,7 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
         if (!toffs[(size_t)i]) continue;
         ebbkc_graph* g = b->graphs[(size_t)i];
         hipLaunchKernelGGL(k_btask_fill, dim3(gridn(seeds_of(g))), dim3(256), 0, s, sizes_of(g), seeds_of(g),
-                           b->ks[(size_t)i] - 2, log_thr, toffs[(size_t)i], gbase[(size_t)i], (int32_t)i, gbits, tasks,
+                           b->ks[(size_t)i] - 2, log_thr_of(b->ks[(size_t)i] - 2), toffs[(size_t)i], gbase[(size_t)i], (int32_t)i, gbits, tasks,
                            tg, keys, vals);
     }
     CHKB(radix_sort_u64(keys, vals, keys2, vals2, total, 10 + gbits, hist, htmp, s));

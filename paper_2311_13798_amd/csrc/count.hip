@@ -247,25 +247,27 @@ __global__ void k_task_counts(const int32_t* __restrict__ seed_c, int64_t i0, in
     }
 }
 
-__global__ void k_task_fill(const int32_t* __restrict__ seed_c, int64_t i0, int64_t n, int l0, double log_thr,
+// rest: a task's class is that of the vertices from its first one on (the
+// search drops the others), else its slot's
+__global__ void k_task_fill(const int32_t* __restrict__ seed_c, int64_t i0, int64_t n, int l0, double log_thr, bool rest,
                             const int64_t* __restrict__ toff, int64_t* __restrict__ tasks, uint64_t* __restrict__ keys,
                             uint32_t* __restrict__ vals, unsigned long long* __restrict__ cls_count) {
     uint64_t per_class[4] = {0, 0, 0, 0};  // tasks per width class, added once per wave below
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int c = seed_c[i0 + i];
         if (c < l0) continue;
-        const int W = width_of(c);
         int64_t o = toff[i];
-        const int nt = root_tasks(c, l0, log_thr, [&](int x0, int x1) {
+        root_tasks(c, l0, log_thr, [&](int x0, int x1) {
+            const int W = width_of(rest ? c - x0 : c);
             tasks[o] = task_pack(i0 + i, x0, x1);
             // heaviest first: more vertices after the first one of the range
             const int usable = x0 == 0 && x1 >= c ? c : c - 1 - x0;
             keys[o] = ((uint64_t)(W - 1) << 8) | (uint64_t)(255 - (usable > 255 ? 255 : usable));
             vals[o] = (uint32_t)o;
             ++o;
-        });
 #pragma unroll
-        for (int w = 0; w < 4; ++w) per_class[w] += w == W - 1 ? (uint64_t)nt : 0;
+            for (int w = 0; w < 4; ++w) per_class[w] += w == W - 1;
+        });
     }
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -589,7 +591,7 @@ static ebbkc_status read_total(ebbkc_graph* g, uint64_t* out, hipStream_t s) {
 
 // Task list of slots [i0, i1) at l0 = k-2, sorted (width class, heaviest
 // first) into `sorted`; class sizes into ccount.  Scratch comes from cv.
-static ebbkc_status make_tasks(ebbkc_graph* g, int64_t i0, int64_t n, int l0, double log_thr, hipStream_t s,
+static ebbkc_status make_tasks(ebbkc_graph* g, int64_t i0, int64_t n, int l0, double log_thr, bool rest, hipStream_t s,
                                Carve& cv, int64_t** sorted, int64_t* T_out, uint64_t ccount[4]) {
     int32_t* tcount = cv.take<int32_t>(n);
     int64_t* toff = cv.take<int64_t>(n + 1);
@@ -615,8 +617,8 @@ static ebbkc_status make_tasks(ebbkc_graph* g, int64_t i0, int64_t n, int l0, do
     if (!tasks || !tsorted || !keys || !keys2 || !vals || !vals2 || !hist || !htmp) return EBBKC_E_OOM;
     unsigned long long* cls_count = (unsigned long long*)(g->d_counters + 12);
     CHKH(hipMemsetAsync(cls_count, 0, 4 * sizeof(uint64_t), s));
-    hipLaunchKernelGGL(k_task_fill, dim3(grid_for(n)), dim3(256), 0, s, g->seed_c, i0, n, l0, log_thr, toff, tasks,
-                       keys, vals, cls_count);
+    hipLaunchKernelGGL(k_task_fill, dim3(grid_for(n)), dim3(256), 0, s, g->seed_c, i0, n, l0, log_thr, rest, toff,
+                       tasks, keys, vals, cls_count);
     CHKH(radix_sort_u64(keys, vals, keys2, vals2, T, 10, hist, htmp, s));
     hipLaunchKernelGGL(k_gather_tasks, dim3(grid_for(T)), dim3(256), 0, s, tasks, vals, T, tsorted);
     CHKH(hipGetLastError());
@@ -824,26 +826,30 @@ static bool heavy_root(int c, int l0) {
 static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan& plan, std::vector<TaskSeg>& segs) {
     const SizeCounts& N = g->seed_sizes;
     int64_t T = 0, pos = 0;  // pos: first slot of the size in the slot order
-    for (int W = 1; W <= MAX_W; ++W) {
-        ClassTasks& ct = plan.cls[W - 1];
-        struct Range {
-            int usable, first, x0, x1;
-            int64_t slots;
-        };
-        std::vector<Range> rs;
+    struct Range {
+        int usable, first, x0, x1;
+        int64_t slots;
+    };
+    std::vector<Range> ranges[MAX_W];  // by the class of the vertices a range can use
+    for (ClassTasks& ct : plan.cls) {
         ct.slots = nullptr;
         ct.cmax = 0;
         ct.heavy = 0;
+    }
+    for (int W = 1; W <= MAX_W; ++W) {
+        ClassTasks& ct = plan.cls[W - 1];
         for (int c = 64 * W; c > 64 * (W - 1); --c) {
             const int64_t nc = N.n[c];
             if (nc == 0) continue;
             if (c >= l0) {
-                if (!ct.cmax) ct.cmax = c;
                 if (root_split(c, l0, log_thr)) {
                     root_tasks(c, l0, log_thr, [&](int x0, int x1) {
-                        rs.push_back({x0 == 0 && x1 >= c ? c : c - 1 - x0, (int)pos, x0, x1, nc});
+                        const int w = width_of(c - x0) - 1;
+                        ranges[w].push_back({x0 == 0 && x1 >= c ? c : c - 1 - x0, (int)pos, x0, x1, nc});
+                        plan.cls[w].cmax = std::max(plan.cls[w].cmax, c - x0);
                     });
                 } else {
+                    ct.cmax = std::max(ct.cmax, c);
                     if (!ct.slots) ct.slots = g->seed_order + pos;
                     ct.nslots += nc;
                     if (heavy_root(c, l0)) ct.heavy += nc;
@@ -851,6 +857,10 @@ static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan
             }
             pos += nc;
         }
+    }
+    for (int w = 0; w < MAX_W; ++w) {
+        ClassTasks& ct = plan.cls[w];
+        std::vector<Range>& rs = ranges[w];
         std::stable_sort(rs.begin(), rs.end(), [](const Range& a, const Range& b) { return a.usable > b.usable; });
         for (const Range& r : rs) {
             segs.push_back(TaskSeg{T, r.first, (int16_t)r.x0, (int16_t)r.x1});
@@ -928,8 +938,8 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     }
     if (n <= 0) return read_total(g, out, s);
     const int l0 = k - 2;
-    const double thr = g->opt.split_threshold > 0 ? (double)g->opt.split_threshold : (double)(1 << 22);
-    const double log_thr = g->opt.split_threshold < 0 ? 1e300 : std::log(thr);
+    // (the fixed scratch holds what it held with every class split)
+    const double log_thr = split_log(g->opt, l0, !noalloc && g->opt.ordering != EBBKC_ORDER_TRUSS);
 
     // ---- tasks (the scratch is sized for the worst case: every slot split)
     const int64_t Tmax = n * (int64_t)(64 * MAX_W);
@@ -986,7 +996,7 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     int64_t* tsorted = nullptr;
     uint64_t ccount[4] = {0, 0, 0, 0};
     int64_t T2 = 0;
-    st = make_tasks(g, i0, n, l0, log_thr, s, cv, &tsorted, &T2, ccount);
+    st = make_tasks(g, i0, n, l0, log_thr, noalloc || g->opt.ordering != EBBKC_ORDER_TRUSS, s, cv, &tsorted, &T2, ccount);
     if (st) return st == EBBKC_E_OOM ? e_space : st;
     void* gframes = deep ? (void*)cv.take<char>((int64_t)fbytes) : nullptr;
     if (deep && !gframes) return e_space;
@@ -1051,8 +1061,7 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
         const int64_t n = i1 - i0;
         if (n > 0) {
             const int l0 = k - 2;
-            const double thr = g->opt.split_threshold > 0 ? (double)g->opt.split_threshold : (double)(1 << 22);
-            const double log_thr = g->opt.split_threshold < 0 ? 1e300 : std::log(thr);
+            const double log_thr = split_log(g->opt, l0, false);
             // every slot and none split (nor of size 256, whose place among
             // the tasks of size 255 the order does not keep): the slot order
             // is the task order
@@ -1089,7 +1098,7 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
                     int64_t* tsorted = nullptr;
                     uint64_t ccount[4] = {0, 0, 0, 0};
                     int64_t T2 = 0;
-                    st = make_tasks(g, i0, n, l0, log_thr, s, cv, &tsorted, &T2, ccount);
+                    st = make_tasks(g, i0, n, l0, log_thr, false, s, cv, &tsorted, &T2, ccount);
                     if (st) return st;
                     plan = TaskPlan::of_list(tsorted, ccount);
                 }
