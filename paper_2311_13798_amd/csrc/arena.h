@@ -25,6 +25,7 @@ constexpr int LIST_LDS_FRAMES = 16;      // listing frames kept in LDS
 // listing kernel); a listing runs both kernels
 constexpr int SEARCH_DEEP_K = 2 + 2 * LDS_FRAMES + 4;
 constexpr int LIST_DEEP_K = 2 + 2 * LIST_LDS_FRAMES + 2;
+constexpr int SEARCH_BRANCH_K = 8;       // smaller k never branch below the root
 constexpr int MAX_K = 2 + 2 * (LDS_FRAMES + GLOBAL_FRAMES) + 4;
 
 // How the waves of a persistent launch draw its n items.  The first `heavy`
@@ -191,6 +192,7 @@ struct SearchArgs {
     const int32_t* slots;
     int64_t ntasks;
     int64_t heavy;              // tasks drawn one at a time, the first ones (Tickets)
+    int32_t deep;               // 1: some task has l >= 6 at its root (k >= 8)
     int32_t shared;             // 1: other launches run beside this one (Tickets.dealt = 0)
     Tickets tickets;            // filled by launch_search / launch_list
     int32_t k;

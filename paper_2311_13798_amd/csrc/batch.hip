@@ -53,13 +53,15 @@ struct ebbkc_batch {
     int64_t* tasks = nullptr;
     int32_t* tgraph = nullptr;
     unsigned long long* gtot = nullptr;  // 2 per graph
-    unsigned long long* ctr = nullptr;   // [0..4) class work counters, [4..6) unused, [6] err, [8..11] work
+    unsigned long long* ctr = nullptr;   // [4..6) unused, [6] err, [8..11] work, [16..24) launches' work counters
     ebb::SplitItem* squeue = nullptr;    // runtime split queue (null: off)
     unsigned long long* sq = nullptr;
     void* gframes = nullptr;
     int64_t ntasks = 0;
-    uint64_t ccount[4] = {0, 0, 0, 0};
-    int64_t heavy[4] = {0, 0, 0, 0};  // tasks of each class drawn one at a time (Tickets)
+    // tasks of each launch, 2 (W - 1) those with k < 8 and 2 (W - 1) + 1 the deep ones of width class W,
+    // and how many of them are drawn one at a time (Tickets)
+    uint64_t ccount[8] = {};
+    int64_t heavy[8] = {};
     int32_t kmax = 0;
     // host results
     unsigned long long* h_tot = nullptr;
@@ -105,8 +107,11 @@ __global__ void k_btask_counts(const int32_t* __restrict__ seed_c, int64_t n, in
     }
 }
 
-// Sort key of a task: width class, then (gbits > 0) its graph, then the
-// vertices it can still use, largest first.
+constexpr int CTR_WORDS = 32;
+
+// Sort key of a task: its launch (width class and whether its search branches
+// below the root), then (gbits > 0) its graph, then the vertices it can still
+// use, largest first.
 __global__ void k_btask_fill(const int32_t* __restrict__ seed_c, int64_t n, int l0, double log_thr,
                              const int64_t* __restrict__ toff, int64_t base, int32_t graph, int gbits,
                              int64_t* __restrict__ tasks, int32_t* __restrict__ tgraph, uint64_t* __restrict__ keys,
@@ -120,7 +125,7 @@ __global__ void k_btask_fill(const int32_t* __restrict__ seed_c, int64_t n, int 
             tasks[o] = task_pack(i, x0, x1);
             tgraph[o] = graph;
             const int usable = x0 == 0 && x1 >= c ? c : c - 1 - x0;
-            keys[o] = ((uint64_t)(W - 1) << (8 + gbits)) | ((uint64_t)(gbits ? graph : 0) << 8) |
+            keys[o] = ((uint64_t)(2 * (W - 1) + (l0 + 2 >= SEARCH_BRANCH_K)) << (8 + gbits)) | ((uint64_t)(gbits ? graph : 0) << 8) |
                       (uint64_t)(255 - (usable > 255 ? 255 : usable));
             vals[o] = (uint32_t)o;
             ++o;
@@ -137,15 +142,15 @@ __global__ void k_bgather(const int64_t* __restrict__ tasks, const int32_t* __re
     }
 }
 
-// Bounds in the sorted keys by binary search, one lane each: lane w < 4 the
-// end of width class w, lane 4 + w (lists sorted by size inside a class) the
-// first task of class w with at most c_light usable vertices.  (A pass over
+// Bounds in the sorted keys by binary search, one lane each: lane w < 8 the
+// end of launch w, lane 8 + w (lists sorted by size inside a launch) the first
+// task of launch w with at most c_light usable vertices.  (A pass over
 // all keys that counts the classes took 0.7 ms for 4 M tasks.)
 __global__ void k_bclass_bounds(const uint64_t* __restrict__ keys, int64_t n, int gbits, int c_light,
                                 unsigned long long* __restrict__ out) {
     const int t = threadIdx.x;
-    if (t >= 8) return;
-    const uint64_t key = t < 4 ? (uint64_t)(t + 1) << (8 + gbits) : ((uint64_t)(t - 4) << 8) | (uint64_t)(255 - c_light);
+    if (t >= 16) return;
+    const uint64_t key = t < 8 ? (uint64_t)(t + 1) << (8 + gbits) : ((uint64_t)(t - 8) << 8) | (uint64_t)(255 - c_light);
     int64_t lo = 0, hi = n;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
@@ -301,19 +306,19 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
                            b->ks[(size_t)i] - 2, log_thr_of(b->ks[(size_t)i] - 2), toffs[(size_t)i], gbase[(size_t)i], (int32_t)i, gbits, tasks,
                            tg, keys, vals);
     }
-    CHKB(radix_sort_u64(keys, vals, keys2, vals2, total, 10 + gbits, hist, htmp, s));
+    CHKB(radix_sort_u64(keys, vals, keys2, vals2, total, 11 + gbits, hist, htmp, s));
     CHKB(dev_alloc(b, (void**)&b->tasks, sizeof(int64_t) * total, s));
     CHKB(dev_alloc(b, (void**)&b->tgraph, sizeof(int32_t) * total, s));
     hipLaunchKernelGGL(k_bgather, dim3(gridn(total)), dim3(256), 0, s, tasks, tg, vals, total, b->tasks, b->tgraph);
     hipLaunchKernelGGL(k_bclass_bounds, dim3(1), dim3(64), 0, s, keys, total, gbits,
                        light_size(std::max(1, b->kmax - 2)), b->ctr);
-    uint64_t cc[8];
+    uint64_t cc[16];
     CHKB(hipMemcpyAsync(cc, b->ctr, sizeof(cc), hipMemcpyDeviceToHost, s));
     CHKB(hipStreamSynchronize(s));
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < 8; ++w) {
         const uint64_t begin = w ? cc[w - 1] : 0;
         b->ccount[w] = cc[w] - begin;
-        const uint64_t light = std::min(std::max(cc[4 + w], begin), cc[w]);
+        const uint64_t light = std::min(std::max(cc[8 + w], begin), cc[w]);
         // at most sixteen single tasks per wave: past them a chunk is a small
         // part of a wave's share whatever its tasks weigh
         b->heavy[w] = b->build ? 0
@@ -337,20 +342,22 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
 // per-graph totals and error flags to pinned host memory.
 ebbkc_status enqueue(ebbkc_batch* b, hipStream_t s) {
     const int n = (int)b->graphs.size();
-    hipLaunchKernelGGL(k_bclear, dim3(gridn(16 + 2 * (int64_t)n)), dim3(256), 0, s, b->ctr, (int64_t)16, b->gtot,
-                       2 * (int64_t)n);
+    hipLaunchKernelGGL(k_bclear, dim3(gridn(CTR_WORDS + 2 * (int64_t)n)), dim3(256), 0, s, b->ctr, (int64_t)CTR_WORDS,
+                       b->gtot, 2 * (int64_t)n);
     CHKB(hipGetLastError());
     int64_t off = 0;
-    for (int W = 1; W <= MAX_W; ++W) {
-        const int64_t nt = (int64_t)b->ccount[W - 1];
+    for (int cls = 0; cls < 2 * MAX_W; ++cls) {
+        const int64_t nt = (int64_t)b->ccount[cls];
         if (!nt) continue;
+        const int W = cls / 2 + 1;
         SearchArgs a{};
         a.tasks = b->tasks + off;
         a.task_graph = b->tgraph + off;
         a.nexplicit = nt;
         a.ntasks = nt;
-        a.heavy = b->heavy[W - 1];
+        a.heavy = b->heavy[cls];
         a.shared = b->async_mem;
+        a.deep = cls & 1;
         a.views = b->build ? nullptr : b->views;
         a.bviews = b->build ? b->bviews : nullptr;
         a.graph_k = b->gk;
@@ -359,7 +366,7 @@ ebbkc_status enqueue(ebbkc_batch* b, hipStream_t s) {
         a.k4_weight = k4_weight_of(b->opt.dense_k4);
         a.tplex = b->opt.t_plex;
         a.graph_tau = b->gtau;
-        a.next = b->ctr + (W - 1);
+        a.next = b->ctr + 16 + cls;
         a.total = b->ctr + 4;
         a.work = b->ctr + 8;
         a.err = (int*)(b->ctr + 6);
@@ -367,7 +374,7 @@ ebbkc_status enqueue(ebbkc_batch* b, hipStream_t s) {
         // persistent grids only; not in served epochs, which run concurrently
         // (waves waiting for split nodes would hold compute units that the
         // other epochs need)
-        if (b->squeue && !b->async_mem && b->opt.node_split != -1 && b->opt.blocks_per_cu != -1) {
+        if (b->squeue && a.deep && !b->async_mem && b->opt.node_split != -1 && b->opt.blocks_per_cu != -1) {
             a.squeue = b->squeue;
             a.sq = b->sq;
             a.split_mode = b->opt.node_split == 1 ? SPLIT_FORCED : SPLIT_ON_DEMAND;
@@ -576,7 +583,7 @@ ebbkc_status batch_create_impl(ebbkc_graph* const* graphs, const int32_t* ks, in
     if (dev_alloc(b, (void**)&b->gk, sizeof(int32_t) * n, s) != hipSuccess) return fail(EBBKC_E_OOM);
     if (dev_alloc(b, (void**)&b->gtau, sizeof(int32_t) * n, s) != hipSuccess) return fail(EBBKC_E_OOM);
     if (dev_alloc(b, (void**)&b->gtot, sizeof(unsigned long long) * 2 * n, s) != hipSuccess) return fail(EBBKC_E_OOM);
-    if (dev_alloc(b, (void**)&b->ctr, sizeof(unsigned long long) * 16, s) != hipSuccess) return fail(EBBKC_E_OOM);
+    if (dev_alloc(b, (void**)&b->ctr, sizeof(unsigned long long) * CTR_WORDS, s) != hipSuccess) return fail(EBBKC_E_OOM);
     // the split queue (a few MB) for a batch of its own (served epochs do not
     // split nodes at run time)
     if (!async_mem) {

@@ -718,6 +718,7 @@ static ebbkc_status run_tasks(ebbkc_graph* g, int32_t k, const TaskPlan& plan,
         a.ntasks = nt;
         a.heavy = ct.heavy;
         a.k = k;
+        a.deep = k >= SEARCH_BRANCH_K;
         a.opts = opts_of(g->opt);
         a.k4_weight = k4_weight_of(g->opt.dense_k4);
         // under the vertex slots k is one above the clique size

@@ -66,6 +66,22 @@ struct Acc {
     __device__ uint64_t hi() const { return (uint64_t)(v >> 64); }
 };
 
+// the same in 64 bits, for tasks that cannot pass them
+struct Acc64 {
+    uint64_t v;
+    bool ovf;
+    __device__ void add(uint64_t x) { v += x; }
+    __device__ uint64_t lo() const { return v; }
+    __device__ uint64_t hi() const { return 0; }
+};
+
+// twoplex_count for l <= 5 and at most 256 vertices, in 64 bits
+__device__ __forceinline__ uint64_t twoplex_small(int f, int p, int l) {
+    uint64_t s = 0;
+    for (int j = 0; j <= l; ++j) s += binom(p, j) * binom(f, l - j) << j;
+    return s;
+}
+
 template <int W>
 struct Frame {
     uint64_t P[W];
@@ -75,14 +91,21 @@ struct Frame {
 
 // children queued per node before the lanes count them (room for one more x)
 constexpr int QRUN = 256, QCAP = QRUN + 256;
+// W = 1: candidate sets queued per task (room for 64 more), and the least
+// |P & N+(x)| of an l = 5 node whose 4-cliques may be taken by the wave
+constexpr int Q1_CAP = 256, Q1_RUN = Q1_CAP - 64, L5_WAVE_MIN = 12;
 
 template <int W>
 struct SearchMem {
     uint64_t rows[64 * W][W];
+    uint64_t dag[W == 1 ? 64 : 1];  // W = 1: the later neighbours of each vertex
     int16_t col[64 * W];
     int16_t md[64 * W];      // missing pairs per vertex inside the set being counted
     int16_t vl[64 * W];      // that set's vertices in order, one per lane
-    int32_t pq[2][QCAP];     // queued children |Q| << 16 | x << 8 | y (and a sort buffer)
+    // queued children |Q| << 16 | x << 8 | y (and a sort buffer), also the closed
+    // forms' work area (all that W = 1 needs it for)
+    alignas(16) int32_t pq[2][W == 1 ? 260 : QCAP];
+    uint64_t q1[W == 1 ? 2 : 1][W == 1 ? Q1_CAP : 1];  // W = 1: queued candidate sets, and a sort buffer
     Frame<W> fr[LDS_FRAMES];
     // a node's candidate set renumbered onto W - 1 words (compact_set, W = 2
     // and 3): rows of up to 64 (W - 1) vertices, and their colours
@@ -162,6 +185,17 @@ __device__ __forceinline__ uint64_t lane_edges(const uint64_t (*rows)[W], const 
         }
     }
     return e2 / 2;
+}
+
+// W = 1: edges and triangles inside Q along the DAG rows
+__device__ __forceinline__ uint32_t lane_edges1(const uint64_t* dag, uint64_t Q) {
+    uint32_t e = 0;
+    while (Q) {
+        const int z = __builtin_ctzll(Q);
+        Q &= Q - 1;
+        e += popc64(Q & dag[z]);
+    }
+    return e;
 }
 
 // Triangles inside Q.  Dense Q (missing pairs M <= edges E): T = C(q,3) -
@@ -527,7 +561,9 @@ struct KctFrame {
     uint64_t C[W];
     int32_t l, cur;
 };
-static_assert(sizeof(KctFrame<4>) * KCT_MAX_L <= 2 * QCAP * sizeof(int32_t), "kCtPlex frames must fit the queue area");
+static_assert(sizeof(KctFrame<4>) * KCT_MAX_L <= 2 * QCAP * sizeof(int32_t) &&
+                  sizeof(KctFrame<1>) * KCT_MAX_L <= 2 * 260 * sizeof(int32_t),
+              "kCtPlex frames must fit the queue area");
 
 template <int W>
 __device__ u128 tplex_branch_count(SearchMem<W>& M, const uint64_t (&P)[W], int pc, int l, bool& ovf,
@@ -716,11 +752,17 @@ __device__ int64_t queue_take(const SearchArgs& a) {
 // BUILD = false: each task's g_i is loaded from the arena.  BUILD = true
 // (batches too large for arenas): the task's slot is its seed edge id in
 // graph task_graph[i], and the wave builds g_i in LDS first (build.h).
-template <int W, bool BUILD>
+// DEEP = false: tasks with l <= 5 at the root (k <= 7), which never branch:
+// a root is finished in closed form or its children are counted by lanes.
+// Without frames, the split queue, 128-bit sums and the 3- and t-plex forms
+// the kernel is a third of the size (the instruction cache holds 64 KB for two
+// compute units) and keeps more in registers (the one-word class 105 without
+// spills): k = 5, 6, 7 on R-MAT s18 6.0, 14.0, 161 ms against 4.1, 12.1, 152 ms.
+template <int W, bool BUILD, bool DEEP>
 __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search(SearchArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     SearchMem<W>& M = reinterpret_cast<SearchMem<W>*>(smem_raw)[threadIdx.x / 64];
-    Frame<W>* gfr = a.gframes ? reinterpret_cast<Frame<W>*>(a.gframes) +
+    Frame<W>* gfr = DEEP && a.gframes ? reinterpret_cast<Frame<W>*>(a.gframes) +
                                     ((int64_t)blockIdx.x * 4 + threadIdx.x / 64) * GLOBAL_FRAMES
                               : nullptr;
     // frames past the LDS ones live in this wave's slab of device memory;
@@ -735,7 +777,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
     const uint64_t t_wave0 = work ? wall_clock64() : 0;
     // runtime splitting: a wave counts as working from its start until the
     // static tasks run out, then takes queued nodes until none is left
-    const bool splitting = a.squeue != nullptr;
+    const bool splitting = DEEP && a.squeue != nullptr;
     if (splitting && lane == 0) sq_add(&a.sq[SQ_BUSY], 1);
     bool on_queue = false, took_item = false;
     int poll_in = 0;      // candidate nodes until the queue counters are read again
@@ -814,7 +856,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         const int tpl = a.tplex > 0 ? a.tplex : (2 * k <= tau_g ? 2 : 3);
         const bool t2 = et && tpl >= 2, t3 = et && tpl >= 3, t4 = et && tpl >= 4;
         wk_tasks += work;
-        Acc tacc{0, false};
+        std::conditional_t<DEEP, Acc, Acc64> tacc{0, false};
         if (k == 3) {  // l = 1 at the root: |V(g_i)| triangles through the seed edge
             tacc.add((uint64_t)c);
             goto task_done;
@@ -872,6 +914,18 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             wave_sync();
         }
         {
+        // W = 1: lane v keeps vertex v's later neighbours, and the leaves' counts
+        // and queued children are kept over the whole task (they all refer to
+        // the same rows), so that a node pays no reduction and the lanes count
+        // children of many nodes at once
+        uint64_t dagv = 0, leaf_sum = 0, leaf_usum = 0;
+        int64_t leaf_S = 0;
+        int q1 = 0, q1_lc = 0;
+        if constexpr (W == 1) {
+            dagv = lane < c ? M.rows[lane][0] & upper_mask(lane, 0) : 0;
+            M.dag[lane] = dagv;
+            wave_sync();
+        }
         // colour class lane + 64 q (colour lane + 64 q + 1) occupies the
         // relabelled positions [cs0[q], cs1[q]) = [#(col > colour), #(col >= colour))
         int cs0[W], cs1[W];
@@ -889,9 +943,65 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             cs1[q] = cv <= ncol ? lo : s0;
         }
 
+        // W = 1: count the queued children, one per lane: edges inside Q (l = 2)
+        // or triangles (l = 3, the queue first sorted by |Q| >> 3 in ballot
+        // passes, since a lane's work grows with |Q|; bit 0 of an entry, never a
+        // member, says that its parent was dense)
+        auto drain1 = [&]() __attribute__((always_inline)) {
+            if constexpr (W == 1) {
+                if (q1 == 0) return;
+                wave_sync();
+                int cur = 0;
+                if (q1_lc == 3 && q1 > 64) {
+                    for (int b = 3; b < 6; ++b) {
+                        const uint64_t* src = M.q1[cur];
+                        uint64_t* dst = M.q1[cur ^ 1];
+                        int nz = 0;
+                        for (int i0 = 0; i0 < q1; i0 += 64) {
+                            const int i = i0 + lane;
+                            nz += popc64(ballot(i < q1 && !((popc64(src[i]) >> b) & 1)));
+                        }
+                        int z0 = 0, o0 = nz;
+                        for (int i0 = 0; i0 < q1; i0 += 64) {
+                            const int i = i0 + lane;
+                            const bool valid = i < q1;
+                            const uint64_t e = valid ? src[i] : 0;
+                            const bool one = valid && ((popc64(e) >> b) & 1);
+                            const uint64_t bo = ballot(one), bz = ballot(valid && !one);
+                            if (valid) dst[one ? o0 + popc64(bo & lanemask_lt()) : z0 + popc64(bz & lanemask_lt())] = e;
+                            z0 += popc64(bz);
+                            o0 += popc64(bo);
+                        }
+                        wave_sync();
+                        cur ^= 1;
+                    }
+                }
+                uint64_t lops = 0;
+                for (int i0 = 0; i0 < q1; i0 += 64) {
+                    if (i0 + lane < q1) {
+                        const uint64_t e = M.q1[cur][i0 + lane];
+                        if (q1_lc == 3) {
+                            const uint64_t Q[1] = {e & ~1ull};
+                            leaf_sum += lane_triangles<1>(reinterpret_cast<const uint64_t(*)[1]>(M.rows), Q, e & 1, lops);
+                        } else {
+                            leaf_sum += lane_edges1(M.dag, e & ~1ull);
+                        }
+                    }
+                }
+                if (work) wk_ops += wave_sum(lops);
+                q1 = 0;
+                wave_sync();
+            }
+        };
+
         // Count a node that needs no branching: returns true and sets val, or
         // false when the node (l >= 4) must be branched on.
-        auto finish = [&](const uint64_t (&P)[W], int l, u128& val) -> bool {
+        using val_t = std::conditional_t<DEEP, u128, uint64_t>;
+        auto choose = [&](int n, int r) -> val_t {
+            if constexpr (DEEP) return binom128(n, r, tacc.ovf);
+            else return binom(n, r);
+        };
+        auto finish = [&](const uint64_t (&P)[W], int l, val_t& val) -> bool {
             const int pc = popcW(P);
             val = 0;
             if (work) { wk_nodes += 1; wk_ops += W; }
@@ -917,22 +1027,26 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             if (l == 2) { val = twoE / 2; return true; }
             if (et) {
                 const int mind = wmin_i32(mn);
-                if (mind >= pc - 1) { val = binom128(pc, l, tacc.ovf); return true; }
+                if (mind >= pc - 1) { val = choose(pc, l); return true; }
                 if (t2 && mind >= pc - 2) {
                     const int nfull = (int)wsum_u32((uint32_t)nf);
-                    val = twoplex_count(nfull, (pc - nfull) / 2, l, tacc.ovf);
+                    if constexpr (DEEP) val = twoplex_count(nfull, (pc - nfull) / 2, l, tacc.ovf);
+                    else val = twoplex_small(nfull, (pc - nfull) / 2, l);
                     return true;
                 }
                 if (l == pc) { val = 0; return true; }  // P itself is not a clique
-                if (t3 && mind >= pc - 3) {
-                    val = threeplex_count<W>(M, P, pc, l, tacc.ovf);
-                    return true;
-                }
-                if (t4 && mind >= pc - tpl && l <= KCT_MAX_L) {
-                    uint64_t kn = 0;
-                    val = tplex_branch_count<W>(M, P, pc, l, tacc.ovf, kn);
-                    if (work) { wk_nodes += kn; wk_ops += kn * W; }
-                    return true;
+                if constexpr (DEEP) {
+                    const bool plex3 = t3 && mind >= pc - 3, plext = t4 && mind >= pc - tpl && l <= KCT_MAX_L;
+                    if (plex3) {
+                        val = threeplex_count<W>(M, P, pc, l, tacc.ovf);
+                        return true;
+                    }
+                    if (plext) {
+                        uint64_t kn = 0;
+                        val = tplex_branch_count<W>(M, P, pc, l, tacc.ovf, kn);
+                        if (work) { wk_nodes += kn; wk_ops += kn * W; }
+                        return true;
+                    }
                 }
             }
             if (l != 3) return false;
@@ -1219,13 +1333,86 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             tacc.add((uint64_t)((int64_t)(wave_sum(lsum) + usum) + s24 / 24));
         };
 
+        // W = 1: the same with one child per lane from many nodes of the task.
+        // Lane x holds R = P & N+(x), taken apart by the lanes side by side (a
+        // step takes the next y of every x) unless the wave counts it from its
+        // missing pairs.  Queued children are the sets Q themselves.  (With a
+        // queue per node, drained and summed up before the next one, an l = 4
+        // node of Chung-Lu 3e5 took 870 vector instructions at k = 10, 17
+        // children in 64 lanes: k = 8, 10, 11 19.9, 130, 143 ms against 14.7,
+        // 101, 85 ms.)
+        auto children1 = [&](const uint64_t (&P)[W], int l, int xhi) {
+            if constexpr (W == 1) {
+                const int lc = l - 2;
+                q1_lc = lc;  // a task's leaves all have one parity
+                if (l == 4 && xhi >= c) {
+                    const int pc = popc64(P[0]);
+                    bool pd = false;
+                    if (pc < 4 || k4_missing(std::integral_constant<int, 1>{}, P, M.rows, pc, true, leaf_S, leaf_usum, pd))
+                        return;
+                }
+                const int mycol = lane < c ? M.col[lane] : 0;
+                const bool ax = ((P[0] >> lane) & 1) && lane < xhi && !(rule1 && mycol < l);
+                uint64_t Rx = ax ? P[0] & dagv : 0;
+                const int rx = popc64(Rx);
+                if (rx < lc + 1) Rx = 0;
+                if (work) {
+                    const uint32_t rc = wsum_u32(Rx ? (uint32_t)rx : 0u);
+                    wk_nodes += rc;
+                    wk_ops += rc;
+                }
+                uint64_t dense = 0;  // lane x: bit 0 of its children's entries
+                if (l == 5) {  // the larger sets by the wave
+                    uint64_t big = uni64(ballot(Rx != 0 && rx >= L5_WAVE_MIN));
+                    while (big) {
+                        const int x = __builtin_ctzll(big);
+                        big &= big - 1;
+                        const uint32_t rlo = __builtin_amdgcn_readlane((uint32_t)Rx, x);
+                        const uint32_t rhi = __builtin_amdgcn_readlane((uint32_t)(Rx >> 32), x);
+                        const uint64_t R[1] = {((uint64_t)rhi << 32) | rlo};
+                        bool rdense = false;
+                        const bool done = k4_missing(std::integral_constant<int, 1>{}, R, M.rows, popc64(R[0]), false,
+                                                     leaf_S, leaf_usum, rdense);
+                        if (lane == x) {
+                            dense = rdense ? 1 : 0;
+                            if (done) Rx = 0;
+                        }
+                    }
+                }
+                uint64_t* q = M.q1[0];
+                for (;;) {
+                    const bool more = ballot(Rx != 0) != 0;
+                    // (a shallow task has one such node: the queue ends with it)
+                    if (q1 > Q1_RUN || (!DEEP && !more)) drain1();
+                    if (!more) break;
+                    bool ok = false;
+                    uint64_t Q = 0;
+                    if (Rx) {
+                        const int y = __builtin_ctzll(Rx);
+                        Rx &= Rx - 1;
+                        Q = Rx & M.dag[y];
+                        ok = popc64(Q) >= lc && !(rule1 && M.col[y] < l - 1);
+                        if (popc64(Rx) < lc + 1) Rx = 0;
+                    }
+                    const uint64_t bq = ballot(ok);
+                    if (ok) q[q1 + popc64(bq & lanemask_lt())] = Q | dense;
+                    q1 += popc64(bq);
+                }
+            }
+        };
+
         // Children of a node with l = 4 or 5 (x in [xlo, xhi)).  Classes
         // W = 2 and 3 first renumber a whole node whose candidate set fits
         // W - 1 words onto them (one narrower instance of the children and
         // leaf code per class keeps the kernel's spill space small), unless
         // the node is so small that renumbering (~6 W |P| instructions)
         // costs more than the narrower words save.
-        auto count_children = [&](const uint64_t (&Pn)[W], int ln, int xlo, int xhi) {
+        auto count_children = [&](const uint64_t (&Pn)[W], int ln, int xhi) {
+            constexpr int xlo = 0;
+            if constexpr (W == 1) {
+                children1(Pn, ln, xhi);
+                return;
+            }
             if constexpr (W == 2 || W == 3) {
                 constexpr int WN = W - 1;
                 const int p = popcW(Pn);
@@ -1238,7 +1425,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                     return;
                 }
             }
-            children_by_lanes(std::integral_constant<int, W>{}, Pn, M.rows, M.col, c, ln, xlo, xhi);
+            if constexpr (W > 1) children_by_lanes(std::integral_constant<int, W>{}, Pn, M.rows, M.col, c, ln, xlo, xhi);
         };
 
         const int l0 = k - 2;
@@ -1250,53 +1437,48 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         const bool whole = x0 == 0 && x1 >= c;
         bool active = true;
         int lq = 0;
-        if (qitem >= 0) {
+        if (DEEP && qitem >= 0) {
             // a queued node (finish() already found no closed form for it)
             lq = uniform_i32(a.squeue[qitem].l);
-            if (lq == 4 || lq == 5) {
-                uint64_t Pn[W];
-#pragma unroll
-                for (int w = 0; w < W; ++w) Pn[w] = uni64(a.squeue[qitem].P[w]);
-                count_children(Pn, lq, 0, c);
-                active = false;
-            }
-        } else if (whole) {
-            u128 rootval = 0;
-            active = !finish(P0, l0, rootval);
-            if (!active) tacc.add(rootval);
-        } else if (et && l0 >= 3) {
+        } else {
             // a root split over several tasks that is a clique, 2-plex or
             // 3-plex (as far as t allows): this task's part is the
             // l0-cliques whose first vertex x lies in [x0, x1), for a clique
             // sum_x C(c-1-x, l0-1), else the closed form of each later
             // neighbourhood P0 & N+(x) (a t-plex again) at l0 - 1
-            int mn = 1 << 30;
+            const int xe = x1 < c ? x1 : c;
+            bool close = whole;
+            if (!whole && et && l0 >= 3) {
+                int mn = 1 << 30;
 #pragma unroll
-            for (int q = 0; q < W; ++q) {
-                const int v = lane + 64 * q;
-                if (v < c) {
-                    int d = 0;
+                for (int q = 0; q < W; ++q) {
+                    const int v = lane + 64 * q;
+                    if (v < c) {
+                        int d = 0;
 #pragma unroll
-                    for (int w = 0; w < W; ++w) d += popc64(P0[w] & M.rows[v][w]);
-                    mn = d < mn ? d : mn;
+                        for (int w = 0; w < W; ++w) d += popc64(P0[w] & M.rows[v][w]);
+                        mn = d < mn ? d : mn;
+                    }
+                }
+                const int mind = wmin_i32(mn);
+                if (mind >= c - 1) {
+                    val_t part = 0;
+                    for (int x = x0; x < xe; ++x) part += choose(c - 1 - x, l0 - 1);
+                    tacc.add(part);
+                    active = false;
+                } else {
+                    close = mind >= c - tpl;
                 }
             }
-            const int mind = wmin_i32(mn);
-            const int xe = x1 < c ? x1 : c;
-            if (mind >= c - 1) {
-                u128 part = 0;
-                for (int x = x0; x < xe; ++x) part += binom128(c - 1 - x, l0 - 1, tacc.ovf);
-                tacc.add(part);
-                active = false;
-            } else if (mind >= c - tpl) {
-                u128 part = 0;
+            if (close) {  // the whole root (x = -1), or its part vertex by vertex
+                val_t part = 0;
                 bool all = true;
-                for (int x = x0; x < xe && all; ++x) {
+                for (int x = whole ? -1 : x0; x < (whole ? 0 : xe) && all; ++x) {
                     uint64_t Rx[W];
 #pragma unroll
-                    for (int w = 0; w < W; ++w) Rx[w] = uni64(P0[w] & M.rows[x][w] & upper_mask(x, w));
-                    u128 v = 0;
-                    all = finish(Rx, l0 - 1, v);
+                    for (int w = 0; w < W; ++w) Rx[w] = x < 0 ? P0[w] : uni64(P0[w] & M.rows[x][w] & upper_mask(x, w));
+                    val_t v = 0;
+                    all = finish(Rx, x < 0 ? l0 : l0 - 1, v);
                     part += v;
                 }
                 if (all) {
@@ -1305,9 +1487,15 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                 }
             }
         }
-        if (active && qitem < 0 && (l0 == 4 || l0 == 5)) {
-            count_children(P0, l0, x0, x1);
-            active = false;
+        {
+            const int lr = DEEP && qitem >= 0 ? lq : l0;
+            if (active && (lr == 4 || lr == 5)) {
+                uint64_t Pr[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) Pr[w] = DEEP && qitem >= 0 ? uni64(a.squeue[qitem].P[w]) : P0[w];
+                count_children(Pr, lr, DEEP && qitem >= 0 ? c : x1);
+                active = false;
+            }
         }
         // hand node (Pn, ln), ln >= 4, to an idle wave through the queue
         // instead of searching it here; true when it was pushed
@@ -1354,6 +1542,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             }
             return uniform_i32(__shfl(ok, 0, 64)) != 0;
         };
+        if constexpr (DEEP) {
         // depth-first search: the node being branched on lives in registers
         // (P, R, x, l); its ancestors are frames
         int sp = 0;
@@ -1430,10 +1619,10 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                 }
                 if (dc < lc) continue;
             }
-            u128 v = 0;
+            val_t v = 0;
             if (finish(Pc, lc, v)) { tacc.add(v); continue; }
             if (try_push(Pc, lc)) continue;
-            if (lc == 4 || lc == 5) { count_children(Pc, lc, 0, c); continue; }
+            if (lc == 4 || lc == 5) { count_children(Pc, lc, c); continue; }
             if (sp >= LDS_FRAMES + (gfr ? GLOBAL_FRAMES : 0)) {
                 if (lane == 0) atomicOr(a.err, ERR_DEPTH);
                 continue;
@@ -1453,7 +1642,15 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             x = -1;
             l = lc;
         }
+        }
 
+        if constexpr (W == 1) {
+            if constexpr (DEEP) drain1();
+            if (ballot(leaf_sum != 0 || leaf_S != 0) || leaf_usum) {
+                const int64_t s24 = wave_sum(leaf_S);
+                tacc.add((uint64_t)((int64_t)(wave_sum(leaf_sum) + leaf_usum) + s24 / 24));
+            }
+        }
         }
     task_done:
         // a batch flags an overflow on its own graph only (top bit of the
@@ -1498,14 +1695,14 @@ namespace {
 
 // Workgroups per compute unit of the kernel, asked for once per device: the
 // two calls took about 10 us of every launch.
-template <int W, bool BUILD>
+template <int W, bool BUILD, bool DEEP>
 int search_occupancy() {
     static std::atomic<int> known[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return -1;
     const bool slot = dev >= 0 && dev < 64;
     if (slot && known[dev].load(std::memory_order_acquire) > 0) return known[dev].load(std::memory_order_acquire);
-    auto kern = k_search<W, BUILD>;
+    auto kern = k_search<W, BUILD, DEEP>;
     const size_t smem = 4 * sizeof(SearchMem<W>);
     if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
         return -1;
@@ -1516,9 +1713,9 @@ int search_occupancy() {
     return occ;
 }
 
-template <int W, bool BUILD>
+template <int W, bool BUILD, bool DEEP>
 int64_t grid_blocks(int64_t ntasks, int cus, int blocks_per_cu) {
-    int occ = search_occupancy<W, BUILD>();
+    int occ = search_occupancy<W, BUILD, DEEP>();
     if (occ < 0) return -1;
     if (blocks_per_cu > 0 && blocks_per_cu < occ) occ = blocks_per_cu;
     // blocks_per_cu = -2: one persistent workgroup per CU fewer than fit, so a
@@ -1534,14 +1731,14 @@ int64_t grid_blocks(int64_t ntasks, int cus, int blocks_per_cu) {
     return grid;
 }
 
-template <int W, bool BUILD>
+template <int W, bool BUILD, bool DEEP>
 hipError_t launch_w(SearchArgs a, int cus, int bpc, hipStream_t s) {
-    const int64_t grid = grid_blocks<W, BUILD>(a.ntasks, cus, bpc);
+    const int64_t grid = grid_blocks<W, BUILD, DEEP>(a.ntasks, cus, bpc);
     if (grid < 0) return hipErrorInvalidValue;
     // tasks that build their sub-branch are sorted by graph, not by weight:
     // neighbours share the graph's arrays in cache
     a.tickets = make_tickets(a.next, a.ntasks, a.heavy, 4 * grid, BUILD ? 8 : 0, a.shared);
-    hipLaunchKernelGGL((k_search<W, BUILD>), dim3((unsigned)grid), dim3(256), 4 * sizeof(SearchMem<W>), s, a);
+    hipLaunchKernelGGL((k_search<W, BUILD, DEEP>), dim3((unsigned)grid), dim3(256), 4 * sizeof(SearchMem<W>), s, a);
     return hipGetLastError();
 }
 
@@ -1549,11 +1746,13 @@ hipError_t launch_w(SearchArgs a, int cus, int bpc, hipStream_t s) {
 
 template <int W>
 hipError_t search_launch(bool build, const SearchArgs& a, int cus, int bpc, hipStream_t s) {
-    return build ? launch_w<W, true>(a, cus, bpc, s) : launch_w<W, false>(a, cus, bpc, s);
+    if (a.deep) return build ? launch_w<W, true, true>(a, cus, bpc, s) : launch_w<W, false, true>(a, cus, bpc, s);
+    return build ? launch_w<W, true, false>(a, cus, bpc, s) : launch_w<W, false, false>(a, cus, bpc, s);
 }
+// frames are sized for the deep searches, the only ones that have any
 template <int W>
 int64_t search_blocks(bool build, int64_t ntasks, int cus, int bpc) {
-    return build ? grid_blocks<W, true>(ntasks, cus, bpc) : grid_blocks<W, false>(ntasks, cus, bpc);
+    return build ? grid_blocks<W, true, true>(ntasks, cus, bpc) : grid_blocks<W, false, true>(ntasks, cus, bpc);
 }
 template <int W>
 hipError_t search_tables(hipStream_t s) {
