@@ -289,6 +289,9 @@ int64_t list_grid_waves(int W, int64_t ntasks, int cus);
 hipError_t canon_tuples(int32_t* buf, int64_t n, int k, hipStream_t s);
 hipError_t sort_tuples(int32_t* buf, int64_t n, int k, int bits, uint64_t* keys, uint64_t* keys2, uint32_t* idx,
                        uint32_t* idx2, int64_t* hist, int64_t* htmp, int32_t* tmpbuf, hipStream_t s);
+// the same for tuples whose k ids fit one 64-bit key; their checksums to d_sums
+hipError_t sort_packed_tuples(int32_t* buf, int64_t n, int k, int bits, uint64_t* keys, uint64_t* keys2, int64_t* hist,
+                              int64_t* htmp, unsigned long long* d_sums, hipStream_t s);
 hipError_t tuple_checksums(const int32_t* buf, int64_t n, int k, unsigned long long* d_out, hipStream_t s);
 hipError_t list_small(const int32_t* byrank, const int32_t* eu, const int32_t* ev, int64_t lo, int64_t hi, int k,
                       int32_t* out, hipStream_t s);

@@ -193,12 +193,14 @@ __global__ void k_arena_bytes(const int32_t* __restrict__ subsize, int64_t m, un
         if (c > 0) b += (uint64_t)c * (uint64_t)width_of(c) * 8 + 6 * (uint64_t)c;
         mx = c > mx ? c : mx;
     }
-    b = wave_sum(b);
+    __shared__ uint64_t sm[256 / EBB_WAVE];
+    __shared__ int smx;
+    if (threadIdx.x == 0) smx = 0;
+    block_add(b, sm, &out[0]);
     mx = wave_max(mx);
-    if (lane_id() == 0) {
-        if (b) atomicAdd(&out[0], (unsigned long long)b);
-        atomicMax(&out[1], (unsigned long long)mx);
-    }
+    if (lane_id() == 0) atomicMax(&smx, mx);
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(&out[1], (unsigned long long)smx);
 }
 
 GraphView graph_arrays(const ebbkc_graph* g) {
@@ -540,7 +542,7 @@ ebbkc_status batch_create_impl(ebbkc_graph* const* graphs, const int32_t* ks, in
             if (ks[i] < 3 || ks[i] - 2 > g->tau) continue;
             ebbkc_status st = subsize_impl(g, s);
             if (st) { (void)hipFree(est); delete b; return st; }
-            if (g->m) hipLaunchKernelGGL(k_arena_bytes, dim3(gridn(g->m)), dim3(256), 0, s, g->subsize, g->m, est + 2 * i);
+            if (g->m) hipLaunchKernelGGL(k_arena_bytes, dim3(std::min(gridn(g->m), SUM_GRID)), dim3(256), 0, s, g->subsize, g->m, est + 2 * i);
         }
         std::vector<unsigned long long> h((size_t)2 * n);
         const bool ok = hipMemcpyAsync(h.data(), est, sizeof(unsigned long long) * 2 * n, hipMemcpyDeviceToHost, s) ==

@@ -11,24 +11,8 @@ namespace {
 typedef unsigned __int128 u128;
 
 // C(n, r) for n < BIN_N, r < BIN_R, saturated to UINT64_MAX when it does not fit
-constexpr int BIN_N = 1025, BIN_R = 65;
+constexpr int BIN_N = 258, BIN_R = 65;
 __device__ uint64_t g_binom[BIN_N * BIN_R];
-
-__global__ void k_binom_init() {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= BIN_N) return;
-    unsigned __int128 c = 1;
-    bool sat = false;
-    g_binom[n * BIN_R + 0] = 1;
-    for (int r = 1; r < BIN_R; ++r) {
-        if (r > n) { g_binom[n * BIN_R + r] = 0; continue; }
-        if (!sat) {
-            c = c * (unsigned __int128)(n - r + 1) / (unsigned __int128)r;
-            if (c > (unsigned __int128)UINT64_MAX) sat = true;
-        }
-        g_binom[n * BIN_R + r] = sat ? UINT64_MAX : (uint64_t)c;
-    }
-}
 
 // C(n, r) or UINT64_MAX if it does not fit 64 bits
 __device__ uint64_t binom(int n, int r) {
@@ -48,10 +32,10 @@ __device__ uint64_t binom(int n, int r) {
 constexpr int B128_N = 258, B128_R = 129;
 __device__ uint64_t g_binom128[B128_N * B128_R * 2];
 
-// Pascal's rule row by row in one workgroup: thread r - 1 owns column r and
-// reads its left neighbour's value of the row before from LDS.  (One thread for
-// the whole table took 8.3 ms, most of the first count of every process.)
-__global__ void k_binom128_init() {
+// Pascal's rule row by row in one workgroup: thread r owns column r and reads
+// its left neighbour's value of the row before from LDS.  (One thread for the
+// whole 128-bit table took 8.3 ms of every process's first count.)
+__global__ void k_binom_init() {
     __shared__ u128 row[2][B128_R];
     __shared__ bool sat[2][B128_R];
     const int r = threadIdx.x;
@@ -70,10 +54,12 @@ __global__ void k_binom128_init() {
             uint64_t* o = &g_binom128[(n * B128_R + r) * 2];
             o[0] = s ? ~0ull : (uint64_t)v;
             o[1] = s ? ~0ull : (uint64_t)(v >> 64);
+            if (r < BIN_R) g_binom[n * BIN_R + r] = s || (v >> 64) ? UINT64_MAX : (uint64_t)v;
         }
         __syncthreads();
     }
 }
+static_assert(BIN_N == B128_N && BIN_R <= B128_R, "one pass fills both tables");
 
 // C(n, r) exactly in 128 bits; sets ovf when it does not fit
 __device__ __forceinline__ u128 binom128(int n, int r, bool& ovf) {
@@ -100,8 +86,7 @@ __device__ __forceinline__ u128 mul128(u128 a, u128 b, bool& ovf) {
 }
 
 inline hipError_t launch_tables(hipStream_t s) {
-    hipLaunchKernelGGL(k_binom_init, dim3((BIN_N + 63) / 64), dim3(64), 0, s);
-    hipLaunchKernelGGL(k_binom128_init, dim3(1), dim3(192), 0, s);
+    hipLaunchKernelGGL(k_binom_init, dim3(1), dim3(192), 0, s);
     return hipGetLastError();
 }
 

@@ -63,6 +63,23 @@ __device__ __forceinline__ T wave_incl_scan(T v) {
     return v;
 }
 
+// Sum over the workgroup added to *out by one thread: a counter takes about
+// 140 M atomics a second whatever their number of waves, so sums over many
+// waves are folded per workgroup and their grids kept to a few hundred.  Every
+// thread of the workgroup calls it; smem holds one value per wave.
+template <typename T>
+__device__ __forceinline__ void block_add(T v, T* smem, unsigned long long* out) {
+    v = wave_sum(v);
+    __syncthreads();
+    if (lane_id() == 0) smem[threadIdx.x / EBB_WAVE] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (unsigned i = 1; i < blockDim.x / EBB_WAVE; ++i) v += smem[i];
+        if (v) atomicAdd(out, (unsigned long long)v);
+    }
+}
+constexpr unsigned SUM_GRID = 512;  // workgroups of a pass that ends in block_add
+
 __device__ __forceinline__ int uniform_i32(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // first index in sorted a[lo,hi) with a[i] >= key

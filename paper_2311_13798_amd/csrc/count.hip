@@ -289,8 +289,8 @@ __global__ void k_sum_range(const int32_t* __restrict__ byrank, const int32_t* _
     uint64_t acc = 0;
     for (int64_t i = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < hi; i += (int64_t)gridDim.x * blockDim.x)
         acc += vals32 ? (uint64_t)vals32[byrank ? byrank[i] : i] : vals64[i];
-    acc = wave_sum(acc);
-    if (lane_id() == 0 && acc) atomicAdd(out, (unsigned long long)acc);
+    __shared__ uint64_t sm[256 / EBB_WAVE];
+    block_add(acc, sm, out);
 }
 
 // bump allocator over one scratch buffer
@@ -915,7 +915,7 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
         if (st) return st;
         CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
         if (r_end > r_begin)
-            hipLaunchKernelGGL(k_sum_range, dim3(grid_for(r_end - r_begin)), dim3(256), 0, s, g->byrank, g->subsize,
+            hipLaunchKernelGGL(k_sum_range, dim3(std::min(grid_for(r_end - r_begin), SUM_GRID)), dim3(256), 0, s, g->byrank, g->subsize,
                                (const uint64_t*)nullptr, r_begin, r_end, total);
         CHKH(hipGetLastError());
         return read_total(g, out, s);
@@ -932,7 +932,7 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     const int64_t n = i1 - i0;
     if (k == 4) {  // sum of |E(g_i)| over the seeds
         if (n > 0)
-            hipLaunchKernelGGL(k_sum_range, dim3(grid_for(n)), dim3(256), 0, s, (const int32_t*)nullptr,
+            hipLaunchKernelGGL(k_sum_range, dim3(std::min(grid_for(n), SUM_GRID)), dim3(256), 0, s, (const int32_t*)nullptr,
                                (const int32_t*)nullptr, g->nedges, i0, i1, total);
         CHKH(hipGetLastError());
         return read_total(g, out, s);
@@ -1133,11 +1133,29 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
     // k_list wrote sorted tuples and their checksums (buffer order) for 3 <= k <= 8
     const bool fused = k >= 3 && k <= LIST_FUSED_K;
     const bool resorted = (flags & EBBKC_LIST_SORTED) && N > 1;
+    bool packed = false;
     if (N > 0) {
         if (!fused) CHKH(canon_tuples(d_buf, (int64_t)N, k, s));
         if (resorted) {
             const int bits = std::max(1, bits_for((uint64_t)(g->n > 0 ? g->n - 1 : 0)));
             const int64_t hn = radix_hist_elems((int64_t)N);
+            // a tuple that fits one key is sorted as that key alone, and the
+            // sorted tuples are unpacked and hashed in one pass
+            packed = bits * k <= 64;
+            if (packed) {
+                const size_t bytes = 2 * rnd256(N * 8) + rnd256((size_t)hn * 8) +
+                                     rnd256((size_t)(scan_tmp_elems(hn) + 64) * 8) + 4096;
+                CHKH(hipMalloc(&tmp_sort, bytes));
+                Carve cv{(char*)tmp_sort, 0, bytes};
+                uint64_t* keys = cv.take<uint64_t>((int64_t)N);
+                uint64_t* keys2 = cv.take<uint64_t>((int64_t)N);
+                int64_t* hist = cv.take<int64_t>(hn);
+                int64_t* htmp = cv.take<int64_t>(scan_tmp_elems(hn) + 64);
+                if (!keys || !keys2 || !hist || !htmp) return EBBKC_E_OOM;
+                if (N >= ((uint64_t)1 << 32)) return EBBKC_E_INVALID_ARG;
+                CHKH(sort_packed_tuples(d_buf, (int64_t)N, k, bits, keys, keys2, hist, htmp,
+                                        (unsigned long long*)(g->d_counters + 12), s));
+            } else {
             const size_t bytes = 2 * rnd256(N * 8) + 2 * rnd256(N * 4) + rnd256((size_t)hn * 8) +
                                  rnd256((size_t)(scan_tmp_elems(hn) + 64) * 8) + rnd256(N * (size_t)k * 4) + 4096;
             CHKH(hipMalloc(&tmp_sort, bytes));
@@ -1152,13 +1170,14 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
             if (!keys || !keys2 || !idx || !idx2 || !hist || !htmp || !tbuf) return EBBKC_E_OOM;
             if (N >= ((uint64_t)1 << 32)) return EBBKC_E_INVALID_ARG;
             CHKH(sort_tuples(d_buf, (int64_t)N, k, bits, keys, keys2, idx, idx2, hist, htmp, tbuf, s));
+            }
         }
     }
     if (out_checksums) {
         if (fused && !resorted && N > 0) {
             CHKH(hipMemcpyAsync(out_checksums, g->d_counters + 8, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
         } else {
-            CHKH(tuple_checksums(d_buf, (int64_t)N, k, (unsigned long long*)(g->d_counters + 12), s));
+            if (!packed) CHKH(tuple_checksums(d_buf, (int64_t)N, k, (unsigned long long*)(g->d_counters + 12), s));
             CHKH(hipMemcpyAsync(out_checksums, g->d_counters + 12, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
         }
     }

@@ -414,12 +414,9 @@ __global__ __launch_bounds__(256) void k_list(SearchArgs a) {
         wave_sync();
     }
     if (fused) {
-        ho = wave_sum(ho);
-        hu = wave_sum(hu);
-        if (lane == 0) {
-            atomicAdd(&a.list_checksums[0], (unsigned long long)ho);
-            atomicAdd(&a.list_checksums[1], (unsigned long long)hu);
-        }
+        __shared__ uint64_t sm[256 / EBB_WAVE];
+        block_add(ho, sm, &a.list_checksums[0]);
+        block_add(hu, sm, &a.list_checksums[1]);
     }
 }
 
@@ -467,6 +464,38 @@ __global__ void k_gather_tuples(const int32_t* __restrict__ src, const uint32_t*
 }
 
 
+// keys of whole tuples (k ids of `bits` bits, first id highest)
+__global__ void k_pack_tuples(const int32_t* __restrict__ buf, int64_t n, int k, int bits, uint64_t* __restrict__ keys) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t* t = buf + i * k;
+        uint64_t key = 0;
+        for (int c = 0; c < k; ++c) key = (key << bits) | (uint64_t)(uint32_t)t[c];
+        keys[i] = key;
+    }
+}
+
+// tuples of sorted keys, and their [ordered, unordered] checksums
+__global__ void k_unpack_tuples(const uint64_t* __restrict__ keys, int64_t n, int k, int bits,
+                                int32_t* __restrict__ buf, unsigned long long* __restrict__ out) {
+    __shared__ uint64_t sm[256 / EBB_WAVE];
+    const uint64_t mask = (1ull << bits) - 1;
+    uint64_t ho = 0, hu = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t key = keys[i];
+        int32_t* t = buf + i * k;
+        uint64_t h = (uint64_t)k;
+        for (int j = 0; j < k; ++j) {
+            const uint64_t v = (key >> (bits * (k - 1 - j))) & mask;
+            t[j] = (int32_t)v;
+            h = sm64(h ^ v);
+        }
+        hu += h;
+        ho += sm64(h ^ sm64((uint64_t)i));
+    }
+    block_add(ho, sm, &out[0]);
+    block_add(hu, sm, &out[1]);
+}
+
 // [ordered, unordered] checksums (sums mod 2^64)
 __global__ void k_checksums(const int32_t* __restrict__ buf, int64_t n, int k, unsigned long long* __restrict__ out) {
     uint64_t ho = 0, hu = 0;
@@ -477,12 +506,9 @@ __global__ void k_checksums(const int32_t* __restrict__ buf, int64_t n, int k, u
         hu += h;
         ho += sm64(h ^ sm64((uint64_t)i));
     }
-    ho = wave_sum(ho);
-    hu = wave_sum(hu);
-    if (lane_id() == 0) {
-        atomicAdd(&out[0], (unsigned long long)ho);
-        atomicAdd(&out[1], (unsigned long long)hu);
-    }
+    __shared__ uint64_t sm[256 / EBB_WAVE];
+    block_add(ho, sm, &out[0]);
+    block_add(hu, sm, &out[1]);
 }
 
 __global__ void k_list_small(const int32_t* __restrict__ byrank, const int32_t* __restrict__ eu,
@@ -504,6 +530,10 @@ inline unsigned gridn(int64_t n) {
     if (b > 16384) b = 16384;
     return (unsigned)b;
 }
+
+// eight workgroups a compute unit: enough for the hashes' latency, 4,096
+// atomics at the end (a wave each of up to 65,536 took 0.9 ms)
+inline unsigned sum_grid(int64_t n) { return gridn(n) < 2048u ? gridn(n) : 2048u; }
 
 template <int W, bool FUSED>
 hipError_t launch_list_w(SearchArgs a, int cus, hipStream_t s) {
@@ -587,10 +617,21 @@ hipError_t sort_tuples(int32_t* buf, int64_t n, int k, int bits, uint64_t* keys,
     return hipGetLastError();
 }
 
+hipError_t sort_packed_tuples(int32_t* buf, int64_t n, int k, int bits, uint64_t* keys, uint64_t* keys2, int64_t* hist,
+                              int64_t* htmp, unsigned long long* d_sums, hipStream_t s) {
+    hipError_t e = hipMemsetAsync(d_sums, 0, 2 * sizeof(uint64_t), s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_pack_tuples, dim3(gridn(n)), dim3(256), 0, s, buf, n, k, bits, keys);
+    e = radix_sort_u64(keys, nullptr, keys2, nullptr, n, bits * k, hist, htmp, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_unpack_tuples, dim3(sum_grid(n)), dim3(256), 0, s, keys, n, k, bits, buf, d_sums);
+    return hipGetLastError();
+}
+
 hipError_t tuple_checksums(const int32_t* buf, int64_t n, int k, unsigned long long* d_out, hipStream_t s) {
     hipError_t e = hipMemsetAsync(d_out, 0, 2 * sizeof(uint64_t), s);
     if (e != hipSuccess) return e;
-    if (n > 0) hipLaunchKernelGGL(k_checksums, dim3(gridn(n)), dim3(256), 0, s, buf, n, k, d_out);
+    if (n > 0) hipLaunchKernelGGL(k_checksums, dim3(sum_grid(n)), dim3(256), 0, s, buf, n, k, d_out);
     return hipGetLastError();
 }
 
