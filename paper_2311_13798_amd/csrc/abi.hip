@@ -41,11 +41,8 @@ void ebbkc_destroy(ebbkc_graph* g) {
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(g->device);
-    void* ptrs[] = {g->rp, g->ci, g->erank, g->eu, g->ev, g->sup0, g->rank, g->level, g->rrow, g->orp, g->orow,
-                    g->byrank, g->subsize, g->scratch, g->d_counters, g->seed_eid, g->seed_c, g->seed_order, g->row_off,
-                    g->vtx_off, g->arows, g->agid, g->acol, g->nedges, g->vpos, g->vcol, g->rho_slab, g->adj, g->acum,
-                    g->varena.seed_v, g->varena.seed_c, g->varena.seed_rthr, g->varena.seed_order, g->varena.row_off,
-                    g->varena.vtx_off, g->varena.rows, g->varena.gid, g->varena.col, g->varena.nedges};
+    void* ptrs[] = {g->held, g->arena_held, g->varena.held, g->subsize_own ? g->subsize : nullptr, g->scratch,
+                    g->d_counters, g->vpos, g->vcol, g->rho_slab, g->adj, g->acum};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (g->h_counters) (void)hipHostFree(g->h_counters);

@@ -19,6 +19,7 @@
 #include "common.h"
 #include "handle.h"
 #include "prims.h"
+#include "slab.h"
 
 namespace ebb {
 
@@ -352,8 +353,13 @@ ebbkc_status ensure_counters(ebbkc_graph* g) {
 
 ebbkc_status subsize_impl(ebbkc_graph* g, hipStream_t s) {
     if (g->subsize_ready) return EBBKC_OK;
-    if (!g->subsize && hipMalloc((void**)&g->subsize, sizeof(int32_t) * (size_t)(g->m > 0 ? g->m : 1)) != hipSuccess)
-        return EBBKC_E_OOM;
+    if (!g->subsize) {
+        if (hipMalloc((void**)&g->subsize, sizeof(int32_t) * (size_t)(g->m > 0 ? g->m : 1)) != hipSuccess) {
+            g->subsize = nullptr;
+            return EBBKC_E_OOM;
+        }
+        g->subsize_own = true;
+    }
     CHKH(launch_subsize(graph_view(g), g->m, g->subsize, s));
     g->subsize_ready = true;
     return EBBKC_OK;
@@ -381,11 +387,12 @@ constexpr int BUILD_LIGHT_C = 40;
 // A set of slots and their sub-branches, built from n items: ids (edges by
 // rank, or vertices by position) and sizes (by id, or by item).
 struct SlotSet {
-    DBuf<int32_t> seed, c, rthr, order;
-    DBuf<int64_t> roff, voff;
-    DBuf<uint64_t> rows, ned;
-    DBuf<int32_t> gid;
-    DBuf<int16_t> col;
+    Slab held;  // all of these
+    SBuf<int32_t> seed, c, rthr, order;
+    SBuf<int64_t> roff, voff;
+    SBuf<uint64_t> rows, ned;
+    SBuf<int32_t> gid;
+    SBuf<int16_t> col;
     SizeCounts count;
     SeedSums tot{0, 0, 0};
 };
@@ -399,10 +406,31 @@ static ebbkc_status build_slots(ebbkc_graph* g, const int32_t* id, const int32_t
         SeedSums tot;
         unsigned long long bins[SIZE_BINS];
     } h{};
-    DBuf<SeedSums> part;
-    DBuf<Head> head;
-    CHKH(part.alloc(nt));
-    CHKH(head.alloc(1));
+    Slab tmp;
+    SBuf<SeedSums> part;
+    SBuf<Head> head;
+    SBuf<unsigned long long> next;
+    SBuf<int32_t> trows;
+    SBuf<uint8_t> key;
+    SBuf<int64_t> hist, htmp;
+    const int64_t hn = radix_hist_elems(n), hn_tmp = scan_tmp_elems(hn) + 64, ntr = 2 + 2 * (int64_t)g->n;
+    CHKH(tmp.init(SlabSize{}
+                      .add<SeedSums>(nt)
+                      .add<Head>(1)
+                      .add<unsigned long long>(n)
+                      .add<int32_t>(ntr)
+                      .add<uint8_t>(n)
+                      .add<int64_t>(hn)
+                      .add<int64_t>(hn_tmp)));
+    CHKH(part.alloc(tmp, nt));
+    CHKH(head.alloc(tmp, 1));
+    CHKH(hist.alloc(tmp, hn));
+    CHKH(htmp.alloc(tmp, hn_tmp));
+    CHKH(key.alloc(tmp, n));
+    if (!vertex) {
+        CHKH(next.alloc(tmp, n));
+        CHKH(trows.alloc(tmp, ntr));
+    }
     CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
     CHKH(hipMemsetAsync(head.p, 0, sizeof(Head), s));
     if (n > 0) {
@@ -418,28 +446,23 @@ static ebbkc_status build_slots(ebbkc_graph* g, const int32_t* id, const int32_t
     S.tot = h.tot;
     for (int c = 0; c < SIZE_BINS; ++c) S.count.n[c] = (int64_t)h.bins[c];
     const int64_t ns = S.tot.slots;
-    CHKH(S.seed.alloc(ns));
-    CHKH(S.c.alloc(ns));
-    if (vertex) CHKH(S.rthr.alloc(ns));
-    CHKH(S.order.alloc(ns));
-    CHKH(S.roff.alloc(ns));
-    CHKH(S.voff.alloc(ns));
-    CHKH(S.rows.alloc(S.tot.words));
-    CHKH(S.gid.alloc(S.tot.vtx));
-    CHKH(S.col.alloc(S.tot.vtx));
-    CHKH(S.ned.alloc(ns));
+    CHKH(S.held.init(SlabSize{}
+                         .add<int32_t>(ns, 4)
+                         .add<int64_t>(ns, 3)
+                         .add<uint64_t>(S.tot.words)
+                         .add<int32_t>(S.tot.vtx)
+                         .add<int16_t>(S.tot.vtx)));
+    CHKH(S.rows.alloc(S.held, S.tot.words));
+    CHKH(S.gid.alloc(S.held, S.tot.vtx));
+    CHKH(S.col.alloc(S.held, S.tot.vtx));
+    CHKH(S.seed.alloc(S.held, ns));
+    CHKH(S.c.alloc(S.held, ns));
+    if (vertex) CHKH(S.rthr.alloc(S.held, ns));
+    CHKH(S.order.alloc(S.held, ns));
+    CHKH(S.roff.alloc(S.held, ns));
+    CHKH(S.voff.alloc(S.held, ns));
+    CHKH(S.ned.alloc(S.held, ns));
     if (ns == 0) return EBBKC_OK;
-    DBuf<uint8_t> key;
-    DBuf<int64_t> hist, htmp;
-    CHKH(key.alloc(ns));
-    CHKH(hist.alloc(radix_hist_elems(ns)));
-    CHKH(htmp.alloc(scan_tmp_elems(radix_hist_elems(ns)) + 64));
-    DBuf<unsigned long long> next;
-    DBuf<int32_t> trows;
-    if (!vertex) {
-        CHKH(next.alloc(n));
-        CHKH(trows.alloc(2 + 2 * (int64_t)g->n));
-    }
     hipLaunchKernelGGL(k_seed_fill, dim3((unsigned)nt), dim3(SEED_BLOCK), 0, s, id, size, by_id, n, part.p, S.seed.p,
                        S.c.p, S.rthr.p, S.roff.p, S.voff.p, key.p, next.p);
     CHKH(hipGetLastError());
@@ -484,16 +507,17 @@ ebbkc_status arena_impl(ebbkc_graph* g, hipStream_t s) {
     st = build_slots(g, g->byrank, g->subsize, true, g->m, false, S, s);
     if (st) return st;
     g->nseeds = S.tot.slots;
-    g->seed_eid = S.seed.release();
-    g->seed_c = S.c.release();
-    g->seed_order = S.order.release();
+    g->seed_eid = S.seed.p;
+    g->seed_c = S.c.p;
+    g->seed_order = S.order.p;
     g->seed_sizes = S.count;
-    g->row_off = S.roff.release();
-    g->vtx_off = S.voff.release();
-    g->arows = S.rows.release();
-    g->agid = S.gid.release();
-    g->acol = S.col.release();
-    g->nedges = S.ned.release();
+    g->row_off = S.roff.p;
+    g->vtx_off = S.voff.p;
+    g->arows = S.rows.p;
+    g->agid = S.gid.p;
+    g->acol = S.col.p;
+    g->nedges = S.ned.p;
+    g->arena_held = S.held.release();
     g->arena_bytes = (int64_t)(S.tot.words * 8 + S.tot.vtx * 6 + S.tot.slots * 32);
     g->device_bytes += g->arena_bytes;
     g->arena_built = true;
@@ -522,17 +546,18 @@ static ebbkc_status vertex_arena_impl(ebbkc_graph* g, hipStream_t s) {
     st = build_slots(g, byvpos.p, cout.p, false, n, true, S, s);
     if (st) return st;
     A.nseeds = S.tot.slots;
-    A.seed_v = S.seed.release();
-    A.seed_c = S.c.release();
-    A.seed_rthr = S.rthr.release();
-    A.seed_order = S.order.release();
+    A.seed_v = S.seed.p;
+    A.seed_c = S.c.p;
+    A.seed_rthr = S.rthr.p;
+    A.seed_order = S.order.p;
     A.seed_sizes = S.count;
-    A.row_off = S.roff.release();
-    A.vtx_off = S.voff.release();
-    A.rows = S.rows.release();
-    A.gid = S.gid.release();
-    A.col = S.col.release();
-    A.nedges = S.ned.release();
+    A.row_off = S.roff.p;
+    A.vtx_off = S.voff.p;
+    A.rows = S.rows.p;
+    A.gid = S.gid.p;
+    A.col = S.col.p;
+    A.nedges = S.ned.p;
+    A.held = S.held.release();
     A.bytes = (int64_t)(S.tot.words * 8 + S.tot.vtx * 6 + S.tot.slots * 36);
     g->device_bytes += A.bytes;
     A.built = true;
@@ -553,6 +578,7 @@ static void swap_arenas(ebbkc_graph* g) {
     std::swap(g->agid, A.gid);
     std::swap(g->acol, A.col);
     std::swap(g->nedges, A.nedges);
+    std::swap(g->arena_held, A.held);
     std::swap(g->arena_built, A.built);
     g->np_active = !g->np_active;
 }

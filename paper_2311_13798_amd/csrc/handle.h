@@ -47,6 +47,7 @@ struct VertexArena {
     int32_t* gid = nullptr;
     int16_t* col = nullptr;
     uint64_t* nedges = nullptr;
+    char* held = nullptr;  // the allocation of all of them
     int64_t bytes = 0;
 };
 
@@ -58,6 +59,11 @@ struct ebbkc_graph {
     double prepare_ms = 0.0;
     ebbkc_options opt{};
     int cu_count = 256;
+
+    // one allocation each: the prepared arrays (rp .. byrank below, and subsize
+    // under the truss order), and the edge and vertex arenas
+    char* held = nullptr;
+    char* arena_held = nullptr;
 
     // id-sorted CSR (input copy) and per-entry edge rank
     int32_t* rp = nullptr;    // n+1
@@ -80,7 +86,8 @@ struct ebbkc_graph {
     uint64_t* adj = nullptr;
     uint16_t* acum = nullptr;
     int32_t adjw = 0;
-    int32_t* subsize = nullptr; // m: |V(g_i)| per edge (filled on demand)
+    int32_t* subsize = nullptr; // m: |V(g_i)| per edge (from the peel, or filled on demand)
+    bool subsize_own = false;   // an allocation of its own
     int32_t* vpos = nullptr;    // n: position in the root vertex order (orderings COLOR, DEGEN_VERTEX)
     int32_t* vcol = nullptr;    // n: greedy colour of G (ordering COLOR)
     bool subsize_ready = false;

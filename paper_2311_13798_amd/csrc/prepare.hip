@@ -23,6 +23,7 @@
 #include "device_util.h"
 #include "handle.h"
 #include "prims.h"
+#include "slab.h"
 
 namespace ebb {
 namespace {
@@ -986,9 +987,36 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     CHK(hipEventCreate(&ev1));
     CHK(hipEventRecord(ev0, s));
 
-    DBuf<int32_t> rp, ci;
-    CHK(rp.alloc(n + 1));
-    CHK(ci.alloc(nnz));
+    // the arrays the handle keeps and the ones only this call uses, a slab each
+    // (m = nnz / 2 edges, if the input turns out valid)
+    const int64_t mm = nnz / 2, rsort = radix_hist_elems(nnz);
+    const int64_t tmp_elems = scan_tmp_elems(nnz + n + 2) + 1024, rtmp_elems = scan_tmp_elems(rsort) + 64;
+    const int64_t live_elems = mm + PEEL_TB * (PEEL_GRID_WIDE + 1);
+    Slab held, tmp;
+    CHK(held.init(SlabSize{}
+                      .add<int32_t>(n + 1, 2)
+                      .add<int32_t>(nnz, 2)
+                      .add<int32_t>(mm, 7)
+                      .add<int2>(nnz)
+                      .add<int2>(mm)));
+    CHK(tmp.init(SlabSize{}
+                     .add<int32_t>(n, 2)
+                     .add<int64_t>(n + 1)
+                     .add<int32_t>(2 + 2 * (int64_t)n)
+                     .add<int64_t>(tmp_elems)
+                     .add<int32_t>(nnz, 3)
+                     .add<int64_t>(nnz)
+                     .add<int2>(mm)
+                     .add<int32_t>(mm, 6)
+                     .add<int64_t>(mm + 1, 2)
+                     .add<uint32_t>(nnz, 4)
+                     .add<int64_t>(rsort)
+                     .add<int64_t>(rtmp_elems)
+                     .add<PeelCtl>(1)
+                     .add<int32_t>(live_elems)));
+    SBuf<int32_t> rp, ci;
+    CHK(rp.alloc(held, n + 1));
+    CHK(ci.alloc(held, nnz));
     hipMemcpyKind kind = ptr_kind == EBBKC_PTR_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
     CHK(hipMemcpyAsync(rp.p, row_ptr, sizeof(int32_t) * (size_t)(n + 1), kind, s));
     if (nnz) CHK(hipMemcpyAsync(ci.p, col_idx, sizeof(int32_t) * (size_t)nnz, kind, s));
@@ -1010,17 +1038,16 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     g->m = m;
 
     // ---- edge ids
-    DBuf<int32_t> ustart, ucnt, eid, src, eu, ev;
-    DBuf<int64_t> eoff, scan_tmp;
-    CHK(ustart.alloc(n));
-    CHK(ucnt.alloc(n));
-    CHK(eoff.alloc(n + 1));
-    int64_t tmp_elems = scan_tmp_elems(nnz + n + 2) + 1024;
-    CHK(scan_tmp.alloc(tmp_elems));
-    CHK(eid.alloc(nnz));
-    CHK(src.alloc(nnz));
-    CHK(eu.alloc(m));
-    CHK(ev.alloc(m));
+    SBuf<int32_t> ustart, ucnt, eid, src, eu, ev;
+    SBuf<int64_t> eoff, scan_tmp;
+    CHK(ustart.alloc(tmp, n));
+    CHK(ucnt.alloc(tmp, n));
+    CHK(eoff.alloc(tmp, n + 1));
+    CHK(scan_tmp.alloc(tmp, tmp_elems));
+    CHK(eid.alloc(tmp, nnz));
+    CHK(src.alloc(tmp, nnz));
+    CHK(eu.alloc(held, m));
+    CHK(ev.alloc(held, m));
     if (n) hipLaunchKernelGGL(k_ustart, dim3(grid_for(n)), dim3(TB), 0, s, rp.p, ci.p, n, ustart.p, ucnt.p, dstat + 1);
     CHK(exclusive_scan_i32(ucnt.p, eoff.p, n, eoff.p + n, scan_tmp.p, s));
     if (nnz)
@@ -1029,13 +1056,13 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     CHK(hipGetLastError());
 
     // ---- degree orientation (id-sorted out rows with edge ids)
-    DBuf<int32_t> oflag, orp;
-    DBuf<int64_t> opos;
-    DBuf<int2> orow_id;
-    CHK(oflag.alloc(nnz));
-    CHK(opos.alloc(nnz));
-    CHK(orp.alloc(n + 1));
-    CHK(orow_id.alloc(m));
+    SBuf<int32_t> oflag, orp;
+    SBuf<int64_t> opos;
+    SBuf<int2> orow_id;
+    CHK(oflag.alloc(tmp, nnz));
+    CHK(opos.alloc(tmp, nnz));
+    CHK(orp.alloc(held, n + 1));
+    CHK(orow_id.alloc(tmp, m));
     if (nnz)
         hipLaunchKernelGGL(k_out_flags, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, src.p, ci.p, (const int2*)nullptr,
                            nnz, oflag.p);
@@ -1045,13 +1072,13 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     CHK(hipGetLastError());
 
     // ---- supports and triangle incidence
-    DBuf<int32_t> sup, nab, naw, trows;
-    DBuf<int64_t> inc_off, cursor;
-    CHK(sup.alloc(m));
-    CHK(nab.alloc(m));
-    CHK(naw.alloc(m));
-    CHK(trows.alloc(2 + 2 * (int64_t)n));
-    CHK(inc_off.alloc(m + 1));
+    SBuf<int32_t> sup, nab, naw, trows;
+    SBuf<int64_t> inc_off, cursor;
+    CHK(sup.alloc(tmp, m));
+    CHK(nab.alloc(tmp, m));
+    CHK(naw.alloc(tmp, m));
+    CHK(trows.alloc(tmp, 2 + 2 * (int64_t)n));
+    CHK(inc_off.alloc(tmp, m + 1));
     CHK(hipMemsetAsync(sup.p, 0, sizeof(int32_t) * (size_t)(m > 0 ? m : 1), s));
     CHK(hipMemsetAsync(trows.p, 0, 2 * sizeof(int32_t), s));
     TriArgs tri{};
@@ -1074,7 +1101,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     g->max_degree = hstat[1];
     DBuf<int2> inc;
     CHK(inc.alloc(h_ninc));
-    CHK(cursor.alloc(m + 1));
+    CHK(cursor.alloc(tmp, m + 1));
     if (m) {
         hipLaunchKernelGGL(k_tri_cursor, dim3(grid_for(m)), dim3(TB), 0, s, orow_id.p, nab.p, naw.p, inc_off.p, m,
                            (unsigned long long*)cursor.p);
@@ -1084,31 +1111,31 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
         if (h_ninc) CHK(launch_tri<1>(tri, trows.p, s));
     }
     CHK(hipGetLastError());
-    DBuf<int32_t> sup0;
-    CHK(sup0.alloc(m));
+    SBuf<int32_t> sup0;
+    CHK(sup0.alloc(held, m));
     CHK(hipMemcpyAsync(sup0.p, sup.p, sizeof(int32_t) * (size_t)(m > 0 ? m : 1), hipMemcpyDeviceToDevice, s));
 
     // ---- level-synchronous peel: rounds, levels and |V(g_i)|, then the ranks
     // by a stable sort of the rounds over the edge ids
-    DBuf<int32_t> live, front0, front1, rnd, level, rank, subsize, byrank;
-    DBuf<PeelCtl> ctl;
-    DBuf<uint32_t> rk1, rk2, rv2;
-    DBuf<int64_t> rhist, rtmp;
+    SBuf<int32_t> live, front0, front1, rnd, level, rank, subsize, byrank;
+    SBuf<PeelCtl> ctl;
+    SBuf<uint32_t> rk1, rk2, rv2;
+    SBuf<int64_t> rhist, rtmp;
     const int64_t sorted = nnz;  // the larger of the two sorts that share the buffers
-    CHK(level.alloc(m));
-    CHK(rank.alloc(m));
-    CHK(subsize.alloc(m));
-    CHK(byrank.alloc(m));
-    CHK(rk1.alloc(sorted));
-    CHK(rk2.alloc(sorted));
-    CHK(rv2.alloc(sorted));
-    CHK(rhist.alloc(radix_hist_elems(sorted)));
-    CHK(rtmp.alloc(scan_tmp_elems(radix_hist_elems(sorted)) + 64));
+    CHK(level.alloc(held, m));
+    CHK(rank.alloc(held, m));
+    CHK(subsize.alloc(held, m));
+    CHK(byrank.alloc(held, m));
+    CHK(rk1.alloc(tmp, sorted));
+    CHK(rk2.alloc(tmp, sorted));
+    CHK(rv2.alloc(tmp, sorted));
+    CHK(rhist.alloc(tmp, radix_hist_elems(sorted)));
+    CHK(rtmp.alloc(tmp, rtmp_elems));
     if (m) {
-        CHK(rnd.alloc(m));
-        CHK(front0.alloc(m));
-        CHK(front1.alloc(m));
-        CHK(ctl.alloc(1));
+        CHK(rnd.alloc(tmp, m));
+        CHK(front0.alloc(tmp, m));
+        CHK(front1.alloc(tmp, m));
+        CHK(ctl.alloc(tmp, 1));
         const int64_t chunks = (m + PEEL_TB - 1) / PEEL_TB;
         const int64_t grid = std::min<int64_t>(m >= PEEL_WIDE_M ? PEEL_GRID_WIDE : PEEL_GRID, (chunks + 1) / 2);
         PeelArgs pa{};
@@ -1122,7 +1149,8 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
         pa.front[0] = front0.p;
         pa.front[1] = front1.p;
         pa.live_chunks = (int32_t)((chunks + grid - 1) / grid);
-        CHK(live.alloc(grid * pa.live_chunks * PEEL_TB));
+        if (grid * pa.live_chunks * PEEL_TB > live_elems) return EBBKC_E_HIP;
+        CHK(live.alloc(tmp, grid * pa.live_chunks * PEEL_TB));
         pa.live = live.p;
         pa.ctl = ctl.p;
         hipLaunchKernelGGL(k_peel_begin, dim3(std::min(grid_for(m), 2048u)), dim3(TB), 0, s, ctl.p, rnd.p, (int32_t)m);
@@ -1135,9 +1163,12 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
         if (hc->err) return EBBKC_E_HIP;
         g->tau = hc->tau;
         g->rounds = hc->rounds;
-        hipLaunchKernelGGL(k_round_keys, dim3(grid_for(m)), dim3(TB), 0, s, rnd.p, m, rk1.p, (uint32_t*)byrank.p);
-        CHK(radix_sort_u32(rk1.p, (uint32_t*)byrank.p, rk2.p, rv2.p, m, bits_for((uint64_t)(g->rounds - 1)), rhist.p,
-                           rtmp.p, s));
+        // (the sorted ids end in byrank: an odd number of passes starts from the other buffer)
+        const int rbits = bits_for((uint64_t)(g->rounds - 1));
+        const bool odd = radix_passes(m, rbits) & 1;
+        uint32_t* va = odd ? rv2.p : (uint32_t*)byrank.p;
+        hipLaunchKernelGGL(k_round_keys, dim3(grid_for(m)), dim3(TB), 0, s, rnd.p, m, rk1.p, va);
+        CHK(radix_sort_u32(rk1.p, va, rk2.p, odd ? (uint32_t*)byrank.p : rv2.p, m, rbits, rhist.p, rtmp.p, s, false));
         hipLaunchKernelGGL(k_scatter_pos, dim3(grid_for(m)), dim3(TB), 0, s, (const uint32_t*)byrank.p, m, rank.p);
         CHK(hipGetLastError());
     }
@@ -1239,18 +1270,20 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     }
 
     // ---- rank-tagged adjacency
-    DBuf<int32_t> erank;
-    DBuf<uint32_t> rv1;
-    DBuf<int2> rrow, orow;
-    CHK(erank.alloc(nnz));
-    CHK(rv1.alloc(nnz));
-    CHK(rrow.alloc(nnz));
-    CHK(orow.alloc(m));
+    SBuf<int32_t> erank;
+    SBuf<uint32_t> rv1;
+    SBuf<int2> rrow, orow;
+    CHK(erank.alloc(held, nnz));
+    CHK(rv1.alloc(tmp, nnz));
+    CHK(rrow.alloc(held, nnz));
+    CHK(orow.alloc(held, m));
     if (nnz) {
         hipLaunchKernelGGL(k_erank, dim3(grid_for(nnz)), dim3(TB), 0, s, eid.p, rank.p, nnz, erank.p);
         hipLaunchKernelGGL(k_rrow_keys, dim3(grid_for(m)), dim3(TB), 0, s, byrank.p, eu.p, ev.p, m, rk1.p, rv1.p);
-        CHK(radix_sort_u32(rk1.p, rv1.p, rk2.p, rv2.p, nnz, bits_for((uint64_t)(n - 1)), rhist.p, rtmp.p, s));
-        hipLaunchKernelGGL(k_gather_rrow, dim3(grid_for(nnz)), dim3(TB), 0, s, rv1.p, byrank.p, eu.p, ev.p, m, rrow.p);
+        const int vbits = bits_for((uint64_t)(n - 1));
+        CHK(radix_sort_u32(rk1.p, rv1.p, rk2.p, rv2.p, nnz, vbits, rhist.p, rtmp.p, s, false));
+        const uint32_t* perm = radix_passes(nnz, vbits) & 1 ? rv2.p : rv1.p;
+        hipLaunchKernelGGL(k_gather_rrow, dim3(grid_for(nnz)), dim3(TB), 0, s, perm, byrank.p, eu.p, ev.p, m, rrow.p);
         hipLaunchKernelGGL(k_out_flags, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, src.p, ci.p, rrow.p, nnz, oflag.p);
         CHK(exclusive_scan_i32(oflag.p, opos.p, nnz, nullptr, scan_tmp.p, s));
         hipLaunchKernelGGL(k_out_fill, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, ci.p, eid.p, rrow.p, n, nnz, oflag.p,
@@ -1279,20 +1312,21 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     (void)hipEventDestroy(ev1);
     g->prepare_ms = ms;
 
-    g->rp = rp.release();
-    g->ci = ci.release();
-    g->erank = erank.release();
-    g->eu = eu.release();
-    g->ev = ev.release();
-    g->sup0 = sup0.release();
-    g->rank = rank.release();
-    g->level = level.release();
-    g->rrow = rrow.release();
-    g->orp = orp.release();
-    g->orow = orow.release();
-    g->byrank = byrank.release();
+    g->held = held.release();
+    g->rp = rp.p;
+    g->ci = ci.p;
+    g->erank = erank.p;
+    g->eu = eu.p;
+    g->ev = ev.p;
+    g->sup0 = sup0.p;
+    g->rank = rank.p;
+    g->level = level.p;
+    g->rrow = rrow.p;
+    g->orp = orp.p;
+    g->orow = orow.p;
+    g->byrank = byrank.p;
     if (g->opt.ordering == EBBKC_ORDER_HYBRID || g->opt.ordering == EBBKC_ORDER_TRUSS) {
-        g->subsize = subsize.release();  // of pi_tau; another edge order has other sub-branches
+        g->subsize = subsize.p;  // of pi_tau; another edge order has other sub-branches
         g->subsize_ready = true;
     }
     if (with_adj) {

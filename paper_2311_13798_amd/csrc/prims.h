@@ -22,8 +22,11 @@ hipError_t exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_
 int64_t radix_hist_elems(int64_t n);
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
                           int bits, int64_t* hist, int64_t* tmp, hipStream_t s);
+// copy_back false: the result stays where the last pass left it, in the _alt
+// arrays after an odd number of passes.
+int radix_passes(int64_t n, int bits);
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, int64_t n,
-                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s);
+                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s, bool copy_back = true);
 
 // Stable counting sort of n byte keys: out[i] = index of the i-th item in key
 // order.  hist and tmp as for radix_sort_u64.

@@ -1,4 +1,6 @@
 // prims.hip -- exclusive scan and stable LSD radix sort (wave64, gfx950).
+#include <algorithm>
+
 #include "common.h"
 #include "prims.h"
 
@@ -104,17 +106,22 @@ hipError_t scan_impl(const T* in, int64_t* out, int64_t n, int64_t* d_total, int
 
 // ---------------------------------------------------------------- radix sort
 constexpr int RS_BLOCK = 256;
-constexpr int RS_ITEMS = 16;
-constexpr int RS_TILE = RS_BLOCK * RS_ITEMS;
+// Items a thread takes one after the other, each with four barriers: 16 keep
+// the histograms small, 4 keep a short sort short (40,000 items: 20 us a
+// scatter with 16, which is ten workgroups).
+constexpr int RS_ITEMS = 16, RS_ITEMS_SHORT = 4;
+constexpr int64_t RS_SHORT_N = 1 << 20;
+inline int rs_items(int64_t n) { return n <= RS_SHORT_N ? RS_ITEMS_SHORT : RS_ITEMS; }
+inline int64_t rs_blocks(int64_t n) { return (n + RS_BLOCK * rs_items(n) - 1) / (RS_BLOCK * rs_items(n)); }
 constexpr int RS_WAVES = RS_BLOCK / EBB_WAVE;
 
-template <typename K>
+template <typename K, int RS_ITEMS>
 __global__ void k_rs_hist(const K* __restrict__ keys, int64_t n, int shift, int64_t nb,
                           int64_t* __restrict__ hist) {
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
-    int64_t base = (int64_t)blockIdx.x * RS_TILE;
+    int64_t base = (int64_t)blockIdx.x * (RS_BLOCK * RS_ITEMS);
     for (int j = 0; j < RS_ITEMS; ++j) {
         int64_t i = base + j * RS_BLOCK + threadIdx.x;
         if (i < n) atomicAdd(&h[(keys[i] >> shift) & 0xFF], 1u);
@@ -124,7 +131,7 @@ __global__ void k_rs_hist(const K* __restrict__ keys, int64_t n, int shift, int6
 }
 
 // vin null: an item's value is its index; kout / vout null: not written
-template <typename K>
+template <typename K, int RS_ITEMS>
 __global__ void k_rs_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
                              K* __restrict__ kout, uint32_t* __restrict__ vout, int64_t n, int shift,
                              int64_t nb, const int64_t* __restrict__ off) {
@@ -132,7 +139,7 @@ __global__ void k_rs_scatter(const K* __restrict__ kin, const uint32_t* __restri
     __shared__ uint32_t wcnt[RS_WAVES][256];
     const int tid = threadIdx.x, lane = lane_id(), w = tid / EBB_WAVE;
     run[tid] = 0;
-    int64_t base = (int64_t)blockIdx.x * RS_TILE;
+    int64_t base = (int64_t)blockIdx.x * (RS_BLOCK * RS_ITEMS);
     for (int j = 0; j < RS_ITEMS; ++j) {
         int64_t i = base + j * RS_BLOCK + tid;
         bool valid = i < n;
@@ -180,38 +187,58 @@ hipError_t exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_
     return scan_impl<int64_t>(in, out, n, d_total, tmp, s);
 }
 
-int64_t radix_hist_elems(int64_t n) { return 256 * ((n + RS_TILE - 1) / RS_TILE) + 1; }
+// (of a short sort also what a longer one of up to the limit needs, so that a
+// buffer sized for n serves any smaller sort)
+int64_t radix_hist_elems(int64_t n) {
+    return 256 * std::max(rs_blocks(n), rs_blocks(std::min(n, RS_SHORT_N))) + 1;
+}
+int radix_passes(int64_t n, int bits) { return n <= 1 || bits <= 0 ? 0 : (bits + 7) / 8; }
+
+template <typename K>
+static void rs_hist(const K* keys, int64_t n, int shift, int64_t* hist, hipStream_t s) {
+    const int64_t nb = rs_blocks(n);
+    if (n <= RS_SHORT_N)
+        hipLaunchKernelGGL((k_rs_hist<K, RS_ITEMS_SHORT>), dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, keys, n, shift, nb,
+                           hist);
+    else
+        hipLaunchKernelGGL((k_rs_hist<K, RS_ITEMS>), dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, keys, n, shift, nb, hist);
+}
+template <typename K>
+static void rs_scatter(const K* kin, const uint32_t* vin, K* kout, uint32_t* vout, int64_t n, int shift,
+                       const int64_t* off, hipStream_t s) {
+    const int64_t nb = rs_blocks(n);
+    if (n <= RS_SHORT_N)
+        hipLaunchKernelGGL((k_rs_scatter<K, RS_ITEMS_SHORT>), dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, kin, vin, kout,
+                           vout, n, shift, nb, off);
+    else
+        hipLaunchKernelGGL((k_rs_scatter<K, RS_ITEMS>), dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, kin, vin, kout, vout, n,
+                           shift, nb, off);
+}
 
 hipError_t bin_sort_u8(const uint8_t* keys, int64_t n, uint32_t* out, int64_t* hist, int64_t* tmp, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const int64_t nb = (n + RS_TILE - 1) / RS_TILE;
-    hipLaunchKernelGGL(k_rs_hist<uint8_t>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, keys, n, 0, nb, hist);
-    hipError_t e = exclusive_scan_i64(hist, hist, 256 * nb, nullptr, tmp, s);
+    rs_hist(keys, n, 0, hist, s);
+    hipError_t e = exclusive_scan_i64(hist, hist, 256 * rs_blocks(n), nullptr, tmp, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rs_scatter<uint8_t>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, keys, (const uint32_t*)nullptr,
-                       (uint8_t*)nullptr, out, n, 0, nb, hist);
+    rs_scatter(keys, nullptr, (uint8_t*)nullptr, out, n, 0, hist, s);
     return hipGetLastError();
 }
 
 template <typename K>
-static hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, int64_t n,
-                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s) {
-    if (n <= 1 || bits <= 0) return hipSuccess;
-    int64_t nb = (n + RS_TILE - 1) / RS_TILE;
+static hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, int64_t n, int bits,
+                             int64_t* hist, int64_t* tmp, hipStream_t s, bool copy_back) {
+    const int passes = radix_passes(n, bits);
     K *ka = keys, *kb = keys_alt;
     uint32_t *va = vals, *vb = vals ? vals_alt : nullptr;
-    int passes = (bits + 7) / 8;
     for (int p = 0; p < passes; ++p) {
-        int shift = p * 8;
-        hipLaunchKernelGGL(k_rs_hist<K>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, n, shift, nb, hist);
-        hipError_t e = exclusive_scan_i64(hist, hist, 256 * nb, nullptr, tmp, s);
+        rs_hist(ka, n, p * 8, hist, s);
+        hipError_t e = exclusive_scan_i64(hist, hist, 256 * rs_blocks(n), nullptr, tmp, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_rs_scatter<K>, dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, ka, va, kb, vb, n, shift, nb,
-                           hist);
+        rs_scatter(ka, va, kb, vb, n, p * 8, hist, s);
         K* kt = ka; ka = kb; kb = kt;
         uint32_t* vt = va; va = vb; vb = vt;
     }
-    if (passes & 1) {
+    if ((passes & 1) && copy_back) {
         hipError_t e = hipMemcpyAsync(keys, ka, sizeof(K) * n, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return e;
         if (vals) e = hipMemcpyAsync(vals, va, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s);
@@ -222,11 +249,11 @@ static hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* val
 
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
                           int bits, int64_t* hist, int64_t* tmp, hipStream_t s) {
-    return radix_sort<uint64_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s);
+    return radix_sort<uint64_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s, true);
 }
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, int64_t n,
-                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s) {
-    return radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s);
+                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s, bool copy_back) {
+    return radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s, copy_back);
 }
 
 }  // namespace ebb
