@@ -319,9 +319,9 @@ ebbkc_status ebbkc_batch_create(ebbkc_graph *const *graphs, const int32_t *ks, i
                                 const ebbkc_options *opt, void *stream, ebbkc_batch **out);
 
 /* Run the batch and write the exact count of graph i to out_counts[i] (may be
- * NULL).  use_graph = 1 replays a HIP graph captured on the first call (the
- * counter reset, the per-class launches and the result copy); 0 launches the
- * same sequence directly.  Synchronises stream.  A failure belongs to the
+ * NULL).  use_graph = 1 replays a HIP graph captured on the second call (the
+ * counter reset, the per-class launches and the result copy; the first call
+ * launches them); 0 always launches the same sequence directly.  Synchronises stream.  A failure belongs to the
  * graph that met it: a graph whose count reaches 2^64 gets 0 in out_counts
  * and the call returns EBBKC_E_OVERFLOW, while every other graph's count is
  * still written (out_counts is written in full whenever the launches ran). */

@@ -1,5 +1,5 @@
 // batch.hip -- many (graph, k) counts in one fused launch per bitmap width
-// class, captured once in a HIP graph and replayed.
+// class; a batch run more than once replays them from a HIP graph.
 //
 // Every graph of the batch is prepared; its sub-branches come from its arena
 // or, for batches whose arenas would not fit device memory, are built by
@@ -35,6 +35,7 @@
 #include "common.h"
 #include "handle.h"
 #include "prims.h"
+#include "slab.h"
 
 struct ebbkc_batch {
     int device = 0;
@@ -46,14 +47,16 @@ struct ebbkc_batch {
     // LDS from the graph's arrays (bviews)
     bool build = false;
     ebb::BuildGraph* bviews = nullptr;
-    // device
+    // device: one allocation each for the arrays of a batch and for its tasks
+    char* held = nullptr;
+    char* task_mem = nullptr;
     ebb::ArenaView* views = nullptr;
     int32_t* gk = nullptr;
     int32_t* gtau = nullptr;
     int64_t* tasks = nullptr;
     int32_t* tgraph = nullptr;
-    unsigned long long* gtot = nullptr;  // 2 per graph
     unsigned long long* ctr = nullptr;   // [4..6) unused, [6] err, [8..11] work, [16..24) launches' work counters
+    unsigned long long* gtot = nullptr;  // 2 per graph, right behind the counters
     ebb::SplitItem* squeue = nullptr;    // runtime split queue (null: off)
     unsigned long long* sq = nullptr;
     void* gframes = nullptr;
@@ -63,19 +66,19 @@ struct ebbkc_batch {
     uint64_t ccount[8] = {};
     int64_t heavy[8] = {};
     int32_t kmax = 0;
-    // host results
-    unsigned long long* h_tot = nullptr;
-    unsigned long long* h_ctr = nullptr;
+    // host results (pinned): the counters, then the totals
+    unsigned long long* h_res = nullptr;
     // captured launch sequence
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool dirty = true;  // tasks changed since capture
+    bool ran = false;   // launched directly since then
     double last_ms = 0.0;
     // device memory: stream-ordered on mem_stream when async_mem (the served
     // form, whose epochs overlap: a plain free would wait for the device)
     bool async_mem = false;
     hipStream_t mem_stream = nullptr;
-    bool own_host = true;  // h_tot / h_ctr allocated by the batch
+    bool own_host = true;  // h_res allocated by the batch
 };
 
 namespace ebb {
@@ -99,37 +102,53 @@ inline unsigned gridn(int64_t n) {
     return (unsigned)b;
 }
 
-__global__ void k_btask_counts(const int32_t* __restrict__ seed_c, int64_t n, int l0, double log_thr,
-                               int32_t* __restrict__ tcount) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int c = seed_c[i];
-        tcount[i] = c >= l0 ? root_tasks(c, l0, log_thr, [](int, int) {}) : 0;
+// Tasks of the arena slots: segment j is the range [x0, x1) of the slots
+// order[0 ..] of one graph; its tasks start at pref[j].
+struct BatchSeg {
+    int64_t pref;
+    const int32_t* order;
+    int32_t graph;
+    int16_t x0, x1;
+};
+
+__global__ void k_bexpand(const BatchSeg* __restrict__ seg, int nseg, int64_t n, int64_t* __restrict__ tasks,
+                          int32_t* __restrict__ tgraph) {
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
+        int lo = 0, hi = nseg;  // the last segment starting at or before t
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (seg[mid].pref <= t) lo = mid; else hi = mid;
+        }
+        const BatchSeg g = seg[lo];
+        tasks[t] = task_pack(g.order[t - g.pref], g.x0, g.x1);
+        tgraph[t] = g.graph;
     }
+}
+
+// tasks that build their g_i, one per edge with enough vertices
+__global__ void k_btask_counts(const int32_t* __restrict__ subsize, int64_t n, int l0, int32_t* __restrict__ tcount) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        tcount[i] = subsize[i] >= l0;
 }
 
 constexpr int CTR_WORDS = 32;
 
-// Sort key of a task: its launch (width class and whether its search branches
-// below the root), then (gbits > 0) its graph, then the vertices it can still
-// use, largest first.
-__global__ void k_btask_fill(const int32_t* __restrict__ seed_c, int64_t n, int l0, double log_thr,
-                             const int64_t* __restrict__ toff, int64_t base, int32_t graph, int gbits,
-                             int64_t* __restrict__ tasks, int32_t* __restrict__ tgraph, uint64_t* __restrict__ keys,
-                             uint32_t* __restrict__ vals) {
+// the launch that runs a task: its width class, and whether its search
+// branches below the root
+__host__ __device__ inline int launch_of(int c, int l0) { return 2 * (width_of(c) - 1) + (l0 + 2 >= SEARCH_BRANCH_K); }
+
+// Sort key of a task: its launch, then its graph, then its size, largest first.
+__global__ void k_btask_fill(const int32_t* __restrict__ subsize, int64_t n, int l0, const int64_t* __restrict__ toff,
+                             int64_t base, int32_t graph, int gbits, int64_t* __restrict__ tasks,
+                             int32_t* __restrict__ tgraph, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int c = seed_c[i];
+        const int c = subsize[i];
         if (c < l0) continue;
-        int64_t o = base + toff[i];
-        root_tasks(c, l0, log_thr, [&](int x0, int x1) {
-            const int W = width_of(c - x0);  // the search drops the vertices before x0
-            tasks[o] = task_pack(i, x0, x1);
-            tgraph[o] = graph;
-            const int usable = x0 == 0 && x1 >= c ? c : c - 1 - x0;
-            keys[o] = ((uint64_t)(2 * (W - 1) + (l0 + 2 >= SEARCH_BRANCH_K)) << (8 + gbits)) | ((uint64_t)(gbits ? graph : 0) << 8) |
-                      (uint64_t)(255 - (usable > 255 ? 255 : usable));
-            vals[o] = (uint32_t)o;
-            ++o;
-        });
+        const int64_t o = base + toff[i];
+        tasks[o] = task_pack(i, 0, c);
+        tgraph[o] = graph;
+        keys[o] = ((uint64_t)launch_of(c, l0) << (8 + gbits)) | ((uint64_t)graph << 8) | (uint64_t)(255 - min(c, 255));
+        vals[o] = (uint32_t)o;
     }
 }
 
@@ -142,15 +161,13 @@ __global__ void k_bgather(const int64_t* __restrict__ tasks, const int32_t* __re
     }
 }
 
-// Bounds in the sorted keys by binary search, one lane each: lane w < 8 the
-// end of launch w, lane 8 + w (lists sorted by size inside a launch) the first
-// task of launch w with at most c_light usable vertices.  (A pass over
-// all keys that counts the classes took 0.7 ms for 4 M tasks.)
-__global__ void k_bclass_bounds(const uint64_t* __restrict__ keys, int64_t n, int gbits, int c_light,
+// Bounds in the sorted keys by binary search, lane w the end of launch w.  (A
+// pass over all keys that counts the classes took 0.7 ms for 4 M tasks.)
+__global__ void k_bclass_bounds(const uint64_t* __restrict__ keys, int64_t n, int gbits,
                                 unsigned long long* __restrict__ out) {
     const int t = threadIdx.x;
-    if (t >= 16) return;
-    const uint64_t key = t < 8 ? (uint64_t)(t + 1) << (8 + gbits) : ((uint64_t)(t - 8) << 8) | (uint64_t)(255 - c_light);
+    if (t >= 8) return;
+    const uint64_t key = (uint64_t)(t + 1) << (8 + gbits);
     int64_t lo = 0, hi = n;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
@@ -175,12 +192,8 @@ int light_size(int l0) {
 
 // zero the counters and per-graph totals (a kernel, so the captured graph
 // holds no memset node)
-__global__ void k_bclear(unsigned long long* __restrict__ a, int64_t na, unsigned long long* __restrict__ b,
-                         int64_t nb) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb; i += (int64_t)gridDim.x * blockDim.x) {
-        if (i < na) a[i] = 0;
-        else b[i - na] = 0;
-    }
+__global__ void k_bclear(unsigned long long* __restrict__ a, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) a[i] = 0;
 }
 
 // bytes of the arena slots of graph g (|V(g_i)| >= 1): c W words of rows plus
@@ -226,47 +239,141 @@ void dev_free(const ebbkc_batch* b, void* p, hipStream_t s) {
 }
 
 void free_tasks(ebbkc_batch* b) {
-    dev_free(b, b->tasks, b->mem_stream);
-    dev_free(b, b->tgraph, b->mem_stream);
+    dev_free(b, b->task_mem, b->mem_stream);
     dev_free(b, b->gframes, b->mem_stream);
+    b->task_mem = nullptr;
     b->tasks = nullptr;
     b->tgraph = nullptr;
     b->gframes = nullptr;
     b->ntasks = 0;
     b->dirty = true;
+    b->ran = false;
 }
 
-// Build the merged, sorted task list under the batch's current options.
-ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
-    free_tasks(b);
+ebbkc_status alloc_tasks(ebbkc_batch* b, int64_t total, size_t tail, hipStream_t s) {
+    const size_t tb = slab_round(sizeof(int64_t) * (size_t)total), gb = slab_round(sizeof(int32_t) * (size_t)total);
+    CHKB(dev_alloc(b, (void**)&b->task_mem, tb + gb + tail, s));
+    b->tasks = (int64_t*)b->task_mem;
+    b->tgraph = (int32_t*)(b->task_mem + tb);
+    return EBBKC_OK;
+}
+
+// Tasks over arena slots, planned on the host from the slots' sizes: the slot
+// order of an arena holds the slots of one size next to each other, so a root
+// range of one size of one graph is one segment, and only the segments are
+// sorted (by launch, then by the vertices a task can still use, largest
+// first).  One kernel writes the list.  (Counting, scanning and filling each
+// graph's tasks on the device, then sorting them, was 33 us of launches and
+// copies a graph: a
+// batch of 192 small graphs took 6.3 ms, now 1.5; a served burst of 200
+// requests 6.8 ms, now 1.1.)
+ebbkc_status arena_tasks(ebbkc_batch* b, hipStream_t s) {
+    struct Range {
+        int x0, x1, key;
+    };
+    std::map<int, std::vector<Range>> ranges;  // of a root of c vertices at l0, by 512 l0 + c
+    auto of_size = [&](int c, int l0) -> const std::vector<Range>& {
+        std::vector<Range>& r = ranges[512 * l0 + c];
+        if (r.empty())
+            root_tasks(c, l0, split_log(b->opt, l0, true), [&](int x0, int x1) {
+                // the search drops the vertices before x0
+                const int usable = x0 == 0 && x1 >= c ? c : c - 1 - x0;
+                r.push_back({x0, x1, 256 * launch_of(c - x0, l0) + 255 - std::min(usable, 255)});
+            });
+        return r;
+    };
+    constexpr int KEYS = 8 * 256;
+    std::vector<int64_t> tasks_of(KEYS, 0);  // per key
+    std::vector<int64_t> at(KEYS + 1, 0);
+    struct Item {
+        BatchSeg seg;
+        int64_t slots;
+        int key;
+    };
+    std::vector<Item> items;
+    for (int i = 0; i < (int)b->graphs.size(); ++i) {
+        const ebbkc_graph* g = b->graphs[(size_t)i];
+        const int l0 = b->ks[(size_t)i] - 2;
+        if (l0 < 1) continue;
+        int64_t pos = 0;  // first slot of the size in the slot order
+        for (int W = 1; W <= MAX_W; ++W)
+            for (int c = 64 * W; c > 64 * (W - 1); --c) {
+                const int64_t nc = g->seed_sizes.n[c];
+                if (nc && c >= l0)
+                    for (const Range& r : of_size(c, l0)) {
+                        items.push_back({{0, g->seed_order + pos, i, (int16_t)r.x0, (int16_t)r.x1}, nc, r.key});
+                        tasks_of[r.key] += nc;
+                        at[r.key + 1]++;
+                    }
+                pos += nc;
+            }
+    }
+    const int light = light_size(std::max(1, b->kmax - 2));
+    int64_t total = 0;
+    for (int w = 0; w < 8; ++w) {
+        int64_t n = 0, heavy = 0;
+        for (int u = 255; u >= 0; --u) {
+            const int64_t t = tasks_of[256 * w + 255 - u];
+            n += t;
+            if (u > light) heavy += t;
+        }
+        b->ccount[w] = (uint64_t)n;
+        // at most sixteen single tasks per wave: past them a chunk is a small
+        // part of a wave's share whatever its tasks weigh
+        b->heavy[w] = std::min<int64_t>(heavy, (int64_t)64 * 16 * b->cu_count);
+        total += n;
+    }
+    if (total >= ((int64_t)1 << 32)) return EBBKC_E_OOM;
+    b->ntasks = total;
+    if (total == 0) return EBBKC_OK;
+    for (int k = 0; k < KEYS; ++k) at[k + 1] += at[k];
+    std::vector<BatchSeg> segs(items.size());
+    std::vector<int64_t> len(items.size());
+    for (const Item& it : items) {
+        const int64_t j = at[it.key]++;
+        segs[(size_t)j] = it.seg;
+        len[(size_t)j] = it.slots;
+    }
+    int64_t pref = 0;
+    for (size_t j = 0; j < segs.size(); ++j) {
+        segs[j].pref = pref;
+        pref += len[j];
+    }
+    const size_t bytes = sizeof(BatchSeg) * segs.size();
+    if (ebbkc_status st = alloc_tasks(b, total, bytes, s)) return st;
+    BatchSeg* dseg = (BatchSeg*)((char*)b->tgraph + slab_round(sizeof(int32_t) * (size_t)total));
+    CHKB(hipMemcpyAsync(dseg, segs.data(), bytes, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_bexpand, dim3(gridn(total)), dim3(256), 0, s, dseg, (int)segs.size(), total, b->tasks,
+                       b->tgraph);
+    CHKB(hipGetLastError());
+    CHKB(hipStreamSynchronize(s));  // segs has been read
+    return EBBKC_OK;
+}
+
+// Tasks that build their g_i, one per edge with enough vertices (a range of a
+// root would build it again; the runtime split queue balances heavy ones),
+// graph by graph within a launch, so that its waves share one graph's arrays
+// in cache.
+ebbkc_status build_mode_tasks(ebbkc_batch* b, hipStream_t s) {
     const int n = (int)b->graphs.size();
-    // a task that builds its g_i would rebuild it for every root range: one
-    // task per seed there (the runtime split queue balances heavy ones)
-    auto log_thr_of = [&](int l0) { return b->build ? 1e300 : split_log(b->opt, l0, true); };
-    // per graph: task counts and offsets (scratch sized for the largest graph)
-    std::vector<int64_t> gbase((size_t)n + 1, 0);
+    std::vector<int64_t> gbase((size_t)n, 0), tcount((size_t)n, 0);
     std::vector<int64_t*> toffs((size_t)n, nullptr);
-    // seeds: arena slots, or (build mode) every edge with its |V(g_i)|
-    auto seeds_of = [&](const ebbkc_graph* g) -> int64_t { return b->build ? g->m : g->nseeds; };
-    auto sizes_of = [&](const ebbkc_graph* g) -> const int32_t* { return b->build ? g->subsize : g->seed_c; };
-    int64_t total = 0, nsmax = 0;
-    for (int i = 0; i < n; ++i) nsmax = std::max(nsmax, seeds_of(b->graphs[(size_t)i]));
+    // scratch sized for the largest graph
+    int64_t total = 0, mmax = 0;
+    for (const ebbkc_graph* g : b->graphs) mmax = std::max(mmax, g->m);
     int32_t* tc = nullptr;
     int64_t* tmp = nullptr;
-    CHKB(dev_alloc(b, (void**)&tc, sizeof(int32_t) * (nsmax + 1), s));
-    CHKB(dev_alloc(b, (void**)&tmp, sizeof(int64_t) * (scan_tmp_elems(nsmax + 1) + 64), s));
-    std::vector<int64_t> tcount((size_t)n, 0);
+    CHKB(dev_alloc(b, (void**)&tc, sizeof(int32_t) * (mmax + 1), s));
+    CHKB(dev_alloc(b, (void**)&tmp, sizeof(int64_t) * (scan_tmp_elems(mmax + 1) + 64), s));
     for (int i = 0; i < n; ++i) {
         ebbkc_graph* g = b->graphs[(size_t)i];
         const int k = b->ks[(size_t)i];
-        if (k < 3 || seeds_of(g) == 0) continue;
-        const int64_t ns = seeds_of(g);
+        if (k < 3 || g->m == 0) continue;
         int64_t* to = nullptr;
-        CHKB(dev_alloc(b, (void**)&to, sizeof(int64_t) * (ns + 1), s));
-        hipLaunchKernelGGL(k_btask_counts, dim3(gridn(ns)), dim3(256), 0, s, sizes_of(g), ns, k - 2, log_thr_of(k - 2),
-                           tc);
-        CHKB(exclusive_scan_i32(tc, to, ns, to + ns, tmp, s));
-        CHKB(hipMemcpyAsync(&tcount[(size_t)i], to + ns, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        CHKB(dev_alloc(b, (void**)&to, sizeof(int64_t) * (g->m + 1), s));
+        hipLaunchKernelGGL(k_btask_counts, dim3(gridn(g->m)), dim3(256), 0, s, g->subsize, g->m, k - 2, tc);
+        CHKB(exclusive_scan_i32(tc, to, g->m, to + g->m, tmp, s));
+        CHKB(hipMemcpyAsync(&tcount[(size_t)i], to + g->m, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         toffs[(size_t)i] = to;
     }
     CHKB(hipStreamSynchronize(s));
@@ -276,7 +383,6 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
         gbase[(size_t)i] = total;
         total += tcount[(size_t)i];
     }
-    gbase[(size_t)n] = total;
     b->ntasks = total;
     if (total == 0) {
         for (auto p : toffs) dev_free(b, p, s);
@@ -296,47 +402,42 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
     CHKB(dev_alloc(b, (void**)&vals2, sizeof(uint32_t) * total, s));
     CHKB(dev_alloc(b, (void**)&hist, sizeof(int64_t) * hn, s));
     CHKB(dev_alloc(b, (void**)&htmp, sizeof(int64_t) * (scan_tmp_elems(hn) + 64), s));
-    // tasks that build their g_i run graph by graph within a width class, so
-    // that the waves of a launch share one graph's arrays in cache
     int gbits = 0;
-    if (b->build)
-        while (((int64_t)1 << gbits) < (int64_t)n) ++gbits;
+    while (((int64_t)1 << gbits) < (int64_t)n) ++gbits;
     for (int i = 0; i < n; ++i) {
         if (!toffs[(size_t)i]) continue;
         ebbkc_graph* g = b->graphs[(size_t)i];
-        hipLaunchKernelGGL(k_btask_fill, dim3(gridn(seeds_of(g))), dim3(256), 0, s, sizes_of(g), seeds_of(g),
-                           b->ks[(size_t)i] - 2, log_thr_of(b->ks[(size_t)i] - 2), toffs[(size_t)i], gbase[(size_t)i], (int32_t)i, gbits, tasks,
-                           tg, keys, vals);
+        hipLaunchKernelGGL(k_btask_fill, dim3(gridn(g->m)), dim3(256), 0, s, g->subsize, g->m, b->ks[(size_t)i] - 2,
+                           toffs[(size_t)i], gbase[(size_t)i], (int32_t)i, gbits, tasks, tg, keys, vals);
     }
     CHKB(radix_sort_u64(keys, vals, keys2, vals2, total, 11 + gbits, hist, htmp, s));
-    CHKB(dev_alloc(b, (void**)&b->tasks, sizeof(int64_t) * total, s));
-    CHKB(dev_alloc(b, (void**)&b->tgraph, sizeof(int32_t) * total, s));
+    if (ebbkc_status st = alloc_tasks(b, total, 0, s)) return st;
     hipLaunchKernelGGL(k_bgather, dim3(gridn(total)), dim3(256), 0, s, tasks, tg, vals, total, b->tasks, b->tgraph);
-    hipLaunchKernelGGL(k_bclass_bounds, dim3(1), dim3(64), 0, s, keys, total, gbits,
-                       light_size(std::max(1, b->kmax - 2)), b->ctr);
-    uint64_t cc[16];
+    hipLaunchKernelGGL(k_bclass_bounds, dim3(1), dim3(64), 0, s, keys, total, gbits, b->ctr);
+    uint64_t cc[8];
     CHKB(hipMemcpyAsync(cc, b->ctr, sizeof(cc), hipMemcpyDeviceToHost, s));
     CHKB(hipStreamSynchronize(s));
     for (int w = 0; w < 8; ++w) {
-        const uint64_t begin = w ? cc[w - 1] : 0;
-        b->ccount[w] = cc[w] - begin;
-        const uint64_t light = std::min(std::max(cc[8 + w], begin), cc[w]);
-        // at most sixteen single tasks per wave: past them a chunk is a small
-        // part of a wave's share whatever its tasks weigh
-        b->heavy[w] = b->build ? 0
-                               : std::min<int64_t>((int64_t)(light - begin), (int64_t)64 * 16 * b->cu_count);
+        b->ccount[w] = cc[w] - (w ? cc[w - 1] : 0);
+        b->heavy[w] = 0;
     }
     for (auto p : toffs) dev_free(b, p, s);
     void* ptrs[] = {tasks, tg, keys, keys2, vals, vals2, hist, htmp};
     for (void* p : ptrs) dev_free(b, p, s);
+    return EBBKC_OK;
+}
+
+// Build the merged, sorted task list under the batch's current options.
+ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
+    free_tasks(b);
+    if (ebbkc_status st = b->build ? build_mode_tasks(b, s) : arena_tasks(b, s)) return st;
     // frames for deep searches
-    if (b->kmax > SEARCH_DEEP_K) {
+    if (b->ntasks && b->kmax > SEARCH_DEEP_K) {
         int64_t waves = 0;
         for (int W = 1; W <= MAX_W; ++W)
-            waves = std::max(waves, search_grid_waves(W, b->build, total, b->cu_count, b->opt.blocks_per_cu));
+            waves = std::max(waves, search_grid_waves(W, b->build, b->ntasks, b->cu_count, b->opt.blocks_per_cu));
         CHKB(dev_alloc(b, &b->gframes, (size_t)waves * GLOBAL_FRAMES * search_frame_bytes(MAX_W), s));
     }
-    b->dirty = true;
     return EBBKC_OK;
 }
 
@@ -344,8 +445,8 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
 // per-graph totals and error flags to pinned host memory.
 ebbkc_status enqueue(ebbkc_batch* b, hipStream_t s) {
     const int n = (int)b->graphs.size();
-    hipLaunchKernelGGL(k_bclear, dim3(gridn(CTR_WORDS + 2 * (int64_t)n)), dim3(256), 0, s, b->ctr, (int64_t)CTR_WORDS,
-                       b->gtot, 2 * (int64_t)n);
+    hipLaunchKernelGGL(k_bclear, dim3(gridn(CTR_WORDS + 2 * (int64_t)n)), dim3(256), 0, s, b->ctr,
+                       CTR_WORDS + 2 * (int64_t)n);
     CHKB(hipGetLastError());
     int64_t off = 0;
     for (int cls = 0; cls < 2 * MAX_W; ++cls) {
@@ -386,8 +487,8 @@ ebbkc_status enqueue(ebbkc_batch* b, hipStream_t s) {
         CHKB(launch_search(W, b->build, a, b->cu_count, b->opt.blocks_per_cu, s));
         off += nt;
     }
-    CHKB(hipMemcpyAsync(b->h_tot, b->gtot, sizeof(unsigned long long) * 2 * n, hipMemcpyDeviceToHost, s));
-    CHKB(hipMemcpyAsync(b->h_ctr, b->ctr, sizeof(unsigned long long) * 16, hipMemcpyDeviceToHost, s));
+    CHKB(hipMemcpyAsync(b->h_res, b->ctr, sizeof(unsigned long long) * (CTR_WORDS + 2 * (size_t)n),
+                        hipMemcpyDeviceToHost, s));
     return EBBKC_OK;
 }
 
@@ -416,7 +517,8 @@ ebbkc_status capture(ebbkc_batch* b, hipStream_t s) {
 // or EBBKC_OK.
 ebbkc_status finish(ebbkc_batch* b, uint64_t* out, ebbkc_status* status = nullptr) {
     const int n = (int)b->graphs.size();
-    const int err = (int)b->h_ctr[6];
+    const int err = (int)b->h_res[6];
+    const unsigned long long* tot = b->h_res + CTR_WORDS;
     ebbkc_status first = EBBKC_OK;
     for (int i = 0; i < n; ++i) {
         const int k = b->ks[(size_t)i];
@@ -429,8 +531,8 @@ ebbkc_status finish(ebbkc_batch* b, uint64_t* out, ebbkc_status* status = nullpt
         else if (k == 1) v = (uint64_t)g->n;
         else if (k == 2) v = (uint64_t)g->m;
         else if (k - 2 > g->tau) v = 0;
-        else if (b->h_tot[2 * i + 1] != 0 || (err & ERR_OVERFLOW)) st = EBBKC_E_OVERFLOW;
-        else v = b->h_tot[2 * i];
+        else if (tot[2 * i + 1] != 0 || (err & ERR_OVERFLOW)) st = EBBKC_E_OVERFLOW;
+        else v = tot[2 * i];
         if (out) out[i] = st ? 0 : v;
         if (status) status[i] = st;
         if (st && !first) first = st;
@@ -492,22 +594,16 @@ void batch_destroy_impl(ebbkc_batch* b) {
     free_tasks(b);
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
-    void* ptrs[] = {b->views, b->bviews, b->gk, b->gtau, b->gtot, b->ctr, b->squeue, b->sq};
-    for (void* p : ptrs) dev_free(b, p, b->mem_stream);
-    if (b->own_host) {
-        if (b->h_tot) (void)hipHostFree(b->h_tot);
-        if (b->h_ctr) (void)hipHostFree(b->h_ctr);
-    }
+    dev_free(b, b->held, b->mem_stream);
+    if (b->own_host && b->h_res) (void)hipHostFree(b->h_res);
     delete b;
 }
 
 // Batch of n (graph, k) counts.  async_mem: device memory is stream-ordered on
-// s; h_tot / h_ctr: caller-owned pinned result buffers (2 n and 16 words), or
-// null to allocate them.  use_cache: take a cached tuning choice when opt is
-// null.
+// s; h_res: caller-owned pinned result buffer (CTR_WORDS + 2 n words), or null
+// to allocate it.  A cached tuning choice is taken when opt is null.
 ebbkc_status batch_create_impl(ebbkc_graph* const* graphs, const int32_t* ks, int32_t n, const ebbkc_options* opt,
-                               hipStream_t s, bool async_mem, unsigned long long* h_tot, unsigned long long* h_ctr,
-                               ebbkc_batch** out) {
+                               hipStream_t s, bool async_mem, unsigned long long* h_res, ebbkc_batch** out) {
     ebbkc_batch* b = new ebbkc_batch();
     b->async_mem = async_mem;
     b->mem_stream = s;
@@ -520,8 +616,6 @@ ebbkc_status batch_create_impl(ebbkc_graph* const* graphs, const int32_t* ks, in
         delete b;
         return EBBKC_E_HIP;
     }
-    std::vector<ArenaView> views((size_t)n);
-    std::vector<BuildGraph> bviews((size_t)n);
     bool all_arenas = true;
     for (int i = 0; i < n; ++i) {
         ebbkc_graph* g = graphs[i];
@@ -570,9 +664,6 @@ ebbkc_status batch_create_impl(ebbkc_graph* const* graphs, const int32_t* ks, in
                 if (st) { delete b; return st; }
             }
         }
-        views[(size_t)i] = ArenaView{g->seed_eid, g->seed_c, g->row_off, g->vtx_off, g->arows, g->agid, g->acol};
-        bviews[(size_t)i] = BuildGraph{graph_arrays(g), g->subsize,
-                                       g->opt.ordering == EBBKC_ORDER_COLOR ? g->vcol : nullptr};
     }
     // graphs whose k exceeds tau + 2 or is below 3 contribute no task
     std::vector<int32_t> kk(b->ks);
@@ -580,38 +671,55 @@ ebbkc_status batch_create_impl(ebbkc_graph* const* graphs, const int32_t* ks, in
         if (kk[(size_t)i] >= 3 && kk[(size_t)i] - 2 > graphs[i]->tau) kk[(size_t)i] = 0;
     b->ks = kk;
     auto fail = [&](ebbkc_status st) { batch_destroy_impl(b); return st; };
-    if (dev_alloc(b, (void**)&b->views, sizeof(ArenaView) * n, s) != hipSuccess) return fail(EBBKC_E_OOM);
-    if (b->build && dev_alloc(b, (void**)&b->bviews, sizeof(BuildGraph) * n, s) != hipSuccess) return fail(EBBKC_E_OOM);
-    if (dev_alloc(b, (void**)&b->gk, sizeof(int32_t) * n, s) != hipSuccess) return fail(EBBKC_E_OOM);
-    if (dev_alloc(b, (void**)&b->gtau, sizeof(int32_t) * n, s) != hipSuccess) return fail(EBBKC_E_OOM);
-    if (dev_alloc(b, (void**)&b->gtot, sizeof(unsigned long long) * 2 * n, s) != hipSuccess) return fail(EBBKC_E_OOM);
-    if (dev_alloc(b, (void**)&b->ctr, sizeof(unsigned long long) * CTR_WORDS, s) != hipSuccess) return fail(EBBKC_E_OOM);
-    // the split queue (a few MB) for a batch of its own (served epochs do not
-    // split nodes at run time)
+    // one allocation: the per-graph arrays, uploaded as one image, then the
+    // counters, the totals and the split queue (a few MB, for a batch of its
+    // own: served epochs do not split nodes at run time)
+    const size_t N = (size_t)n;
+    const size_t at_bviews = slab_round(sizeof(ArenaView) * N);
+    const size_t at_gk = at_bviews + (b->build ? slab_round(sizeof(BuildGraph) * N) : 0);
+    const size_t at_gtau = at_gk + slab_round(sizeof(int32_t) * N);
+    const size_t at_ctr = at_gtau + slab_round(sizeof(int32_t) * N);
+    const size_t at_sq = at_ctr + slab_round(sizeof(unsigned long long) * (CTR_WORDS + 2 * N));
+    const size_t at_queue = at_sq + slab_round(sizeof(unsigned long long) * SQ_WORDS);
+    const size_t bytes = async_mem ? at_sq : at_queue + sizeof(SplitItem) * SQ_CAP;
+    if (dev_alloc(b, (void**)&b->held, bytes, s) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(EBBKC_E_OOM);
+    }
+    b->views = (ArenaView*)b->held;
+    if (b->build) b->bviews = (BuildGraph*)(b->held + at_bviews);
+    b->gk = (int32_t*)(b->held + at_gk);
+    b->gtau = (int32_t*)(b->held + at_gtau);
+    b->ctr = (unsigned long long*)(b->held + at_ctr);
+    b->gtot = b->ctr + CTR_WORDS;
     if (!async_mem) {
-        if (dev_alloc(b, (void**)&b->squeue, sizeof(SplitItem) * SQ_CAP, s) != hipSuccess ||
-            dev_alloc(b, (void**)&b->sq, sizeof(unsigned long long) * SQ_WORDS, s) != hipSuccess)
-            return fail(EBBKC_E_OOM);
+        b->sq = (unsigned long long*)(b->held + at_sq);
+        b->squeue = (SplitItem*)(b->held + at_queue);
     }
-    if (h_tot && h_ctr) {
+    if (h_res) {
         b->own_host = false;
-        b->h_tot = h_tot;
-        b->h_ctr = h_ctr;
-    } else {
-        if (hipHostMalloc((void**)&b->h_tot, sizeof(unsigned long long) * 2 * n, hipHostMallocDefault) != hipSuccess)
-            return fail(EBBKC_E_OOM);
-        if (hipHostMalloc((void**)&b->h_ctr, sizeof(unsigned long long) * 16, hipHostMallocDefault) != hipSuccess)
-            return fail(EBBKC_E_OOM);
+        b->h_res = h_res;
+    } else if (hipHostMalloc((void**)&b->h_res, sizeof(unsigned long long) * (CTR_WORDS + 2 * N),
+                             hipHostMallocDefault) != hipSuccess) {
+        return fail(EBBKC_E_OOM);
     }
-    std::vector<int32_t> taus((size_t)n);
-    for (int i = 0; i < n; ++i) taus[(size_t)i] = graphs[i]->tau;
-    if ((b->build && hipMemcpyAsync(b->bviews, bviews.data(), sizeof(BuildGraph) * n, hipMemcpyHostToDevice, s) !=
-                         hipSuccess) ||
-        hipMemcpyAsync(b->views, views.data(), sizeof(ArenaView) * n, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(b->gk, b->ks.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(b->gtau, taus.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s) != hipSuccess)
+    std::vector<char> image(at_ctr, 0);
+    for (size_t i = 0; i < N; ++i) {
+        const ebbkc_graph* g = graphs[i];
+        const ArenaView av{g->seed_eid, g->seed_c, g->row_off, g->vtx_off, g->arows, g->agid, g->acol};
+        memcpy(image.data() + sizeof(av) * i, &av, sizeof(av));
+        if (b->build) {
+            const BuildGraph bv{graph_arrays(g), g->subsize, g->opt.ordering == EBBKC_ORDER_COLOR ? g->vcol : nullptr};
+            memcpy(image.data() + at_bviews + sizeof(bv) * i, &bv, sizeof(bv));
+        }
+        memcpy(image.data() + at_gk + sizeof(int32_t) * i, &b->ks[i], sizeof(int32_t));
+        memcpy(image.data() + at_gtau + sizeof(int32_t) * i, &g->tau, sizeof(int32_t));
+    }
+    if (hipMemcpyAsync(b->held, image.data(), at_ctr, hipMemcpyHostToDevice, s) != hipSuccess) return fail(EBBKC_E_HIP);
+    if (ensure_tables(b->device, s) != hipSuccess) {
+        (void)hipStreamSynchronize(s);
         return fail(EBBKC_E_HIP);
-    if (ensure_tables(b->device, s) != hipSuccess) return fail(EBBKC_E_HIP);
+    }
     if (!async_mem) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         if (g_tune_cache.empty()) load_cache_file();
@@ -623,6 +731,8 @@ ebbkc_status batch_create_impl(ebbkc_graph* const* graphs, const int32_t* ks, in
         }
     }
     ebbkc_status st = build_tasks(b, s);
+    // the image must have been read before it goes
+    if (hipStreamSynchronize(s) != hipSuccess && !st) st = EBBKC_E_HIP;
     if (st) return fail(st);
     *out = b;
     return EBBKC_OK;
@@ -638,22 +748,26 @@ extern "C" {
 ebbkc_status ebbkc_batch_create(ebbkc_graph* const* graphs, const int32_t* ks, int32_t n, const ebbkc_options* opt,
                                 void* stream, ebbkc_batch** out) {
     if (!graphs || !ks || n <= 0 || !out) return EBBKC_E_INVALID_ARG;
-    return batch_create_impl(graphs, ks, n, opt, (hipStream_t)stream, false, nullptr, nullptr, out);
+    return batch_create_impl(graphs, ks, n, opt, (hipStream_t)stream, false, nullptr, out);
 }
 
 ebbkc_status ebbkc_batch_run(ebbkc_batch* b, int32_t use_graph, uint64_t* out_counts, void* stream) {
     if (!b) return EBBKC_E_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     auto t0 = std::chrono::steady_clock::now();
-    if (use_graph) {
-        if (b->dirty || !b->exec) {
-            ebbkc_status st = capture(b, s);
-            if (st) return st;
-        }
+    // captured once a sequence is run for the second time: capturing and
+    // instantiating it takes several times the host time of its launches, so a
+    // batch run once goes without
+    if (use_graph && b->ran && (b->dirty || !b->exec)) {
+        ebbkc_status st = capture(b, s);
+        if (st) return st;
+    }
+    if (use_graph && !b->dirty && b->exec) {
         CHKB(hipGraphLaunch(b->exec, s));
     } else {
         ebbkc_status st = enqueue(b, s);
         if (st) return st;
+        b->ran = true;
     }
     CHKB(hipStreamSynchronize(s));
     b->last_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -760,8 +874,7 @@ struct ebbkc_server {
         ebbkc_batch* batch = nullptr;
         std::vector<ebbkc_result> reqs;
         int64_t bytes = 0;
-        unsigned long long* h_tot = nullptr;  // pinned, 2 * SLOT_REQUESTS
-        unsigned long long* h_ctr = nullptr;  // pinned, 16
+        unsigned long long* h_res = nullptr;  // pinned, CTR_WORDS + 2 * SLOT_REQUESTS
     } slots[SLOTS];
     std::thread worker;
     std::mutex mu;
@@ -912,8 +1025,8 @@ void serve_loop(ebbkc_server* S) {
             ebbkc_options o = S->opt;
             o.blocks_per_cu = -2;  // leave room on every CU for the epochs of the other slots
             ebbkc_batch* b = nullptr;
-            ebbkc_status st = batch_create_impl(gs.data(), ks.data(), (int32_t)gs.size(), &o, sl.stream, true, sl.h_tot,
-                                                sl.h_ctr, &b);
+            ebbkc_status st = batch_create_impl(gs.data(), ks.data(), (int32_t)gs.size(), &o, sl.stream, true, sl.h_res,
+                                                &b);
             if (!st) st = enqueue(b, sl.stream);
             if (!st && hipEventRecord(sl.done, sl.stream) != hipSuccess) st = EBBKC_E_HIP;
             if (st) {
@@ -959,8 +1072,7 @@ void server_free(ebbkc_server* S) {
         if (sl.stream) (void)hipStreamSynchronize(sl.stream);
         if (sl.done) (void)hipEventDestroy(sl.done);
         if (sl.stream) (void)hipStreamDestroy(sl.stream);
-        if (sl.h_tot) (void)hipHostFree(sl.h_tot);
-        if (sl.h_ctr) (void)hipHostFree(sl.h_ctr);
+        if (sl.h_res) (void)hipHostFree(sl.h_res);
     }
     delete S;
 }
@@ -1000,9 +1112,8 @@ ebbkc_status ebbkc_server_create(ebbkc_graph* const* graphs, int32_t n, const eb
     for (auto& sl : S->slots) {
         if (hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking) != hipSuccess ||
             hipEventCreateWithFlags(&sl.done, hipEventDisableTiming) != hipSuccess ||
-            hipHostMalloc((void**)&sl.h_tot, sizeof(unsigned long long) * 2 * SLOT_REQUESTS, hipHostMallocDefault) !=
-                hipSuccess ||
-            hipHostMalloc((void**)&sl.h_ctr, sizeof(unsigned long long) * 16, hipHostMallocDefault) != hipSuccess) {
+            hipHostMalloc((void**)&sl.h_res, sizeof(unsigned long long) * (ebb::CTR_WORDS + 2 * SLOT_REQUESTS),
+                          hipHostMallocDefault) != hipSuccess) {
             ebb::server_free(S);
             return EBBKC_E_HIP;
         }
