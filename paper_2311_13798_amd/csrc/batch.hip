@@ -264,9 +264,8 @@ ebbkc_status alloc_tasks(ebbkc_batch* b, int64_t total, size_t tail, hipStream_t
 // sorted (by launch, then by the vertices a task can still use, largest
 // first).  One kernel writes the list.  (Counting, scanning and filling each
 // graph's tasks on the device, then sorting them, was 33 us of launches and
-// copies a graph: a
-// batch of 192 small graphs took 6.3 ms, now 1.5; a served burst of 200
-// requests 6.8 ms, now 1.1.)
+// copies a graph: a batch of 192 small graphs took 6.3 ms, now
+// 1.5; a served burst of 200 requests 6.8 ms, now 1.1.)
 ebbkc_status arena_tasks(ebbkc_batch* b, hipStream_t s) {
     struct Range {
         int x0, x1, key;

@@ -1,0 +1,73 @@
+"""Per-seed counts of listed edges are looked up and sorted on the device: against counts of single
+ranks and whole counts, over all width classes, repeated and unordered ids, list lengths at the edges
+of the sort tiles, more ids than one pass takes, and host and device arrays."""
+import math
+
+import numpy as np
+import pytest
+
+import graphgen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ebb():
+    import torch
+    import paper_2311_13798_amd as m
+    torch.cuda.set_device(0)
+    return m
+
+
+def query(ebb, G, k, eids):
+    out = np.full(len(eids), 77, np.uint64)
+    ebb.ebbkc_count_seeds(G.handle, k, np.ascontiguousarray(eids, np.int64), out)
+    return out
+
+
+@pytest.mark.parametrize("name", ["k67", "k131", "k195", "k258", "er", "path"])
+def test_all_edges_then_some(ebb, name):
+    g = {"er": lambda: graphgen.er_planted(300, 0.1, 1, 30, 30, 4), "path": lambda: graphgen.er_planted(50, 0.03, 0, 2, 2, 1)}.get(
+        name, lambda: graphgen.complete(int(name[1:])))()
+    G = ebb.Graph.from_csr(g)
+    m = G.info.m
+    rank = np.zeros(m, np.int32)
+    ebb.ebbkc_export(G.handle, ebb.ARR_RANK, rank)
+    rng = np.random.default_rng(5)
+    for k in (3, 4, 5, 8):
+        print(f"case {name} k={k}", flush=True)
+        if name.startswith("k") and math.comb(int(name[1:]), k) >= 2**64:
+            continue
+        perm = rng.permutation(m)
+        full = query(ebb, G, k, perm)
+        assert int(full.sum()) == G.count(k), k
+        by_edge = np.zeros(m, np.uint64)
+        by_edge[perm] = full
+        for e in rng.choice(m, min(m, 25), replace=False):
+            r = int(rank[e])
+            assert int(by_edge[e]) == G.count_range(k, r, r + 1), (k, e)
+        for n in (1, 2, 255, 1023, 1024, 1025, 4097):
+            e = rng.integers(0, m, n)
+            assert np.array_equal(query(ebb, G, k, e), by_edge[e]), (k, n)
+    G.close()
+
+
+def test_refused_ids_and_long_lists(ebb):
+    import torch
+    g = graphgen.er_planted(120, 0.2, 1, 12, 12, 9)
+    G = ebb.Graph.from_csr(g)
+    m = G.info.m
+    by_edge = query(ebb, G, 5, np.arange(m))
+    for bad in (-1, m, 1 << 40):
+        out = np.full(3, 77, np.uint64)
+        with pytest.raises(Exception):
+            ebb.ebbkc_count_seeds(G.handle, 5, np.array([0, bad, 1], np.int64), out)
+        assert (out == 77).all()
+    n = (1 << 22) + 3  # one pass takes 2^22 ids
+    e = np.arange(n, dtype=np.int64) % m
+    assert np.array_equal(query(ebb, G, 5, e), by_edge[e])
+    d = torch.arange(m, device="cuda", dtype=torch.int64).flip(0)
+    o = torch.zeros(m, device="cuda", dtype=torch.int64)
+    ebb.ebbkc_count_seeds(G.handle, 5, d, o)
+    assert np.array_equal(o.cpu().numpy().view(np.uint64), by_edge[::-1])
+    G.close()
