@@ -158,16 +158,39 @@ __device__ __forceinline__ void later_edges(const GraphView& G, const int32_t (&
 // pairs (or row entries) a lane tests per round of the build
 constexpr int BUILD_PB = 4;
 
-// number of entries of row x (rank-sorted, descending) ranked after r
-__device__ __forceinline__ int prefix_after(const int32_t* __restrict__ rp, const int2* __restrict__ rrow, int32_t x,
-                                            int32_t r) {
-    int lo = rp[x], hi = rp[x + 1];
-    const int base = lo;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (rrow[mid].y > r) lo = mid + 1; else hi = mid;
+// Numbers of entries of rows u and v (rank-sorted, descending) ranked after r,
+// found by the whole wave: a step loads the last entry of each 64th of what is
+// left of either row, so a row of up to 4,096 entries takes two dependent
+// loads and the rows are searched side by side (two binary searches one after
+// the other, about 18 dependent loads of up to 1 us for rows of 500, were a
+// third of a task).
+__device__ __forceinline__ void wave_prefixes(const int32_t* __restrict__ rp, const int2* __restrict__ rrow, int32_t u,
+                                              int32_t v, int32_t r, int& lu, int& lv) {
+    const int lane = lane_id();
+    const int bu = uniform_i32(rp[u]), bv = uniform_i32(rp[v]);
+    int pu = 0, pv = 0;  // entries known to rank after r; the first n* of the others are undecided
+    int nu = uniform_i32(rp[u + 1]) - bu, nv = uniform_i32(rp[v + 1]) - bv;
+    while (nu > 0 || nv > 0) {
+        const int su = (nu + 63) >> 6, sv = (nv + 63) >> 6;  // entries a lane stands for
+        const bool au = lane * su < nu, av = lane * sv < nv;
+        int yu = r, yv = r;
+        if (au) yu = rrow[bu + pu + min(lane * su + su, nu) - 1].y;
+        if (av) yv = rrow[bv + pv + min(lane * sv + sv, nv) - 1].y;
+        if (nu > 0) {
+            const int full = popc64(ballot(au && yu > r));  // 64ths that are prefix to their last entry
+            const int done = min(full * su, nu);
+            pu += done;
+            nu = min(su, nu - done) - 1;  // the next one's last entry is not
+        }
+        if (nv > 0) {
+            const int full = popc64(ballot(av && yv > r));
+            const int done = min(full * sv, nv);
+            pv += done;
+            nv = min(sv, nv - done) - 1;
+        }
     }
-    return lo - base;
+    lu = pu;
+    lv = pv;
 }
 
 // Edges of g_i by streaming the members' degree-oriented rows: rows[j] |= bit
@@ -262,16 +285,26 @@ __device__ __forceinline__ void scan_edges(const GraphView& G, int32_t r, int c,
         }
 }
 
+// Whether a sub-branch of c vertices and twoE / 2 edges goes without colours:
+// `plain` says which may (for a search that does not branch, colours only
+// bound its leaves' counts, which sparse sub-branches are cheap to make
+// without).
+enum : int { PLAIN_NEVER = 0, PLAIN_SPARSE = 1, PLAIN_ALWAYS = 2 };
+__device__ __forceinline__ bool plain_build(int plain, int c, uint32_t twoE) {
+    return plain == PLAIN_ALWAYS || (plain == PLAIN_SPARSE && 2 * twoE < (uint32_t)c * (uint32_t)c);
+}
+
 // Steps 1-3 for the seed (u, v) of rank r (a vertex slot passes u = v and the
 // rank threshold of its out-edges): candidates into S.gid -- those given (the
 // c = expect members in any order), else found --, their symmetric adjacency
 // bitmap into rows (candidate order), colours into col.  Returns c = |V(g_i)|
 // (uniform), or -1 when c exceeds 64 W or differs from expect (expect < 0: not
-// checked); *twoE = 2 |E(g_i)|.
+// checked); *twoE = 2 |E(g_i)|.  Without step 3 where plain_build holds.
 template <int W>
 __device__ int build_subbranch(const GraphView& G, int32_t u, int32_t v, int32_t r, int expect,
                                const int32_t* __restrict__ given, const int32_t* __restrict__ vcol,
-                               uint64_t (*rows)[W], int16_t* col, const BuildScratch<W>& S, uint32_t* twoE) {
+                               uint64_t (*rows)[W], int16_t* col, const BuildScratch<W>& S, uint32_t* twoE,
+                               int plain = PLAIN_NEVER) {
     const int lane = lane_id();
     constexpr int CAP = 64 * W;
 
@@ -282,7 +315,8 @@ __device__ int build_subbranch(const GraphView& G, int32_t u, int32_t v, int32_t
         if (c > CAP) return -1;
         for (int i = lane; i < c; i += 64) S.gid[i] = given[i];
     } else {
-    const int lu = prefix_after(G.rp, G.rrow, u, r), lv = prefix_after(G.rp, G.rrow, v, r);
+    int lu, lv;
+    wave_prefixes(G.rp, G.rrow, u, v, r, lu, lv);
     const int32_t xs = lu <= lv ? u : v, ys = lu <= lv ? v : u;
     const int lx = lu <= lv ? lu : lv;
     const int32_t xrow = G.rp[xs];
@@ -316,26 +350,47 @@ __device__ int build_subbranch(const GraphView& G, int32_t u, int32_t v, int32_t
 #pragma unroll
         for (int w = 0; w < W; ++w) rows[i][w] = 0;
     if (G.adj) {
+        for (int i = lane; i < c; i += 64) S.key[i] = G.rp[S.gid[i]];
         wave_sync();
+        // the pairs (i, j), i < j, two rows folded to c pairs: fold a holds row a
+        // (c - 1 - a pairs), then row c - 2 - a (a + 1 pairs), so an index needs
+        // no root and the lanes of a step read few rows of the bitmap (ten
+        // graphs of up to 5,000 vertices, every task building: 43 ms; 49 with the
+        // row found from a square root, 56 with 64 different rows a step)
         const int U = c * (c - 1) / 2;
+        const float inv = 1.0f / (float)c;
         for (int u0 = 0; u0 < U; u0 += 64 * BUILD_PB) {
             int pi[BUILD_PB], pj[BUILD_PB];
-            int32_t xa[BUILD_PB], wb[BUILD_PB];
-            bool val[BUILD_PB], okv[BUILD_PB];
+            uint64_t word[BUILD_PB], bit[BUILD_PB];
+            int32_t pos[BUILD_PB];
 #pragma unroll
             for (int t = 0; t < BUILD_PB; ++t) {
                 const int u = u0 + 64 * t + lane;
-                val[t] = u < U;
-                pi[t] = 0;
-                pj[t] = 0;
-                if (val[t]) upper_pair(u, c, pi[t], pj[t]);
-                xa[t] = val[t] ? S.gid[pi[t]] : 0;
-                wb[t] = val[t] ? S.gid[pj[t]] : 0;
+                const int fold = (int)(((float)u + 0.5f) * inv);  // u / c: exact below 2^16
+                const int b = u - fold * c;
+                const bool first = b < c - 1 - fold;
+                pi[t] = first ? fold : c - 2 - fold;
+                pj[t] = first ? fold + 1 + b : b;
+                word[t] = 0;
+                bit[t] = 0;
+                pos[t] = 0;
+                if (u < U) {
+                    const int32_t w = S.gid[pj[t]];
+                    const int64_t o = (int64_t)S.gid[pi[t]] * G.adjw + (w >> 6);
+                    word[t] = G.adj[o];
+                    pos[t] = S.key[pi[t]] + (int32_t)G.acum[o];
+                    bit[t] = 1ull << (w & 63);
+                }
             }
-            later_edges<BUILD_PB>(G, xa, wb, val, r, okv);
 #pragma unroll
             for (int t = 0; t < BUILD_PB; ++t) {
-                if (okv[t]) {
+                int32_t rk = -1;
+                if (word[t] & bit[t]) rk = G.erank[pos[t] + popc64(word[t] & (bit[t] - 1))];
+                pos[t] = rk;
+            }
+#pragma unroll
+            for (int t = 0; t < BUILD_PB; ++t) {
+                if (pos[t] > r) {
                     atomicOr((unsigned long long*)&rows[pi[t]][pj[t] >> 6], 1ull << (pj[t] & 63));
                     atomicOr((unsigned long long*)&rows[pj[t]][pi[t] >> 6], 1ull << (pi[t] & 63));
                 }
@@ -363,6 +418,7 @@ __device__ int build_subbranch(const GraphView& G, int32_t u, int32_t v, int32_t
     }
     *twoE = wave_sum(dsum);
     wave_sync();
+    if (plain_build(plain, c, *twoE)) return c;
     if (vcol) {
         // ---- 3'. G's colouring kept (EBBkC-C): the colours present are
         // renumbered 1..D in their order, which changes neither the order

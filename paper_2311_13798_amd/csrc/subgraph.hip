@@ -28,7 +28,8 @@ __global__ void k_subsize(GraphView G, int64_t m, int32_t* __restrict__ out) {
     int64_t nw = (int64_t)gridDim.x * blockDim.x / 64;
     for (int64_t e = wid; e < m; e += nw) {
         const int32_t u = G.eu[e], v = G.ev[e], r = G.rank[e];
-        const int lu = prefix_after(G.rp, G.rrow, u, r), lv = prefix_after(G.rp, G.rrow, v, r);
+        int lu, lv;
+        wave_prefixes(G.rp, G.rrow, u, v, r, lu, lv);
         const int32_t xs = lu <= lv ? u : v, ys = lu <= lv ? v : u;
         const int lx = lu <= lv ? lu : lv;
         int c = 0;

@@ -43,3 +43,21 @@ def test_cliques_of_cliques(cliques, split, build):
     for rep, use_graph in enumerate((True, True, False, True)):
         assert B.run(use_graph=use_graph) == want, rep
     B.close()
+
+
+@pytest.mark.parametrize("p", [0.03, 0.3, 0.7])
+def test_built_sub_branches_of_every_density(cliques, p):
+    # tasks that build: with and without colours (a search that does not branch colours the dense
+    # ones), edges alone at k = 4, rows of G up to and beyond the 64 entries of one search step
+    ebb, _, _ = cliques
+    n = 180 if p < 0.7 else 90
+    graphs = [ebb.Graph.from_csr(graphgen.er_planted(n + d, p, 1, 20, 20, 11 + d)) for d in range(3)]
+    ks = [3, 4, 5, 6, 7, 8]
+    o = ebb.ebbkc_default_options()
+    o.batch_build = ebb.BATCH_BUILD
+    print(f"case p={p}", flush=True)
+    B = ebb.Batch([g for g in graphs for _ in ks], ks * 3, options=o)
+    assert B.run() == [g.count(k) for g in graphs for k in ks]
+    B.close()
+    for g in graphs:
+        g.close()
