@@ -107,6 +107,8 @@ struct ebbkc_graph {
     uint64_t* nedges = nullptr;
     int64_t arena_bytes = 0;
     std::vector<int32_t> seed_rank_host; // rank of each slot (ascending; filled on demand)
+    std::vector<int32_t> seed_c_host;    // |V(g_i)| of each slot (filled on demand)
+    std::vector<int32_t> rank_host;      // rank of each edge (filled on demand)
 
     // per-call scratch (grown on demand, freed by destroy)
     void* scratch = nullptr;

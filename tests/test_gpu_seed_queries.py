@@ -1,4 +1,4 @@
-"""Per-seed counts of listed edges are looked up and sorted on the device: against counts of single
+"""Per-seed counts of more than 1,024 listed edges are looked up and sorted on the device: against counts of single
 ranks and whole counts, over all width classes, repeated and unordered ids, list lengths at the edges
 of the sort tiles, more ids than one pass takes, and host and device arrays."""
 import math
@@ -59,10 +59,13 @@ def test_refused_ids_and_long_lists(ebb):
     m = G.info.m
     by_edge = query(ebb, G, 5, np.arange(m))
     for bad in (-1, m, 1 << 40):
-        out = np.full(3, 77, np.uint64)
-        with pytest.raises(Exception):
-            ebb.ebbkc_count_seeds(G.handle, 5, np.array([0, bad, 1], np.int64), out)
-        assert (out == 77).all()
+        for n in (3, 3000):  # looked up on the host, on the device
+            ids = np.arange(n, dtype=np.int64) % m
+            ids[1] = bad
+            out = np.full(n, 77, np.uint64)
+            with pytest.raises(Exception):
+                ebb.ebbkc_count_seeds(G.handle, 5, ids, out)
+            assert (out == 77).all()
     n = (1 << 22) + 3  # one pass takes 2^22 ids
     e = np.arange(n, dtype=np.int64) % m
     assert np.array_equal(query(ebb, G, 5, e), by_edge[e])
