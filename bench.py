@@ -163,7 +163,7 @@ def traffic_record(fetch_dir: str, write_dir: str, out_json: str, k: int = 9, co
     wf = COPY_BYTES / (copy_kib(write) * 1024.0)
     launches = {}
     for (name, _), fk in sorted(fetch.items(), key=lambda kv: kv[0][1]):
-        mm = re.search(r"k_search<(\d), false>", name)
+        mm = re.search(r"k_search<(\d), false(?:, true)?>", name)
         if not mm:
             continue
         wk = next((v for (n2, _), v in write.items() if n2 == name), None)

@@ -222,24 +222,26 @@ __global__ void k_vertex_out(const int32_t* __restrict__ rp, const int32_t* __re
 // Listed edges: the slot of edge eids[i] by binary search of its rank in the
 // slots' ranks (ascending), as a whole-root task, and the bin that sorts the
 // tasks by class, larger sub-branches first (sizes 64 W - 2 q and one less are
-// bin 32 (W - 1) + q; QUERY_BINS: no task).  Bound by latency: a chain of
+// bin 32 (W - 1) + q; QUERY_BINS, not counted: no task).  An id that is no edge
+// sets the top bit of bins[0] (counts stay below it).  Bound by latency: a chain of
 // about 2 log2(slots) loads per lane.
 constexpr int QUERY_BINS = 32 * MAX_W;
+constexpr unsigned int QUERY_BAD = 1u << 31;
 __global__ __launch_bounds__(256) void k_query_tasks(const int64_t* __restrict__ eids, int64_t n, int64_t m, int l0,
                                                      const int32_t* __restrict__ rank,
                                                      const int32_t* __restrict__ seed_eid,
                                                      const int32_t* __restrict__ seed_c, int64_t nseeds,
                                                      int64_t* __restrict__ tasks, uint8_t* __restrict__ key,
                                                      unsigned int* __restrict__ bins) {
-    __shared__ unsigned int h[QUERY_BINS + 1];
-    for (int i = threadIdx.x; i <= QUERY_BINS; i += blockDim.x) h[i] = 0;
+    __shared__ unsigned int h[QUERY_BINS];
+    for (int i = threadIdx.x; i < QUERY_BINS; i += blockDim.x) h[i] = 0;
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t e = eids[i];
         int b = QUERY_BINS;
         int64_t task = 0;
         if (e < 0 || e >= m) {
-            bins[QUERY_BINS + 1] = 1;  // not an edge
+            atomicOr(&bins[0], QUERY_BAD);
         } else {
             const int32_t r = rank[e];
             int64_t lo = 0, hi = nseeds;
@@ -255,10 +257,10 @@ __global__ __launch_bounds__(256) void k_query_tasks(const int64_t* __restrict__
         }
         tasks[i] = task;
         key[i] = (uint8_t)b;
-        atomicAdd(&h[b], 1u);
+        if (b < QUERY_BINS) atomicAdd(&h[b], 1u);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i <= QUERY_BINS; i += blockDim.x)
+    for (int i = threadIdx.x; i < QUERY_BINS; i += blockDim.x)
         if (h[i]) atomicAdd(&bins[i], h[i]);
 }
 
@@ -1386,8 +1388,9 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
     if (ne <= 0) return EBBKC_OK;
     // a dozen launches and one more wait against 0.1 us a seed on the host:
     // 100 and 1,000 seeds of a 20,000-vertex R-MAT graph 65 and 133 us on the
-    // host, 119 and 122 us on the device; 10,000 seeds 923 and 201
-    constexpr int64_t QUERY_FEW = 1024;
+    // host, 119 and 122 us on the device; 10,000 seeds 923 and 201 (a host
+    // lookup that finds no task saves the launches altogether: hence not 1,000)
+    constexpr int64_t QUERY_FEW = 2048;
     if (ne <= QUERY_FEW) return count_few_seeds(g, k, eids, ne, ptr_kind, out, s);
     constexpr int64_t QUERY_CHUNK = (int64_t)1 << 22;
     const bool dev = ptr_kind == EBBKC_PTR_DEVICE;
@@ -1411,7 +1414,7 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
     uint32_t* idx = cv.take<uint32_t>(nc);
     int64_t* hist = cv.take<int64_t>(hn);
     int64_t* htmp = cv.take<int64_t>(scan_tmp_elems(hn) + 64);
-    unsigned int* bins = cv.take<unsigned int>(QUERY_BINS + 2);
+    unsigned int* bins = cv.take<unsigned int>(QUERY_BINS);
     void* gframes = deep ? (void*)cv.take<char>((int64_t)fbytes) : nullptr;
     // nothing is written to out before every chunk has been counted
     std::vector<uint64_t> kept(ne > nc ? (size_t)ne : 0);
@@ -1425,23 +1428,28 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
         } else {
             CHKH(hipMemcpyAsync(de, eids + i0, sizeof(int64_t) * n, hipMemcpyHostToDevice, s));
         }
-        CHKH(hipMemsetAsync(bins, 0, sizeof(unsigned int) * (QUERY_BINS + 2), s));
+        CHKH(hipMemsetAsync(bins, 0, sizeof(unsigned int) * QUERY_BINS, s));
         hipLaunchKernelGGL(k_query_tasks, dim3(grid_for(n)), dim3(256), 0, s, de, n, g->m, l0, g->rank, g->seed_eid,
                            g->seed_c, g->nseeds, tasks, key, bins);
         CHKH(hipGetLastError());
         CHKH(bin_sort_u8(key, n, idx, hist, htmp, s));
         hipLaunchKernelGGL(k_gather_tasks, dim3(grid_for(n)), dim3(256), 0, s, tasks, idx, n, sorted);
         CHKH(hipGetLastError());
-        unsigned int hb[QUERY_BINS + 2];
-        CHKH(hipMemcpyAsync(hb, bins, sizeof(hb), hipMemcpyDeviceToHost, s));
+        static_assert(sizeof(unsigned int) * QUERY_BINS <= sizeof(uint64_t) * CNT_WORDS, "pinned mirror");
+        const unsigned int* hb = (const unsigned int*)g->h_counters;
+        CHKH(hipMemcpyAsync(g->h_counters, bins, sizeof(unsigned int) * QUERY_BINS, hipMemcpyDeviceToHost, s));
         CHKH(hipStreamSynchronize(s));
-        if (hb[QUERY_BINS + 1]) return EBBKC_E_INVALID_ARG;
+        if (hb[0] & QUERY_BAD) return EBBKC_E_INVALID_ARG;
         uint64_t ccount[4] = {0, 0, 0, 0};
         int64_t heavy[4] = {0, 0, 0, 0}, T = 0;
         for (int b = 0; b < QUERY_BINS; ++b) {
             ccount[b / 32] += hb[b];
             if (heavy_root(64 * (b / 32 + 1) - 2 * (b % 32), l0)) heavy[b / 32] += hb[b];
             T += hb[b];
+        }
+        if (T == 0 && !dev && ne <= nc) {
+            std::fill(out, out + ne, (uint64_t)0);
+            return EBBKC_OK;
         }
         if (T) {
             TaskPlan plan = TaskPlan::of_list(sorted, ccount);

@@ -1,4 +1,4 @@
-"""Per-seed counts of more than 1,024 listed edges are looked up and sorted on the device: against counts of single
+"""Per-seed counts of more than 2,048 listed edges are looked up and sorted on the device: against counts of single
 ranks and whole counts, over all width classes, repeated and unordered ids, list lengths at the edges
 of the sort tiles, more ids than one pass takes, and host and device arrays."""
 import math
@@ -46,7 +46,7 @@ def test_all_edges_then_some(ebb, name):
         for e in rng.choice(m, min(m, 25), replace=False):
             r = int(rank[e])
             assert int(by_edge[e]) == G.count_range(k, r, r + 1), (k, e)
-        for n in (1, 2, 255, 1023, 1024, 1025, 4097):
+        for n in (1, 2, 255, 2047, 2048, 2049, 4096, 4097):
             e = rng.integers(0, m, n)
             assert np.array_equal(query(ebb, G, k, e), by_edge[e]), (k, n)
     G.close()
