@@ -720,6 +720,7 @@ struct ClassTasks {
     int64_t ntasks = 0;
     const int32_t* slots = nullptr;
     int64_t nslots = 0;
+    int64_t first = 0;          // where the explicit words start in the list of all classes
     int64_t heavy = INT64_MAX;  // tasks drawn one at a time, the first ones
     int cmax = 64 * MAX_W;  // no sub-branch of the class's tasks is larger
 };
@@ -902,8 +903,8 @@ static bool heavy_root(int c, int l0) {
 // split, heaviest first, as segments over the slot order (their number is
 // returned, -1 past 2^32), and the sizes below them as whole roots, taken
 // straight from the slot order.
-static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan& plan, std::vector<TaskSeg>& segs) {
-    const SizeCounts& N = g->seed_sizes;
+static int64_t plan_whole(const SizeCounts& N, const int32_t* order, int l0, double log_thr, TaskPlan& plan,
+                          std::vector<TaskSeg>& segs) {
     int64_t T = 0, pos = 0;  // pos: first slot of the size in the slot order
     struct Range {
         int usable, first, x0, x1;
@@ -929,7 +930,7 @@ static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan
                     });
                 } else {
                     ct.cmax = std::max(ct.cmax, c);
-                    if (!ct.slots) ct.slots = g->seed_order + pos;
+                    if (!ct.slots) ct.slots = order + pos;
                     ct.nslots += nc;
                     if (heavy_root(c, l0)) ct.heavy += nc;
                 }
@@ -941,6 +942,7 @@ static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan
         ClassTasks& ct = plan.cls[w];
         std::vector<Range>& rs = ranges[w];
         std::stable_sort(rs.begin(), rs.end(), [](const Range& a, const Range& b) { return a.usable > b.usable; });
+        ct.first = T;
         for (const Range& r : rs) {
             segs.push_back(TaskSeg{T, r.first, (int16_t)r.x0, (int16_t)r.x1});
             T += r.slots;
@@ -949,6 +951,14 @@ static int64_t plan_whole(const ebbkc_graph* g, int l0, double log_thr, TaskPlan
         }
     }
     return T < ((int64_t)1 << 32) ? T : -1;
+}
+
+int64_t plan_ranges(const SizeCounts& N, int l0, double log_thr, int64_t first[MAX_W]) {
+    TaskPlan plan;
+    std::vector<TaskSeg> segs;
+    const int64_t T = plan_whole(N, nullptr, l0, log_thr, plan, segs);
+    for (int w = 0; w < MAX_W; ++w) first[w] = plan.cls[w].first;
+    return T;
 }
 
 ebbkc_status count_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end, const int64_t* d_eids, int64_t ne,
@@ -1033,7 +1043,7 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
         // counted, sorted or stored but the ranges of split roots
         TaskPlan plan;
         std::vector<TaskSeg> segs;
-        const int64_t T = plan_whole(g, l0, log_thr, plan, segs);
+        const int64_t T = plan_whole(g->seed_sizes, g->seed_order, l0, log_thr, plan, segs);
         if (T < 0) return EBBKC_E_OOM;
         const size_t sbytes = rnd256(segs.size() * sizeof(TaskSeg));
         Carve cv = carve_for(g, src, rnd256((size_t)T * 8) + sbytes + rnd256(fbytes) + qbytes + 4096);
@@ -1049,10 +1059,7 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
             hipLaunchKernelGGL(k_task_expand, dim3(grid_for(T)), dim3(256), 0, s, dseg, (int)segs.size(), T,
                                g->seed_order, tasks);
             CHKH(hipGetLastError());
-            for (int w = 0, o = 0; w < MAX_W; ++w) {
-                plan.cls[w].tasks = tasks + o;
-                o += plan.cls[w].ntasks;
-            }
+            for (ClassTasks& ct : plan.cls) ct.tasks = tasks + ct.first;
         }
         st = run_tasks(g, k, plan, nullptr, nullptr, nullptr, gframes, false, s, noalloc, squeue, sq);
         if (st) return st;
@@ -1098,7 +1105,7 @@ static bool plan_unsplit(const ebbkc_graph* g, int l0, double log_thr, TaskPlan&
     for (int c = l0; c < 64 * MAX_W; ++c)
         if (N.n[c] && root_split(c, l0, log_thr)) return false;
     std::vector<TaskSeg> none;
-    (void)plan_whole(g, l0, log_thr, plan, none);
+    (void)plan_whole(N, g->seed_order, l0, log_thr, plan, none);
     *T = 0;
     for (const ClassTasks& ct : plan.cls) *T += ct.nslots;
     return true;

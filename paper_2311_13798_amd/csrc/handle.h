@@ -142,5 +142,8 @@ hipError_t ensure_tables(int dev, hipStream_t s);
 ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, int64_t ne, int32_t ptr_kind,
                               uint64_t* out, hipStream_t s);
 void* scratch_get(ebbkc_graph* g, size_t bytes);
+// The plan of a whole count at l0 over slots of these sizes: the number of
+// root ranges (-1 past 2^32) and where each class's start in their list.
+int64_t plan_ranges(const SizeCounts& N, int l0, double log_thr, int64_t first[4]);
 ebbkc_status count_noalloc_impl(ebbkc_graph* g, int32_t k, uint64_t* out, hipStream_t s);
 }  // namespace ebb
