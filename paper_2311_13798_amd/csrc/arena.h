@@ -280,6 +280,13 @@ hipError_t search_tables(hipStream_t s);
 hipError_t launch_search(int W, bool build, const SearchArgs& a, int cus, int blocks_per_cu, hipStream_t s);
 int64_t search_grid_waves(int W, bool build, int64_t ntasks, int cus, int blocks_per_cu);
 size_t search_frame_bytes(int W);
+// Device-memory frames one buffer needs to serve the launches of all width
+// classes, each of at most ntasks tasks, one after the other: every wave of a
+// launch owns GLOBAL_FRAMES of them, found by its number, and a narrower class
+// runs more waves than the widest.  waves[W - 1]: the waves of class W's launch.
+size_t frames_for_waves(const int64_t waves[MAX_W]);
+// (0 when the device cannot say how many waves it runs)
+size_t search_frames_bytes(bool build, int64_t ntasks, int cus, int blocks_per_cu);
 hipError_t launch_binom_init(hipStream_t s);
 hipError_t launch_sq_reset(unsigned long long* sq, SplitItem* items, hipStream_t s);
 float k4_weight_of(int32_t dense_k4);

@@ -432,10 +432,9 @@ ebbkc_status build_tasks(ebbkc_batch* b, hipStream_t s) {
     if (ebbkc_status st = b->build ? build_mode_tasks(b, s) : arena_tasks(b, s)) return st;
     // frames for deep searches
     if (b->ntasks && b->kmax > SEARCH_DEEP_K) {
-        int64_t waves = 0;
-        for (int W = 1; W <= MAX_W; ++W)
-            waves = std::max(waves, search_grid_waves(W, b->build, b->ntasks, b->cu_count, b->opt.blocks_per_cu));
-        CHKB(dev_alloc(b, &b->gframes, (size_t)waves * GLOBAL_FRAMES * search_frame_bytes(MAX_W), s));
+        const size_t bytes = search_frames_bytes(b->build, b->ntasks, b->cu_count, b->opt.blocks_per_cu);
+        if (!bytes) return EBBKC_E_HIP;
+        CHKB(dev_alloc(b, &b->gframes, bytes, s));
     }
     return EBBKC_OK;
 }

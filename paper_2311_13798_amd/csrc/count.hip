@@ -1033,10 +1033,8 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     // ---- tasks (the scratch is sized for the worst case: every slot split)
     const int64_t Tmax = n * (int64_t)(64 * MAX_W);
     const bool deep = k > SEARCH_DEEP_K;
-    int64_t waves_max = 0;
-    for (int W = 1; W <= MAX_W && deep; ++W)
-        waves_max = std::max(waves_max, search_grid_waves(W, false, Tmax, g->cu_count, g->opt.blocks_per_cu));
-    const size_t fbytes = deep ? (size_t)waves_max * GLOBAL_FRAMES * search_frame_bytes(MAX_W) : 0;
+    const size_t fbytes = deep ? search_frames_bytes(false, Tmax, g->cu_count, g->opt.blocks_per_cu) : 0;
+    if (deep && !fbytes) return EBBKC_E_HIP;
     const size_t qbytes = rnd256((size_t)SQ_CAP * sizeof(SplitItem)) + rnd256(SQ_WORDS * sizeof(uint64_t));
     if (whole && !noalloc && g->opt.ordering != EBBKC_ORDER_TRUSS) {
         // every slot: the tasks follow from the slot order, so none is
@@ -1171,11 +1169,13 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
                 // pass 1 runs the count kernel, pass 2 the listing kernel: frames
                 // in device memory when either needs them
                 const bool deep = k > std::min(SEARCH_DEEP_K, LIST_DEEP_K);
-                const int64_t waves = list_grid_waves(MAX_W, T, g->cu_count);
-                const int64_t wsearch = search_grid_waves(MAX_W, false, T, g->cu_count, g->opt.blocks_per_cu);
-                const size_t fbytes = deep ? (size_t)std::max(waves, wsearch) * GLOBAL_FRAMES *
-                                                 std::max(list_frame_bytes(MAX_W), search_frame_bytes(MAX_W))
-                                           : 0;
+                size_t fbytes = 0;
+                if (deep) {
+                    fbytes = search_frames_bytes(false, T, g->cu_count, g->opt.blocks_per_cu);
+                    if (!fbytes) return EBBKC_E_HIP;
+                    fbytes = std::max(fbytes, (size_t)list_grid_waves(MAX_W, T, g->cu_count) * GLOBAL_FRAMES *
+                                                  list_frame_bytes(MAX_W));
+                }
                 const size_t need = (by_order ? 4096 : task_bytes(n, T)) + rnd256(fbytes) + 2 * rnd256((size_t)(T + 1) * 8) +
                                     rnd256((size_t)(scan_tmp_elems(T + 1) + 64) * 8);
                 if (!scratch_get(g, need)) return EBBKC_E_OOM;
@@ -1350,15 +1350,14 @@ static ebbkc_status count_few_seeds(ebbkc_graph* g, int32_t k, const int64_t* ei
     for (int W = 0; W < MAX_W; ++W) { ccount[W] = tasks[W].size(); T += (int64_t)tasks[W].size(); }
     if (T) {
         const bool deep = k > SEARCH_DEEP_K;
-        const size_t fbytes =
-            deep ? (size_t)search_grid_waves(MAX_W, false, T, g->cu_count, g->opt.blocks_per_cu) * GLOBAL_FRAMES *
-                       search_frame_bytes(MAX_W)
-                 : 0;
+        const size_t fbytes = deep ? search_frames_bytes(false, T, g->cu_count, g->opt.blocks_per_cu) : 0;
+        if (deep && !fbytes) return EBBKC_E_HIP;
         if (!scratch_get(g, rnd256(T * 8) * 2 + rnd256(fbytes) + 4096)) return EBBKC_E_OOM;
         Carve cv{(char*)g->scratch, 0, g->scratch_bytes};
         int64_t* dt = cv.take<int64_t>(T);
         uint64_t* pt = cv.take<uint64_t>(T);
         void* gframes = deep ? (void*)cv.take<char>((int64_t)fbytes) : nullptr;
+        if (!dt || !pt || (deep && !gframes)) return EBBKC_E_OOM;
         std::vector<int64_t> flat;
         flat.reserve((size_t)T);
         for (int W = 0; W < MAX_W; ++W) flat.insert(flat.end(), tasks[W].begin(), tasks[W].end());
@@ -1404,10 +1403,8 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
     const int l0 = k - 2;
     const int64_t nc = std::min(ne, QUERY_CHUNK), hn = radix_hist_elems(nc);
     const bool deep = k > SEARCH_DEEP_K;
-    const size_t fbytes =
-        deep ? (size_t)search_grid_waves(MAX_W, false, nc, g->cu_count, g->opt.blocks_per_cu) * GLOBAL_FRAMES *
-                   search_frame_bytes(MAX_W)
-             : 0;
+    const size_t fbytes = deep ? search_frames_bytes(false, nc, g->cu_count, g->opt.blocks_per_cu) : 0;
+    if (deep && !fbytes) return EBBKC_E_HIP;
     if (!scratch_get(g, rnd256(nc * 8) * 5 + rnd256(nc) + rnd256(nc * 4) + rnd256((size_t)hn * 8) +
                             rnd256((size_t)(scan_tmp_elems(hn) + 64) * 8) + rnd256(fbytes) + 4096))
         return EBBKC_E_OOM;
@@ -1423,6 +1420,8 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
     int64_t* htmp = cv.take<int64_t>(scan_tmp_elems(hn) + 64);
     unsigned int* bins = cv.take<unsigned int>(QUERY_BINS);
     void* gframes = deep ? (void*)cv.take<char>((int64_t)fbytes) : nullptr;
+    if (!de || !tasks || !sorted || !pt || !res || !key || !idx || !hist || !htmp || !bins || (deep && !gframes))
+        return EBBKC_E_OOM;
     // nothing is written to out before every chunk has been counted
     std::vector<uint64_t> kept(ne > nc ? (size_t)ne : 0);
     unsigned __int128 total = 0;

@@ -267,6 +267,21 @@ size_t search_frame_bytes(int W) {
     return 0;
 }
 
+size_t frames_for_waves(const int64_t waves[MAX_W]) {
+    int64_t most = 0;
+    for (int W = 1; W <= MAX_W; ++W) {
+        if (waves[W - 1] < 0) return 0;
+        most = waves[W - 1] > most ? waves[W - 1] : most;
+    }
+    return (size_t)most * GLOBAL_FRAMES * search_frame_bytes(MAX_W);
+}
+
+size_t search_frames_bytes(bool build, int64_t ntasks, int cus, int bpc) {
+    int64_t waves[MAX_W];
+    for (int W = 1; W <= MAX_W; ++W) waves[W - 1] = search_grid_waves(W, build, ntasks, cus, bpc);
+    return frames_for_waves(waves);
+}
+
 namespace {
 template <int W>
 hipError_t launch_truss_w(const TrussArgs& a, int cus, hipStream_t s) {

@@ -1,5 +1,5 @@
 """Host arithmetic of the launches (no GPU calls), through the library's internal functions: where each
-width class's root ranges start in one task list of up to 2^32 entries."""
+width class's root ranges start in one task list of up to 2^32 entries, and the frames of deep searches."""
 import ctypes
 import math
 import os
@@ -52,3 +52,19 @@ def test_classes_start_where_the_ones_before_end(sizes):
     if total >= 0:
         assert list(first) == [sum(want[:w]) for w in range(MAX_W)]
 
+
+
+@pytest.mark.parametrize("waves", [(4096, 4096, 3072, 2048), (2048, 2048, 2048, 2048), (4, 4, 4, 4), (1024, 8192, 1024, 512),
+                                   (512, 512, 4096, 256)])
+def test_deep_frames_serve_every_class(waves):
+    # a wave's frames start at its number times the class's frame size, whatever class is launched
+    frame = internal("_ZN3ebb18search_frame_bytesEi", ctypes.c_size_t, ctypes.c_int)
+    total = internal("_ZN3ebb16frames_for_wavesEPKl", ctypes.c_size_t, ctypes.c_void_p)((ctypes.c_int64 * MAX_W)(*waves))
+    per_wave = 124  # GLOBAL_FRAMES
+    for w in range(MAX_W):
+        assert total >= waves[w] * per_wave * frame(w + 1), w + 1
+
+
+def test_deep_frames_of_an_unknown_device():
+    f = internal("_ZN3ebb16frames_for_wavesEPKl", ctypes.c_size_t, ctypes.c_void_p)
+    assert f((ctypes.c_int64 * MAX_W)(4, -1, 4, 4)) == 0
