@@ -192,6 +192,8 @@ void ebbkc_default_options(ebbkc_options *opt);
  * level-synchronous truss ordering, ranks and the rank-tagged adjacency.
  * row_ptr: n+1 int32; col_idx: nnz int32 (nnz = 2m).  The caller keeps
  * ownership of the input arrays; they may be freed when this returns.
+ * Calls on other streams and in other processes may keep the device busy
+ * meanwhile: the call then waits for room, however long that takes.
  * opt may be NULL (defaults).  On success *out owns the handle. */
 ebbkc_status ebbkc_prepare(const int32_t *row_ptr, const int32_t *col_idx, int32_t n, int64_t nnz,
                            int32_t ptr_kind, const ebbkc_options *opt, void *stream,

@@ -131,6 +131,13 @@ struct ebbkc_graph {
 namespace ebb {
 ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t* col_idx, int32_t ptr_kind,
                           hipStream_t s);
+// The peel's launch: its workgroups wait for each other, so no more of them
+// than the device holds at once.  attempt(arg, grid) runs the whole peel with
+// `grid` workgroups and returns a status, or PEEL_AGAIN when some found no
+// room beside other launches: then again with a quarter of them, down to one.
+constexpr int PEEL_AGAIN = 1;
+int64_t peel_grid(int64_t m, int64_t resident);
+int peel_attempts(int64_t grid, int (*attempt)(void*, int64_t), void* arg);
 ebbkc_status count_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end, const int64_t* d_eids,
                         int64_t ne, uint64_t* d_per_seed, uint64_t* out, hipStream_t s);
 ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end, int32_t* d_buf, uint64_t cap,

@@ -17,6 +17,7 @@
 //   adjacency  erank (rank of each CSR entry), rows re-sorted by rank
 //              descending, and degree-oriented rows in the same order
 #include <algorithm>
+#include <atomic>
 
 #include "arena.h"
 #include "common.h"
@@ -464,7 +465,10 @@ __global__ void k_peel_assign(const int32_t* __restrict__ front, int64_t nf, int
 // arrives at the barrier.  (Release / acquire fences there instead write back
 // and drop whole caches: 14 us a barrier of 256 workgroups against 4.3 us,
 // 1.7 us with 64.)  Every wait is bounded: past PEEL_WAIT_TICKS a workgroup
-// sets the error word and returns, and so do the others.
+// sets the error word and returns, and so do the others.  That happens when
+// some of the workgroups found no room beside other launches (another
+// stream's, another process's) for that long; the peel then starts over with
+// fewer of them (peel_attempts), in the end with one, which waits for nobody.
 constexpr int PEEL_TB = 1024, PEEL_GROUP = 16;
 // 64 workgroups, 128 from 2 M edges on: more of them share a round's triangles,
 // fewer make the barrier cheaper (prepare of R-MAT s18, m = 3.8 M: 55.3 ms with
@@ -745,6 +749,22 @@ __global__ __launch_bounds__(PEEL_TB) void k_peel(PeelArgs A) {
     }
 }
 
+// Workgroups of k_peel the current device holds at once, asked for once per
+// device; 0 when it cannot say.
+int64_t peel_resident(int dev, int cus) {
+    static std::atomic<int> known[64];
+    const bool slot = dev >= 0 && dev < 64;
+    int occ = slot ? known[dev].load(std::memory_order_acquire) : 0;
+    if (occ == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_peel, PEEL_TB, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return 0;
+        }
+        if (slot) known[dev].store(occ, std::memory_order_release);
+    }
+    return (int64_t)occ * cus;
+}
+
 // frontier sizes and minima before the launch
 __global__ void k_peel_begin(PeelCtl* ctl, int32_t* __restrict__ rnd, int32_t m) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -969,6 +989,23 @@ hipError_t launch_candidates(const GraphView& G, int32_t n, unsigned long long* 
     return launch_tri<2>(T, rows_tmp, s);
 }
 
+// Workgroups of the peel of m edges on a device that holds `resident` of them
+// at once: every one of them has to run for a barrier to pass.
+int64_t peel_grid(int64_t m, int64_t resident) {
+    const int64_t chunks = (m + PEEL_TB - 1) / PEEL_TB;
+    const int64_t want = std::min<int64_t>(m >= PEEL_WIDE_M ? PEEL_GRID_WIDE : PEEL_GRID, (chunks + 1) / 2);
+    return std::max<int64_t>(1, std::min(want, resident));
+}
+
+int peel_attempts(int64_t grid, int (*attempt)(void*, int64_t), void* arg) {
+    for (;; grid /= 4) {
+        if (grid < 1) grid = 1;
+        const int st = attempt(arg, grid);
+        if (st != PEEL_AGAIN) return st;
+        if (grid == 1) return EBBKC_E_HIP;
+    }
+}
+
 #define CHK(expr)                                   \
     do {                                            \
         hipError_t e_ = (expr);                     \
@@ -1136,8 +1173,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
         CHK(front0.alloc(tmp, m));
         CHK(front1.alloc(tmp, m));
         CHK(ctl.alloc(tmp, 1));
-        const int64_t chunks = (m + PEEL_TB - 1) / PEEL_TB;
-        const int64_t grid = std::min<int64_t>(m >= PEEL_WIDE_M ? PEEL_GRID_WIDE : PEEL_GRID, (chunks + 1) / 2);
+        CHK(live.alloc(tmp, live_elems));
         PeelArgs pa{};
         pa.m = (int32_t)m;
         pa.inc_off = inc_off.p;
@@ -1148,19 +1184,38 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
         pa.subsize = subsize.p;
         pa.front[0] = front0.p;
         pa.front[1] = front1.p;
-        pa.live_chunks = (int32_t)((chunks + grid - 1) / grid);
-        if (grid * pa.live_chunks * PEEL_TB > live_elems) return EBBKC_E_HIP;
-        CHK(live.alloc(tmp, grid * pa.live_chunks * PEEL_TB));
         pa.live = live.p;
         pa.ctl = ctl.p;
-        hipLaunchKernelGGL(k_peel_begin, dim3(std::min(grid_for(m), 2048u)), dim3(TB), 0, s, ctl.p, rnd.p, (int32_t)m);
-        CHK(hipGetLastError());
-        void* args[] = {&pa};
-        CHK(hipLaunchCooperativeKernel((void*)k_peel, dim3((unsigned)grid), dim3(PEEL_TB), args, 0, s));
-        CHK(hipMemcpyAsync(g->h_counters, ctl.p, sizeof(PeelCtl), hipMemcpyDeviceToHost, s));
-        CHK(hipStreamSynchronize(s));
         const PeelCtl* hc = (const PeelCtl*)g->h_counters;
-        if (hc->err) return EBBKC_E_HIP;
+        bool fresh = true;  // the supports are those of G
+        auto attempt = [&](int64_t grid) -> int {
+            const int64_t chunks = (m + PEEL_TB - 1) / PEEL_TB;
+            pa.live_chunks = (int32_t)((chunks + grid - 1) / grid);
+            if (grid * pa.live_chunks * PEEL_TB > live_elems) return EBBKC_E_HIP;
+            if (!fresh) CHK(hipMemcpyAsync(sup.p, sup0.p, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToDevice, s));
+            fresh = false;
+            hipLaunchKernelGGL(k_peel_begin, dim3(std::min(grid_for(m), 2048u)), dim3(TB), 0, s, ctl.p, rnd.p,
+                               (int32_t)m);
+            CHK(hipGetLastError());
+            if (grid == 1) {
+                hipLaunchKernelGGL(k_peel, dim3(1), dim3(PEEL_TB), 0, s, pa);
+                CHK(hipGetLastError());
+            } else {
+                void* args[] = {&pa};
+                if (hipLaunchCooperativeKernel((void*)k_peel, dim3((unsigned)grid), dim3(PEEL_TB), args, 0, s) !=
+                    hipSuccess) {
+                    (void)hipGetLastError();
+                    return PEEL_AGAIN;
+                }
+            }
+            CHK(hipMemcpyAsync(g->h_counters, ctl.p, sizeof(PeelCtl), hipMemcpyDeviceToHost, s));
+            CHK(hipStreamSynchronize(s));
+            return hc->err ? PEEL_AGAIN : (int)EBBKC_OK;
+        };
+        const int st = peel_attempts(
+            peel_grid(m, peel_resident(g->device, g->cu_count)),
+            [](void* f, int64_t grid) { return (*static_cast<decltype(attempt)*>(f))(grid); }, &attempt);
+        if (st) return (ebbkc_status)st;
         g->tau = hc->tau;
         g->rounds = hc->rounds;
         // (the sorted ids end in byrank: an odd number of passes starts from the other buffer)

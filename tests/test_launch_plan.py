@@ -1,5 +1,6 @@
 """Host arithmetic of the launches (no GPU calls), through the library's internal functions: where each
-width class's root ranges start in one task list of up to 2^32 entries, and the frames of deep searches."""
+width class's root ranges start in one task list of up to 2^32 entries, the frames of deep searches, and the
+workgroups of the peel."""
 import ctypes
 import math
 import os
@@ -68,3 +69,29 @@ def test_deep_frames_serve_every_class(waves):
 def test_deep_frames_of_an_unknown_device():
     f = internal("_ZN3ebb16frames_for_wavesEPKl", ctypes.c_size_t, ctypes.c_void_p)
     assert f((ctypes.c_int64 * MAX_W)(4, -1, 4, 4)) == 0
+
+
+@pytest.mark.parametrize("m", [1, 1024, 1025, 100_000, (2 << 20) - 1, 2 << 20, 1 << 30])
+@pytest.mark.parametrize("resident", [0, 1, 20, 38, 64, 100, 128, 256])
+def test_the_peel_fits_the_device(m, resident):
+    # its workgroups wait for each other: no more than run side by side
+    grid = internal("_ZN3ebb9peel_gridEll", ctypes.c_int64, ctypes.c_int64, ctypes.c_int64)(m, resident)
+    assert 1 <= grid <= max(1, resident)
+    assert grid == max(1, min(resident, 128 if m >= 2 << 20 else 64, ((m + 1023) // 1024 + 1) // 2))
+
+
+@pytest.mark.parametrize("grid,room,tried", [(128, 128, [128]), (128, 100, [128, 32]), (64, 5, [64, 16, 4]),
+                                             (64, 1, [64, 16, 4, 1]), (3, 1, [3, 1]), (2, 1, [2, 1]), (1, 1, [1])])
+def test_a_peel_without_room_starts_over_with_fewer(grid, room, tried):
+    CB = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_int64)
+    f = internal("_ZN3ebb13peel_attemptsElPFiPvlES0_", ctypes.c_int, ctypes.c_int64, CB, ctypes.c_void_p)
+    seen = []
+
+    def attempt(_, g):
+        seen.append(g)
+        return 0 if g <= room else 1
+
+    assert f(grid, CB(attempt), None) == 0 and seen == tried
+    # an error is final, and so is one workgroup that gives up
+    assert f(grid, CB(lambda _, g: ebb.E_OOM), None) == ebb.E_OOM
+    assert f(grid, CB(lambda _, g: 1), None) == ebb.E_HIP
