@@ -533,8 +533,8 @@ __device__ bool peel_barrier(PeelMem& M, PeelCtl* ctl, uint32_t gen) {
         const uint32_t target = gen * gridDim.x;
         const uint64_t t0 = wall_clock64();
         int ok = 1;
-        __hip_atomic_fetch_add(&ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (uint32_t spin = 0; (int32_t)(dev_load(&ctl->arrived) - target) < 0; ++spin) {
+        if (gridDim.x > 1) __hip_atomic_fetch_add(&ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (uint32_t spin = 0; gridDim.x > 1 && (int32_t)(dev_load(&ctl->arrived) - target) < 0; ++spin) {
             if (dev_load(&ctl->err) || wall_clock64() - t0 > PEEL_WAIT_TICKS || spin > PEEL_WAIT_SPINS) {
                 dev_store(&ctl->err, 1);
                 ok = 0;
