@@ -223,12 +223,12 @@ __device__ __forceinline__ void scan_edges(const GraphView& G, int32_t r, int c,
         while (more) {
             int y[W];
 #pragma unroll
-            for (int q = 0; q < W; ++q) y[q] = lo[q] < hi[q] ? G.orow[(lo[q] + hi[q]) >> 1].y : 0;
+            for (int q = 0; q < W; ++q) y[q] = lo[q] < hi[q] ? G.orow[midpoint(lo[q], hi[q])].y : 0;
             more = false;
 #pragma unroll
             for (int q = 0; q < W; ++q) {
                 if (lo[q] < hi[q]) {
-                    const int mid = (lo[q] + hi[q]) >> 1;
+                    const int mid = midpoint(lo[q], hi[q]);
                     if (y[q] > r) lo[q] = mid + 1; else hi[q] = mid;
                 }
                 more |= lo[q] < hi[q];

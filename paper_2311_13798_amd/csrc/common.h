@@ -82,10 +82,13 @@ constexpr unsigned SUM_GRID = 512;  // workgroups of a pass that ends in block_a
 
 __device__ __forceinline__ int uniform_i32(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// of two indices from 0 on (their sum may pass 2^31)
+__device__ __forceinline__ int midpoint(int lo, int hi) { return (int)(((unsigned)lo + (unsigned)hi) >> 1); }
+
 // first index in sorted a[lo,hi) with a[i] >= key
 __device__ __forceinline__ int lower_bound_i32(const int32_t* __restrict__ a, int lo, int hi, int32_t key) {
     while (lo < hi) {
-        int mid = (lo + hi) >> 1;
+        const int mid = midpoint(lo, hi);
         if (a[mid] < key) lo = mid + 1; else hi = mid;
     }
     return lo;

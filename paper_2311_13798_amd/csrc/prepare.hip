@@ -42,18 +42,18 @@ inline unsigned grid_for(int64_t n, int per = TB) {
 __device__ __forceinline__ int32_t row_of(const int32_t* __restrict__ rp, int32_t n, int64_t p) {
     int lo = 0, hi = n;  // find largest u with rp[u] <= p
     while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
+        const int mid = midpoint(lo, hi);
         if ((int64_t)rp[mid] <= p) lo = mid; else hi = mid;
     }
     return lo;
 }
 
 __global__ void k_validate_rows(const int32_t* __restrict__ rp, int32_t n, int64_t nnz, int* __restrict__ err) {
-    int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u > n) return;
-    if (u == 0 && rp[0] != 0) atomicOr(err, 1);
-    if (u == n && (int64_t)rp[n] != nnz) atomicOr(err, 2);
-    if (u < n && rp[u + 1] < rp[u]) atomicOr(err, 4);
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u <= n; u += (int64_t)gridDim.x * blockDim.x) {
+        if (u == 0 && rp[0] != 0) atomicOr(err, 1);
+        if (u == n && (int64_t)rp[n] != nnz) atomicOr(err, 2);
+        if (u < n && rp[u + 1] < rp[u]) atomicOr(err, 4);
+    }
 }
 
 // Runs after k_validate_rows on the same stream and reads nothing through row
@@ -74,12 +74,12 @@ __global__ void k_validate_entries(const int32_t* __restrict__ rp, const int32_t
 // ustart[u] = first entry of row u with neighbour > u; ucnt[u] = entries after it; degree max
 __global__ void k_ustart(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci, int32_t n,
                          int32_t* __restrict__ ustart, int32_t* __restrict__ ucnt, int* __restrict__ dmax) {
-    int32_t u = blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= n) return;
-    int q = lower_bound_i32(ci, rp[u], rp[u + 1], u + 1);
-    ustart[u] = q;
-    ucnt[u] = rp[u + 1] - q;
-    atomicMax(dmax, rp[u + 1] - rp[u]);
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x) {
+        int q = lower_bound_i32(ci, rp[u], rp[u + 1], (int32_t)u + 1);
+        ustart[u] = q;
+        ucnt[u] = rp[u + 1] - q;
+        atomicMax(dmax, rp[u + 1] - rp[u]);
+    }
 }
 
 __global__ void k_edge_ids(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci, int32_t n, int64_t nnz,
@@ -255,8 +255,8 @@ __device__ __forceinline__ void tri_stream(const TriArgs& T, int a, int a0, int 
 // hold the listed rows' numbers, then list + 2 the short ones and list + 2 + n
 // the long ones.
 __global__ void k_tri_rows(const int32_t* __restrict__ orp, int32_t n, int32_t* __restrict__ list) {
-    for (int32_t base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
-        const int32_t a = base + threadIdx.x;
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t a = base + threadIdx.x;
         const int d = a < n ? orp[a + 1] - orp[a] : 0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -266,7 +266,7 @@ __global__ void k_tri_rows(const int32_t* __restrict__ orp, int32_t n, int32_t* 
             int at = 0;
             if (lane_id() == 0) at = atomicAdd(&list[q], popc64(mk));
             at = uniform_i32(at);
-            if (mine) list[2 + (int64_t)q * n + at + popc64(mk & lanemask_lt())] = a;
+            if (mine) list[2 + (int64_t)q * n + at + popc64(mk & lanemask_lt())] = (int32_t)a;
         }
     }
 }
@@ -281,7 +281,8 @@ __global__ __launch_bounds__(TB) void k_tri_wave(TriArgs T) {
     const int lane = lane_id();
     const int wid = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / EBB_WAVE);
     const int nw = (int)(gridDim.x * (int64_t)blockDim.x / EBB_WAVE);
-    for (int a = wid; a < T.n; a += nw) {
+    for (int64_t v = wid; v < T.n; v += nw) {
+        const int a = (int)v;
         const int a0 = uniform_i32(T.orp[a]), d = uniform_i32(T.orp[a + 1]) - a0;
         if (d > TRI_WAVE_D) continue;
         if (d < 2) {
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(TB) void k_tri_block(TriArgs T, const int32_t* __re
                 [&](int32_t w) {
                     int lo = s0, hi = s1;
                     while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
+                        const int mid = midpoint(lo, hi);
                         if ((ids ? ids[mid] : T.orow[mid].x) < w) lo = mid + 1; else hi = mid;
                     }
                     return lo < s1 && (ids ? ids[lo] : T.orow[lo].x) == w ? lo - s0 : -1;
@@ -1031,14 +1032,14 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     const int64_t live_elems = mm + PEEL_TB * (PEEL_GRID_WIDE + 1);
     Slab held, tmp;
     CHK(held.init(SlabSize{}
-                      .add<int32_t>(n + 1, 2)
+                      .add<int32_t>((int64_t)n + 1, 2)
                       .add<int32_t>(nnz, 2)
                       .add<int32_t>(mm, 7)
                       .add<int2>(nnz)
                       .add<int2>(mm)));
     CHK(tmp.init(SlabSize{}
                      .add<int32_t>(n, 2)
-                     .add<int64_t>(n + 1)
+                     .add<int64_t>((int64_t)n + 1)
                      .add<int32_t>(2 + 2 * (int64_t)n)
                      .add<int64_t>(tmp_elems)
                      .add<int32_t>(nnz, 3)
@@ -1052,10 +1053,10 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
                      .add<PeelCtl>(1)
                      .add<int32_t>(live_elems)));
     SBuf<int32_t> rp, ci;
-    CHK(rp.alloc(held, n + 1));
+    CHK(rp.alloc(held, (int64_t)n + 1));
     CHK(ci.alloc(held, nnz));
     hipMemcpyKind kind = ptr_kind == EBBKC_PTR_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
-    CHK(hipMemcpyAsync(rp.p, row_ptr, sizeof(int32_t) * (size_t)(n + 1), kind, s));
+    CHK(hipMemcpyAsync(rp.p, row_ptr, sizeof(int32_t) * ((size_t)n + 1), kind, s));
     if (nnz) CHK(hipMemcpyAsync(ci.p, col_idx, sizeof(int32_t) * (size_t)nnz, kind, s));
 
     // status words: [0] err, [1] dmax, [2] vertices still uncoloured; read back
@@ -1064,7 +1065,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     int* dstat = (int*)g->d_counters;
     int* hstat = (int*)g->h_counters;
     CHK(hipMemsetAsync(dstat, 0, 4 * sizeof(int), s));
-    hipLaunchKernelGGL(k_validate_rows, dim3(grid_for(n + 1)), dim3(TB), 0, s, rp.p, n, nnz, dstat);
+    hipLaunchKernelGGL(k_validate_rows, dim3(grid_for((int64_t)n + 1)), dim3(TB), 0, s, rp.p, n, nnz, dstat);
     if (nnz) hipLaunchKernelGGL(k_validate_entries, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, ci.p, n, nnz, dstat);
     CHK(hipGetLastError());
     CHK(hipMemcpyAsync(hstat, dstat, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1079,7 +1080,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     SBuf<int64_t> eoff, scan_tmp;
     CHK(ustart.alloc(tmp, n));
     CHK(ucnt.alloc(tmp, n));
-    CHK(eoff.alloc(tmp, n + 1));
+    CHK(eoff.alloc(tmp, (int64_t)n + 1));
     CHK(scan_tmp.alloc(tmp, tmp_elems));
     CHK(eid.alloc(tmp, nnz));
     CHK(src.alloc(tmp, nnz));
@@ -1098,13 +1099,13 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     SBuf<int2> orow_id;
     CHK(oflag.alloc(tmp, nnz));
     CHK(opos.alloc(tmp, nnz));
-    CHK(orp.alloc(held, n + 1));
+    CHK(orp.alloc(held, (int64_t)n + 1));
     CHK(orow_id.alloc(tmp, m));
     if (nnz)
         hipLaunchKernelGGL(k_out_flags, dim3(grid_for(nnz)), dim3(TB), 0, s, rp.p, src.p, ci.p, (const int2*)nullptr,
                            nnz, oflag.p);
     CHK(exclusive_scan_i32(oflag.p, opos.p, nnz, nullptr, scan_tmp.p, s));
-    hipLaunchKernelGGL(k_out_fill, dim3(grid_for(nnz > n ? nnz : n + 1)), dim3(TB), 0, s, rp.p, ci.p, eid.p,
+    hipLaunchKernelGGL(k_out_fill, dim3(grid_for(std::max<int64_t>(nnz, (int64_t)n + 1))), dim3(TB), 0, s, rp.p, ci.p, eid.p,
                        (const int2*)nullptr, n, nnz, oflag.p, opos.p, orow_id.p, orp.p);
     CHK(hipGetLastError());
 
@@ -1278,7 +1279,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
             CHK(vfront.alloc(n));
             CHK(vflag.alloc(n));
             CHK(vrnd.alloc(n));
-            CHK(vps.alloc(n + 1));
+            CHK(vps.alloc((int64_t)n + 1));
             hipLaunchKernelGGL(k_degrees, dim3(grid_for(n)), dim3(TB), 0, s, rp.p, n, deg.p);
             hipLaunchKernelGGL(k_iota, dim3(grid_for(n)), dim3(TB), 0, s, vlive.p, (int64_t)n);
             hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n)), dim3(TB), 0, s, vrnd.p, (int64_t)n, -1);
@@ -1389,7 +1390,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
         g->acum = acum.release();
         g->adjw = aw;
     }
-    g->device_bytes = (int64_t)sizeof(int32_t) * ((n + 1) * 2 + nnz * 2 + m * 6) + (int64_t)sizeof(int2) * (nnz + m) +
+    g->device_bytes = (int64_t)sizeof(int32_t) * (((int64_t)n + 1) * 2 + nnz * 2 + m * 6) + (int64_t)sizeof(int2) * (nnz + m) +
                       (int64_t)sizeof(int32_t) * n * ((g->vpos ? 1 : 0) + (g->vcol ? 1 : 0)) +
                       (with_adj ? (int64_t)n * aw * (int64_t)(sizeof(uint64_t) + sizeof(uint16_t)) : 0);
     return EBBKC_OK;
