@@ -41,8 +41,8 @@ void ebbkc_destroy(ebbkc_graph* g) {
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(g->device);
-    void* ptrs[] = {g->held, g->arena_held, g->varena.held, g->subsize_own ? g->subsize : nullptr, g->scratch,
-                    g->d_counters, g->vpos, g->vcol, g->rho_slab, g->adj, g->acum};
+    void* ptrs[] = {g->held, g->arena_held, g->varena.held, g->scratch, g->d_counters,
+                    g->vpos, g->vcol, g->rho_slab, g->adj, g->acum};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (g->h_counters) (void)hipHostFree(g->h_counters);

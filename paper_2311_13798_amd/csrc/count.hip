@@ -405,13 +405,6 @@ ebbkc_status ensure_counters(ebbkc_graph* g) {
 
 ebbkc_status subsize_impl(ebbkc_graph* g, hipStream_t s) {
     if (g->subsize_ready) return EBBKC_OK;
-    if (!g->subsize) {
-        if (hipMalloc((void**)&g->subsize, sizeof(int32_t) * (size_t)(g->m > 0 ? g->m : 1)) != hipSuccess) {
-            g->subsize = nullptr;
-            return EBBKC_E_OOM;
-        }
-        g->subsize_own = true;
-    }
     CHKH(launch_subsize(graph_view(g), g->m, g->subsize, s));
     g->subsize_ready = true;
     return EBBKC_OK;
@@ -499,7 +492,7 @@ static ebbkc_status build_slots(ebbkc_graph* g, const int32_t* id, const int32_t
     for (int c = 0; c < SIZE_BINS; ++c) S.count.n[c] = (int64_t)h.bins[c];
     const int64_t ns = S.tot.slots;
     CHKH(S.held.init(SlabSize{}
-                         .add<int32_t>(ns, 4)
+                         .add<int32_t>(ns, vertex ? 4 : 3)
                          .add<int64_t>(ns, 3)
                          .add<uint64_t>(S.tot.words)
                          .add<int32_t>(S.tot.vtx)
@@ -570,7 +563,7 @@ ebbkc_status arena_impl(ebbkc_graph* g, hipStream_t s) {
     g->acol = S.col.p;
     g->nedges = S.ned.p;
     g->arena_held = S.held.release();
-    g->arena_bytes = (int64_t)(S.tot.words * 8 + S.tot.vtx * 6 + S.tot.slots * 32);
+    g->arena_bytes = (int64_t)(S.tot.words * 8 + S.tot.vtx * 6 + S.tot.slots * 36);
     g->device_bytes += g->arena_bytes;
     g->arena_built = true;
     return EBBKC_OK;
@@ -610,7 +603,7 @@ static ebbkc_status vertex_arena_impl(ebbkc_graph* g, hipStream_t s) {
     A.col = S.col.p;
     A.nedges = S.ned.p;
     A.held = S.held.release();
-    A.bytes = (int64_t)(S.tot.words * 8 + S.tot.vtx * 6 + S.tot.slots * 36);
+    A.bytes = (int64_t)(S.tot.words * 8 + S.tot.vtx * 6 + S.tot.slots * 40);
     g->device_bytes += A.bytes;
     A.built = true;
     return EBBKC_OK;

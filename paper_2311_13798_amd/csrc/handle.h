@@ -60,8 +60,8 @@ struct ebbkc_graph {
     ebbkc_options opt{};
     int cu_count = 256;
 
-    // one allocation each: the prepared arrays (rp .. byrank below, and subsize
-    // under the truss order), and the edge and vertex arenas
+    // one allocation each: the prepared arrays (rp .. byrank and subsize below),
+    // and the edge and vertex arenas
     char* held = nullptr;
     char* arena_held = nullptr;
 
@@ -87,7 +87,6 @@ struct ebbkc_graph {
     uint16_t* acum = nullptr;
     int32_t adjw = 0;
     int32_t* subsize = nullptr; // m: |V(g_i)| per edge (from the peel, or filled on demand)
-    bool subsize_own = false;   // an allocation of its own
     int32_t* vpos = nullptr;    // n: position in the root vertex order (orderings COLOR, DEGEN_VERTEX)
     int32_t* vcol = nullptr;    // n: greedy colour of G (ordering COLOR)
     bool subsize_ready = false;

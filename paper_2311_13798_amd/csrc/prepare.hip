@@ -1381,16 +1381,14 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     g->orp = orp.p;
     g->orow = orow.p;
     g->byrank = byrank.p;
-    if (g->opt.ordering == EBBKC_ORDER_HYBRID || g->opt.ordering == EBBKC_ORDER_TRUSS) {
-        g->subsize = subsize.p;  // of pi_tau; another edge order has other sub-branches
-        g->subsize_ready = true;
-    }
+    g->subsize = subsize.p;  // of pi_tau; another edge order has other sub-branches
+    g->subsize_ready = g->opt.ordering == EBBKC_ORDER_HYBRID || g->opt.ordering == EBBKC_ORDER_TRUSS;
     if (with_adj) {
         g->adj = adj.release();
         g->acum = acum.release();
         g->adjw = aw;
     }
-    g->device_bytes = (int64_t)sizeof(int32_t) * (((int64_t)n + 1) * 2 + nnz * 2 + m * 6) + (int64_t)sizeof(int2) * (nnz + m) +
+    g->device_bytes = (int64_t)sizeof(int32_t) * (((int64_t)n + 1) * 2 + nnz * 2 + m * 7) + (int64_t)sizeof(int2) * (nnz + m) +
                       (int64_t)sizeof(int32_t) * n * ((g->vpos ? 1 : 0) + (g->vcol ? 1 : 0)) +
                       (with_adj ? (int64_t)n * aw * (int64_t)(sizeof(uint64_t) + sizeof(uint16_t)) : 0);
     return EBBKC_OK;
