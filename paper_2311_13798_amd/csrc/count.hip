@@ -661,9 +661,10 @@ static ebbkc_status read_total(ebbkc_graph* g, uint64_t* out, hipStream_t s) {
 }
 
 // Task list of slots [i0, i1) at l0 = k-2, sorted (width class, heaviest
-// first) into `sorted`; class sizes into ccount.  Scratch comes from cv.
+// first) into `sorted`; class sizes into ccount.  Scratch comes from cv;
+// small_hist as for radix_sort_u64.
 static ebbkc_status make_tasks(ebbkc_graph* g, int64_t i0, int64_t n, int l0, double log_thr, bool rest, hipStream_t s,
-                               Carve& cv, int64_t** sorted, int64_t* T_out, uint64_t ccount[4]) {
+                               Carve& cv, int64_t** sorted, int64_t* T_out, uint64_t ccount[4], bool small_hist = false) {
     int32_t* tcount = cv.take<int32_t>(n);
     int64_t* toff = cv.take<int64_t>(n + 1);
     int64_t* tmp = cv.take<int64_t>(scan_tmp_elems(n + 1) + 64);
@@ -676,7 +677,7 @@ static ebbkc_status make_tasks(ebbkc_graph* g, int64_t i0, int64_t n, int l0, do
     *T_out = T;
     if (T == 0) return EBBKC_OK;
     if (T >= ((int64_t)1 << 32)) return EBBKC_E_OOM;
-    const int64_t hn = radix_hist_elems(T);
+    const int64_t hn = radix_hist_elems(T, small_hist);
     int64_t* tasks = cv.take<int64_t>(T);
     int64_t* tsorted = cv.take<int64_t>(T);
     uint64_t* keys = cv.take<uint64_t>(T);
@@ -690,7 +691,7 @@ static ebbkc_status make_tasks(ebbkc_graph* g, int64_t i0, int64_t n, int l0, do
     CHKH(hipMemsetAsync(cls_count, 0, 4 * sizeof(uint64_t), s));
     hipLaunchKernelGGL(k_task_fill, dim3(grid_for(n)), dim3(256), 0, s, g->seed_c, i0, n, l0, log_thr, rest, toff,
                        tasks, keys, vals, cls_count);
-    CHKH(radix_sort_u64(keys, vals, keys2, vals2, T, 10, hist, htmp, s));
+    CHKH(radix_sort_u64(keys, vals, keys2, vals2, T, 10, hist, htmp, s, small_hist));
     hipLaunchKernelGGL(k_gather_tasks, dim3(grid_for(T)), dim3(256), 0, s, tasks, vals, T, tsorted);
     CHKH(hipGetLastError());
     CHKH(hipMemcpyAsync(ccount, cls_count, 4 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
@@ -700,8 +701,8 @@ static ebbkc_status make_tasks(ebbkc_graph* g, int64_t i0, int64_t n, int l0, do
 }
 
 // scratch bytes for make_tasks over n slots with at most T tasks
-static size_t task_bytes(int64_t n, int64_t T) {
-    const int64_t hn = radix_hist_elems(T);
+size_t task_bytes(int64_t n, int64_t T, bool small_hist) {
+    const int64_t hn = radix_hist_elems(T, small_hist);
     return rnd256((size_t)n * 4) + rnd256((size_t)(n + 1) * 8) + rnd256((size_t)(scan_tmp_elems(n + 1) + 64) * 8) +
            4 * rnd256((size_t)T * 8) + 2 * rnd256((size_t)T * 4) + rnd256((size_t)hn * 8) +
            rnd256((size_t)(scan_tmp_elems(hn) + 64) * 8) + 4096;
@@ -1068,12 +1069,16 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     CHKH(hipMemcpyAsync(&T, toff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     CHKH(hipStreamSynchronize(s));
     if (T == 0) return read_total(g, out, s);
-    Carve cv = carve_for(g, src, task_bytes(n, T) + rnd256(fbytes) + qbytes);
+    // (a fixed buffer too small for the short tiles' histograms may hold the long ones')
+    const size_t rest = rnd256(fbytes) + qbytes;
+    const bool small_hist = noalloc && task_bytes(n, T) + rest > src.cap;
+    Carve cv = carve_for(g, src, task_bytes(n, T, small_hist) + rest);
     if (!cv.base) return e_space;
     int64_t* tsorted = nullptr;
     uint64_t ccount[4] = {0, 0, 0, 0};
     int64_t T2 = 0;
-    st = make_tasks(g, i0, n, l0, log_thr, noalloc || g->opt.ordering != EBBKC_ORDER_TRUSS, s, cv, &tsorted, &T2, ccount);
+    st = make_tasks(g, i0, n, l0, log_thr, noalloc || g->opt.ordering != EBBKC_ORDER_TRUSS, s, cv, &tsorted, &T2, ccount,
+                    small_hist);
     if (st) return st == EBBKC_E_OOM ? e_space : st;
     void* gframes = deep ? (void*)cv.take<char>((int64_t)fbytes) : nullptr;
     if (deep && !gframes) return e_space;

@@ -148,6 +148,8 @@ hipError_t ensure_tables(int dev, hipStream_t s);
 ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, int64_t ne, int32_t ptr_kind,
                               uint64_t* out, hipStream_t s);
 void* scratch_get(ebbkc_graph* g, size_t bytes);
+// Scratch bytes of the sorted task list of n slots with T tasks.
+size_t task_bytes(int64_t n, int64_t T, bool small_hist = false);
 // The plan of a whole count at l0 over slots of these sizes: the number of
 // root ranges (-1 past 2^32) and where each class's start in their list.
 int64_t plan_ranges(const SizeCounts& N, int l0, double log_thr, int64_t first[4]);

@@ -18,10 +18,12 @@ hipError_t exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_
 // Stable LSD radix sort of (key, value) pairs on key bits [0, bits).
 // keys/vals are sorted in place; keys_alt/vals_alt are same-sized scratch;
 // hist must hold radix_hist_elems(n) int64 values and tmp scan_tmp_elems of
-// that.  vals may be null (keys only).
-int64_t radix_hist_elems(int64_t n);
+// that.  vals may be null (keys only).  small_hist: long tiles also for a short
+// sort, which is slower and takes a quarter of the histograms (for a buffer
+// that cannot grow).
+int64_t radix_hist_elems(int64_t n, bool small_hist = false);
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
-                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s);
+                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s, bool small_hist = false);
 // copy_back false: the result stays where the last pass left it, in the _alt
 // arrays after an odd number of passes.
 int radix_passes(int64_t n, int bits);

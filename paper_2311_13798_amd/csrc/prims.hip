@@ -111,8 +111,11 @@ constexpr int RS_BLOCK = 256;
 // scatter with 16, which is ten workgroups).
 constexpr int RS_ITEMS = 16, RS_ITEMS_SHORT = 4;
 constexpr int64_t RS_SHORT_N = 1 << 20;
-inline int rs_items(int64_t n) { return n <= RS_SHORT_N ? RS_ITEMS_SHORT : RS_ITEMS; }
-inline int64_t rs_blocks(int64_t n) { return (n + RS_BLOCK * rs_items(n) - 1) / (RS_BLOCK * rs_items(n)); }
+inline bool rs_short(int64_t n, bool small_hist) { return n <= RS_SHORT_N && !small_hist; }
+inline int64_t rs_blocks(int64_t n, bool small_hist = false) {
+    const int64_t tile = RS_BLOCK * (rs_short(n, small_hist) ? RS_ITEMS_SHORT : RS_ITEMS);
+    return (n + tile - 1) / tile;
+}
 constexpr int RS_WAVES = RS_BLOCK / EBB_WAVE;
 
 template <typename K, int RS_ITEMS>
@@ -189,15 +192,16 @@ hipError_t exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_
 
 // (of a short sort also what a longer one of up to the limit needs, so that a
 // buffer sized for n serves any smaller sort)
-int64_t radix_hist_elems(int64_t n) {
+int64_t radix_hist_elems(int64_t n, bool small_hist) {
+    if (small_hist) return 256 * rs_blocks(n, true) + 1;
     return 256 * std::max(rs_blocks(n), rs_blocks(std::min(n, RS_SHORT_N))) + 1;
 }
 int radix_passes(int64_t n, int bits) { return n <= 1 || bits <= 0 ? 0 : (bits + 7) / 8; }
 
 template <typename K>
-static void rs_hist(const K* keys, int64_t n, int shift, int64_t* hist, hipStream_t s) {
-    const int64_t nb = rs_blocks(n);
-    if (n <= RS_SHORT_N)
+static void rs_hist(const K* keys, int64_t n, int shift, int64_t* hist, hipStream_t s, bool small_hist) {
+    const int64_t nb = rs_blocks(n, small_hist);
+    if (rs_short(n, small_hist))
         hipLaunchKernelGGL((k_rs_hist<K, RS_ITEMS_SHORT>), dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, keys, n, shift, nb,
                            hist);
     else
@@ -205,9 +209,9 @@ static void rs_hist(const K* keys, int64_t n, int shift, int64_t* hist, hipStrea
 }
 template <typename K>
 static void rs_scatter(const K* kin, const uint32_t* vin, K* kout, uint32_t* vout, int64_t n, int shift,
-                       const int64_t* off, hipStream_t s) {
-    const int64_t nb = rs_blocks(n);
-    if (n <= RS_SHORT_N)
+                       const int64_t* off, hipStream_t s, bool small_hist) {
+    const int64_t nb = rs_blocks(n, small_hist);
+    if (rs_short(n, small_hist))
         hipLaunchKernelGGL((k_rs_scatter<K, RS_ITEMS_SHORT>), dim3((unsigned)nb), dim3(RS_BLOCK), 0, s, kin, vin, kout,
                            vout, n, shift, nb, off);
     else
@@ -217,24 +221,24 @@ static void rs_scatter(const K* kin, const uint32_t* vin, K* kout, uint32_t* vou
 
 hipError_t bin_sort_u8(const uint8_t* keys, int64_t n, uint32_t* out, int64_t* hist, int64_t* tmp, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    rs_hist(keys, n, 0, hist, s);
+    rs_hist(keys, n, 0, hist, s, false);
     hipError_t e = exclusive_scan_i64(hist, hist, 256 * rs_blocks(n), nullptr, tmp, s);
     if (e != hipSuccess) return e;
-    rs_scatter(keys, nullptr, (uint8_t*)nullptr, out, n, 0, hist, s);
+    rs_scatter(keys, nullptr, (uint8_t*)nullptr, out, n, 0, hist, s, false);
     return hipGetLastError();
 }
 
 template <typename K>
 static hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt, int64_t n, int bits,
-                             int64_t* hist, int64_t* tmp, hipStream_t s, bool copy_back) {
+                             int64_t* hist, int64_t* tmp, hipStream_t s, bool copy_back, bool small_hist) {
     const int passes = radix_passes(n, bits);
     K *ka = keys, *kb = keys_alt;
     uint32_t *va = vals, *vb = vals ? vals_alt : nullptr;
     for (int p = 0; p < passes; ++p) {
-        rs_hist(ka, n, p * 8, hist, s);
-        hipError_t e = exclusive_scan_i64(hist, hist, 256 * rs_blocks(n), nullptr, tmp, s);
+        rs_hist(ka, n, p * 8, hist, s, small_hist);
+        hipError_t e = exclusive_scan_i64(hist, hist, 256 * rs_blocks(n, small_hist), nullptr, tmp, s);
         if (e != hipSuccess) return e;
-        rs_scatter(ka, va, kb, vb, n, p * 8, hist, s);
+        rs_scatter(ka, va, kb, vb, n, p * 8, hist, s, small_hist);
         K* kt = ka; ka = kb; kb = kt;
         uint32_t* vt = va; va = vb; vb = vt;
     }
@@ -248,12 +252,12 @@ static hipError_t radix_sort(K* keys, uint32_t* vals, K* keys_alt, uint32_t* val
 }
 
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
-                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s) {
-    return radix_sort<uint64_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s, true);
+                          int bits, int64_t* hist, int64_t* tmp, hipStream_t s, bool small_hist) {
+    return radix_sort<uint64_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s, true, small_hist);
 }
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, int64_t n,
                           int bits, int64_t* hist, int64_t* tmp, hipStream_t s, bool copy_back) {
-    return radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s, copy_back);
+    return radix_sort<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, hist, tmp, s, copy_back, false);
 }
 
 }  // namespace ebb

@@ -95,3 +95,16 @@ def test_a_peel_without_room_starts_over_with_fewer(grid, room, tried):
     # an error is final, and so is one workgroup that gives up
     assert f(grid, CB(lambda _, g: ebb.E_OOM), None) == ebb.E_OOM
     assert f(grid, CB(lambda _, g: 1), None) == ebb.E_HIP
+
+
+@pytest.mark.parametrize("slots,tasks", [(1, 1), (10**6, 10**6), (21_000_000, 1 << 20), (20_900_000, 100_000), (1, 6_000_000)])
+def test_sorting_few_tasks_needs_no_more_scratch_than_many(slots, tasks):
+    # the task list of a count that may not allocate: 12 bytes a slot, 40 a task, and one histogram of 256
+    # for every 4,096 tasks (2 KB); shorter tiles only where there is room for their histograms
+    rnd = lambda b: (b + 255) // 256 * 256
+    scan = lambda n: (n + 2047) // 2048 + 65
+    hist = 256 * ((tasks + 4095) // 4096) + 1
+    want = (rnd(4 * slots) + rnd(8 * (slots + 1)) + rnd(8 * scan(slots + 1)) + 4 * rnd(8 * tasks) + 2 * rnd(4 * tasks) +
+            rnd(8 * hist) + rnd(8 * scan(hist)) + 4096)
+    f = internal("_ZN3ebb10task_bytesEllb", ctypes.c_size_t, ctypes.c_int64, ctypes.c_int64, ctypes.c_bool)
+    assert f(slots, tasks, True) == want <= f(slots, tasks, False)
