@@ -5,6 +5,19 @@
 
 namespace ebb {
 
+// instantiated by search_w1.hip .. search_w4.hip (used here without these
+// declarations, they were compiled a second time, and the linker took this
+// file's kernels)
+#define EBB_SEARCH_CLASS(W)                                                                       \
+    extern template hipError_t search_launch<W>(bool, const SearchArgs&, int, int, hipStream_t); \
+    extern template int64_t search_blocks<W>(bool, int64_t, int, int);                            \
+    extern template hipError_t search_tables<W>(hipStream_t);
+EBB_SEARCH_CLASS(1)
+EBB_SEARCH_CLASS(2)
+EBB_SEARCH_CLASS(3)
+EBB_SEARCH_CLASS(4)
+#undef EBB_SEARCH_CLASS
+
 // the split queue's counters and ready flags zeroed before a launch (a kernel,
 // so that captured launch sequences hold no memset node)
 __global__ void k_sq_reset(unsigned long long* sq, SplitItem* items, int64_t cap) {

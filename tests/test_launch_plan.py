@@ -1,6 +1,6 @@
-"""Host arithmetic of the launches (no GPU calls), through the library's internal functions: where each
-width class's root ranges start in one task list of up to 2^32 entries, the frames of deep searches, and the
-workgroups of the peel."""
+"""The library without a GPU: host arithmetic of the launches, through internal functions (where each width
+class's root ranges start in one task list of up to 2^32 entries, the frames of deep searches, the workgroups
+of the peel, the bytes of task lists), and its kernels."""
 import ctypes
 import math
 import os
@@ -108,3 +108,13 @@ def test_sorting_few_tasks_needs_no_more_scratch_than_many(slots, tasks):
             rnd(8 * hist) + rnd(8 * scan(hist)) + 4096)
     f = internal("_ZN3ebb10task_bytesEllb", ctypes.c_size_t, ctypes.c_int64, ctypes.c_int64, ctypes.c_bool)
     assert f(slots, tasks, True) == want <= f(slots, tasks, False)
+
+
+def test_every_kernel_is_compiled_once():
+    # two copies of a kernel would each have binomial tables of their own, of which one is filled; a code
+    # object names a kernel's descriptor twice, in its two symbol tables
+    import re
+    data = open(ebb.LIB_PATH, "rb").read()
+    names = {n for n in re.findall(rb"_Z[A-Za-z0-9_]+\.kd", data) if b"_GLOBAL__N_1" not in n}
+    assert sum(b"k_search" in n for n in names) >= 16
+    assert [n for n in names if data.count(n + b"\0") != 2] == []
