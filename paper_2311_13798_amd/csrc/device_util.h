@@ -12,6 +12,26 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Words that several workgroups exchange while a kernel runs: relaxed
+// device-scope accesses, which go past the compute units' vector caches and the
+// L2s of the eight dies.  Order between them comes from waiting for one before
+// the next is issued (wait_memory, or the use of a returned value); release and
+// acquire would write back and drop whole caches instead.
+template <typename T>
+__device__ __forceinline__ T dev_load(const T* p) {
+    return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void dev_store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T dev_add(T* p, T v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// the wave's loads have returned and its stores and atomics are done
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
+
 // a wave-uniform 64-bit value in scalar registers
 __device__ __forceinline__ uint64_t uni64(uint64_t x) {
     uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);

@@ -494,15 +494,6 @@ struct PeelCtl {
     int32_t tau, rounds;
 };
 
-template <typename T>
-__device__ __forceinline__ T dev_load(const T* p) {
-    return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ void dev_store(T* p, T v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 struct PeelArgs {
     int32_t m;
     const int64_t* inc_off;
@@ -528,13 +519,13 @@ struct PeelMem {
 // Every workgroup has arrived (generation gen, counted from 1) and its stores
 // are done; false after PEEL_WAIT_TICKS or when another one gave up.
 __device__ bool peel_barrier(PeelMem& M, PeelCtl* ctl, uint32_t gen) {
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    wait_memory();
     __syncthreads();
     if (threadIdx.x == 0) {
         const uint32_t target = gen * gridDim.x;
         const uint64_t t0 = wall_clock64();
         int ok = 1;
-        if (gridDim.x > 1) __hip_atomic_fetch_add(&ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (gridDim.x > 1) dev_add(&ctl->arrived, 1u);
         for (uint32_t spin = 0; gridDim.x > 1 && (int32_t)(dev_load(&ctl->arrived) - target) < 0; ++spin) {
             if (dev_load(&ctl->err) || wall_clock64() - t0 > PEEL_WAIT_TICKS || spin > PEEL_WAIT_SPINS) {
                 dev_store(&ctl->err, 1);

@@ -99,6 +99,7 @@ template <int W>
 struct SearchMem {
     uint64_t rows[64 * W][W];
     uint64_t dag[W == 1 ? 64 : 1];  // W = 1: the later neighbours of each vertex
+    int32_t pushed;                 // this wave handed a node over in this launch
     int16_t col[64 * W];
     int16_t md[64 * W];      // missing pairs per vertex inside the set being counted
     int16_t vl[64 * W];      // that set's vertices in order, one per lane
@@ -660,20 +661,26 @@ static_assert(build_fits<1>() && build_fits<2>() && build_fits<3>() && build_fit
               "sub-branch build scratch must fit the search's LDS");
 
 // ---------------------------------------------------------------- split queue
-// Counters are touched once per queue operation, sequentially consistent at
-// device scope, so that a wave that sees no working wave also sees every item
-// pushed before the last one stopped.
-__device__ __forceinline__ unsigned long long sq_load(unsigned long long* p) {
-    return __hip_atomic_load(p, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long sq_add(unsigned long long* p, long long v) {
-    return __hip_atomic_fetch_add(p, (unsigned long long)v, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
-}
-// a hint only (whether to push): no ordering, no wait for the wave's other
-// memory operations
-__device__ __forceinline__ unsigned long long sq_peek(unsigned long long* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// The counters and the items are accessed relaxed at device scope, and order
+// comes from waiting (device_util.h): a wave's reservation has returned before
+// the wave can stop counting as working, and a wave that has read that no wave
+// works reads the reservations after it, so it sees every item pushed before
+// the last one stopped; an item's fields are done before its ready flag is set,
+// and read after it.  (Sequentially consistent counters and a released flag
+// wrote back and dropped whole caches several times an item.)
+//
+// The loads of the waiting waves queue up with the counters' updates: with all
+// 4,096 waves of a launch waiting, an item cost some 13 us of the launch, one
+// after the other and whatever it held.  So at most SQ_WAITERS waves wait, and
+// the longer one has waited the longer it naps, up to a sixteenth of its wait
+// (which the end of the launch may be noticed later) or 256 sleeps, 0.5 ms.
+// R-MAT s13 at k = 32 and 35 (733,122 and 14,193 nodes) 381 and 21.3 ms before,
+// 24.9 and 2.5 now; G(300, 0.6) at k = 12 136 and 59 ms.  512 waiting waves:
+// 20.9, 1.8 and 57 ms, but a quarter of the device's waves should be at hand
+// where a few roots hold most of the work.  Without the limit, with the naps
+// 41.9, 6.6 and 63 ms; with the limit of 512 alone 21.3, 1.7 and 74 ms.
+constexpr unsigned long long SQ_WAITERS = 1024;
+constexpr uint64_t SQ_NAP_TICKS = 3200;  // sixteen sleeps of about 2 us, in ticks of the 100 MHz clock
 constexpr int SQ_POLL_BUSY = 256, SQ_POLL_HUNGRY = 4;
 constexpr uint64_t SQ_POLL_TICKS = 2000;  // 20 us of the 100 MHz clock
 // longest time a wave waits while the queue shows no progress (no item
@@ -684,28 +691,34 @@ constexpr uint64_t SQ_POLL_TICKS = 2000;  // 20 us of the 100 MHz clock
 constexpr uint64_t SQ_WAIT_TICKS = 6000000000ull;
 constexpr uint64_t SQ_WAIT_SPINS = 1ull << 26;
 
+__device__ __forceinline__ void sq_add(unsigned long long* p, long long v) { (void)dev_add(p, (unsigned long long)v); }
+// No wave works and no item waits, read in this order.
+__device__ __forceinline__ bool nothing_left(unsigned long long* sq) {
+    if (dev_load(&sq[SQ_BUSY]) != 0) return false;
+    wait_memory();
+    const unsigned long long r = dev_load(&sq[SQ_RESERVE]);
+    return dev_load(&sq[SQ_HEAD]) >= r;
+}
+
 // An idle wave claims a queued node: returns its index once its producer has
 // written it, or -1 when no wave is working and the queue is empty (then no
 // item can appear any more: an item is pushed only by a working wave, before
 // that wave stops counting as working) or after SQ_WAIT_TICKS without work
 // (ERR_QUEUE).  A claim takes the head first and counts the wave as working
 // after it; a wave in between may process that node while others have
-// finished, and handles whatever it pushes itself.  Idle polling backs off
-// and reads the counters without ordering (an ordered atomic would also
-// drop the compute unit's vector cache, which the working waves beside it
-// use for their spilled registers); only a claim and the final check that
-// nothing is left are ordered.
+// finished, and handles whatever it pushes itself.  Idle polling backs off.
 __device__ int64_t queue_take(const SearchArgs& a) {
     unsigned long long* sq = a.sq;
     uint64_t t0 = wall_clock64();
+    const uint64_t t_in = t0;
     unsigned long long seen_h = ~0ull, seen_r = ~0ull, seen_b = ~0ull;
     int nap = 1;
     for (uint64_t spin = 0;; ++spin) {
         long long got = -1;
         int done = 0;
         if (lane_id() == 0) {
-            const unsigned long long h = sq_peek(&sq[SQ_HEAD]), r = sq_peek(&sq[SQ_RESERVE]);
-            const unsigned long long bz = sq_peek(&sq[SQ_BUSY]);
+            const unsigned long long h = dev_load(&sq[SQ_HEAD]), r = dev_load(&sq[SQ_RESERVE]);
+            const unsigned long long bz = dev_load(&sq[SQ_BUSY]);
             if (h != seen_h || r != seen_r || bz != seen_b) {  // progress: the wait starts again
                 seen_h = h;
                 seen_r = r;
@@ -717,16 +730,14 @@ __device__ int64_t queue_take(const SearchArgs& a) {
                 got = (long long)h;
                 sq_add(&sq[SQ_BUSY], 1);
                 sq_add(&sq[SQ_IDLE], -1);
-            } else if (h >= r && bz == 0 && sq_load(&sq[SQ_BUSY]) == 0 &&
-                       sq_load(&sq[SQ_HEAD]) >= sq_load(&sq[SQ_RESERVE])) {
+            } else if (h >= r && bz == 0 && nothing_left(sq)) {
                 done = 1;
             } else if (wall_clock64() - t0 > SQ_WAIT_TICKS || spin > SQ_WAIT_SPINS) {
                 atomicOr(a.err, ERR_QUEUE);
                 done = 1;
             }
             if (got >= 0) {  // the producer reserved the slot before writing it
-                for (uint64_t wspin = 0;
-                     __hip_atomic_load(&a.squeue[got].ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 0; ++wspin) {
+                for (uint64_t wspin = 0; dev_load(&a.squeue[got].ready) == 0; ++wspin) {
                     if (wall_clock64() - t0 > SQ_WAIT_TICKS || wspin > SQ_WAIT_SPINS) {
                         atomicOr(a.err, ERR_QUEUE);
                         got = -1;
@@ -740,12 +751,13 @@ __device__ int64_t queue_take(const SearchArgs& a) {
         got = (long long)uni64((uint64_t)__shfl(got, 0, 64));
         done = uniform_i32(__shfl(done, 0, 64));
         if (got >= 0) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // every lane sees the item
+            wait_memory();  // the flag was read before the fields are
             return got;
         }
         if (done) return -1;
         for (int i = 0; i < nap; ++i) __builtin_amdgcn_s_sleep(64);
-        nap = nap < 32 ? 2 * nap : 32;
+        const uint64_t most = (wall_clock64() - t_in) / SQ_NAP_TICKS;
+        nap = nap < 32 ? 2 * nap : (most > 256 ? 256 : (most > 32 ? (int)most : 32));
     }
 }
 
@@ -778,7 +790,10 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
     // runtime splitting: a wave counts as working from its start until the
     // static tasks run out, then takes queued nodes until none is left
     const bool splitting = DEEP && a.squeue != nullptr;
-    if (splitting && lane == 0) sq_add(&a.sq[SQ_BUSY], 1);
+    if (splitting && lane == 0) {
+        sq_add(&a.sq[SQ_BUSY], 1);
+        M.pushed = 0;
+    }
     bool on_queue = false, took_item = false;
     int poll_in = 0;      // candidate nodes until the queue counters are read again
     uint64_t poll_t = 0;  // when they were read last
@@ -808,10 +823,15 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             if (it < 0) {
                 if (!splitting) break;
                 on_queue = true;
+                int stay = 1;
                 if (lane == 0) {
-                    sq_add(&a.sq[SQ_IDLE], 1);
+                    // waiting waves enough: this one ends, unless it handed nodes
+                    // over (whoever did stays until the queue is empty)
+                    stay = dev_add(&a.sq[SQ_IDLE], 1ull) < SQ_WAITERS || M.pushed;
+                    if (!stay) sq_add(&a.sq[SQ_IDLE], -1);
                     sq_add(&a.sq[SQ_BUSY], -1);
                 }
+                if (!uniform_i32(stay)) break;
             }
         }
         if (on_queue) {
@@ -822,7 +842,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             qitem = queue_take(a);
             if (qitem < 0) break;
             took_item = true;
-            it = (int64_t)uni64((uint64_t)a.squeue[qitem].it);
+            it = (int64_t)uni64((uint64_t)dev_load(&a.squeue[qitem].it));
         }
         const bool listed = it < a.nexplicit;
         const int64_t task = listed ? a.tasks[it] : 0;
@@ -1456,7 +1476,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         int lq = 0;
         if (DEEP && qitem >= 0) {
             // a queued node (finish() already found no closed form for it)
-            lq = uniform_i32(a.squeue[qitem].l);
+            lq = uniform_i32(dev_load(&a.squeue[qitem].l));
         } else {
             // a root split over several tasks that is a clique, 2-plex or
             // 3-plex (as far as t allows): this task's part is the
@@ -1509,7 +1529,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             if (active && (lr == 4 || lr == 5)) {
                 uint64_t Pr[W];
 #pragma unroll
-                for (int w = 0; w < W; ++w) Pr[w] = DEEP && qitem >= 0 ? uni64(a.squeue[qitem].P[w]) : P0[w];
+                for (int w = 0; w < W; ++w) Pr[w] = DEEP && qitem >= 0 ? uni64(dev_load(&a.squeue[qitem].P[w])) : P0[w];
                 count_children(Pr, lr, DEEP && qitem >= 0 ? c : x1);
                 active = false;
             }
@@ -1533,8 +1553,8 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                     int hg = 0;
                     if (lane == 0) {
                         unsigned long long* sq = a.sq;
-                        const unsigned long long r = sq_peek(&sq[SQ_RESERVE]), h = sq_peek(&sq[SQ_HEAD]);
-                        hg = sq_peek(&sq[SQ_IDLE]) > r - h;
+                        const unsigned long long r = dev_load(&sq[SQ_RESERVE]), h = dev_load(&sq[SQ_HEAD]);
+                        hg = dev_load(&sq[SQ_IDLE]) > r - h;
                     }
                     hungry = uniform_i32(__shfl(hg, 0, 64)) != 0;
                     poll_in = hungry ? SQ_POLL_HUNGRY : SQ_POLL_BUSY;
@@ -1544,16 +1564,17 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             int ok = 0;
             if (lane == 0) {
                 unsigned long long* sq = a.sq;
-                const unsigned long long r = sq_peek(&sq[SQ_RESERVE]);
+                const unsigned long long r = dev_load(&sq[SQ_RESERVE]);
                 if (r + SQ_SLACK < (unsigned long long)SQ_CAP) {
-                    const unsigned long long si = sq_add(&sq[SQ_RESERVE], 1);
-                    SplitItem& I = a.squeue[si];
-                    I.it = it;
+                    SplitItem& I = a.squeue[dev_add(&sq[SQ_RESERVE], 1ull)];
+                    dev_store(&I.it, it);
 #pragma unroll
-                    for (int w = 0; w < MAX_W; ++w) I.P[w] = w < W ? Pn[w] : 0;
-                    I.l = ln;
-                    __hip_atomic_store(&I.ready, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                    for (int w = 0; w < W; ++w) dev_store(&I.P[w], Pn[w]);
+                    dev_store(&I.l, (int32_t)ln);
+                    wait_memory();
+                    dev_store(&I.ready, 1);
                     sq_add(&sq[SQ_PUSHED], 1);
+                    M.pushed = 1;
                     ok = 1;
                 }
             }
@@ -1566,7 +1587,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         uint64_t P[W], R[W];
         int x = x0 - 1, l = qitem >= 0 ? lq : l0;
 #pragma unroll
-        for (int w = 0; w < W; ++w) { P[w] = qitem >= 0 ? uni64(a.squeue[qitem].P[w]) : P0[w]; R[w] = 0; }
+        for (int w = 0; w < W; ++w) { P[w] = qitem >= 0 ? uni64(dev_load(&a.squeue[qitem].P[w])) : P0[w]; R[w] = 0; }
         while (active) {
             int y = -1;
             while (true) {
