@@ -129,8 +129,8 @@ typedef struct {
     int32_t node_split;        /* runtime splitting of search nodes over waves through a device
                                   queue (root sub-branches and their subtrees are independent,
                                   Section 6.2 (7)): 0 (default): a node with l >= 4 and at least
-                                  2^20 l-subsets is handed to a waiting wave while some wave waits
-                                  for work; n >= 2: the same with n l-subsets; 1: every node with
+                                  2^20 l-subsets (2^18 in single counts at k = 10 and 11) is handed
+                                  to a waiting wave while some wave waits for work; n >= 2: the same with n l-subsets; 1: every node with
                                   l >= 4 is handed over while the queue has room (exercises the
                                   queue at every depth); -1: off.  Not used by listings, per-seed
                                   counts, EBBkC-T, non-persistent launches (blocks_per_cu = -1)

@@ -174,6 +174,15 @@ constexpr int SPLIT_OFF = 0, SPLIT_ON_DEMAND = 1, SPLIT_FORCED = 2;
 // filled early and its round trips cost more than they saved; 2^20 was best
 // on R-MAT s12/s13 and Chung-Lu 3e5 at k = 11, 12)
 constexpr uint64_t NODE_SPLIT_DEFAULT = 1ull << 20;
+// At l0 = 8 and 9 a node that can be handed over and branches has l = 6 or 7:
+// its children are leaves, one for each of its edges, and l is far below its
+// size, so it holds more work for its l-subsets than the deeper nodes of larger
+// k (where the lower bound fills the queue early: R-MAT s13 at k = 12 961 ms
+// with 2^20, 2,548 with 2^18), and the launch ends with its largest ones.  2^18
+// against 2^20: R-MAT s13 at k = 10, 11 140 and 179 against 166 and 204 ms, R-MAT
+// s12 36.7 and 47.6 against 40.8 and 62.2, G(300, 0.6) 103 and 64.6 against 108
+// and 62.0, Chung-Lu 3e5 at k = 11 77 against 82.
+inline uint64_t node_split_default(int l0) { return l0 == 8 || l0 == 9 ? 1ull << 18 : NODE_SPLIT_DEFAULT; }
 
 // A graph whose sub-branches are built by the search tasks themselves (no
 // arena): its arrays, |V(g_i)| of every edge, and the colours of G kept in

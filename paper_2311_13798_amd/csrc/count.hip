@@ -809,7 +809,9 @@ static ebbkc_status run_tasks(ebbkc_graph* g, int32_t k, const TaskPlan& plan,
         a.list_checksums = fused;
         a.gframes = gframes;
         // runtime splitting: counts only (a queued node's count is not a task's own)
-        const uint64_t bound = g->opt.node_split == 1 ? 0 : (g->opt.node_split >= 2 ? (uint64_t)g->opt.node_split : NODE_SPLIT_DEFAULT);
+        const uint64_t bound = g->opt.node_split == 1   ? 0
+                               : g->opt.node_split >= 2 ? (uint64_t)g->opt.node_split
+                                                        : node_split_default(k - 2);
         if (squeue && !list && !truss && !per_task && g->opt.node_split != -1 && g->opt.blocks_per_cu != -1 &&
             can_split(k - 2, ct.cmax, bound)) {
             a.squeue = squeue;
