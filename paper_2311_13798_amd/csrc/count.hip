@@ -1241,20 +1241,20 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
                 CHKH(sort_packed_tuples(d_buf, (int64_t)N, k, bits, keys, keys2, hist, htmp,
                                         (unsigned long long*)(g->d_counters + 12), s));
             } else {
-            const size_t bytes = 2 * rnd256(N * 8) + 2 * rnd256(N * 4) + rnd256((size_t)hn * 8) +
-                                 rnd256((size_t)(scan_tmp_elems(hn) + 64) * 8) + rnd256(N * (size_t)k * 4) + 4096;
-            CHKH(hipMalloc(&tmp_sort, bytes));
-            Carve cv{(char*)tmp_sort, 0, bytes};
-            uint64_t* keys = cv.take<uint64_t>((int64_t)N);
-            uint64_t* keys2 = cv.take<uint64_t>((int64_t)N);
-            uint32_t* idx = cv.take<uint32_t>((int64_t)N);
-            uint32_t* idx2 = cv.take<uint32_t>((int64_t)N);
-            int64_t* hist = cv.take<int64_t>(hn);
-            int64_t* htmp = cv.take<int64_t>(scan_tmp_elems(hn) + 64);
-            int32_t* tbuf = cv.take<int32_t>((int64_t)N * k);
-            if (!keys || !keys2 || !idx || !idx2 || !hist || !htmp || !tbuf) return EBBKC_E_OOM;
-            if (N >= ((uint64_t)1 << 32)) return EBBKC_E_INVALID_ARG;
-            CHKH(sort_tuples(d_buf, (int64_t)N, k, bits, keys, keys2, idx, idx2, hist, htmp, tbuf, s));
+                const size_t bytes = 2 * rnd256(N * 8) + 2 * rnd256(N * 4) + rnd256((size_t)hn * 8) +
+                                     rnd256((size_t)(scan_tmp_elems(hn) + 64) * 8) + rnd256(N * (size_t)k * 4) + 4096;
+                CHKH(hipMalloc(&tmp_sort, bytes));
+                Carve cv{(char*)tmp_sort, 0, bytes};
+                uint64_t* keys = cv.take<uint64_t>((int64_t)N);
+                uint64_t* keys2 = cv.take<uint64_t>((int64_t)N);
+                uint32_t* idx = cv.take<uint32_t>((int64_t)N);
+                uint32_t* idx2 = cv.take<uint32_t>((int64_t)N);
+                int64_t* hist = cv.take<int64_t>(hn);
+                int64_t* htmp = cv.take<int64_t>(scan_tmp_elems(hn) + 64);
+                int32_t* tbuf = cv.take<int32_t>((int64_t)N * k);
+                if (!keys || !keys2 || !idx || !idx2 || !hist || !htmp || !tbuf) return EBBKC_E_OOM;
+                if (N >= ((uint64_t)1 << 32)) return EBBKC_E_INVALID_ARG;
+                CHKH(sort_tuples(d_buf, (int64_t)N, k, bits, keys, keys2, idx, idx2, hist, htmp, tbuf, s));
             }
         }
     }

@@ -108,13 +108,6 @@ __device__ __forceinline__ int popcW(const uint64_t (&p)[W]) {
     return c;
 }
 
-// word w of the mask of rows [0, c)
-template <int W>
-__device__ __forceinline__ uint64_t prefix_word(int c, int w) {
-    const int lo = 64 * w;
-    return c >= lo + 64 ? ~0ull : (c > lo ? ((1ull << (c - lo)) - 1) : 0ull);
-}
-
 // rows [0, c) as a W-word mask
 template <int W>
 __device__ __forceinline__ void prefix_mask(int c, uint64_t (&p)[W]) {

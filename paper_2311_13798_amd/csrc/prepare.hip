@@ -434,16 +434,6 @@ __global__ void k_peel_compact(const int32_t* __restrict__ live, int64_t nlive, 
     }
 }
 
-__global__ void k_peel_assign(const int32_t* __restrict__ front, int64_t nf, int32_t s, int64_t ranked, int32_t r,
-                              int32_t* __restrict__ level, int32_t* __restrict__ rank, int32_t* __restrict__ rnd) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nf; i += (int64_t)gridDim.x * blockDim.x) {
-        int32_t e = front[i];
-        level[e] = s;
-        rank[e] = (int32_t)(ranked + i);
-        rnd[e] = r;
-    }
-}
-
 // ---------------------------------------------------------------- truss peel
 // The whole level-synchronous peel in one cooperative launch.  A round's
 // frontier is the edges whose support reached the level in the round before:
@@ -804,11 +794,6 @@ __global__ void k_round_keys(const int32_t* __restrict__ rnd, int64_t m, uint32_
         keys[e] = (uint32_t)rnd[e];
         vals[e] = (uint32_t)e;
     }
-}
-
-__global__ void k_byrank(const int32_t* __restrict__ rank, int64_t m, int32_t* __restrict__ byrank) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x)
-        byrank[rank[e]] = (int32_t)e;
 }
 
 // adjacency bitmap: one bit per CSR entry (a row's entries may share a word)

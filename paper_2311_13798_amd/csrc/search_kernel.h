@@ -2,7 +2,7 @@
 // wavefront per task).
 //
 // A task is a seed's g_i (from the arena, or built in LDS by the task) and a
-// range [x0, x1) of first vertices of the root's children; light seeds are
+// range of first vertices of the root's children; light seeds are
 // one task, heavy seeds one task per range of root vertices.  While some
 // waves wait for work, a node can also be handed to one of them through a
 // device queue.  On the DAG of g_i (vertices in colour order, edges
@@ -855,7 +855,6 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         // range on its slot's width).  A queued node is a whole node below the
         // root: every first vertex.
         const int sx = listed && !BUILD ? task_x0(task) : 0;
-        constexpr int x0 = 0;
         const int x1 = !listed || qitem >= 0 ? 64 * W : task_x1(task) - sx;
         const int gi = a.task_graph ? uniform_i32(a.task_graph[it]) : 0;
         const int k = a.graph_k ? uniform_i32(a.graph_k[gi]) : a.k;
@@ -1267,13 +1266,12 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             return true;
         };
 
-        // children of a node with l = 5 (l = 4), x in [xlo, xhi): the
+        // children of a node with l = 5 (l = 4), x below xhi: the
         // 4-cliques (triangles) of R = P & N+(x) for each x.  A dense R is
         // counted by the wave from its missing pairs; otherwise its children
         // (x, y) join a queue in LDS and every 64 queued children are counted
         // one per lane.
-        auto children_by_lanes = [&](auto wv, const auto& P, auto rows, const int16_t* col, int cn, int l, int xlo,
-                                     int xhi) {
+        auto children_by_lanes = [&](auto wv, const auto& P, auto rows, const int16_t* col, int cn, int l, int xhi) {
             constexpr int WV = decltype(wv)::value;
             uint64_t lsum = 0, lops = 0, usum = 0;
             int64_t S = 0;
@@ -1326,12 +1324,12 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                 wave_sync();
             };
             bool done = false;
-            if (l == 4 && xlo == 0 && xhi >= cn) {
+            if (l == 4 && xhi >= cn) {
                 const int pc = popcW(P);
                 bool pd = false;
                 done = pc < 4 || k4_missing(wv, P, rows, pc, true, S, usum, pd);
             }
-            int xx = xlo - 1;
+            int xx = -1;
             while (!done) {
                 int nx = -1;
 #pragma unroll
@@ -1438,14 +1436,13 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             }
         };
 
-        // Children of a node with l = 4 or 5 (x in [xlo, xhi)).  Classes
+        // Children of a node with l = 4 or 5 (x below xhi).  Classes
         // W = 2 and 3 first renumber a whole node whose candidate set fits
         // W - 1 words onto them (one narrower instance of the children and
         // leaf code per class keeps the kernel's spill space small), unless
         // the node is so small that renumbering (~6 W |P| instructions)
         // costs more than the narrower words save.
         auto count_children = [&](const uint64_t (&Pn)[W], int ln, int xhi) {
-            constexpr int xlo = 0;
             if constexpr (W == 1) {
                 children1(Pn, ln, xhi);
                 return;
@@ -1453,25 +1450,25 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             if constexpr (W == 2 || W == 3) {
                 constexpr int WN = W - 1;
                 const int p = popcW(Pn);
-                if (xlo == 0 && xhi >= c && p <= 64 * WN && p >= COMPACT_MIN) {
+                if (xhi >= c && p <= 64 * WN && p >= COMPACT_MIN) {
                     uint64_t (*cr)[WN] = reinterpret_cast<uint64_t (*)[WN]>(M.crow);
                     compact_set<W, WN>(M, Pn, cr, M.ccol);
                     uint64_t Pc[WN];
                     prefix_mask<WN>(p, Pc);
-                    children_by_lanes(std::integral_constant<int, WN>{}, Pc, cr, M.ccol, p, ln, 0, 64 * WN);
+                    children_by_lanes(std::integral_constant<int, WN>{}, Pc, cr, M.ccol, p, ln, 64 * WN);
                     return;
                 }
             }
-            if constexpr (W > 1) children_by_lanes(std::integral_constant<int, W>{}, Pn, M.rows, M.col, c, ln, xlo, xhi);
+            if constexpr (W > 1) children_by_lanes(std::integral_constant<int, W>{}, Pn, M.rows, M.col, c, ln, xhi);
         };
 
         const int l0 = k - 2;
         uint64_t P0[W];
         prefix_mask<W>(c, P0);
         // A task covering the whole root may finish it in closed form; a
-        // task holding only the root children with x in [x0, x1) counts
+        // task holding only the root children with x below x1 counts
         // exactly the cliques of that part (so tasks can be listed alone).
-        const bool whole = x0 == 0 && x1 >= c;
+        const bool whole = x1 >= c;
         bool active = true;
         int lq = 0;
         if (DEEP && qitem >= 0) {
@@ -1480,7 +1477,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         } else {
             // a root split over several tasks that is a clique, 2-plex or
             // 3-plex (as far as t allows): this task's part is the
-            // l0-cliques whose first vertex x lies in [x0, x1), for a clique
+            // l0-cliques whose first vertex x lies below x1, for a clique
             // sum_x C(c-1-x, l0-1), else the closed form of each later
             // neighbourhood P0 & N+(x) (a t-plex again) at l0 - 1
             const int xe = x1 < c ? x1 : c;
@@ -1500,7 +1497,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                 const int mind = wmin_i32(mn);
                 if (mind >= c - 1) {
                     val_t part = 0;
-                    for (int x = x0; x < xe; ++x) part += choose(c - 1 - x, l0 - 1);
+                    for (int x = 0; x < xe; ++x) part += choose(c - 1 - x, l0 - 1);
                     tacc.add(part);
                     active = false;
                 } else {
@@ -1510,7 +1507,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             if (close) {  // the whole root (x = -1), or its part vertex by vertex
                 val_t part = 0;
                 bool all = true;
-                for (int x = whole ? -1 : x0; x < (whole ? 0 : xe) && all; ++x) {
+                for (int x = whole ? -1 : 0; x < (whole ? 0 : xe) && all; ++x) {
                     uint64_t Rx[W];
 #pragma unroll
                     for (int w = 0; w < W; ++w) Rx[w] = x < 0 ? P0[w] : uni64(P0[w] & M.rows[x][w] & upper_mask(x, w));
@@ -1585,7 +1582,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         // (P, R, x, l); its ancestors are frames
         int sp = 0;
         uint64_t P[W], R[W];
-        int x = x0 - 1, l = qitem >= 0 ? lq : l0;
+        int x = -1, l = qitem >= 0 ? lq : l0;
 #pragma unroll
         for (int w = 0; w < W; ++w) { P[w] = qitem >= 0 ? uni64(dev_load(&a.squeue[qitem].P[w])) : P0[w]; R[w] = 0; }
         while (active) {
