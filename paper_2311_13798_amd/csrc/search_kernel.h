@@ -54,11 +54,14 @@ __device__ u128 twoplex_count(int f, int p, int l, bool& ovf) {
     return s;
 }
 
-// exact 128-bit accumulator with an overflow flag
+// exact 128-bit accumulator with an overflow flag, of wave-uniform values:
+// they come from table loads and lane sums, which the compiler would keep, and
+// the accumulators with them, in vector registers
 struct Acc {
     u128 v;
     bool ovf;
     __device__ void add(u128 x) {
+        x = ((u128)uni64((uint64_t)(x >> 64)) << 64) | uni64((uint64_t)x);
         v += x;
         ovf |= v < x;
     }
@@ -70,7 +73,7 @@ struct Acc {
 struct Acc64 {
     uint64_t v;
     bool ovf;
-    __device__ void add(uint64_t x) { v += x; }
+    __device__ void add(uint64_t x) { v += uni64(x); }
     __device__ uint64_t lo() const { return v; }
     __device__ uint64_t hi() const { return 0; }
 };
@@ -336,10 +339,13 @@ __device__ __forceinline__ v4i missing_fragment(const uint64_t (&R)[WV], const u
     return f;
 }
 
-template <int WV>
+// GI row blocks are held at a time: four in the shallow kernels of up to two
+// words (R-MAT s18 at k = 7, two words 71.4 ms, with two 73.7), two in the deep
+// ones, which have fewer registers left (with four they kept 344 bytes a lane in
+// scratch at two words, now 220).
+template <int WV, int GI>
 __device__ __forceinline__ uint32_t codegree_squares(const uint64_t (&R)[WV], const uint64_t (*rows)[WV],
                                                      const int16_t* vl, int r) {
-    constexpr int GI = WV <= 2 ? 4 : 2;  // row blocks held at a time
     const int row = lane_id() & 15;
     const int nb = (r + 15) >> 4;
     uint32_t sum = 0;
@@ -953,7 +959,11 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
         // W = 1: lane v keeps vertex v's later neighbours, and the leaves' counts
         // and queued children are kept over the whole task (they all refer to
         // the same rows), so that a node pays no reduction and the lanes count
-        // children of many nodes at once
+        // children of many nodes at once.  A set of at most 64 vertices adds at
+        // most 2^25 to a lane's leaf_S (each of its terms below is under 6
+        // million) and 2^22 to leaf_usum, a child under 2^16 to leaf_sum, so
+        // 64-bit sums over the lanes hold 2^32 sets: over an hour of one wave at
+        // a microsecond a set
         uint64_t dagv = 0, leaf_sum = 0, leaf_usum = 0;
         int64_t leaf_S = 0;
         int q1 = 0, q1_lc = 0;
@@ -1024,7 +1034,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                         }
                     }
                 }
-                if (work) wk_ops += wave_sum(lops);
+                if (work) wk_ops += uni64(wave_sum(lops));
                 q1 = 0;
                 wave_sync();
             }
@@ -1262,7 +1272,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             // exceeds that of codeg^2 by 4 (2 sum_pairs cc) + 4 sum m + sum
             // (m + 1)^2.  C4 enters
             // with 24 Z / 4 = 3 (2 Z):
-            S += 3 * (int64_t)codegree_squares<WV>(R, rows, M.vl, r);
+            S += 3 * (int64_t)codegree_squares<WV, WV <= 2 && !DEEP ? 4 : 2>(R, rows, M.vl, r);
             return true;
         };
 
@@ -1363,7 +1373,7 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
                 if (qn >= QRUN) drain();
             }
             if (qn > 0) drain();
-            if (work) wk_ops += wave_sum(lops);
+            if (work) wk_ops += uni64(wave_sum(lops));
             const int64_t s24 = wave_sum(S);
             tacc.add((uint64_t)((int64_t)(wave_sum(lsum) + usum) + s24 / 24));
         };
