@@ -41,8 +41,9 @@ struct Tickets {
     unsigned long long* next;
     int64_t n, heavy, nchunks;
     int32_t chunk_len;
-    int32_t dealt;  // 1: first tickets by wave number; 0: every ticket from the counter (launches that
-                    // share the device with others, whose workgroups may start late)
+    int32_t dealt;  // first tickets by wave number, 1: consecutive ones to different workgroups, 2: to one;
+                    // 0: every ticket from the counter (launches that share the device with others, whose
+                    // workgroups may start late)
 };
 
 // Graph arrays the build kernel reads.

@@ -129,8 +129,9 @@ struct Drawn {
             const int64_t waves = T.dealt ? (int64_t)gridDim.x * (blockDim.x / EBB_WAVE) : 0;
             const int64_t total = T.heavy + T.nchunks;
             uint64_t t;
-            if (!started && T.dealt) {  // consecutive tickets on different compute units
-                t = (uint64_t)(threadIdx.x / EBB_WAVE) * gridDim.x + blockIdx.x;
+            if (!started && T.dealt) {
+                const uint64_t wave = threadIdx.x / EBB_WAVE, per = blockDim.x / EBB_WAVE;
+                t = T.dealt == 2 ? blockIdx.x * per + wave : wave * gridDim.x + blockIdx.x;
                 started = true;
             } else {
                 if (total <= waves) return -1;
@@ -165,9 +166,14 @@ struct Drawn {
 // one chunk per wave when nothing heavy comes first (then no wave touches the
 // counter), else two per wave, since the waves come to them at different times.
 // consecutive > 0: chunks of up to that many neighbours, sixteen or more per wave.
+// once: a launch that is not persistent, each wave drawing once; a workgroup
+// leaves with its slowest wave, so its waves take neighbours, which weigh alike
+// (Chung-Lu 3e5 at k = 10 135 ms, against 249 with one task of each quarter of
+// the list; a persistent launch puts neighbours, heavy ones first, on different
+// compute units).
 inline Tickets make_tickets(unsigned long long* next, int64_t n, int64_t heavy, int64_t waves, int consecutive,
-                            bool shared) {
-    Tickets T{next, n, heavy < n ? heavy : n, 0, 0, shared ? 0 : 1};
+                            bool shared, bool once = false) {
+    Tickets T{next, n, heavy < n ? heavy : n, 0, 0, shared ? 0 : (once ? 2 : 1)};
     const int64_t light = T.n - T.heavy;
     if (consecutive > 0) {
         int64_t len = light / (16 * waves);

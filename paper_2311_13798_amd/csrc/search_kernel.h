@@ -1782,7 +1782,7 @@ hipError_t launch_w(SearchArgs a, int cus, int bpc, hipStream_t s) {
     if (grid < 0) return hipErrorInvalidValue;
     // tasks that build their sub-branch are sorted by graph, not by weight:
     // neighbours share the graph's arrays in cache
-    a.tickets = make_tickets(a.next, a.ntasks, a.heavy, 4 * grid, BUILD ? 8 : 0, a.shared);
+    a.tickets = make_tickets(a.next, a.ntasks, a.heavy, 4 * grid, BUILD ? 8 : 0, a.shared, bpc == -1);
     hipLaunchKernelGGL((k_search<W, BUILD, DEEP>), dim3((unsigned)grid), dim3(256), 4 * sizeof(SearchMem<W>), s, a);
     return hipGetLastError();
 }
