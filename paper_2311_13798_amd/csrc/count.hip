@@ -628,12 +628,24 @@ static void swap_arenas(ebbkc_graph* g) {
     g->np_active = !g->np_active;
 }
 
+// A new count starts: no class has run yet.
+static void reset_last(ebbkc_graph* g) {
+    for (int i = 0; i < 4; ++i) {
+        g->last_ms[i] = 0.0;
+        g->last_work[i] = 0;
+        for (int j = 0; j < 4; ++j) g->last_work_class[i][j] = 0;
+    }
+    for (bool& b : g->tev_set) b = false;
+}
+
+// Adds the launches just made to the times and work figures of this count (a
+// list of more than QUERY_CHUNK seeds takes several passes).
 static ebbkc_status read_total(ebbkc_graph* g, uint64_t* out, hipStream_t s) {
     CHKH(hipMemcpyAsync(g->h_counters, g->d_counters, CNT_WORDS * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     CHKH(hipStreamSynchronize(s));
     for (int w = 0; w < MAX_W; ++w) {
         float ms = 0.f;
-        if (g->tev_set[w] && hipEventElapsedTime(&ms, g->tev[w][0], g->tev[w][1]) == hipSuccess) g->last_ms[w] = ms;
+        if (g->tev_set[w] && hipEventElapsedTime(&ms, g->tev[w][0], g->tev[w][1]) == hipSuccess) g->last_ms[w] += ms;
         g->tev_set[w] = false;
     }
     const int err = (int)g->h_counters[6];
@@ -646,15 +658,14 @@ static ebbkc_status read_total(ebbkc_graph* g, uint64_t* out, hipStream_t s) {
     g->last_total_ovf = (err & ERR_OVERFLOW) != 0;
     if ((err & ERR_OVERFLOW) || g->h_counters[5] != 0) return EBBKC_E_OVERFLOW;
     *out = g->h_counters[4];
-    for (int i = 0; i < 4; ++i) g->last_work[i] = 0;
     for (int W = 1; W <= 4; ++W) {
         for (int i = 0; i < 3; ++i) {
-            g->last_work_class[W - 1][i] = g->h_counters[16 + 4 * (W - 1) + i];
-            g->last_work[i] += g->last_work_class[W - 1][i];
+            g->last_work_class[W - 1][i] += g->h_counters[16 + 4 * (W - 1) + i];
+            g->last_work[i] += g->h_counters[16 + 4 * (W - 1) + i];
         }
         // wave-finish tail: latest end minus the mean end (10 ns ticks)
         const uint64_t* t = g->h_counters + 32 + 4 * (W - 1);
-        g->last_work_class[W - 1][3] = t[2] ? 10 * (t[1] - t[0] / t[2]) : 0;
+        if (t[2]) g->last_work_class[W - 1][3] += 10 * (t[1] - t[0] / t[2]);
         g->last_work[3] += g->h_counters[48 + W - 1];
     }
     return EBBKC_OK;
@@ -988,11 +999,7 @@ static ebbkc_status count_core(ebbkc_graph* g, int32_t k, int64_t r_begin, int64
     if (ensure_binom(g->device, s) != hipSuccess) return EBBKC_E_HIP;
     if (r_end < 0 || r_end > g->m) r_end = g->m;
     if (r_begin < 0) r_begin = 0;
-    for (int i = 0; i < 4; ++i) g->last_ms[i] = 0.0;
-    for (bool& b : g->tev_set) b = false;
-    for (int i = 0; i < 4; ++i) g->last_work[i] = 0;
-    for (int W = 0; W < 4; ++W)
-        for (int i = 0; i < 4; ++i) g->last_work_class[W][i] = 0;
+    reset_last(g);
     unsigned long long* total = (unsigned long long*)(g->d_counters + 4);
     if (k == 3) {  // sum of |V(g_i)| over the seeds
         st = subsize_impl(g, s);
@@ -1194,6 +1201,7 @@ ebbkc_status list_impl(ebbkc_graph* g, int32_t k, int64_t r_begin, int64_t r_end
                 int64_t* stmp = cv.take<int64_t>(scan_tmp_elems(T + 1) + 64);
                 if ((deep && !gframes) || !per_task || !task_off || !stmp) return EBBKC_E_OOM;
                 // pass 1: per-task counts
+                reset_last(g);
                 CHKH(hipMemsetAsync(g->d_counters, 0, CNT_WORDS * sizeof(uint64_t), s));
                 st = run_tasks(g, k, plan, per_task, nullptr, nullptr, gframes, false, s);
                 if (st) return st;
@@ -1392,6 +1400,7 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
     st = arena_impl(g, s);
     if (st) return st;
     if (ne <= 0) return EBBKC_OK;
+    reset_last(g);
     // a dozen launches and one more wait against 0.1 us a seed on the host:
     // 100 and 1,000 seeds of a 20,000-vertex R-MAT graph 65 and 133 us on the
     // host, 119 and 122 us on the device; 10,000 seeds 923 and 201 (a host
