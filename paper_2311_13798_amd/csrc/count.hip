@@ -1401,11 +1401,16 @@ ebbkc_status count_seeds_impl(ebbkc_graph* g, int32_t k, const int64_t* eids, in
     if (st) return st;
     if (ne <= 0) return EBBKC_OK;
     reset_last(g);
-    // a dozen launches and one more wait against 0.1 us a seed on the host:
-    // 100 and 1,000 seeds of a 20,000-vertex R-MAT graph 65 and 133 us on the
-    // host, 119 and 122 us on the device; 10,000 seeds 923 and 201 (a host
-    // lookup that finds no task saves the launches altogether: hence not 1,000)
-    constexpr int64_t QUERY_FEW = 2048;
+    // On the device a list costs a dozen launches and one more wait, on the host
+    // a search in the ranks for each seed.  Host / device in us at k = 6:
+    //   seeds                            512      1,024    1,280    2,048
+    //   R-MAT, 2^13 vertices           79/112  103/114  118/115  173/121
+    //   R-MAT, 2^16 vertices          159/166  225/172  257/176  315/176
+    //   Chung-Lu, 300,000 vertices     94/112  147/116  176/116  232/114
+    //   G(2000, 0.01): no task at all   13/66    21/66    24/67    35/67
+    // The larger graphs cross between 512 and 800 seeds, the smallest at 1,200,
+    // and lists in which no seed has a task past 3,072.
+    constexpr int64_t QUERY_FEW = 1024;
     if (ne <= QUERY_FEW) return count_few_seeds(g, k, eids, ne, ptr_kind, out, s);
     constexpr int64_t QUERY_CHUNK = (int64_t)1 << 22;
     const bool dev = ptr_kind == EBBKC_PTR_DEVICE;

@@ -74,3 +74,19 @@ def test_refused_ids_and_long_lists(ebb):
     ebb.ebbkc_count_seeds(G.handle, 5, d, o)
     assert np.array_equal(o.cpu().numpy().view(np.uint64), by_edge[::-1])
     G.close()
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025])
+def test_the_longest_list_looked_up_on_the_host(ebb, n):
+    g = graphgen.er_planted(200, 0.2, 1, 20, 20, 3)
+    G = ebb.Graph.from_csr(g)
+    by_edge = query(ebb, G, 5, np.arange(G.info.m))
+    assert int(by_edge.sum()) == G.count(5)
+    e = np.random.default_rng(n).integers(0, G.info.m, n)
+    assert np.array_equal(query(ebb, G, 5, e), by_edge[e])
+    rank = np.zeros(G.info.m, np.int32)
+    ebb.ebbkc_export(G.handle, ebb.ARR_RANK, rank)
+    for i in (0, n // 2, n - 1):
+        r = int(rank[e[i]])
+        assert int(by_edge[e[i]]) == G.count_range(5, r, r + 1)
+    G.close()
