@@ -983,6 +983,37 @@ int peel_attempts(int64_t grid, int (*attempt)(void*, int64_t), void* arg) {
     }
 }
 
+static int64_t scan_elems(int32_t n, int64_t nnz) { return scan_tmp_elems(nnz + n + 2) + 1024; }
+static int64_t peel_live_elems(int64_t nnz) { return nnz / 2 + PEEL_TB * (PEEL_GRID_WIDE + 1); }
+
+// Slabs of the arrays the handle keeps and of the ones only prepare uses (m =
+// nnz / 2 edges, if the input turns out valid): 68 and 116 bytes an edge, and
+// the triangle incidence beside them.
+void prepare_sizes(int32_t n, int64_t nnz, SlabSize out[2]) {
+    const int64_t mm = nnz / 2, rsort = radix_hist_elems(nnz);
+    out[0] = SlabSize{}
+                  .add<int32_t>((int64_t)n + 1, 2)
+                  .add<int32_t>(nnz, 2)
+                  .add<int32_t>(mm, 7)
+                  .add<int2>(nnz)
+                  .add<int2>(mm);
+    out[1] = SlabSize{}
+                  .add<int32_t>(n, 2)
+                  .add<int64_t>((int64_t)n + 1)
+                  .add<int32_t>(2 + 2 * (int64_t)n)
+                  .add<int64_t>(scan_elems(n, nnz))
+                  .add<int32_t>(nnz, 3)
+                  .add<int64_t>(nnz)
+                  .add<int2>(mm)
+                  .add<int32_t>(mm, 4)
+                  .add<int64_t>(mm + 1, 2)
+                  .add<uint32_t>(nnz, 4)
+                  .add<int64_t>(rsort)
+                  .add<int64_t>(scan_tmp_elems(rsort) + 64)
+                  .add<PeelCtl>(1)
+                  .add<int32_t>(peel_live_elems(nnz));
+}
+
 #define CHK(expr)                                   \
     do {                                            \
         hipError_t e_ = (expr);                     \
@@ -1001,33 +1032,13 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     CHK(hipEventCreate(&ev1));
     CHK(hipEventRecord(ev0, s));
 
-    // the arrays the handle keeps and the ones only this call uses, a slab each
-    // (m = nnz / 2 edges, if the input turns out valid)
-    const int64_t mm = nnz / 2, rsort = radix_hist_elems(nnz);
-    const int64_t tmp_elems = scan_tmp_elems(nnz + n + 2) + 1024, rtmp_elems = scan_tmp_elems(rsort) + 64;
-    const int64_t live_elems = mm + PEEL_TB * (PEEL_GRID_WIDE + 1);
     Slab held, tmp;
-    CHK(held.init(SlabSize{}
-                      .add<int32_t>((int64_t)n + 1, 2)
-                      .add<int32_t>(nnz, 2)
-                      .add<int32_t>(mm, 7)
-                      .add<int2>(nnz)
-                      .add<int2>(mm)));
-    CHK(tmp.init(SlabSize{}
-                     .add<int32_t>(n, 2)
-                     .add<int64_t>((int64_t)n + 1)
-                     .add<int32_t>(2 + 2 * (int64_t)n)
-                     .add<int64_t>(tmp_elems)
-                     .add<int32_t>(nnz, 3)
-                     .add<int64_t>(nnz)
-                     .add<int2>(mm)
-                     .add<int32_t>(mm, 6)
-                     .add<int64_t>(mm + 1, 2)
-                     .add<uint32_t>(nnz, 4)
-                     .add<int64_t>(rsort)
-                     .add<int64_t>(rtmp_elems)
-                     .add<PeelCtl>(1)
-                     .add<int32_t>(live_elems)));
+    SlabSize size[2];
+    prepare_sizes(n, nnz, size);
+    CHK(held.init(size[0]));
+    CHK(tmp.init(size[1]));
+    const int64_t tmp_elems = scan_elems(n, nnz), rtmp_elems = scan_tmp_elems(radix_hist_elems(nnz)) + 64;
+    const int64_t live_elems = peel_live_elems(nnz);
     SBuf<int32_t> rp, ci;
     CHK(rp.alloc(held, (int64_t)n + 1));
     CHK(ci.alloc(held, nnz));
@@ -1131,7 +1142,7 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
 
     // ---- level-synchronous peel: rounds, levels and |V(g_i)|, then the ranks
     // by a stable sort of the rounds over the edge ids
-    SBuf<int32_t> live, front0, front1, rnd, level, rank, subsize, byrank;
+    SBuf<int32_t> live, rnd, level, rank, subsize, byrank;
     SBuf<PeelCtl> ctl;
     SBuf<uint32_t> rk1, rk2, rv2;
     SBuf<int64_t> rhist, rtmp;
@@ -1147,8 +1158,6 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
     CHK(rtmp.alloc(tmp, rtmp_elems));
     if (m) {
         CHK(rnd.alloc(tmp, m));
-        CHK(front0.alloc(tmp, m));
-        CHK(front1.alloc(tmp, m));
         CHK(ctl.alloc(tmp, 1));
         CHK(live.alloc(tmp, live_elems));
         PeelArgs pa{};
@@ -1159,8 +1168,9 @@ ebbkc_status prepare_impl(ebbkc_graph* g, const int32_t* row_ptr, const int32_t*
         pa.rnd = rnd.p;
         pa.level = level.p;
         pa.subsize = subsize.p;
-        pa.front[0] = front0.p;
-        pa.front[1] = front1.p;
+        // the triangle pass is through with its places: 8 (m + 1) bytes
+        pa.front[0] = (int32_t*)cursor.p;
+        pa.front[1] = pa.front[0] + m;
         pa.live = live.p;
         pa.ctl = ctl.p;
         const PeelCtl* hc = (const PeelCtl*)g->h_counters;

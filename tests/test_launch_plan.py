@@ -1,6 +1,6 @@
 """The library without a GPU: host arithmetic of the launches, through internal functions (where each width
 class's root ranges start in one task list of up to 2^32 entries, the frames of deep searches, the workgroups
-of the peel, the bytes of task lists), and its kernels."""
+of the peel, the bytes of task lists and of preparing), and its kernels."""
 import ctypes
 import math
 import os
@@ -118,3 +118,15 @@ def test_every_kernel_is_compiled_once():
     names = {n for n in re.findall(rb"_Z[A-Za-z0-9_]+\.kd", data) if b"_GLOBAL__N_1" not in n}
     assert sum(b"k_search" in n for n in names) >= 16
     assert [n for n in names if data.count(n + b"\0") != 2] == []
+
+
+def test_prepare_takes_184_bytes_an_edge():
+    # beside the triangle incidence; arrays of one entry a vertex and the sort's histograms come on top
+    f = internal("_ZN3ebb13prepare_sizesEilPNS_8SlabSizeE", None, ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p)
+    size = (ctypes.c_size_t * 2)()
+    n, m = 1 << 20, 1 << 29
+    f(n, 2 * m, size)
+    assert 68 * m <= size[0] <= 68 * m + 16 * n + 4096
+    assert size[0] + size[1] <= 188 * m
+    f(1, 0, size)
+    assert 0 < size[0] + size[1] < 4 << 20
