@@ -95,8 +95,13 @@ struct Frame {
 // children queued per node before the lanes count them (room for one more x)
 constexpr int QRUN = 256, QCAP = QRUN + 256;
 // W = 1: candidate sets queued per task (room for 64 more), and the least
-// |P & N+(x)| of an l = 5 node whose 4-cliques may be taken by the wave
-constexpr int Q1_CAP = 256, Q1_RUN = Q1_CAP - 64, L5_WAVE_MIN = 12;
+// |P & N+(x)| of an l = 5 node whose 4-cliques may be taken by the wave: the
+// matrix cores take a set in much the same time whatever its size, the queue's
+// lanes in time that grows with its pairs.  With 8 / 12 / 16 / 24 / 65 (never),
+// ms: R-MAT s16 k = 7 13.4 / 13.3 / 13.2 / 13.1 / 15.6, s13 k = 9 12.3 / 11.8 /
+// 11.2 / 10.4 / 10.8; planted cliques on 300,000 vertices k = 7 1.71 / 1.64 /
+// 1.63 / 1.60 / 1.52, k = 9 17.8 / 16.1 / 15.0 / 14.2 / 13.7.
+constexpr int Q1_CAP = 256, Q1_RUN = Q1_CAP - 64, L5_WAVE_MIN = 24;
 
 template <int W>
 struct SearchMem {
