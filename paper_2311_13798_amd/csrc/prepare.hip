@@ -461,11 +461,13 @@ __global__ void k_peel_compact(const int32_t* __restrict__ live, int64_t nlive, 
 // stream's, another process's) for that long; the peel then starts over with
 // fewer of them (peel_attempts), in the end with one, which waits for nobody.
 constexpr int PEEL_TB = 1024, PEEL_GROUP = 16;
-// 64 workgroups, 128 from 2 M edges on: more of them share a round's triangles,
-// fewer make the barrier cheaper (prepare of R-MAT s18, m = 3.8 M: 55.3 ms with
-// 64, 50.0 with 128, 52.1 with 256; R-MAT of 50,000 vertices, m = 0.65 M: 14.8,
-// 15.2, 17.3 ms).
-constexpr int64_t PEEL_GRID = 64, PEEL_GRID_WIDE = 128, PEEL_WIDE_M = 2 << 20;
+// 64 workgroups, 128 from 2^20 edges on: more of them share a round's triangles,
+// fewer make the barrier cheaper.  Preparing with 64 / 128, in ms: R-MAT of
+// 0.44 M edges 10.8 / 11.3, 0.91 M 17.4 / 17.2, 1.9 M 28.0 / 26.7, 3.8 M 49.9 /
+// 45.4 (256 take 2 ms more there); Chung-Lu with planted cliques, 1.5 M edges
+// 9.6 / 9.8, 3.0 M 15.8 / 15.9; G(n, p) of 1.25 M edges 13.9 / 11.8, 1.8 M 81.6
+// / 63.6.
+constexpr int64_t PEEL_GRID = 64, PEEL_GRID_WIDE = 128, PEEL_WIDE_M = 1 << 20;
 constexpr int PEEL_Q = 4096;      // appended edges collected per workgroup before they are written
 // Edges with more than PEEL_SHORT triangles are listed and taken by a wave
 // each, those with more than PEEL_LONG by the whole workgroup: a step of four

@@ -15,5 +15,5 @@ def test_edges_at_the_lines(ebb, pages):  # noqa: F811
 
 
 def test_several_long_edges_a_workgroup(ebb):  # noqa: F811
-    # 1.1 M edges on 64 workgroups; the 132 spines leave together in the second round
-    check(ebb, book(4097, 132), "132 books", 4097 * 132)
+    # 1.0 M edges on 64 workgroups; the 124 spines leave together in the second round
+    check(ebb, book(4097, 124), "124 books", 4097 * 124)
