@@ -286,9 +286,14 @@ __device__ __forceinline__ void scan_edges(const GraphView& G, int32_t r, int c,
 }
 
 // Whether a sub-branch of c vertices and twoE / 2 edges goes without colours:
-// `plain` says which may (for a search that does not branch, colours only
-// bound its leaves' counts, which sparse sub-branches are cheap to make
-// without).
+// `plain` says which may.  In a search that does not branch, colours only save
+// counting leaves that hold nothing, and they are cheap to count where less
+// than half of the pairs are edges; a bipartite sub-branch can reach a half,
+// and one of few colours and many edges costs most without them.  32 graphs a
+// batch, none / up to a half / all plain, ms: G(200, .4) k = 7 1.13 / 1.03 /
+// 1.01, G(150, .5) k = 7 1.30 / 1.27 / 1.25, G(80, .9) k = 6 1.14 / 1.15 / 1.03;
+// complete multipartite of 5 x 24 vertices k = 7 1.76 / 1.70 / 4.17, of 6 x 20
+// 1.97 / 1.99 / 4.83, of 4 x 30 1.16 / 1.09 / 1.09.
 enum : int { PLAIN_NEVER = 0, PLAIN_SPARSE = 1, PLAIN_ALWAYS = 2 };
 __device__ __forceinline__ bool plain_build(int plain, int c, uint32_t twoE) {
     return plain == PLAIN_ALWAYS || (plain == PLAIN_SPARSE && 2 * twoE < (uint32_t)c * (uint32_t)c);

@@ -445,8 +445,8 @@ __global__ void k_peel_compact(const int32_t* __restrict__ live, int64_t nlive, 
 // already appended to the next one (round r + 1) still counts as present.
 //
 // The rounds are bound by latency: a chain of about seven dependent accesses
-// and the barrier each, 1,278 of them on R-MAT s18 (26 ms, 20 us a round) and
-// 796 on R-MAT of 50,000 vertices (9 ms).  The host loop this replaces (six
+// and the barrier each, 1,245 of them on R-MAT s18 (27.2 ms, 21.8 us a round
+// with its triangles) and some 850 on R-MAT of 49,999 vertices (9.7 ms, 11 us).  The host loop this replaces (six
 // launches, a copy and a wait per round, every live edge read three times)
 // took 90 and 51 ms.
 //

@@ -1185,7 +1185,9 @@ __global__ __launch_bounds__(256, (W <= 2 ? 4 : (W <= 3 ? 3 : 2))) void k_search
             // holds (half of those at its vertices) and ~12 for each triangle
             // of missing pairs there (about its pairs' pairs times the density
             // of H), plus ~150 for the reductions and ~12 for each tile of the
-            // codegrees.
+            // codegrees.  Weights of 50 / 100 / 200 / 500 % of the estimate: R-MAT
+            // s14 k = 8 17.4 / 17.5 / 17.9 / 20.0 ms, s16 222 / 223 / 228 / 257,
+            // G(250, .8) 71.7 / 74.9 / 80.9 / 99.0; never 42.7, 999 and 285.
             // The alternative for one R = P & N+(x) of an l = 5 node is one
             // child y per lane counting the triangles of R & N+(y): ~35
             // instructions per vertex of the largest child, ~ r * d, per 64
